@@ -1,24 +1,31 @@
 // Per-KV-head selection: the "ArgSort(...)[:B]" of Eq. 4 done as a radix select (no sort).
 //
-// One workgroup of 16 waves ranks the prefix scores of one (instance, KV head).  Scores
-// are mapped to order-preserving 32-bit keys; four most-significant-digit-first passes
-// over 8-bit digits find the key T of the k-th largest score and how many keys equal to
-// T still fit (ties go to the lower position).  A last sweep emits, in ascending
-// position order, every key above T plus the first `want` keys equal to T, then the `keep`
-// window positions.  Keys live in registers (each wave owns a contiguous segment of the
-// prefix, 64 consecutive positions per register row -- or, where the scores need no pooling
-// here and lie 16-byte aligned, 256 consecutive positions per four registers, a lane holding
-// four neighbours that it fetched with one load) for prefixes up to 32768; longer prefixes
-// re-read the scores from memory in every pass.
+// One workgroup of 16 waves ranks the prefix scores of one (instance, KV head).  Scores are mapped to
+// order-preserving 32-bit keys, which live in registers for prefixes up to 32768 (longer ones re-read the
+// scores from memory in every sweep).
+//   1. A lower bound of the k-th largest key: the keys are cut into at least k groups (a thread's, or halves
+//      or quarters of them); the k-th largest of the groups' maxima is such a bound, and only one key per
+//      group is counted for it (by its 11 leading bits; the bound is the lower edge of a bin).  Few more
+//      than k keys are left above it.  (Short prefixes with many keys wanted: every key is a group.)
+//   2. These are counted by their distance from the bound, 2048 bins up to the largest key, and the bin of
+//      the k-th one is refined, 11 bits at a time, until its keys are all wanted or so few (CANDIDATES)
+//      that comparing all pairs tells the key T of the k-th largest and how many keys equal to T still
+//      fit (ties go to the lower position).
+//   3. A last sweep emits, in ascending position order, every key above T plus the first `want` keys equal to
+//      T, then the `keep` window positions.
+// What bounds it: latency -- loads, LDS adds and barriers of one workgroup per head.  The scores of a head
+// crowd into few values of the leading bits, and LDS adds of many lanes to one word go one after the other
+// (counting every key of a 32768-key head by its leading byte took 9 us of 25); so few keys are counted
+// there, into COPIES histograms side by side, one per lane number modulo COPIES.
 #include "laq_internal.h"
 
 namespace laq {
 
 namespace {
 
-constexpr int SEL_THREADS = 1024;
-constexpr int SEL_WAVES = SEL_THREADS / 64;
-constexpr int SEL_MANY_WORKGROUPS = 768;   // from here on two workgroups per compute unit pay off
+constexpr int SEL_MANY_WORKGROUPS = 768;   // heads of a launch from which on several workgroups share a compute unit
+constexpr int COPIES = 8;                  // histograms of the first pass
+constexpr int CANDIDATES = 128;            // keys that are ranked by comparing all pairs
 
 __device__ __forceinline__ uint32_t order_key(float f) {
   const uint32_t b = __float_as_uint(f);
@@ -29,19 +36,82 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+}
+// inclusive sum over the lanes of a wave
+__device__ __forceinline__ int wave_scan(int x) {
+  x += dpp_or_zero<0x111, 0xf>(x);         // row_shr 1, 2, 4, 8 within 16 lanes
+  x += dpp_or_zero<0x112, 0xf>(x);
+  x += dpp_or_zero<0x114, 0xf>(x);
+  x += dpp_or_zero<0x118, 0xf>(x);
+  x += dpp_or_zero<0x142, 0xa>(x);         // lane 15 of a row to the next row
+  x += dpp_or_zero<0x143, 0xc>(x);         // lane 31 to the upper half
+  return x;
+}
+
+// Sizes that follow from the threads of a workgroup: two bins per thread.
+template <int THREADS> struct Sel {
+  static constexpr int WAVES = THREADS / 64, BINS = 2 * THREADS;
+  static constexpr int BITS = THREADS == 1024 ? 11 : THREADS == 512 ? 10 : 9;
+  static_assert(BINS == 1 << BITS && WAVES <= 16, "");
+  int first[BINS * COPIES];                // first pass: [bin][copy]
+  int later[BINS];                         // the other passes
+  uint32_t cand[CANDIDATES];
+  int n_cand;
+  int wave_total[2][WAVES];
+  int bin, above, count, top;              // result of a pass; top: the highest bin that is not empty
+  uint32_t threshold;
+  int equal_wanted;
+};
+
+// The bin (from the top) in which the `want`-th key lies, the number of keys above it and in it.  Ends
+// behind a barrier.
+template <int C, int THREADS>
+__device__ __forceinline__ void find_bin(Sel<THREADS>& sh, const int* hist, int want, int tid) {
+  const int lane = tid & 63, wave = tid >> 6, b = Sel<THREADS>::BINS - 2 - 2 * tid;   // this thread: bins b + 1, then b
+  int h0, h1;
+  if constexpr (C == 1) {
+    const int2 v = *reinterpret_cast<const int2*>(hist + b);
+    h0 = v.y;
+    h1 = v.x;
+  } else {
+    h0 = h1 = 0;
+#pragma unroll
+    for (int c = 0; c < C; c += 4) {
+      const int4 lo = *reinterpret_cast<const int4*>(hist + b * C + c), hi = *reinterpret_cast<const int4*>(hist + (b + 1) * C + c);
+      h1 += lo.x + lo.y + lo.z + lo.w;
+      h0 += hi.x + hi.y + hi.z + hi.w;
+    }
+  }
+  const int upto = wave_scan(h0 + h1);
+  if (lane == 63) sh.wave_total[0][wave] = upto;
+  __syncthreads();
+  int before = lane < wave ? sh.wave_total[0][lane] : 0;                // (at most 16 waves)
+  before = __builtin_amdgcn_readlane(wave_scan(before), 15);
+  const int incl = before + upto, excl = incl - h0 - h1;
+  if (excl == 0 && incl > 0) sh.top = h0 > 0 ? b + 1 : b;
+  if (excl < want && want <= incl) {
+    const bool second = excl + h0 < want;
+    sh.bin = second ? b : b + 1;
+    sh.above = second ? excl + h0 : excl;
+    sh.count = second ? h1 : h0;
+  }
+  __syncthreads();
+}
+
 // ITEMS > 0: keys of the wave's segment are held in ITEMS registers per lane.
 // ITEMS == 0: keys are recomputed from memory on every sweep (any prefix length).
-// WAVES_PER_SIMD = 4: one workgroup per compute unit, up to 128 registers per lane; 8: two workgroups
-// per compute unit on 64 registers (the 32-key variant then spills a few of them, which costs
-// 12 % when there is one workgroup per compute unit anyway and gains 30 % when there are many).
-// QUADS: register 4q + c of a lane holds position seg0 + 256 q + 4 lane + c (one 16-byte load per q).
-template <int ITEMS, int WAVES_PER_SIMD, bool QUADS>
-__global__ __launch_bounds__(SEL_THREADS, WAVES_PER_SIMD) void select_kernel(int Hkv, int L, int keep, int pool, bool avg,
+// QUADS (scores that are final: no pooling here): register 4q + c of a lane holds position
+// seg0 + 256 q + 4 lane + c - shift, where shift (0 .. 3) is how far the row starts behind a 16-byte boundary,
+// fetched with one load per q.  Otherwise register i holds position seg0 + 64 i + lane.
+template <int THREADS, int ITEMS, bool QUADS>
+__global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int keep, int pool, bool avg,
                                                              const float* __restrict__ scores, InstTable tab,
                                                              int inst0, int32_t* __restrict__ idx) {
-  __shared__ int hist[256];
-  __shared__ int sh_bin, sh_above;
-  __shared__ int wtot_gt[SEL_WAVES], wtot_eq[SEL_WAVES];
+  __shared__ __align__(16) Sel<THREADS> sh;
+  constexpr int BINS = Sel<THREADS>::BINS, BITS = Sel<THREADS>::BITS, TOP = 32 - BITS;
 
   const int head = blockIdx.x, li = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -51,37 +121,52 @@ __global__ __launch_bounds__(SEL_THREADS, WAVES_PER_SIMD) void select_kernel(int
   const float* s = scores + ((size_t)(inst0 + li) * Hkv + head) * L;
   int32_t* out = idx + (tab.row0[li] + (int64_t)head * bk);
 
-  for (int w = tid; w < keep; w += SEL_THREADS) out[ksel + w] = P + w;
+  for (int w = tid; w < keep; w += THREADS) out[ksel + w] = P + w;
   if (ksel <= 0) return;
   if (ksel >= P) {
-    for (int j = tid; j < P; j += SEL_THREADS) out[j] = j;
+    for (int j = tid; j < P; j += THREADS) out[j] = j;
     return;
   }
 
   constexpr int UNROLL = ITEMS > 0 ? ITEMS : 1;     // register-resident keys: full unrolling; memory path: none
-  const int items = (ITEMS > 0) ? ITEMS : (P + SEL_THREADS - 1) / SEL_THREADS;
-  const int seg0 = wave * items * 64;          // first position of this wave's segment
+  const int items = (ITEMS > 0) ? ITEMS : (P + THREADS - 1) / THREADS;
+  const int shift = QUADS ? (int)((reinterpret_cast<uintptr_t>(s) >> 2) & 3) : 0;
+  const int seg0 = wave * items * 64 - shift;       // first position of this wave's segment
 
   static_assert(!QUADS || (ITEMS > 0 && ITEMS % 4 == 0), "four registers per load");
   uint32_t key[ITEMS > 0 ? ITEMS : 1];
   if constexpr (QUADS) {
+    float4 v[ITEMS / 4];
 #pragma unroll
     for (int q4 = 0; q4 < ITEMS / 4; ++q4) {
       const int pos = seg0 + q4 * 256 + lane * 4;
-      if (pos + 3 < P) {
-        const float4 v = *reinterpret_cast<const float4*>(s + pos);
-        key[4 * q4] = order_key(v.x); key[4 * q4 + 1] = order_key(v.y);
-        key[4 * q4 + 2] = order_key(v.z); key[4 * q4 + 3] = order_key(v.w);
+      v[q4] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);     // positions outside the prefix: below every score
+      if (pos >= 0 && pos + 3 < P) {
+        v[q4] = *reinterpret_cast<const float4*>(s + pos);
       } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) key[4 * q4 + c] = (pos + c < P) ? order_key(s[pos + c]) : 0u;
+        if (pos >= 0 && pos < P) v[q4].x = s[pos];
+        if (pos + 1 >= 0 && pos + 1 < P) v[q4].y = s[pos + 1];
+        if (pos + 2 >= 0 && pos + 2 < P) v[q4].z = s[pos + 2];
+        if (pos + 3 >= 0 && pos + 3 < P) v[q4].w = s[pos + 3];
       }
     }
-  } else if (ITEMS > 0) {
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const int pos = seg0 + i * 64 + lane;
-      key[i] = (pos < P) ? order_key(pool_window(s, pos, P, half, avg)) : 0u;
+    for (int i = tid * 4; i < BINS * COPIES; i += THREADS * 4) *reinterpret_cast<int4*>(sh.first + i) = make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int q4 = 0; q4 < ITEMS / 4; ++q4) {
+      key[4 * q4] = order_key(v[q4].x);
+      key[4 * q4 + 1] = order_key(v[q4].y);
+      key[4 * q4 + 2] = order_key(v[q4].z);
+      key[4 * q4 + 3] = order_key(v[q4].w);
+    }
+  } else {
+    for (int i = tid * 4; i < BINS * COPIES; i += THREADS * 4) *reinterpret_cast<int4*>(sh.first + i) = make_int4(0, 0, 0, 0);
+    if (ITEMS > 0) {
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) {
+        const int pos = seg0 + i * 64 + lane;
+        key[i] = (pos < P) ? order_key(pool_window(s, pos, P, half, avg)) : 0u;
+      }
     }
   }
   auto key_of = [&](int i) -> uint32_t {
@@ -89,58 +174,98 @@ __global__ __launch_bounds__(SEL_THREADS, WAVES_PER_SIMD) void select_kernel(int
     const int pos = seg0 + i * 64 + lane;
     return (pos < P) ? order_key(pool_window(s, pos, P, half, avg)) : 0u;
   };
+  *reinterpret_cast<int2*>(sh.later + 2 * tid) = make_int2(0, 0);
+  if (tid < CANDIDATES) sh.cand[tid] = 0;
+  if (tid == 0) sh.n_cand = 0;
+  __syncthreads();
 
-  // ---- radix passes: find the key of the ksel-th largest score ----
-  uint32_t prefix = 0, mask = 0;
-  int want = ksel;
-#pragma unroll 1
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    if (tid < 256) hist[tid] = 0;
+  // ---- 1. a lower bound of the ksel-th largest key ----
+  {
+    int* hist = sh.first + (lane & (COPIES - 1));
+    // (groups of ITEMS, ITEMS / 2 or ITEMS / 4 keys: at least P / ITEMS, twice, four times as many of them hold keys)
+    const int groups = ITEMS > 0 ? P / ITEMS : 0;
+    if (ITEMS >= 4 && ksel <= 4 * groups) {
+      constexpr int Q = ITEMS >= 4 ? ITEMS / 4 : 1;
+      uint32_t m[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        m[q] = key_of(q * Q);
+#pragma unroll
+        for (int i = 1; i < Q; ++i) m[q] = max(m[q], key_of(q * Q + i));
+      }
+      m[0] = ksel > 2 * groups ? m[0] : max(m[0], m[1]);
+      m[2] = ksel > 2 * groups ? m[2] : max(m[2], m[3]);
+      if (ksel <= groups) {
+        atomicAdd(&hist[(max(m[0], m[2]) >> TOP) * COPIES], 1);
+      } else {
+        atomicAdd(&hist[(m[0] >> TOP) * COPIES], 1);
+        atomicAdd(&hist[(m[2] >> TOP) * COPIES], 1);
+        if (ksel > 2 * groups) {
+          atomicAdd(&hist[(m[1] >> TOP) * COPIES], 1);
+          atomicAdd(&hist[(m[3] >> TOP) * COPIES], 1);
+        }
+      }
+    } else {
+#pragma unroll UNROLL
+      for (int i = 0; i < items; ++i) atomicAdd(&hist[(key_of(i) >> TOP) * COPIES], 1);
+    }
     __syncthreads();
-    int cur = -1, cnt = 0;            // run-length aggregation: one atomic per run of equal digits
+  }
+  find_bin<COPIES, THREADS>(sh, sh.first, ksel, tid);
+  // ---- 2. the key T of the ksel-th largest score and how many keys equal to it are taken ----
+  // keys base .. base + width - 1 (width <= BINS << low): `want` of them are taken, and all above
+  uint32_t base = (uint32_t)sh.bin << TOP;
+  uint64_t width = (uint64_t)(sh.top - sh.bin + 1) << TOP;
+  int low = TOP - BITS + (32 - __clz(sh.top - sh.bin)), want = ksel, count;
+#pragma unroll 1
+  for (int pass = 0;; ++pass) {
+    int* hist = sh.later;
+    if (pass > 0) {
+      *reinterpret_cast<int2*>(hist + 2 * tid) = make_int2(0, 0);
+      __syncthreads();
+    }
+#pragma unroll UNROLL
+    for (int i = 0; i < items; ++i) {
+      const uint32_t d = key_of(i) - base;
+      if (key_of(i) >= base && d < width) atomicAdd(&hist[d >> low], 1);
+    }
+    __syncthreads();
+    find_bin<1, THREADS>(sh, hist, want, tid);
+    base += (uint32_t)sh.bin << low;
+    width = 1ull << low;
+    count = sh.count;
+    want -= sh.above;
+    if (count == want || count <= CANDIDATES || low == 0) break;
+    low = max(low - BITS, 0);
+  }
+  uint32_t T = base;                       // width 1: the key itself
+  if (count == want) {                     // all of them: everything from T on
+    T -= 1;
+    want = 0;
+  } else if (width > 1) {
 #pragma unroll UNROLL
     for (int i = 0; i < items; ++i) {
       const uint32_t kv = key_of(i);
-      if ((kv & mask) == prefix) {
-        const int dg = (kv >> shift) & 255;
-        if (dg == cur) {
-          ++cnt;
-        } else {
-          if (cnt) atomicAdd(&hist[cur], cnt);
-          cur = dg;
-          cnt = 1;
-        }
-      }
+      if (kv >= base && kv - base < width) sh.cand[atomicAdd(&sh.n_cand, 1)] = kv;
     }
-    if (cnt) atomicAdd(&hist[cur], cnt);
     __syncthreads();
-    if (wave == 0) {
-      // lane l covers bins 255-4l .. 252-4l (descending); scan from the top
-      const int h0 = hist[255 - 4 * lane], h1 = hist[254 - 4 * lane];
-      const int h2 = hist[253 - 4 * lane], h3 = hist[252 - 4 * lane];
-      const int sum = h0 + h1 + h2 + h3;
-      int incl = sum;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
+    if (tid < count) {
+      const uint32_t mine = sh.cand[tid];
+      int gt = 0, eq = 0;
+      for (int j = 0; j < count; j += 4) {
+        const uint4 c = *reinterpret_cast<const uint4*>(sh.cand + j);   // (zeros beyond count)
+        gt += (c.x > mine) + (c.y > mine) + (c.z > mine) + (c.w > mine);
+        eq += (c.x == mine) + (c.y == mine) + (c.z == mine) + (c.w == mine);
       }
-      const int excl = incl - sum;
-      if (excl < want && want <= incl) {
-        int a = excl, bin = 255 - 4 * lane;
-        if (a + h0 < want) { a += h0; --bin;
-          if (a + h1 < want) { a += h1; --bin;
-            if (a + h2 < want) { a += h2; --bin; } } }
-        sh_bin = bin;
-        sh_above = a;
+      if (gt < want && want <= gt + eq) {  // (equal candidates write the same values)
+        sh.threshold = mine;
+        sh.equal_wanted = want - gt;
       }
     }
     __syncthreads();
-    want -= sh_above;
-    prefix |= (uint32_t)sh_bin << shift;
-    mask |= 0xFFu << shift;
+    T = sh.threshold;
+    want = sh.equal_wanted;
   }
-  const uint32_t T = prefix;      // key of the ksel-th largest; take `want` of the keys equal to T
 
   // ---- emission in ascending position order ----
   int wg = 0, we = 0;
@@ -150,20 +275,26 @@ __global__ __launch_bounds__(SEL_THREADS, WAVES_PER_SIMD) void select_kernel(int
     wg += __popcll(__ballot(kv > T));
     we += __popcll(__ballot(kv == T));
   }
-  if (lane == 0) { wtot_gt[wave] = wg; wtot_eq[wave] = we; }
+  if (lane == 0) { sh.wave_total[0][wave] = wg; sh.wave_total[1][wave] = we; }
   __syncthreads();
-  int run_gt = 0, run_eq = 0;
-  for (int v = 0; v < wave; ++v) { run_gt += wtot_gt[v]; run_eq += wtot_eq[v]; }
+  int run_gt = lane < wave ? sh.wave_total[0][lane] : 0, run_eq = lane < wave ? sh.wave_total[1][lane] : 0;
+  run_gt = __builtin_amdgcn_readlane(wave_scan(run_gt), 15);
+  run_eq = __builtin_amdgcn_readlane(wave_scan(run_eq), 15);
   if constexpr (QUADS) {
     // ascending positions = (q, lane, c): before a lane's four come those of the lower lanes
 #pragma unroll
     for (int q4 = 0; q4 < ITEMS / 4; ++q4) {
-      uint64_t mg[4], me[4];
-      int g_before = run_gt, e_before = run_eq;
+      uint64_t mg[4], me[4], some = 0;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         mg[c] = __ballot(key[4 * q4 + c] > T);
         me[c] = __ballot(key[4 * q4 + c] == T);
+        some |= mg[c] | me[c];
+      }
+      if (some == 0) continue;             // (the same in every lane)
+      int g_before = run_gt, e_before = run_eq;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
         g_before += lanes_below(mg[c]);
         e_before += lanes_below(me[c]);
         run_gt += __popcll(mg[c]);
@@ -185,6 +316,7 @@ __global__ __launch_bounds__(SEL_THREADS, WAVES_PER_SIMD) void select_kernel(int
     const uint32_t kv = key_of(i);
     const bool gt = kv > T, eq = kv == T;
     const uint64_t mg = __ballot(gt), me = __ballot(eq);
+    if ((mg | me) == 0) continue;
     const int g_before = run_gt + lanes_below(mg);
     const int e_before = run_eq + lanes_below(me);
     if (gt || (eq && e_before < want)) out[g_before + min(e_before, want)] = seg0 + i * 64 + lane;
@@ -193,23 +325,11 @@ __global__ __launch_bounds__(SEL_THREADS, WAVES_PER_SIMD) void select_kernel(int
   }
 }
 
-template <int ITEMS>
+template <int THREADS, int ITEMS, bool QUADS>
 hipError_t launch_one(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
                       const InstTable& tab, int32_t* idx, hipStream_t st) {
-  // scores that are final (no pooling here) and whose rows start 16-byte aligned: four per load
-  constexpr bool CAN_QUAD = ITEMS > 0 && ITEMS % 4 == 0;
-  const bool quads = CAN_QUAD && pool == 1 && L % 4 == 0 && reinterpret_cast<uintptr_t>(scores) % 16 == 0;
-  const bool many = (long long)Hkv * n_inst >= SEL_MANY_WORKGROUPS;
-  const dim3 grid(Hkv, n_inst), block(SEL_THREADS);
-  if constexpr (CAN_QUAD) {
-    if (quads) {
-      if (many) hipLaunchKernelGGL((select_kernel<ITEMS, 8, true>), grid, block, 0, st, Hkv, L, keep, pool, avg, scores, tab, inst0, idx);
-      else hipLaunchKernelGGL((select_kernel<ITEMS, 4, true>), grid, block, 0, st, Hkv, L, keep, pool, avg, scores, tab, inst0, idx);
-      return hipGetLastError();
-    }
-  }
-  if (many) hipLaunchKernelGGL((select_kernel<ITEMS, 8, false>), grid, block, 0, st, Hkv, L, keep, pool, avg, scores, tab, inst0, idx);
-  else hipLaunchKernelGGL((select_kernel<ITEMS, 4, false>), grid, block, 0, st, Hkv, L, keep, pool, avg, scores, tab, inst0, idx);
+  hipLaunchKernelGGL((select_kernel<THREADS, ITEMS, QUADS>), dim3(Hkv, n_inst), dim3(THREADS), 0, st, Hkv, L, keep, pool, avg, scores,
+                     tab, inst0, idx);
   return hipGetLastError();
 }
 
@@ -235,11 +355,27 @@ hipError_t launch_sink_recent(int n_inst, int Hkv, int L, int n_sink, const Inst
 
 hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
                          const InstTable& tab, int32_t* idx, hipStream_t st) {
-  const int P = L - keep;
-  if (P <= 2 * SEL_THREADS) return launch_one<2>(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st);
-  if (P <= 8 * SEL_THREADS) return launch_one<8>(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st);
-  if (P <= 32 * SEL_THREADS) return launch_one<32>(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st);
-  return launch_one<0>(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st);
+  // The fewest registers that hold the prefix (a row may start three positions behind a 16-byte boundary).
+  // With many heads in the launch, small workgroups of which several share a compute unit: while one
+  // waits at a barrier or for its scores, another one works.
+  const int P = L - keep, most = P + (pool == 1 ? 3 : 0);
+  auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st); };
+  if (pool == 1) {
+    if ((long long)Hkv * n_inst >= SEL_MANY_WORKGROUPS) {
+      if (most <= 256 * 8) return at(launch_one<256, 8, true>);
+      if (most <= 256 * 32) return at(launch_one<256, 32, true>);
+      if (most <= 512 * 64) return at(launch_one<512, 64, true>);
+    }
+    if (most <= 1024 * 4) return at(launch_one<1024, 4, true>);
+    if (most <= 1024 * 8) return at(launch_one<1024, 8, true>);
+    if (most <= 1024 * 16) return at(launch_one<1024, 16, true>);
+    if (most <= 1024 * 32) return at(launch_one<1024, 32, true>);
+    return at(launch_one<1024, 0, false>);
+  }
+  if (most <= 1024 * 2) return at(launch_one<1024, 2, false>);
+  if (most <= 1024 * 8) return at(launch_one<1024, 8, false>);
+  if (most <= 1024 * 32) return at(launch_one<1024, 32, false>);
+  return at(launch_one<1024, 0, false>);
 }
 
 }  // namespace laq

@@ -1,0 +1,46 @@
+"""laq_select at the edges of its variants against the oracle's full sort (needs an MI355X)."""
+import pytest
+import torch
+
+import oracle
+from parity_util import split_packed
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+# (n, Hkv, L, W, budgets): prefixes around the sizes at which a variant ends (4096, 8192, 16384 and 32768 keys;
+# with many heads 2048, 8192 and 32768), rows that start 0 .. 3 scores behind a 16-byte boundary, and numbers of
+# wanted keys around those up to which a group of keys is a thread's, half or a quarter of it
+CASES = [
+    (1, 3, 4093 + 8, 8, [8 + 1, ]), (1, 3, 4096 + 8, 8, [8 + 1023]), (1, 3, 4097 + 8, 8, [8 + 1024]),
+    (1, 3, 8189 + 5, 5, [5 + 2049]), (1, 3, 16381 + 3, 3, [3 + 4097]), (1, 3, 16382 + 3, 3, [3 + 2048]),
+    (1, 3, 32765, 0, [1024]), (1, 3, 32766, 0, [1023]), (1, 3, 30011, 8, [1024]), (1, 2, 517, 16, [516]),
+    (400, 2, 2045 + 4, 4, [4 + 255, 4 + 2044]), (400, 2, 2046 + 4, 4, [4 + 256, 4 + 513]),
+    (400, 2, 8189 + 4, 4, [4 + 300, 4 + 4000]), (400, 2, 8190 + 4, 4, [4 + 512, 4 + 1100]),
+    (384, 2, 32765, 0, [512, 1500]), (384, 2, 32766, 0, [700, 2100]),
+]
+
+
+@pytest.mark.parametrize("values", ["spread", "few", "equal", "plateaus"])
+@pytest.mark.parametrize("n,Hkv,L,W,budgets", CASES)
+def test_select_at_the_edges_of_its_variants(n, Hkv, L, W, budgets, values):
+    import paper_2505_20334_amd as laq
+    print("case:", n, Hkv, L, W, budgets, values, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(L)
+    if values == "spread":                  # many orders of magnitude
+        s = torch.exp(6 * torch.randn(n, Hkv, L, generator=g, device=DEV))
+    elif values == "few":
+        s = torch.randint(0, 9, (n, Hkv, L), generator=g, device=DEV).float() / 7
+    elif values == "equal":
+        s = torch.full((n, Hkv, L), 0.25, device=DEV)
+    else:                                   # what the pooling makes of scores
+        s = torch.exp(torch.randn(n * Hkv, 1, L, generator=g, device=DEV))
+        s = torch.nn.functional.max_pool1d(s, 7, 1, 3).reshape(n, Hkv, L)
+    s = s.contiguous()
+    b = [budgets[i % len(budgets)] for i in range(n)]
+    idx = laq.laq_select(s, b, 1, W)
+    torch.cuda.synchronize()
+    parts = split_packed(idx.cpu(), b, Hkv, L)
+    for i in sorted({0, 1, n // 2, n - 1} & set(range(n))):
+        assert torch.equal(parts[i], oracle.select(s[i].cpu(), W, b[i])), i
