@@ -1,4 +1,5 @@
-"""Compile the HIP sources of the LAQ library for gfx950 into an in-tree shared object."""
+"""Compile the HIP sources of the LAQ library for gfx950, and the Python binding of its hot calls, into in-tree
+shared objects."""
 from __future__ import annotations
 
 import glob
@@ -9,6 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblaq.so")
+NATIVE = os.path.join(PKG, "_native.so")          # the binding of the calls in a model's loop
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -25,10 +27,10 @@ def sources():
 
 
 def needs_build() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    deps = sources() + glob.glob(os.path.join(CSRC, "*.cpp")) + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
     return any(os.path.getmtime(f) > t for f in deps)
 
 
@@ -57,8 +59,28 @@ def build(force: bool = True, verbose: bool = False) -> str:
         run([hipcc] + compile_flags + include + ["-c", "-o", obj, src])
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(8, len(sources()))) as pool:
+    def compile_native():
+        # host code only: CPython and torch headers, no GPU code (torch's libraries are in the process that loads it)
+        import sysconfig
+
+        import torch
+        from torch.utils.cpp_extension import include_paths, library_paths
+        tmp = NATIVE + ".tmp.%d" % os.getpid()
+        try:
+            run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-missing-field-initializers",
+                 "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", os.path.join(ROOT, "include")]
+                + ["-isystem" + p for p in include_paths()] + ["-isystem" + sysconfig.get_paths()["include"]]
+                + [os.path.join(CSRC, "laq_native.cpp")] + ["-L" + p for p in library_paths()]
+                + ["-lc10", "-ltorch_cpu", "-ltorch_python", "-o", tmp])
+            os.replace(tmp, NATIVE)
+        finally:
+            if os.path.exists(tmp):
+                os.remove(tmp)
+
+    with ThreadPoolExecutor(max_workers=min(8, len(sources()) + 1)) as pool:
+        native = pool.submit(compile_native)
         objs = list(pool.map(compile_one, sources()))
+        native.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     try:
         run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)

@@ -1,4 +1,8 @@
-"""ctypes binding of ``liblaq.so`` -- argument marshalling only.
+"""Binding of ``liblaq.so`` -- argument marshalling only.
+
+The three calls that sit in a model's loop (laq_evict, laq_decode_attention, laq_qcache_store) are
+marshalled by the extension module ``_native`` (csrc/laq_native.cpp); ctypes serves the others, and
+these three where an argument is out of the ordinary.
 
 Function names and argument meaning follow ``include/laq.h``.  Tensors are torch
 tensors that already live on the GPU (torch supplies device memory and the
@@ -15,6 +19,7 @@ import torch
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "liblaq.so")
 _lib: Optional[ctypes.CDLL] = None
+_native = None
 
 LAQ_F32, LAQ_BF16 = 0, 1
 LAQ_POOL_MAX, LAQ_POOL_AVG = 0, 1
@@ -44,10 +49,10 @@ def lib_path() -> str:
 def load_library() -> ctypes.CDLL:
     """Load the built library (building it first if nothing is built); raises if that is impossible --
     there is no fallback path."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
+    if not os.path.exists(_LIB_PATH) or not os.path.exists(os.path.join(_PKG, "_native.so")):
         # nothing built yet: build once (hipcc); there is no other way to run, so a failure is final
         try:
             from . import _build
@@ -89,6 +94,15 @@ def load_library() -> ctypes.CDLL:
     lib.laq_workspace_status.restype = i32
     lib.laq_score_kernel.argtypes = [sp]
     lib.laq_score_kernel.restype = i32
+    from . import _native as native
+
+    def address(name):
+        return ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+
+    native.bind(address("laq_evict"), address("laq_workspace_bytes"), address("laq_decode_attention"),
+                address("laq_decode_workspace_bytes"), address("laq_qcache_store"),
+                torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    _native = native
     _lib = lib
     return lib
 
@@ -361,7 +375,13 @@ def laq_recall(idx_pred: torch.Tensor, budget_pred: Sequence[int], idx_gold: tor
 
 def laq_qcache_store(q_cache: torch.Tensor, q_step: torch.Tensor, t: int, stream=None) -> torch.Tensor:
     """q_cache [n, Hq, W, d] (updated in place: rows [.., t, :] = q_step [n, Hq, d]); returns q_cache."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None:
+        got = _native.qcache_store(q_cache, q_step, t)
+        if got is not None:
+            if got is not q_cache:
+                raise LaqError(got, "laq_qcache_store")
+            return got
     _dev(q_cache, "q_cache"), _dev(q_step, "q_step")
     n, Hq, W, d = q_cache.shape
     if q_step.shape != (n, Hq, d) or q_step.dtype != q_cache.dtype:
@@ -379,7 +399,13 @@ def laq_decode_attention(q: torch.Tensor, k_c: torch.Tensor, v_c: torch.Tensor, 
     """q [n, Hq, d] and the packed k_c, v_c [rows, d] of laq_compact -> out [n, Hq, d] fp32: one new
     token's attention over the retained rows of its KV head.  split: let the library spread long
     caches over several workgroups (a workspace of laq_decode_workspace_bytes is made if ws is None)."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None:
+        got = _native.decode(q, k_c, v_c, budget, Hkv, L, scale, out, ws, split)
+        if got is not None:
+            if type(got) is int:
+                raise LaqError(got, "laq_decode_attention")
+            return got
     _dev(q, "q"), _dev(k_c, "k_c"), _dev(v_c, "v_c")
     n, Hq, d = q.shape
     total, _ = packed_rows(budget, Hkv, L)
@@ -453,7 +479,14 @@ def laq_evict(q_win: torch.Tensor, k: torch.Tensor, v: Optional[torch.Tensor], b
     want_scores=False (and no scores buffer): the library hands the scores over inside the workspace and
     None is returned in their place.  static_scratch=True calls laq_evict_static (the library's own scratch
     array instead of a workspace; every output buffer must then be passed in for the call to allocate nothing)."""
-    lib = load_library()
+    lib = _lib or load_library()
+    if stream is None and not static_scratch:
+        got = _native.evict(q_win, k, v, budget, pool_kernel, scale, scores, idx, k_out, v_out, ws, q_pos, keep, pool_mode,
+                            want_scores, block_table, L, choose)
+        if got is not None:
+            if type(got) is int:
+                raise LaqError(got, "laq_evict")
+            return got
     _dev(q_win, "q_win")
     n, Hq, W, d = q_win.shape
     n2, Hkv, L, d2, kvs, paged = _cache(k, "k", block_table, L)
