@@ -41,8 +41,6 @@ static int make_geom(const laq_shape* s, ScoreGeom* g, QueryPos* qp = nullptr) {
       if (last < qmin) qmin = last;
     }
     g->qmin = qmin;
-  } else if (qp && s->W <= MAX_QPOS) {
-    for (int w = 0; w < s->W; ++w) qp->last[w] = g->pos0 + w;
   }
   g->Rpad = (g->R + 31) / 32 * 32;
   g->nchunk = (s->L + CHUNK_ROWS - 1) / CHUNK_ROWS;
@@ -122,9 +120,28 @@ Workspace carve_workspace(const ScoreGeom& g, void* ws) {
   base += round256(heads * g.L * sizeof(float));
   w.fused = base;
   base += round256(fused_sync_bytes(g));
+  w.window = reinterpret_cast<int32_t*>(base - MAX_QPOS * sizeof(int32_t));   // (the end of that area, see make_plan() of the single-read kernel)
   w.ctr = reinterpret_cast<int*>(base);
   w.status = w.ctr + 8;
   return w;
+}
+
+// The positions of a long explicit window, from launch arguments to the workspace.
+__global__ void window_table_kernel(QueryPos qp, int W, int32_t* table) {
+  for (int w = threadIdx.x; w < W; w += blockDim.x) table[w] = qp.last[w];
+}
+
+// What the scoring kernels get of the window's positions.
+static hipError_t window_positions(const ScoreGeom& g, const QueryPos& qp, const Workspace& w, hipStream_t st, WindowPos* out) {
+  memset(out, 0, sizeof *out);
+  if (!g.explicit_pos) return hipSuccess;
+  if (g.W <= WINDOW_INLINE) {
+    memcpy(out->last, qp.last, g.W * sizeof(int32_t));
+    return hipSuccess;
+  }
+  out->table = w.window;
+  hipLaunchKernelGGL(window_table_kernel, dim3(1), dim3(256), 0, st, qp, g.W, w.window);
+  return hipGetLastError();
 }
 
 // Fill the per-instance table for instances [i0, i0+n) and return the largest Bk among them.
@@ -159,6 +176,14 @@ static void fill_compact_table(int Hkv, int L, int pieces_per_row, const int32_t
   *rows_after = row;
 }
 
+// The rows kept per KV head if that is the same number for instances i0 .. i0+n-1, else 0.
+static int uniform_rows(int L, const int32_t* budget, int i0, int n) {
+  const int bk = budget[i0] < L ? budget[i0] : L;
+  for (int i = 1; i < n; ++i)
+    if ((budget[i0 + i] < L ? budget[i0 + i] : L) != bk) return 0;
+  return bk;
+}
+
 static bool budgets_ok(const laq_shape* s, const ScoreGeom& g, const int32_t* budget) {
   if (!budget) return false;
   for (int i = 0; i < s->n_inst; ++i)
@@ -180,7 +205,7 @@ static int init_current_device(int* dev_out) {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return LAQ_ERR_DEVICE;
   if (dev_out) *dev_out = dev;
   if (scratch_of[dev].load(std::memory_order_acquire)) return LAQ_OK;
-  if (score_mfma_init(dev) != hipSuccess || score_fused_init(dev) != hipSuccess) return LAQ_ERR_DEVICE;
+  if (score_mfma_init(dev) != hipSuccess || score_fused_init(dev) != hipSuccess || score_tile_init() != hipSuccess) return LAQ_ERR_DEVICE;
   void* ptr = nullptr;
   if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return LAQ_ERR_DEVICE;
   scratch_of[dev].store(ptr, std::memory_order_release);
@@ -200,26 +225,27 @@ static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g) {
   return g.Rpad <= 64 && key_bytes >= (128LL << 20);
 }
 
-static int score_impl(const laq_shape* shape, const void* q_win, const void* k, int pool, float* scores,
-                      void* ws, size_t ws_bytes, hipStream_t st) {
-  ScoreGeom g;
-  QueryPos qp;
-  memset(&qp, 0, sizeof qp);
-  const int rc = make_geom(shape, &g, &qp);
-  if (rc != LAQ_OK) return rc;
-  KvLayout lay;
-  if (make_layout(shape, g, &lay) != LAQ_OK) return LAQ_ERR_INVALID;
-  if (!pool_ok(pool) || !q_win || !k || !scores) return LAQ_ERR_INVALID;
-  if (!ws || ws_bytes < workspace_bytes(g)) return LAQ_ERR_WORKSPACE;
+// Few enough chunks that each gets a workgroup of its own at once: the kernels that take one chunk each need
+// three launches where the streaming ones need five.
+static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
+  return shape->score_choice == LAQ_CHOOSE_AUTO && (long long)g.n_inst * g.Hkv * g.nchunk <= 512;
+}
+
+// Scores of a validated call into `scores`: pooled, or, with pool == 1, raw.
+static int score_checked(const laq_shape* shape, const ScoreGeom& g, const QueryPos& positions, const KvLayout& lay, const void* q_win,
+                         const void* k, int pool, float* scores, void* ws, hipStream_t st) {
   if (g.Hkv > 65535 || g.n_inst > 65535 || (long long)g.Hkv * g.n_inst > 0x7fffffffLL) return LAQ_ERR_UNSUPPORTED;
   if ((g.L + 255) / 256 > 65535) return LAQ_ERR_UNSUPPORTED;      // grid limit of the pooling kernel
   const int rc_init = init_current_device(nullptr);
   if (rc_init != LAQ_OK) return rc_init;
   const Workspace w = carve_workspace(g, ws);
-  hipError_t e;
+  WindowPos qp;
+  hipError_t e = window_positions(g, positions, w, st, &qp);
+  if (e != hipSuccess) return LAQ_ERR_DEVICE;
   const bool avg = pool_avg(shape) && pool > 1;
   const bool mfma = score_mfma_supported(g, lay, shape->dtype);
   const bool fused = SINGLE_READ_ENABLED && score_fused_supported(g, lay, shape->dtype) && single_read_wanted(shape, g);
+  const bool tile = !mfma || (!fused && tile_wanted(shape, g));
   // matrix cores: the single-read kernel where a team of workgroups can hold a head, else the two
   // streaming passes; both fuse the max pooling, the average goes through the raw-score plane
   auto score_on_matrix_cores = [&](int p, float* dst) -> hipError_t {
@@ -230,14 +256,27 @@ static int score_impl(const laq_shape* shape, const void* q_win, const void* k, 
     }
     return launch_score_mfma(g, qp, lay, p, q_win, k, dst, w, st);
   };
-  if (mfma && !avg) {
+  if (!tile && !avg) {
     e = score_on_matrix_cores(pool, scores);
   } else {
     float* raw = pool > 1 ? w.raw : scores;
-    e = mfma ? score_on_matrix_cores(1, raw) : launch_score_generic(g, qp, lay, shape->dtype, q_win, k, raw, w, st);
+    e = tile ? launch_score_tile(g, qp, lay, shape->dtype, q_win, k, raw, w, st) : score_on_matrix_cores(1, raw);
     if (e == hipSuccess && pool > 1) e = launch_pool(g, pool, avg, raw, scores, st);
   }
   return e == hipSuccess ? LAQ_OK : LAQ_ERR_DEVICE;
+}
+
+static int score_impl(const laq_shape* shape, const void* q_win, const void* k, int pool, float* scores,
+                      void* ws, size_t ws_bytes, hipStream_t st) {
+  ScoreGeom g;
+  QueryPos qp;
+  const int rc = make_geom(shape, &g, &qp);
+  if (rc != LAQ_OK) return rc;
+  KvLayout lay;
+  if (make_layout(shape, g, &lay) != LAQ_OK) return LAQ_ERR_INVALID;
+  if (!pool_ok(pool) || !q_win || !k || !scores) return LAQ_ERR_INVALID;
+  if (!ws || ws_bytes < workspace_bytes(g)) return LAQ_ERR_WORKSPACE;
+  return score_checked(shape, g, qp, lay, q_win, k, pool, scores, ws, st);
 }
 
 static int select_impl(const laq_shape* shape, const float* scores, const int32_t* budget, int pool,
@@ -250,10 +289,17 @@ static int select_impl(const laq_shape* shape, const float* scores, const int32_
   int64_t row = 0;
   for (int i0 = 0; i0 < shape->n_inst; i0 += MAX_INST_PER_LAUNCH) {
     const int n = shape->n_inst - i0 < MAX_INST_PER_LAUNCH ? shape->n_inst - i0 : MAX_INST_PER_LAUNCH;
-    InstTable tab;
-    memset(&tab, 0, sizeof tab);
-    fill_table(g.Hkv, g.L, budget, i0, n, row, &tab, &row);
-    if (launch_select(n, i0, g.Hkv, g.L, g.keep, pool, pool_avg(shape), scores, tab, idx, st) != hipSuccess) return LAQ_ERR_DEVICE;
+    hipError_t e;
+    if (const int bk = uniform_rows(g.L, budget, i0, n)) {
+      const UniformInst u{bk, row, (int64_t)g.Hkv * bk};
+      e = launch_select(n, i0, g.Hkv, g.L, g.keep, pool, pool_avg(shape), scores, u, idx, st);
+      row += n * u.per_inst;
+    } else {
+      InstTable tab;
+      fill_table(g.Hkv, g.L, budget, i0, n, row, &tab, &row);
+      e = launch_select(n, i0, g.Hkv, g.L, g.keep, pool, pool_avg(shape), scores, tab, idx, st);
+    }
+    if (e != hipSuccess) return LAQ_ERR_DEVICE;
   }
   return LAQ_OK;
 }
@@ -271,11 +317,17 @@ static int compact_impl(const laq_shape* shape, const void* k, const void* v, co
   int64_t row = 0;
   for (int i0 = 0; i0 < shape->n_inst; i0 += MAX_INST_PER_LAUNCH) {
     const int n = shape->n_inst - i0 < MAX_INST_PER_LAUNCH ? shape->n_inst - i0 : MAX_INST_PER_LAUNCH;
-    CompactTable tab;
-    memset(&tab, 0, sizeof tab);
-    fill_compact_table(g.Hkv, g.L, row_bytes >> 4, budget, i0, n, row, &tab, &row);
-    if (launch_compact(n, i0, g.Hkv, g.L, row_bytes, lay, k, v, idx, tab, k_out, v_out, st) != hipSuccess)
-      return LAQ_ERR_DEVICE;
+    hipError_t e;
+    if (const int bk = uniform_rows(g.L, budget, i0, n)) {
+      const UniformInst u{bk, row, (int64_t)g.Hkv * bk};
+      e = launch_compact(n, i0, g.Hkv, g.L, row_bytes, lay, k, v, idx, u, k_out, v_out, st);
+      row += n * u.per_inst;
+    } else {
+      CompactTable tab;
+      fill_compact_table(g.Hkv, g.L, row_bytes >> 4, budget, i0, n, row, &tab, &row);
+      e = launch_compact(n, i0, g.Hkv, g.L, row_bytes, lay, k, v, idx, tab, k_out, v_out, st);
+    }
+    if (e != hipSuccess) return LAQ_ERR_DEVICE;
   }
   return LAQ_OK;
 }
@@ -393,6 +445,46 @@ static int decode_impl(const laq_shape* shape, const void* q, const void* kc, co
   return flush() ? LAQ_OK : LAQ_ERR_DEVICE;
 }
 
+// Whether the selection kernel can do the pooling and the gather of this call along with the selection (one
+// workgroup per head: worth it where that is less work than the launches it saves).
+static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, int row_bytes) {
+  if ((pool - 1) / 2 > FINISH_MAX_HALF || g.P > FINISH_MAX_KEYS || (long long)g.n_inst * g.Hkv > FINISH_MAX_HEADS ||
+      shape->n_inst > MAX_INST_PER_LAUNCH)
+    return false;
+  int most = 0;
+  for (int i = 0; i < shape->n_inst; ++i) {
+    const int bk = budget[i] < g.L ? budget[i] : g.L;
+    if (bk > most) most = bk;
+  }
+  return (long long)most * row_bytes <= FINISH_MAX_GATHER;
+}
+
+// Pooling, selection and gather of a small call, from the raw scores.
+static int finish_checked(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const void* k, const void* v,
+                          const int32_t* budget, int pool, const float* raw, float* scores, int32_t* idx, void* k_out, void* v_out,
+                          hipStream_t st) {
+  const int eb = shape->dtype == LAQ_F32 ? 4 : 2;
+  FinishArgs fin;
+  fin.pooled = scores;
+  fin.k = static_cast<const char*>(k); fin.v = static_cast<const char*>(v);
+  fin.k_out = static_cast<char*>(k_out); fin.v_out = static_cast<char*>(v_out);
+  fin.inst_bytes = lay.inst * eb; fin.head_bytes = lay.head * eb;
+  fin.row_bytes = g.d * eb; fin.src_row_bytes = lay.row_bytes; fin.elem_bytes = eb;
+  fin.half = (pool - 1) / 2; fin.avg = pool_avg(shape) ? 1 : 0;
+  fin.lay = lay;
+  hipError_t e;
+  const int n = shape->n_inst;
+  if (const int bk = uniform_rows(g.L, budget, 0, n)) {
+    e = launch_finish(n, 0, g.Hkv, g.L, g.keep, raw, UniformInst{bk, 0, (int64_t)g.Hkv * bk}, idx, fin, st);
+  } else {
+    InstTable tab;
+    int64_t row = 0;
+    fill_table(g.Hkv, g.L, budget, 0, n, 0, &tab, &row);
+    e = launch_finish(n, 0, g.Hkv, g.L, g.keep, raw, tab, idx, fin, st);
+  }
+  return e == hipSuccess ? LAQ_OK : LAQ_ERR_DEVICE;
+}
+
 static int qcache_store_impl(const laq_shape* shape, const void* q_step, int t, void* q_cache, hipStream_t st) {
   ScoreGeom g;
   const int rc = make_geom(shape, &g);
@@ -488,7 +580,8 @@ static int evict_impl(const laq_shape* shape, const void* q_win, const void* k, 
                       size_t ws_bytes, bool use_static_scratch, hipStream_t st) {
   // validate everything first so that a rejected call has enqueued nothing
   laq::ScoreGeom g;
-  const int rc0 = laq::make_geom(shape, &g);
+  laq::QueryPos qp;
+  const int rc0 = laq::make_geom(shape, &g, &qp);
   if (rc0 != LAQ_OK) return rc0;
   if (!laq::pool_ok(pool_kernel) || !q_win || !k || !idx || !k_out ||
       !laq::budgets_ok(shape, g, budget) || ((v == nullptr) != (v_out == nullptr)))
@@ -504,8 +597,16 @@ static int evict_impl(const laq_shape* shape, const void* q_win, const void* k, 
     ws_bytes = (size_t)LAQ_STATIC_SCRATCH_BYTES;
   }
   if (!ws || ws_bytes < laq::workspace_bytes(g)) return LAQ_ERR_WORKSPACE;
-  if (!scores) scores = laq::carve_workspace(g, ws).pooled;      // the hand-over plane between the stages
-  int rc = laq::score_impl(shape, q_win, k, pool_kernel, scores, ws, ws_bytes, st);
+  const laq::Workspace w = laq::carve_workspace(g, ws);
+  if (!scores) scores = w.pooled;        // the hand-over plane between the stages
+  const int row_bytes = g.d * (shape->dtype == LAQ_F32 ? 4 : 2);
+  if (laq::finish_wanted(shape, g, budget, pool_kernel, row_bytes)) {
+    float* raw = pool_kernel > 1 ? w.raw : scores;
+    const int rc = laq::score_checked(shape, g, qp, lay, q_win, k, 1, raw, ws, st);
+    if (rc != LAQ_OK) return rc;
+    return laq::finish_checked(shape, g, lay, k, v, budget, pool_kernel, raw, scores, idx, k_out, v_out, st);
+  }
+  int rc = laq::score_checked(shape, g, qp, lay, q_win, k, pool_kernel, scores, ws, st);
   if (rc != LAQ_OK) return rc;
   rc = laq::select_impl(shape, scores, budget, 1, idx, st);
   if (rc != LAQ_OK) return rc;
@@ -529,9 +630,7 @@ int laq_init(void) { return laq::init_current_device(nullptr); }
 
 int laq_score_kernel(const laq_shape* shape) {
   laq::ScoreGeom g;
-  laq::QueryPos qp;
-  memset(&qp, 0, sizeof qp);
-  const int rc = laq::make_geom(shape, &g, &qp);
+  const int rc = laq::make_geom(shape, &g);
   if (rc != LAQ_OK) return rc;
   laq::KvLayout lay;
   if (laq::make_layout(shape, g, &lay) != LAQ_OK) return LAQ_ERR_INVALID;

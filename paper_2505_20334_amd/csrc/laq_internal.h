@@ -45,16 +45,21 @@ struct ScoreGeom {
   float scale2;  // scale * log2(e): logits are kept in base-2 units
 };
 
-// Last key each window query sees (already clamped to L-1); passed by value to the kernels.
-// Filled for every call with W <= MAX_QPOS (also with the trailing-window positions), so that the
-// matrix-core kernels only ever look positions up; longer trailing windows take the generic path,
-// which computes them.
-struct QueryPos {
+// Last key each window query sees, where positions are explicit (already clamped to L-1); passed by value
+// to the kernels.  Launch arguments cost host time per byte, so only short windows travel in them; a
+// longer one's table (up to MAX_QPOS entries) is written to the workspace first.
+constexpr int WINDOW_INLINE = 32;
+struct WindowPos {
+  int32_t last[WINDOW_INLINE];
+  const int32_t* table;
+};
+__device__ __forceinline__ int last_visible_key(const ScoreGeom& g, const WindowPos& qp, int w) {
+  if (!g.explicit_pos) return g.pos0 + w;
+  return g.W <= WINDOW_INLINE ? qp.last[w] : qp.table[w];
+}
+struct QueryPos {                          // host side
   int32_t last[MAX_QPOS];
 };
-__device__ __forceinline__ int last_visible_key(const ScoreGeom& g, const QueryPos& qp, int w) {
-  return g.explicit_pos ? qp.last[w] : g.pos0 + w;
-}
 
 // Workspace carving: [partials | row constants | raw scores]
 //   part:  float2 (m, z) per (instance, KV head, chunk, padded row): softmax statistics of a chunk
@@ -72,16 +77,41 @@ struct Workspace {
   float* pooled;
   void* fused;      // exchange memory of the single-read kernel (fused_sync_bytes)
   int* ctr;
+  int32_t* window;  // position table of a window longer than WINDOW_INLINE (MAX_QPOS entries)
   int* status;      // != 0 after a call whose single-read kernel gave up a wait (results invalid)
 };
 
 size_t workspace_bytes(const ScoreGeom& g);
 Workspace carve_workspace(const ScoreGeom& g, void* ws);
 
-// Per-instance output table for select / compact (passed by value as a kernel argument).
+// Where the rows of k and v lie: element strides between instances and KV heads, and between
+// consecutive key rows (row_bytes is the latter in bytes).  dense = [n_inst, Hkv, L, d].
+struct KvLayout {
+  int64_t inst, head, row;
+  int32_t row_bytes;
+  int32_t dense;
+  // paged cache (table != nullptr): key row j of instance i is row j % block_rows of block
+  // table[i * blocks_per_inst + j / block_rows]; blocks lie `block` elements apart, head / row are
+  // the strides inside a block, inst is not used
+  const int32_t* table;
+  int32_t blocks_per_inst;
+  int32_t block_rows;
+  int64_t block;
+};
+
+// Where the packed outputs of an instance lie, for select / compact (passed by value as a kernel argument):
+// a table, or, where all instances keep the same number of rows, its arithmetic.
 struct InstTable {
   int32_t bk[MAX_INST_PER_LAUNCH];      // rows kept per KV head
   int64_t row0[MAX_INST_PER_LAUNCH];    // first packed output row (sum of Hkv * Bk of earlier instances)
+  __device__ int rows(int i) const { return bk[i]; }
+  __device__ int64_t first(int i) const { return row0[i]; }
+};
+struct UniformInst {
+  int32_t bk;
+  int64_t row0, per_inst;
+  __device__ int rows(int) const { return bk; }
+  __device__ int64_t first(int i) const { return row0 + i * per_inst; }
 };
 // The gather's own table: its grid covers exactly the rows of every instance, so a workgroup finds
 // its instance by the first workgroup of each (blk0 ascending, blk0[n] = all workgroups).
@@ -90,6 +120,22 @@ struct CompactTable {
   int64_t row0[MAX_INST_PER_LAUNCH];
   int32_t blk0[MAX_INST_PER_LAUNCH + 1];
 };
+// What the selection kernel does besides where it finishes a small eviction in one launch: it pools the raw
+// scores (max or mean over half positions to either side), writes the pooled ones and gathers the rows it
+// has selected.
+struct FinishArgs {
+  float* pooled;
+  const char *k, *v;
+  char *k_out, *v_out;
+  int64_t inst_bytes, head_bytes;
+  int32_t row_bytes, src_row_bytes, elem_bytes;
+  int32_t half, avg;
+  KvLayout lay;
+};
+constexpr int FINISH_MAX_HALF = 4;         // widest pooling it does
+constexpr int FINISH_MAX_KEYS = 16 * 1024; // longest prefix
+constexpr int FINISH_MAX_HEADS = 256;      // one workgroup per head: more of them fill the device without it
+constexpr int FINISH_MAX_GATHER = 64 << 10;   // bytes of K rows per head: one compute unit copies them all
 
 // Pooled score at prefix position pos, the one arithmetic every pooling site uses: the
 // maximum over the part of the window inside [0, P), or (avg) the fp32 sum over it in
@@ -106,21 +152,6 @@ __device__ __forceinline__ float pool_window(const float* __restrict__ s, int po
   for (int i = lo; i <= hi; ++i) v = fmaxf(v, s[i]);
   return v;
 }
-
-// Where the rows of k and v lie: element strides between instances and KV heads, and between
-// consecutive key rows (row_bytes is the latter in bytes).  dense = [n_inst, Hkv, L, d].
-struct KvLayout {
-  int64_t inst, head, row;
-  int32_t row_bytes;
-  int32_t dense;
-  // paged cache (table != nullptr): key row j of instance i is row j % block_rows of block
-  // table[i * blocks_per_inst + j / block_rows]; blocks lie `block` elements apart, head / row are
-  // the strides inside a block, inst is not used
-  const int32_t* table;
-  int32_t blocks_per_inst;
-  int32_t block_rows;
-  int64_t block;
-};
 
 #ifdef __HIPCC__
 // Paged caches: element offset, from the pool's start, of the block that holds key row j of an
@@ -171,8 +202,9 @@ struct DecodeWhole {
 };
 
 // launchers (each returns hipGetLastError() after its last launch); `raw` receives unpooled scores
-hipError_t launch_score_generic(const ScoreGeom& g, const QueryPos& qp, const KvLayout& lay, int dtype, const void* q,
-                                const void* k, float* raw, const Workspace& ws, hipStream_t st);
+hipError_t launch_score_tile(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q,
+                             const void* k, float* raw, const Workspace& ws, hipStream_t st);
+hipError_t score_tile_init();
 hipError_t launch_row_constants(const ScoreGeom& g, const Workspace& ws, hipStream_t st);
 bool score_mfma_supported(const ScoreGeom& g, const KvLayout& lay, int dtype);
 // kernel attributes and residency of every matrix-core scoring kernel on device `dev`, which must be
@@ -183,17 +215,23 @@ size_t fused_sync_bytes(const ScoreGeom& g);
 bool score_fused_supported(const ScoreGeom& g, const KvLayout& lay, int dtype);
 hipError_t score_fused_applies(const ScoreGeom& g, const KvLayout& lay, int dtype, bool* yes);
 // single-read scoring (K streamed once); *done = false: not launched, take the two-pass kernels
-hipError_t launch_score_fused(const ScoreGeom& g, const QueryPos& qp, const KvLayout& lay, int pool, const void* q,
+hipError_t launch_score_fused(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const void* q,
                               const void* k, float* scores, const Workspace& ws, hipStream_t st, bool* done);
 // pooled scores of the prefix keys within `half` of a boundary between two chunks of chunk_rows keys,
 // from the chunks' edge records
 hipError_t launch_pool_boundaries(const ScoreGeom& g, int half, int nchunk, int chunk_rows, const float* edge,
                                   float* scores, hipStream_t st);
-hipError_t launch_score_mfma(const ScoreGeom& g, const QueryPos& qp, const KvLayout& lay, int pool, const void* q,
+hipError_t launch_score_mfma(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const void* q,
                              const void* k, float* scores, const Workspace& ws, hipStream_t st);
 hipError_t launch_pool(const ScoreGeom& g, int pool, bool avg, const float* raw, float* pooled, hipStream_t st);
 hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
                          const InstTable& tab, int32_t* idx, hipStream_t st);
+hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
+                         const UniformInst& tab, int32_t* idx, hipStream_t st);
+hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const InstTable& tab, int32_t* idx,
+                         const FinishArgs& fin, hipStream_t st);
+hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const UniformInst& tab, int32_t* idx,
+                         const FinishArgs& fin, hipStream_t st);
 hipError_t launch_sink_recent(int n_inst, int Hkv, int L, int n_sink, const InstTable& tab, int32_t* idx,
                               hipStream_t st);
 hipError_t launch_recall(int n_inst, int inst0, int Hkv, const PairTable& tab, const int32_t* idx_pred,
@@ -210,6 +248,9 @@ hipError_t launch_qcache_store(long long rows, int W, int t, int row_bytes, cons
 constexpr int COMPACT_THREADS = 256;      // one 16-byte piece of an output row per thread
 hipError_t launch_compact(int n_inst, int inst0, int Hkv, int L, int row_bytes, const KvLayout& lay,
                           const void* k, const void* v, const int32_t* idx, const CompactTable& tab, void* k_out,
+                          void* v_out, hipStream_t st);
+hipError_t launch_compact(int n_inst, int inst0, int Hkv, int L, int row_bytes, const KvLayout& lay,
+                          const void* k, const void* v, const int32_t* idx, const UniformInst& tab, void* k_out,
                           void* v_out, hipStream_t st);
 
 }  // namespace laq

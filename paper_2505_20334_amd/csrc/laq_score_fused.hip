@@ -340,7 +340,7 @@ struct FusedPlan {
 };
 
 template <int NRT, bool PAGED>
-__global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, QueryPos qp, FusedPlan plan, KvLayout lay,
+__global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, WindowPos qp, FusedPlan plan, KvLayout lay,
                                                              const uint16_t* __restrict__ q,
                                                              const uint16_t* __restrict__ k,
                                                              float* __restrict__ scores, float* __restrict__ edge,
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, QueryP
   w.last = last_lds;
   w.stage = smem + S::OFF_STAGE + wave * TILE_BYTES;
   // rows beyond R (zero queries) see every key; their weight is zero
-  for (int r = tid; r < ROWS; r += F_THREADS) last_lds[r] = r < g.R ? qp.last[r % g.W] : g.L - 1;
+  for (int r = tid; r < ROWS; r += F_THREADS) last_lds[r] = r < g.R ? last_visible_key(g, qp, r % g.W) : g.L - 1;
   if (tid < 2 * MAX_HALF) raw_lds[tid < MAX_HALF ? tid - MAX_HALF : KEYS_PER_BLOCK + tid - MAX_HALF] = 0.f;
   if (tid == 0) gave_up[0] = 0;
 
@@ -765,13 +765,14 @@ bool make_plan(const ScoreGeom& g, int pool, int resident, FusedPlan* out) {
   plan.n_teams = resident / plan.T;
   if (plan.n_teams > plan.n_heads) plan.n_teams = plan.n_heads;
   // the exchange memory is sized for FUSED_MAX_RESIDENT workgroups
-  if ((size_t)plan.n_teams * plan.T > (size_t)FUSED_MAX_RESIDENT) return false;
+  // (less the last 2 KiB of it, which hold the position table of a long window)
+  if ((size_t)plan.n_teams * plan.T > (size_t)FUSED_MAX_RESIDENT - 8) return false;
   *out = plan;
   return true;
 }
 
 template <int NRT>
-hipError_t launch_fused_rows(const ScoreGeom& g, const QueryPos& qp, const KvLayout& lay, int pool, const uint16_t* q,
+hipError_t launch_fused_rows(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const uint16_t* q,
                              const uint16_t* k,
                              float* scores, const Workspace& ws, hipStream_t st, bool* done) {
   *done = false;
@@ -792,7 +793,7 @@ hipError_t launch_fused_rows(const ScoreGeom& g, const QueryPos& qp, const KvLay
                      reinterpret_cast<uint4*>(sy.stats), n16, sy.status);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   ScoreGeom gg = g;
-  QueryPos qq = qp;
+  WindowPos qq = qp;
   KvLayout ll = lay;
   float* edge = ws.raw;
   const void* fn = lay.table ? reinterpret_cast<const void*>(&fused_kernel<NRT, true>)
@@ -860,7 +861,7 @@ hipError_t score_fused_applies(const ScoreGeom& g, const KvLayout& lay, int dtyp
 // Scores of every head into `scores`: raw with pool == 1, else max-pooled over the prefix.  *done
 // says whether the kernels were launched: when the device cannot hold a team (very long heads) or
 // has no cooperative launch they are not, and the caller takes the two-pass path.
-hipError_t launch_score_fused(const ScoreGeom& g, const QueryPos& qp, const KvLayout& lay, int pool, const void* q,
+hipError_t launch_score_fused(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const void* q,
                               const void* k, float* scores, const Workspace& ws, hipStream_t st, bool* done) {
   const uint16_t* qq = static_cast<const uint16_t*>(q);
   const uint16_t* kk = static_cast<const uint16_t*>(k);

@@ -344,11 +344,11 @@ __device__ __forceinline__ void pass2_pipe(const char* ldsK, const bf16x8 (&qreg
 // j <= last_visible_key(w); a masked logit enters as -inf through the accumulator's initial value.
 template <int D>
 __device__ __forceinline__ void pass1_masked(const char* ldsK, const bf16x8 (&qreg)[Tile<D>::KSTEPS],
-                                             const ScoreGeom& g, const QueryPos& qp, int rt, int kt0, int kt1,
+                                             const ScoreGeom& g, const WindowPos& qp, int rt, int kt0, int kt1,
                                              int j0, int lane, float& m_run, float& z_run) {
   const int hf = lane >> 5;
   const int w = (rt * 32 + (lane & 31)) % g.W;
-  const int t_hi = qp.last[w] - j0;       // last staged row this lane's score row may see
+  const int t_hi = last_visible_key(g, qp, w) - j0;       // last staged row this lane's score row may see
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int kt = kt0; kt < kt1; ++kt) {
     const int t0 = kt * 32;
@@ -375,7 +375,7 @@ __device__ __forceinline__ void pass1_masked(const char* ldsK, const bf16x8 (&qr
 
 template <int D>
 __device__ __forceinline__ void pass2_masked(const char* ldsK, const bf16x8 (&qreg)[Tile<D>::KSTEPS],
-                                             const ScoreGeom& g, const QueryPos& qp, const float (&c)[16], int rt,
+                                             const ScoreGeom& g, const WindowPos& qp, const float (&c)[16], int rt,
                                              int kt0, int kt1, int j0, int lane, float* slotbuf, bool first) {
   const int hf = lane >> 5, n = lane & 31;
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -388,7 +388,7 @@ __device__ __forceinline__ void pass2_masked(const char* ldsK, const bf16x8 (&qr
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int w = (rt * 32 + acc_row(i, hf)) % g.W;
-        bias[i] = (j <= qp.last[w]) ? 0.f : -INFINITY;
+        bias[i] = (j <= last_visible_key(g, qp, w)) ? 0.f : -INFINITY;
       }
       acc = tile_product<D, false>(ldsK, kt, lane, qreg, bias);
     } else {
@@ -417,7 +417,7 @@ __device__ __forceinline__ void pass2_masked(const char* ldsK, const bf16x8 (&qr
 // this thread holds one, for out[idx_out]): the caller stores them after it has moved the next
 // chunk's rows into LDS, so that the wait for those rows is not also a wait for the store.
 template <int D, int NRT, typename KR>
-__device__ __forceinline__ bool chunk_pass1(char* smem, const ScoreGeom& g, const QueryPos& qp,
+__device__ __forceinline__ bool chunk_pass1(char* smem, const ScoreGeom& g, const WindowPos& qp,
                                             const uint16_t* __restrict__ qg,
                                             bf16x8 (&qreg)[Tile<D>::KSTEPS], bool reload, int j0, int tid, int lane,
                                             int wave, float2* __restrict__ out, int& idx_out, float2& mz_out,
@@ -483,7 +483,7 @@ __device__ __forceinline__ bool chunk_pass1(char* smem, const ScoreGeom& g, cons
 // record, value r_out, when the function sets edge_out) and pool_boundaries_kernel pools those
 // keys from the records.  c points at the head's row constants.
 template <int D, int NRT, typename KR>
-__device__ __forceinline__ bool chunk_pass2(char* smem, const ScoreGeom& g, const QueryPos& qp, int half,
+__device__ __forceinline__ bool chunk_pass2(char* smem, const ScoreGeom& g, const WindowPos& qp, int half,
                                             bool edges,
                                             const uint16_t* __restrict__ qg, const float* __restrict__ c,
                                             bf16x8 (&qreg)[Tile<D>::KSTEPS], float (&cr)[16], bool reload, int j0,
@@ -610,7 +610,7 @@ struct StreamPlan {
 };
 
 template <int D, int NRT, int PASS, bool STRIDED>
-__global__ __launch_bounds__(THREADS, MFMA_BLOCKS) void stream_kernel(ScoreGeom g, QueryPos qp, int half,
+__global__ __launch_bounds__(THREADS, MFMA_BLOCKS) void stream_kernel(ScoreGeom g, WindowPos qp, int half,
                                                                       StreamPlan plan, KvLayout lay,
                                                                       const uint16_t* __restrict__ q,
                                                             const uint16_t* __restrict__ k,
@@ -835,7 +835,7 @@ hipError_t init_variant(int dev, int cus) {
 }
 
 template <int D, int NRT, bool STRIDED>
-hipError_t launch_stream(const ScoreGeom& g, const QueryPos& qp, const KvLayout& lay, int pool, const uint16_t* q,
+hipError_t launch_stream(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const uint16_t* q,
                          const uint16_t* k, float* scores, const Workspace& ws, hipStream_t st) {
   constexpr int bytes = Smem<D, NRT>::BYTES;
   int dev = 0;
@@ -880,9 +880,7 @@ hipError_t launch_stream(const ScoreGeom& g, const QueryPos& qp, const KvLayout&
                      ws.part,
                      (const float*)nullptr, (float*)nullptr, ws.ctr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(row_constants_mfma_kernel, dim3((unsigned)n_heads, g.Rpad / 32), dim3(256), 0, st, gm, ws.part,
-                     ws.rowc, ws.status);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_row_constants(gm, ws, st)) != hipSuccess) return e;
   // (the edge records, at most 124 floats per 256-key chunk and only written when a head has more
   // than one chunk, fit the workspace's raw-score area of L floats per head)
   hipLaunchKernelGGL((stream_kernel<D, NRT, 2, STRIDED>), dim3(grid2), dim3(THREADS), bytes, st, g, qp, half, p2, lay, q, k,
@@ -893,7 +891,7 @@ hipError_t launch_stream(const ScoreGeom& g, const QueryPos& qp, const KvLayout&
 }
 
 template <int D, bool STRIDED>
-hipError_t launch_for_rows(const ScoreGeom& g, const QueryPos& qp, const KvLayout& lay, int pool, const uint16_t* q,
+hipError_t launch_for_rows(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const uint16_t* q,
                            const uint16_t* k, float* scores, const Workspace& ws, hipStream_t st) {
   const int ntile = g.Rpad / 32;
   if (ntile == 1) return launch_stream<D, 1, STRIDED>(g, qp, lay, pool, q, k, scores, ws, st);
@@ -910,6 +908,14 @@ hipError_t launch_pool_boundaries(const ScoreGeom& g, int half, int nchunk, int 
   if (items <= 0) return hipSuccess;
   hipLaunchKernelGGL(pool_boundaries_kernel, dim3((unsigned)n_heads, (items + 255) / 256), dim3(256), 0, st, g.L, g.P,
                      half, nchunk, chunk_rows, edge, scores);
+  return hipGetLastError();
+}
+
+// c = M + log2 Z of every score row from the chunks' statistics
+hipError_t launch_row_constants(const ScoreGeom& g, const Workspace& ws, hipStream_t st) {
+  const long long n_heads = (long long)g.n_inst * g.Hkv;
+  hipLaunchKernelGGL(row_constants_mfma_kernel, dim3((unsigned)n_heads, g.Rpad / 32), dim3(256), 0, st, g, ws.part, ws.rowc,
+                     ws.status);
   return hipGetLastError();
 }
 
@@ -937,7 +943,7 @@ bool score_mfma_supported(const ScoreGeom& g, const KvLayout& lay, int dtype) {
          ((long long)(lay.table ? lay.block_rows : g.L) + MFMA_ROWS) * lay.row_bytes < 0x7fffffffLL;
 }
 
-hipError_t launch_score_mfma(const ScoreGeom& g, const QueryPos& qp, const KvLayout& lay, int pool, const void* q,
+hipError_t launch_score_mfma(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const void* q,
                              const void* k, float* scores, const Workspace& ws, hipStream_t st) {
   const uint16_t* qq = static_cast<const uint16_t*>(q);
   const uint16_t* kk = static_cast<const uint16_t*>(k);

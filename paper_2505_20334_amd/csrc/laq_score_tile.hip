@@ -1,0 +1,334 @@
+// Scoring, one 256-key chunk per workgroup: every head size up to 256 and any number of score rows, fp32 or
+// bf16, on the matrix cores (v_mfma_f32_32x32x2_f32, v_mfma_f32_32x32x16_bf16: products of the stored values,
+// fp32 sums).  Used for fp32 caches and head sizes other than 64 and 128, and for small bf16 calls, which
+// the streaming kernels' set-up, combine and pooling launches would bound.
+//
+// Two kernels: (1) per-row softmax statistics (m, z) of each chunk, (2) after folding the statistics of a
+// head's chunks (by every workgroup itself when they are few, else by row_constants_kernel), the sum over
+// the rows of exp2(s - c): raw scores.  Also here: the sequence pooling over raw scores.
+//
+// A wave holds 32 key rows in registers in operand layout (lane l: row l % 32, the 16-byte pieces 2t + l / 32)
+// and walks the score rows in tiles of 32 that the workgroup stages in LDS, one tile ahead.  The reduction
+// index of a product may run in any order as long as both operands agree, so fp32 takes the four elements
+// of a piece in four instructions: lanes below 32 supply elements 8g + j, the others 8g + 4 + j.
+//   (1) D = K * Q^T: lane = score row, registers = 16 keys: maximum and sum in registers.
+//   (2) D = Q * K^T: lane = key, registers = 16 rows: the sum over the rows in registers.
+//
+// What bounds it: for fp32 the matrix cores (157 TFLOP/s dense), which do the product twice; the vector ALU
+// kernels that stood here took 8 us per (million keys x score row) and pass pair, these about 1.  64 heads x
+// 8191 keys, d = 128, 64 score rows, fp32: 1018 -> 190 us.
+#include "laq_internal.h"
+
+namespace laq {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr float NEG_BIG = -1.0e30f;   // finite "minus infinity" for running maxima
+constexpr int WAVES = CHUNK_ROWS / 32, THREADS = WAVES * 64;
+// Chunks of a head up to which every workgroup of the second kernel folds the statistics itself: beyond, it
+// would read more of them than of keys.
+constexpr int FOLD_CHUNKS = 32;
+
+// Row index (0..31) of accumulator register i for a lane in half hf of the 32x32 output layout.
+__device__ __forceinline__ int acc_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
+
+// bytes between rows of the staged score rows: an odd number of 16-byte pieces, so that 128-bit reads of 16
+// consecutive rows fall on distinct banks
+__host__ __device__ inline int q_stride(int row_bytes) { return row_bytes % 32 == 0 ? row_bytes + 16 : row_bytes; }
+
+// acc += A * B over one piece (16 bytes) per lane of either operand
+__device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 acc, uint16_t) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 acc, float) {
+  const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[j], y[j], acc, 0, 0, 0);
+  return acc;
+}
+
+// What both kernels do around their products.  NP: pairs of 16-byte pieces a row may have (32 bytes each).
+template <typename T, int NP> struct Chunk {
+  u32x4 key[NP];           // this lane's pieces of its key row
+  int np;                  // pairs of pieces a row has, the last one possibly half
+  int row_bytes, stride;   // of a score row in memory / in LDS
+  int lane, hf, n32, wave, j0;
+
+  __device__ __forceinline__ void load_keys(const ScoreGeom& g, const KvLayout& lay, const T* __restrict__ k, int chunk,
+                                            int head, int inst) {
+    const int tid = threadIdx.x;
+    lane = tid & 63; hf = lane >> 5; n32 = lane & 31; wave = tid >> 6;
+    row_bytes = g.d * (int)sizeof(T);
+    stride = q_stride(row_bytes);
+    np = (row_bytes + 31) / 32;
+    j0 = chunk * CHUNK_ROWS;
+    int64_t off = (int64_t)inst * lay.inst;
+    int r0 = j0;
+    if (lay.table) off = paged_block_offset(lay, inst, j0, &r0);      // (a block holds whole chunks)
+    const int row = wave * 32 + n32;
+    const char* p = reinterpret_cast<const char*>(k + off + (int64_t)head * lay.head + (int64_t)(r0 + row) * lay.row);
+    const bool there = j0 + row < g.L;
+#pragma unroll
+    for (int t = 0; t < NP; ++t) {
+      key[t] = u32x4{0u, 0u, 0u, 0u};
+      if (there && (2 * t + hf) * 16 < row_bytes) key[t] = *reinterpret_cast<const u32x4*>(p + (2 * t + hf) * 16);
+    }
+  }
+  // score rows rt * 32 .. + 31 of the group (rows beyond R: zeros), memory -> registers -> LDS
+  static constexpr int PER_THREAD = (32 * NP * 2 + THREADS - 1) / THREADS;
+  __device__ __forceinline__ void fetch_rows(u32x4 (&v)[PER_THREAD], const T* __restrict__ qg, int R, int rt) const {
+    const int per_row = row_bytes >> 4;
+#pragma unroll
+    for (int i = 0; i < PER_THREAD; ++i) {
+      const int p = threadIdx.x + i * THREADS, row = p / per_row, col = p - row * per_row;
+      v[i] = u32x4{0u, 0u, 0u, 0u};
+      if (row < 32 && rt * 32 + row < R)
+        v[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(qg) + (size_t)(rt * 32 + row) * row_bytes + col * 16);
+    }
+  }
+  __device__ __forceinline__ void stage_rows(char* lds, const u32x4 (&v)[PER_THREAD]) const {
+    const int per_row = row_bytes >> 4;
+#pragma unroll
+    for (int i = 0; i < PER_THREAD; ++i) {
+      const int p = threadIdx.x + i * THREADS, row = p / per_row, col = p - row * per_row;
+      if (row < 32) *reinterpret_cast<u32x4*>(lds + row * stride + col * 16) = v[i];
+    }
+  }
+  template <bool KEYS_AS_ROWS>
+  __device__ __forceinline__ f32x16 product(const char* lds) const {
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 acc = zero;
+    const char* p = lds + n32 * stride + hf * 16;
+#pragma unroll
+    for (int t = 0; t < NP; ++t) {
+      if (t < np) {                                      // (the same in every lane)
+        u32x4 q = {0u, 0u, 0u, 0u};
+        if ((2 * t + hf) * 16 < row_bytes) q = *reinterpret_cast<const u32x4*>(p + t * 32);
+        acc = KEYS_AS_ROWS ? mma(key[t], q, acc, T()) : mma(q, key[t], acc, T());
+      }
+    }
+    return acc;
+  }
+};
+
+// Pass 1: part[head][chunk][row] = (m, z) of a score row over the chunk's visible keys, in log2 units.
+template <typename T, int NP>
+__global__ __launch_bounds__(THREADS) void tile_stats_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, const T* __restrict__ q,
+                                                             const T* __restrict__ k, float2* __restrict__ part) {
+  extern __shared__ __align__(16) char smem[];           // two tiles of score rows
+  __shared__ float2 stat[WAVES][32];
+  const int chunk = blockIdx.x, head = blockIdx.y, inst = blockIdx.z, tid = threadIdx.x;
+  Chunk<T, NP> c;
+  c.load_keys(g, lay, k, chunk, head, inst);
+  const T* qg = q + ((size_t)inst * g.Hq + (size_t)head * g.G) * g.W * g.d;
+  float2* out = part + (((size_t)inst * g.Hkv + head) * g.nchunk + chunk) * g.Rpad;
+  const int ntile = g.Rpad / 32, tile_bytes = 32 * c.stride;
+  u32x4 v[Chunk<T, NP>::PER_THREAD];
+  c.fetch_rows(v, qg, g.R, 0);
+  c.stage_rows(smem, v);
+  const int k0 = c.j0 + c.wave * 32;                     // the wave's first key
+  const bool plain = k0 + 31 <= g.qmin;                  // seen by every row
+  for (int rt = 0; rt < ntile; ++rt) {
+    if (rt + 1 < ntile) c.fetch_rows(v, qg, g.R, rt + 1);
+    __syncthreads();
+    f32x16 s = c.template product<true>(smem + (rt & 1) * tile_bytes);
+    if (!plain) {
+      const int row = rt * 32 + c.n32, last = row < g.R ? last_visible_key(g, qp, row % g.W) : g.L - 1;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (k0 + acc_row(i, c.hf) > last) s[i] = -INFINITY;
+    }
+    float m = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) m = fmaxf(m, s[i]);
+    m = fmaxf(m, __shfl_xor(m, 32));
+    m = fmaxf(m, NEG_BIG) * g.scale2;                    // (the logit scale is positive)
+    float z = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f(fmaf(s[i], g.scale2, -m));
+    z += __shfl_xor(z, 32);
+    if (c.hf == 0) stat[c.wave][c.n32] = make_float2(m, z);
+    if (rt + 1 < ntile) c.stage_rows(smem + ((rt + 1) & 1) * tile_bytes, v);
+    __syncthreads();
+    if (tid < 32) {
+      float M = stat[0][tid].x, Z = 0.f;
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) M = fmaxf(M, stat[w][tid].x);
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) Z = fmaf(stat[w][tid].y, __builtin_amdgcn_exp2f(stat[w][tid].x - M), Z);
+      out[rt * 32 + tid] = make_float2(M, Z);
+    }
+  }
+}
+
+// c = M + log2 Z of the score rows rt * 32 .. + 31 from the statistics of all chunks of the head: thread
+// (sub, row) takes the chunks sub, sub + WAVES * 2, ...; fixed order.
+__device__ __forceinline__ void fold_rows(const ScoreGeom& g, const float2* __restrict__ part, int rt, float2 (*fold)[32], float* rowc) {
+  const int tid = threadIdx.x, row = tid & 31, sub = tid >> 5;
+  float M = NEG_BIG, Z = 0.f;
+  for (int ch = sub; ch < g.nchunk; ch += WAVES * 2) {
+    const float2 mz = part[(size_t)ch * g.Rpad + rt * 32 + row];
+    const float Mn = fmaxf(M, mz.x);
+    Z = Z * __builtin_amdgcn_exp2f(M - Mn) + mz.y * __builtin_amdgcn_exp2f(mz.x - Mn);
+    M = Mn;
+  }
+  fold[sub][row] = make_float2(M, Z);
+  __syncthreads();
+  if (tid < 32) {
+    M = fold[0][tid].x; Z = 0.f;
+#pragma unroll
+    for (int w = 1; w < WAVES * 2; ++w) M = fmaxf(M, fold[w][tid].x);
+#pragma unroll
+    for (int w = 0; w < WAVES * 2; ++w) Z = fmaf(fold[w][tid].y, __builtin_amdgcn_exp2f(fold[w][tid].x - M), Z);
+    rowc[tid] = rt * 32 + tid < g.R ? M + __builtin_amdgcn_logf(Z) : 1.0e30f;      // rows beyond R: probability 0
+  }
+}
+
+// Pass 2: raw[j] = sum over the score rows of exp2(s - c[row]) for the keys of the chunk.  rowc_all: the
+// heads' row constants, or null: folded here.
+template <typename T, int NP>
+__global__ __launch_bounds__(THREADS) void tile_score_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, const T* __restrict__ q,
+                                                             const T* __restrict__ k, const float2* __restrict__ part,
+                                                             const float* __restrict__ rowc_all, float* __restrict__ raw,
+                                                             int* __restrict__ status) {
+  extern __shared__ __align__(16) char smem[];           // two tiles of score rows
+  __shared__ __align__(16) float rowc[2][32];
+  __shared__ float2 fold[WAVES * 2][32];
+  const int chunk = blockIdx.x, head = blockIdx.y, inst = blockIdx.z, tid = threadIdx.x;
+  const size_t hg = (size_t)inst * g.Hkv + head;
+  if (chunk == 0 && hg == 0 && tid == 0) *status = 0;    // (these kernels have no wait to give up)
+  Chunk<T, NP> c;
+  c.load_keys(g, lay, k, chunk, head, inst);
+  const T* qg = q + ((size_t)inst * g.Hq + (size_t)head * g.G) * g.W * g.d;
+  const int ntile = g.Rpad / 32, tile_bytes = 32 * c.stride;
+  u32x4 v[Chunk<T, NP>::PER_THREAD];
+  auto constants = [&](int rt) {
+    if (rowc_all == nullptr) fold_rows(g, part + hg * g.nchunk * g.Rpad, rt, fold, rowc[rt & 1]);
+    else if (tid < 32) rowc[rt & 1][tid] = rowc_all[hg * g.Rpad + rt * 32 + tid];
+  };
+  c.fetch_rows(v, qg, g.R, 0);
+  c.stage_rows(smem, v);
+  constants(0);
+  const int k0 = c.j0 + c.wave * 32, key = k0 + c.n32;
+  const bool plain = k0 + 31 <= g.qmin;
+  float sum = 0.f;
+  for (int rt = 0; rt < ntile; ++rt) {
+    if (rt + 1 < ntile) c.fetch_rows(v, qg, g.R, rt + 1);
+    __syncthreads();
+    f32x16 s = c.template product<false>(smem + (rt & 1) * tile_bytes);
+    if (!plain) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int row = rt * 32 + acc_row(i, c.hf);
+        if (key > (row < g.R ? last_visible_key(g, qp, row % g.W) : g.L - 1)) s[i] = -INFINITY;
+      }
+    }
+    const float* rc = rowc[rt & 1];
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      const f32x4 cc = *reinterpret_cast<const f32x4*>(rc + 8 * gq + 4 * c.hf);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + j], g.scale2, -cc[j]));
+    }
+    if (rt + 1 < ntile) {
+      c.stage_rows(smem + ((rt + 1) & 1) * tile_bytes, v);
+      constants(rt + 1);
+    }
+  }
+  sum += __shfl_xor(sum, 32);
+  if (c.hf == 0 && key < g.L) raw[hg * g.L + key] = sum;
+}
+
+// pooled[j] = max (or mean) of raw[i], |i - j| <= half, 0 <= i < P, for prefix keys; the kept
+// trailing columns are copied.  A workgroup stages POOL_TILE scores plus the window margins in
+// LDS, with zeros for positions outside the prefix: the scores are sums of probabilities, never
+// negative, so a zero leaves a maximum alone, and it leaves the ascending fp32 sum of the average
+// bit-identical to pool_window()'s sum over the clipped window.  grid.x walks the (instance, KV
+// head) pairs.
+constexpr int POOL_TILE = 1024;
+__global__ __launch_bounds__(256) void pool_kernel(int L, int P, int half, bool avg, const float* __restrict__ raw,
+                                                   float* __restrict__ pooled) {
+  __shared__ float tile[POOL_TILE + MAX_POOL - 1];
+  const float* r = raw + (size_t)blockIdx.x * L;
+  float* out = pooled + (size_t)blockIdx.x * L;
+  const int j0 = blockIdx.y * POOL_TILE;
+  for (int t = threadIdx.x; t < POOL_TILE + 2 * half; t += 256) {
+    const int i = j0 - half + t;
+    tile[t] = (i >= 0 && i < P) ? r[i] : 0.f;
+  }
+  __syncthreads();
+  const float kernel_size = (float)(2 * half + 1);
+  for (int t = threadIdx.x; t < POOL_TILE && j0 + t < L; t += 256) {
+    const int j = j0 + t;
+    float v;
+    if (j >= P) {
+      v = r[j];
+    } else if (avg) {
+      float acc = 0.f;
+      for (int o = 0; o <= 2 * half; ++o) acc += tile[t + o];
+      v = acc / kernel_size;
+    } else {
+      v = tile[t + half];
+      for (int o = 0; o <= 2 * half; ++o) v = fmaxf(v, tile[t + o]);
+    }
+    out[j] = v;
+  }
+}
+
+template <typename T, int NP>
+hipError_t launch_tile(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, const T* q, const T* k, float* raw,
+                       const Workspace& ws, hipStream_t st) {
+  const dim3 grid(g.nchunk, g.Hkv, g.n_inst), block(THREADS);
+  const int bytes = 2 * 32 * q_stride(g.d * (int)sizeof(T));
+  hipLaunchKernelGGL((tile_stats_kernel<T, NP>), grid, block, bytes, st, g, qp, lay, q, k, ws.part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const bool fold = g.nchunk <= FOLD_CHUNKS;
+  if (!fold && (e = launch_row_constants(g, ws, st)) != hipSuccess) return e;
+  hipLaunchKernelGGL((tile_score_kernel<T, NP>), grid, block, bytes, st, g, qp, lay, q, k, ws.part,
+                     fold ? (const float*)nullptr : ws.rowc, raw, ws.status);
+  return hipGetLastError();
+}
+
+template <typename T, int NP> hipError_t init_tile() {
+  const int bytes = 2 * 32 * (NP * 32 + 16);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_stats_kernel<T, NP>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_score_kernel<T, NP>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+}  // namespace
+
+hipError_t score_tile_init() {
+  hipError_t e;
+  if ((e = init_tile<uint16_t, 8>()) != hipSuccess || (e = init_tile<uint16_t, 16>()) != hipSuccess) return e;
+  if ((e = init_tile<float, 8>()) != hipSuccess || (e = init_tile<float, 16>()) != hipSuccess) return e;
+  return init_tile<float, 32>();
+}
+
+hipError_t launch_score_tile(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q, const void* k,
+                             float* raw, const Workspace& ws, hipStream_t st) {
+  if (dtype == LAQ_F32) {
+    const float *qq = static_cast<const float*>(q), *kk = static_cast<const float*>(k);
+    if (g.d <= 64) return launch_tile<float, 8>(g, qp, lay, qq, kk, raw, ws, st);
+    if (g.d <= 128) return launch_tile<float, 16>(g, qp, lay, qq, kk, raw, ws, st);
+    return launch_tile<float, 32>(g, qp, lay, qq, kk, raw, ws, st);
+  }
+  const uint16_t *qq = static_cast<const uint16_t*>(q), *kk = static_cast<const uint16_t*>(k);
+  if (g.d <= 128) return launch_tile<uint16_t, 8>(g, qp, lay, qq, kk, raw, ws, st);
+  return launch_tile<uint16_t, 16>(g, qp, lay, qq, kk, raw, ws, st);
+}
+
+// pooled scores from raw ones, for the paths that do not pool where they score
+hipError_t launch_pool(const ScoreGeom& g, int pool, bool avg, const float* raw, float* pooled, hipStream_t st) {
+  dim3 grid(g.n_inst * g.Hkv, (g.L + POOL_TILE - 1) / POOL_TILE);
+  hipLaunchKernelGGL(pool_kernel, grid, dim3(256), 0, st, g.L, g.P, (pool - 1) / 2, avg, raw, pooled);
+  return hipGetLastError();
+}
+
+}  // namespace laq

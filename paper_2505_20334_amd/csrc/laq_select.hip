@@ -17,6 +17,8 @@
 // crowd into few values of the leading bits, and LDS adds of many lanes to one word go one after the other
 // (counting every key of a 32768-key head by its leading byte took 9 us of 25); so few keys are counted
 // there, into COPIES histograms side by side, one per lane number modulo COPIES.
+#include <type_traits>
+
 #include "laq_internal.h"
 
 namespace laq {
@@ -106,26 +108,34 @@ __device__ __forceinline__ void find_bin(Sel<THREADS>& sh, const int* hist, int 
 // QUADS (scores that are final: no pooling here): register 4q + c of a lane holds position
 // seg0 + 256 q + 4 lane + c - shift, where shift (0 .. 3) is how far the row starts behind a 16-byte boundary,
 // fetched with one load per q.  Otherwise register i holds position seg0 + 64 i + lane.
-template <int THREADS, int ITEMS, bool QUADS>
+// FIN = FinishArgs: the scores are raw ones, see there; NoFinish: nothing of that.
+struct NoFinish {};
+template <int THREADS, int ITEMS, bool QUADS, typename TAB, typename FIN>
 __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int keep, int pool, bool avg,
-                                                             const float* __restrict__ scores, InstTable tab,
-                                                             int inst0, int32_t* __restrict__ idx) {
+                                                             const float* __restrict__ scores, TAB tab,
+                                                             int inst0, int32_t* __restrict__ idx, FIN fin) {
+  constexpr bool FINISH = std::is_same<FIN, FinishArgs>::value;
+  static_assert(!FINISH || QUADS, "four neighbours per lane");
   __shared__ __align__(16) Sel<THREADS> sh;
   constexpr int BINS = Sel<THREADS>::BINS, BITS = Sel<THREADS>::BITS, TOP = 32 - BITS;
 
   const int head = blockIdx.x, li = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int P = L - keep, half = (pool - 1) / 2;
-  const int bk = tab.bk[li];
+  const int bk = tab.rows(li);
   const int ksel = bk - keep;
   const float* s = scores + ((size_t)(inst0 + li) * Hkv + head) * L;
-  int32_t* out = idx + (tab.row0[li] + (int64_t)head * bk);
+  int32_t* out = idx + (tab.first(li) + (int64_t)head * bk);
 
   for (int w = tid; w < keep; w += THREADS) out[ksel + w] = P + w;
-  if (ksel <= 0) return;
-  if (ksel >= P) {
+  const bool all = ksel >= P, ranked = ksel > 0 && !all;
+  if (all)
     for (int j = tid; j < P; j += THREADS) out[j] = j;
-    return;
+  if constexpr (!FINISH) {
+    if (!ranked) return;
+  } else if (fin.pooled != scores) {
+    float* pooled = fin.pooled + ((size_t)(inst0 + li) * Hkv + head) * L;
+    for (int w = tid; w < keep; w += THREADS) pooled[P + w] = s[P + w];
   }
 
   constexpr int UNROLL = ITEMS > 0 ? ITEMS : 1;     // register-resident keys: full unrolling; memory path: none
@@ -137,17 +147,58 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
   uint32_t key[ITEMS > 0 ? ITEMS : 1];
   if constexpr (QUADS) {
     float4 v[ITEMS / 4];
-#pragma unroll
-    for (int q4 = 0; q4 < ITEMS / 4; ++q4) {
-      const int pos = seg0 + q4 * 256 + lane * 4;
-      v[q4] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);     // positions outside the prefix: below every score
+    // positions pos .. pos + 3 of the prefix, `outside` for those that are not in it
+    auto quad_at = [&](int pos, float outside) {
+      float4 x = make_float4(outside, outside, outside, outside);
       if (pos >= 0 && pos + 3 < P) {
-        v[q4] = *reinterpret_cast<const float4*>(s + pos);
+        x = *reinterpret_cast<const float4*>(s + pos);
       } else {
-        if (pos >= 0 && pos < P) v[q4].x = s[pos];
-        if (pos + 1 >= 0 && pos + 1 < P) v[q4].y = s[pos + 1];
-        if (pos + 2 >= 0 && pos + 2 < P) v[q4].z = s[pos + 2];
-        if (pos + 3 >= 0 && pos + 3 < P) v[q4].w = s[pos + 3];
+        if (pos >= 0 && pos < P) x.x = s[pos];
+        if (pos + 1 >= 0 && pos + 1 < P) x.y = s[pos + 1];
+        if (pos + 2 >= 0 && pos + 2 < P) x.z = s[pos + 2];
+        if (pos + 3 >= 0 && pos + 3 < P) x.w = s[pos + 3];
+      }
+      return x;
+    };
+#pragma unroll
+    for (int q4 = 0; q4 < ITEMS / 4; ++q4) v[q4] = quad_at(seg0 + q4 * 256 + lane * 4, -INFINITY);   // (below every score)
+    if constexpr (FINISH) {
+      if (fin.half > 0) {
+        float* pooled = fin.pooled + ((size_t)(inst0 + li) * Hkv + head) * L;
+        const float kernel_size = (float)(2 * fin.half + 1);
+#pragma unroll
+        for (int q4 = 0; q4 < ITEMS / 4; ++q4) {
+          const int pos = seg0 + q4 * 256 + lane * 4;
+          if (pos + 3 < 0 || pos >= P) continue;
+          // the neighbours (scores are never negative: a zero stands for "not in the window", and leaves an
+          // ascending sum as it is)
+          const float4 lo = quad_at(pos - 4, 0.f), mid = quad_at(pos, 0.f), hi = quad_at(pos + 4, 0.f);
+          const float w[12] = {lo.x, lo.y, lo.z, lo.w, mid.x, mid.y, mid.z, mid.w, hi.x, hi.y, hi.z, hi.w};
+          float r[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            float m = w[4 + c], sum = 0.f;
+#pragma unroll
+            for (int o = -FINISH_MAX_HALF; o <= FINISH_MAX_HALF; ++o) {
+              const float x = abs(o) <= fin.half ? w[4 + c + o] : 0.f;
+              m = fmaxf(m, x);
+              sum += x;
+            }
+            r[c] = fin.avg ? sum / kernel_size : m;
+          }
+          if (pos >= 0 && pos + 3 < P) {
+            *reinterpret_cast<float4*>(pooled + pos) = make_float4(r[0], r[1], r[2], r[3]);
+            v[q4] = make_float4(r[0], r[1], r[2], r[3]);
+          } else {
+            float* e = &v[q4].x;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (pos + c >= 0 && pos + c < P) {
+                pooled[pos + c] = r[c];
+                e[c] = r[c];
+              }
+          }
+        }
       }
     }
 #pragma unroll
@@ -169,6 +220,7 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
       }
     }
   }
+  if (FINISH ? ranked : true) {
   auto key_of = [&](int i) -> uint32_t {
     if (ITEMS > 0) return key[i];
     const int pos = seg0 + i * 64 + lane;
@@ -309,27 +361,53 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
         e_before += eq;
       }
     }
-    return;
-  }
+  } else {
 #pragma unroll UNROLL
-  for (int i = 0; i < items; ++i) {
-    const uint32_t kv = key_of(i);
-    const bool gt = kv > T, eq = kv == T;
-    const uint64_t mg = __ballot(gt), me = __ballot(eq);
-    if ((mg | me) == 0) continue;
-    const int g_before = run_gt + lanes_below(mg);
-    const int e_before = run_eq + lanes_below(me);
-    if (gt || (eq && e_before < want)) out[g_before + min(e_before, want)] = seg0 + i * 64 + lane;
-    run_gt += __popcll(mg);
-    run_eq += __popcll(me);
+    for (int i = 0; i < items; ++i) {
+      const uint32_t kv = key_of(i);
+      const bool gt = kv > T, eq = kv == T;
+      const uint64_t mg = __ballot(gt), me = __ballot(eq);
+      if ((mg | me) == 0) continue;
+      const int g_before = run_gt + lanes_below(mg);
+      const int e_before = run_eq + lanes_below(me);
+      if (gt || (eq && e_before < want)) out[g_before + min(e_before, want)] = seg0 + i * 64 + lane;
+      run_gt += __popcll(mg);
+      run_eq += __popcll(me);
+    }
+  }
+  }
+  if constexpr (FINISH) {
+    // ---- gather: this workgroup's own list, complete behind the barrier ----
+    __syncthreads();
+    const int ppr = fin.row_bytes >> 4, total = bk * ppr;
+    const int64_t row0 = tab.first(li) + (int64_t)head * bk;
+    const char *ks = fin.k + (size_t)head * fin.head_bytes, *vs = fin.v + (fin.v ? (size_t)head * fin.head_bytes : 0);
+    for (int p = tid; p < total; p += THREADS) {
+      const int row = p / ppr, col = p - row * ppr, j = out[row];
+      size_t so;
+      if (fin.lay.table) {
+        int r;
+        so = (size_t)paged_block_offset(fin.lay, inst0 + li, j, &r) * fin.elem_bytes + (size_t)r * fin.src_row_bytes;
+      } else {
+        so = (size_t)(inst0 + li) * fin.inst_bytes + (size_t)j * fin.src_row_bytes;
+      }
+      so += (size_t)col * 16;
+      const size_t dof = (size_t)(row0 + row) * fin.row_bytes + (size_t)col * 16;
+      const uint4 x = *reinterpret_cast<const uint4*>(ks + so);
+      if (fin.v) {
+        const uint4 y = *reinterpret_cast<const uint4*>(vs + so);
+        *reinterpret_cast<uint4*>(fin.v_out + dof) = y;
+      }
+      *reinterpret_cast<uint4*>(fin.k_out + dof) = x;
+    }
   }
 }
 
-template <int THREADS, int ITEMS, bool QUADS>
+template <int THREADS, int ITEMS, bool QUADS, typename TAB, typename FIN>
 hipError_t launch_one(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
-                      const InstTable& tab, int32_t* idx, hipStream_t st) {
-  hipLaunchKernelGGL((select_kernel<THREADS, ITEMS, QUADS>), dim3(Hkv, n_inst), dim3(THREADS), 0, st, Hkv, L, keep, pool, avg, scores,
-                     tab, inst0, idx);
+                      const TAB& tab, int32_t* idx, const FIN& fin, hipStream_t st) {
+  hipLaunchKernelGGL((select_kernel<THREADS, ITEMS, QUADS, TAB, FIN>), dim3(Hkv, n_inst), dim3(THREADS), 0, st, Hkv, L, keep, pool,
+                     avg, scores, tab, inst0, idx, fin);
   return hipGetLastError();
 }
 
@@ -345,6 +423,44 @@ __global__ __launch_bounds__(256) void sink_recent_kernel(int Hkv, int L, int n_
   for (int t = threadIdx.x; t < bk; t += 256) out[t] = t < s ? t : t + shift;
 }
 
+template <typename TAB>
+hipError_t launch_for(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores, const TAB& tab,
+                      int32_t* idx, hipStream_t st) {
+  // The fewest registers that hold the prefix (a row may start three positions behind a 16-byte boundary).
+  // With many heads in the launch, small workgroups of which several share a compute unit: while one
+  // waits at a barrier or for its scores, another one works.
+  const int P = L - keep, most = P + (pool == 1 ? 3 : 0);
+  auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, NoFinish{}, st); };
+  if (pool == 1) {
+    if ((long long)Hkv * n_inst >= SEL_MANY_WORKGROUPS) {
+      if (most <= 256 * 8) return at(launch_one<256, 8, true, TAB, NoFinish>);
+      if (most <= 256 * 32) return at(launch_one<256, 32, true, TAB, NoFinish>);
+      if (most <= 512 * 64) return at(launch_one<512, 64, true, TAB, NoFinish>);
+    }
+    if (most <= 1024 * 4) return at(launch_one<1024, 4, true, TAB, NoFinish>);
+    if (most <= 1024 * 8) return at(launch_one<1024, 8, true, TAB, NoFinish>);
+    if (most <= 1024 * 16) return at(launch_one<1024, 16, true, TAB, NoFinish>);
+    if (most <= 1024 * 32) return at(launch_one<1024, 32, true, TAB, NoFinish>);
+    return at(launch_one<1024, 0, false, TAB, NoFinish>);
+  }
+  if (most <= 1024 * 2) return at(launch_one<1024, 2, false, TAB, NoFinish>);
+  if (most <= 1024 * 8) return at(launch_one<1024, 8, false, TAB, NoFinish>);
+  if (most <= 1024 * 32) return at(launch_one<1024, 32, false, TAB, NoFinish>);
+  return at(launch_one<1024, 0, false, TAB, NoFinish>);
+}
+
+template <typename TAB>
+hipError_t finish_for(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const TAB& tab, int32_t* idx,
+                      const FinishArgs& fin, hipStream_t st) {
+  const int most = L - keep + 3;
+  auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, 1, false, raw, tab, idx, fin, st); };
+  if (most <= 256 * 8) return at(launch_one<256, 8, true, TAB, FinishArgs>);
+  if (most <= 1024 * 4) return at(launch_one<1024, 4, true, TAB, FinishArgs>);
+  if (most <= 1024 * 8) return at(launch_one<1024, 8, true, TAB, FinishArgs>);
+  return at(launch_one<1024, 20, true, TAB, FinishArgs>);
+}
+static_assert(FINISH_MAX_KEYS + 3 <= 1024 * 20, "");
+
 }  // namespace
 
 hipError_t launch_sink_recent(int n_inst, int Hkv, int L, int n_sink, const InstTable& tab, int32_t* idx,
@@ -355,27 +471,19 @@ hipError_t launch_sink_recent(int n_inst, int Hkv, int L, int n_sink, const Inst
 
 hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
                          const InstTable& tab, int32_t* idx, hipStream_t st) {
-  // The fewest registers that hold the prefix (a row may start three positions behind a 16-byte boundary).
-  // With many heads in the launch, small workgroups of which several share a compute unit: while one
-  // waits at a barrier or for its scores, another one works.
-  const int P = L - keep, most = P + (pool == 1 ? 3 : 0);
-  auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st); };
-  if (pool == 1) {
-    if ((long long)Hkv * n_inst >= SEL_MANY_WORKGROUPS) {
-      if (most <= 256 * 8) return at(launch_one<256, 8, true>);
-      if (most <= 256 * 32) return at(launch_one<256, 32, true>);
-      if (most <= 512 * 64) return at(launch_one<512, 64, true>);
-    }
-    if (most <= 1024 * 4) return at(launch_one<1024, 4, true>);
-    if (most <= 1024 * 8) return at(launch_one<1024, 8, true>);
-    if (most <= 1024 * 16) return at(launch_one<1024, 16, true>);
-    if (most <= 1024 * 32) return at(launch_one<1024, 32, true>);
-    return at(launch_one<1024, 0, false>);
-  }
-  if (most <= 1024 * 2) return at(launch_one<1024, 2, false>);
-  if (most <= 1024 * 8) return at(launch_one<1024, 8, false>);
-  if (most <= 1024 * 32) return at(launch_one<1024, 32, false>);
-  return at(launch_one<1024, 0, false>);
+  return launch_for(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st);
+}
+hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
+                         const UniformInst& tab, int32_t* idx, hipStream_t st) {
+  return launch_for(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st);
+}
+hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const InstTable& tab, int32_t* idx,
+                         const FinishArgs& fin, hipStream_t st) {
+  return finish_for(n_inst, inst0, Hkv, L, keep, raw, tab, idx, fin, st);
+}
+hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const UniformInst& tab, int32_t* idx,
+                         const FinishArgs& fin, hipStream_t st) {
+  return finish_for(n_inst, inst0, Hkv, L, keep, raw, tab, idx, fin, st);
 }
 
 }  // namespace laq
