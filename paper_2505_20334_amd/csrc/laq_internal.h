@@ -135,7 +135,7 @@ struct FinishArgs {
 constexpr int FINISH_MAX_HALF = 4;         // widest pooling it does
 constexpr int FINISH_MAX_KEYS = 16 * 1024; // longest prefix
 constexpr int FINISH_MAX_HEADS = 256;      // one workgroup per head: more of them fill the device without it
-constexpr int FINISH_MAX_GATHER = 64 << 10;   // bytes of K rows per head: one compute unit copies them all
+constexpr int FINISH_MAX_GATHER = 128 << 10;   // bytes of K rows per head: one compute unit copies them all
 
 // Pooled score at prefix position pos, the one arithmetic every pooling site uses: the
 // maximum over the part of the window inside [0, P), or (avg) the fp32 sum over it in

@@ -385,11 +385,10 @@ __device__ __forceinline__ void pass2_masked(const char* ldsK, const bf16x8 (&qr
     if (j0 + t0 + 31 > g.qmin) {
       f32x16 bias;
       const int j = j0 + t0 + n;
+      // (lane l looks up the last key that row l of the tile sees; the registers' rows get it from there)
+      const int last = last_visible_key(g, qp, (rt * 32 + n) % g.W);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int w = (rt * 32 + acc_row(i, hf)) % g.W;
-        bias[i] = (j <= last_visible_key(g, qp, w)) ? 0.f : -INFINITY;
-      }
+      for (int i = 0; i < 16; ++i) bias[i] = (j <= __shfl(last, acc_row(i, hf))) ? 0.f : -INFINITY;
       acc = tile_product<D, false>(ldsK, kt, lane, qreg, bias);
     } else {
       acc = tile_product<D, false>(ldsK, kt, lane, qreg, zero);

@@ -16,7 +16,7 @@
 //
 // What bounds it: for fp32 the matrix cores (157 TFLOP/s dense), which do the product twice; the vector ALU
 // kernels that stood here took 8 us per (million keys x score row) and pass pair, these about 1.  64 heads x
-// 8191 keys, d = 128, 64 score rows, fp32: 1018 -> 190 us.
+// 8191 keys, d = 128, 64 score rows, fp32: 1018 -> 216 us.
 #include "laq_internal.h"
 
 namespace laq {
@@ -27,19 +27,22 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float NEG_BIG = -1.0e30f;   // finite "minus infinity" for running maxima
 constexpr int WAVES = CHUNK_ROWS / 32, THREADS = WAVES * 64;
-// Chunks of a head up to which every workgroup of the second kernel folds the statistics itself: beyond, it
-// would read more of them than of keys.
-constexpr int FOLD_CHUNKS = 32;
+// Every workgroup of the second kernel folds the statistics of its head itself where that is little next to
+// its keys and the workgroups are few (one launch less); otherwise row_constants_mfma_kernel does it once.
+// Row tiles of a chunk that are worked on side by side where there are too few chunks to fill the device.
+constexpr int MAX_SPLIT = 4;
+constexpr int FOLD_CHUNKS = 32, FOLD_WORKGROUPS = 512;
 
 // Row index (0..31) of accumulator register i for a lane in half hf of the 32x32 output layout.
 __device__ __forceinline__ int acc_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
 
-// bytes between rows of the staged score rows: an odd number of 16-byte pieces, so that 128-bit reads of 16
-// consecutive rows fall on distinct banks
-__host__ __device__ inline int q_stride(int row_bytes) { return row_bytes % 32 == 0 ? row_bytes + 16 : row_bytes; }
+// bytes between rows of the staged score rows: pairs of 16-byte pieces (the second half of the last one may be
+// padding, zeros) and one more, so that 128-bit reads of 16 consecutive rows fall on distinct banks
+__host__ __device__ inline int q_stride(int row_bytes) { return (row_bytes + 31) / 32 * 32 + 16; }
 
 // acc += A * B over one piece (16 bytes) per lane of either operand
 __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 acc, uint16_t) {
@@ -52,47 +55,49 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 acc, float) {
   return acc;
 }
 
-// What both kernels do around their products.  NP: pairs of 16-byte pieces a row may have (32 bytes each).
-template <typename T, int NP> struct Chunk {
+// What both kernels do around their products.  NP: pairs of 16-byte pieces a row may have (32 bytes each); FULL:
+// it has exactly that many.
+template <typename T, int NP, bool FULL> struct Chunk {
   u32x4 key[NP];           // this lane's pieces of its key row
   int np;                  // pairs of pieces a row has, the last one possibly half
   int row_bytes, stride;   // of a score row in memory / in LDS
-  int lane, hf, n32, wave, j0;
+  int lane, hf, n32, wave;
+  int k0;                  // the wave's first key
 
-  __device__ __forceinline__ void load_keys(const ScoreGeom& g, const KvLayout& lay, const T* __restrict__ k, int chunk,
+  // keys first .. first + 31 of the head, for this wave
+  __device__ __forceinline__ void load_keys(const ScoreGeom& g, const KvLayout& lay, const T* __restrict__ k, int first,
                                             int head, int inst) {
     const int tid = threadIdx.x;
     lane = tid & 63; hf = lane >> 5; n32 = lane & 31; wave = tid >> 6;
-    row_bytes = g.d * (int)sizeof(T);
+    row_bytes = FULL ? NP * 32 : g.d * (int)sizeof(T);
     stride = q_stride(row_bytes);
-    np = (row_bytes + 31) / 32;
-    j0 = chunk * CHUNK_ROWS;
+    np = FULL ? NP : (row_bytes + 31) / 32;
+    k0 = first;
     int64_t off = (int64_t)inst * lay.inst;
-    int r0 = j0;
-    if (lay.table) off = paged_block_offset(lay, inst, j0, &r0);      // (a block holds whole chunks)
-    const int row = wave * 32 + n32;
-    const char* p = reinterpret_cast<const char*>(k + off + (int64_t)head * lay.head + (int64_t)(r0 + row) * lay.row);
-    const bool there = j0 + row < g.L;
+    int r0 = first;
+    if (lay.table && first < g.L) off = paged_block_offset(lay, inst, first, &r0);      // (a block holds whole chunks)
+    const char* p = reinterpret_cast<const char*>(k + off + (int64_t)head * lay.head + (int64_t)(r0 + n32) * lay.row);
+    const bool there = first + n32 < g.L;
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
       key[t] = u32x4{0u, 0u, 0u, 0u};
-      if (there && (2 * t + hf) * 16 < row_bytes) key[t] = *reinterpret_cast<const u32x4*>(p + (2 * t + hf) * 16);
+      if (there && (FULL || (2 * t + hf) * 16 < row_bytes)) key[t] = *reinterpret_cast<const u32x4*>(p + (2 * t + hf) * 16);
     }
   }
   // score rows rt * 32 .. + 31 of the group (rows beyond R: zeros), memory -> registers -> LDS
   static constexpr int PER_THREAD = (32 * NP * 2 + THREADS - 1) / THREADS;
   __device__ __forceinline__ void fetch_rows(u32x4 (&v)[PER_THREAD], const T* __restrict__ qg, int R, int rt) const {
-    const int per_row = row_bytes >> 4;
+    const int per_row = 2 * np;
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
       const int p = threadIdx.x + i * THREADS, row = p / per_row, col = p - row * per_row;
       v[i] = u32x4{0u, 0u, 0u, 0u};
-      if (row < 32 && rt * 32 + row < R)
+      if (row < 32 && rt * 32 + row < R && col * 16 < row_bytes)
         v[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(qg) + (size_t)(rt * 32 + row) * row_bytes + col * 16);
     }
   }
   __device__ __forceinline__ void stage_rows(char* lds, const u32x4 (&v)[PER_THREAD]) const {
-    const int per_row = row_bytes >> 4;
+    const int per_row = 2 * np;
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
       const int p = threadIdx.x + i * THREADS, row = p / per_row, col = p - row * per_row;
@@ -106,42 +111,44 @@ template <typename T, int NP> struct Chunk {
     const char* p = lds + n32 * stride + hf * 16;
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
-      if (t < np) {                                      // (the same in every lane)
-        u32x4 q = {0u, 0u, 0u, 0u};
-        if ((2 * t + hf) * 16 < row_bytes) q = *reinterpret_cast<const u32x4*>(p + t * 32);
+      if (FULL || t < np) {                              // (the same in every lane)
+        const u32x4 q = *reinterpret_cast<const u32x4*>(p + t * 32);
         acc = KEYS_AS_ROWS ? mma(key[t], q, acc, T()) : mma(q, key[t], acc, T());
       }
+      if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (at most four operands of Q requested ahead: registers)
     }
     return acc;
   }
 };
 
-// Pass 1: part[head][chunk][row] = (m, z) of a score row over the chunk's visible keys, in log2 units.
-template <typename T, int NP>
-__global__ __launch_bounds__(THREADS) void tile_stats_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, const T* __restrict__ q,
-                                                             const T* __restrict__ k, float2* __restrict__ part) {
+// Pass 1: part[head][chunk][row] = (m, z) of a score row over the chunk's visible keys, in log2 units.  split
+// workgroups share the row tiles of a chunk.
+template <typename T, int NP, bool FULL>
+__global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_stats_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, int split,
+                                                             const T* __restrict__ q, const T* __restrict__ k,
+                                                             float2* __restrict__ part) {
   extern __shared__ __align__(16) char smem[];           // two tiles of score rows
   __shared__ float2 stat[WAVES][32];
-  const int chunk = blockIdx.x, head = blockIdx.y, inst = blockIdx.z, tid = threadIdx.x;
-  Chunk<T, NP> c;
-  c.load_keys(g, lay, k, chunk, head, inst);
+  const int chunk = blockIdx.x / split, first = blockIdx.x - chunk * split, head = blockIdx.y, inst = blockIdx.z, tid = threadIdx.x;
+  Chunk<T, NP, FULL> c;
+  c.load_keys(g, lay, k, chunk * CHUNK_ROWS + (tid >> 6) * 32, head, inst);
   const T* qg = q + ((size_t)inst * g.Hq + (size_t)head * g.G) * g.W * g.d;
   float2* out = part + (((size_t)inst * g.Hkv + head) * g.nchunk + chunk) * g.Rpad;
   const int ntile = g.Rpad / 32, tile_bytes = 32 * c.stride;
-  u32x4 v[Chunk<T, NP>::PER_THREAD];
-  c.fetch_rows(v, qg, g.R, 0);
+  u32x4 v[Chunk<T, NP, FULL>::PER_THREAD];
+  c.fetch_rows(v, qg, g.R, first);
   c.stage_rows(smem, v);
-  const int k0 = c.j0 + c.wave * 32;                     // the wave's first key
-  const bool plain = k0 + 31 <= g.qmin;                  // seen by every row
-  for (int rt = 0; rt < ntile; ++rt) {
-    if (rt + 1 < ntile) c.fetch_rows(v, qg, g.R, rt + 1);
+  const bool plain = c.k0 + 31 <= g.qmin;                // seen by every row
+  int turn = 0;
+  for (int rt = first; rt < ntile; rt += split, turn ^= 1) {
+    if (rt + split < ntile) c.fetch_rows(v, qg, g.R, rt + split);
     __syncthreads();
-    f32x16 s = c.template product<true>(smem + (rt & 1) * tile_bytes);
+    f32x16 s = c.template product<true>(smem + turn * tile_bytes);
     if (!plain) {
       const int row = rt * 32 + c.n32, last = row < g.R ? last_visible_key(g, qp, row % g.W) : g.L - 1;
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (k0 + acc_row(i, c.hf) > last) s[i] = -INFINITY;
+        if (c.k0 + acc_row(i, c.hf) > last) s[i] = -INFINITY;
     }
     float m = s[0];
 #pragma unroll
@@ -153,7 +160,7 @@ __global__ __launch_bounds__(THREADS) void tile_stats_kernel(ScoreGeom g, Window
     for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f(fmaf(s[i], g.scale2, -m));
     z += __shfl_xor(z, 32);
     if (c.hf == 0) stat[c.wave][c.n32] = make_float2(m, z);
-    if (rt + 1 < ntile) c.stage_rows(smem + ((rt + 1) & 1) * tile_bytes, v);
+    if (rt + split < ntile) c.stage_rows(smem + (turn ^ 1) * tile_bytes, v);
     __syncthreads();
     if (tid < 32) {
       float M = stat[0][tid].x, Z = 0.f;
@@ -171,6 +178,7 @@ __global__ __launch_bounds__(THREADS) void tile_stats_kernel(ScoreGeom g, Window
 __device__ __forceinline__ void fold_rows(const ScoreGeom& g, const float2* __restrict__ part, int rt, float2 (*fold)[32], float* rowc) {
   const int tid = threadIdx.x, row = tid & 31, sub = tid >> 5;
   float M = NEG_BIG, Z = 0.f;
+#pragma unroll 1
   for (int ch = sub; ch < g.nchunk; ch += WAVES * 2) {
     const float2 mz = part[(size_t)ch * g.Rpad + rt * 32 + row];
     const float Mn = fmaxf(M, mz.x);
@@ -181,66 +189,94 @@ __device__ __forceinline__ void fold_rows(const ScoreGeom& g, const float2* __re
   __syncthreads();
   if (tid < 32) {
     M = fold[0][tid].x; Z = 0.f;
-#pragma unroll
+#pragma unroll 4
     for (int w = 1; w < WAVES * 2; ++w) M = fmaxf(M, fold[w][tid].x);
-#pragma unroll
+#pragma unroll 4
     for (int w = 0; w < WAVES * 2; ++w) Z = fmaf(fold[w][tid].y, __builtin_amdgcn_exp2f(fold[w][tid].x - M), Z);
     rowc[tid] = rt * 32 + tid < g.R ? M + __builtin_amdgcn_logf(Z) : 1.0e30f;      // rows beyond R: probability 0
   }
+  __syncthreads();                                       // (`fold` may be written again)
 }
 
-// Pass 2: raw[j] = sum over the score rows of exp2(s - c[row]) for the keys of the chunk.  rowc_all: the
-// heads' row constants, or null: folded here.
-template <typename T, int NP>
-__global__ __launch_bounds__(THREADS) void tile_score_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, const T* __restrict__ q,
-                                                             const T* __restrict__ k, const float2* __restrict__ part,
-                                                             const float* __restrict__ rowc_all, float* __restrict__ raw,
-                                                             int* __restrict__ status) {
-  extern __shared__ __align__(16) char smem[];           // two tiles of score rows
-  __shared__ __align__(16) float rowc[2][32];
+// Pass 2: raw[j] = sum over the score rows of exp2(s - c[row]).  The workgroup has CHUNK_ROWS / split keys; wave
+// (row group rg, key tile) takes the row tiles rg, rg + split, ...  rowc_all: the heads' row constants, or
+// null: folded here.
+template <typename T, int NP, bool FULL>
+__global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, int split,
+                                                             const T* __restrict__ q, const T* __restrict__ k,
+                                                             const float2* __restrict__ part, const float* __restrict__ rowc_all,
+                                                             float* __restrict__ raw, int* __restrict__ status) {
+  extern __shared__ __align__(16) char smem[];           // two tiles of score rows per row group
+  __shared__ __align__(16) float rowc[2][MAX_SPLIT][32];
+  __shared__ __align__(16) int last[2][MAX_SPLIT][32];   // last key the rows see
   __shared__ float2 fold[WAVES * 2][32];
-  const int chunk = blockIdx.x, head = blockIdx.y, inst = blockIdx.z, tid = threadIdx.x;
+  __shared__ float sums[WAVES][32];
+  const int head = blockIdx.y, inst = blockIdx.z, tid = threadIdx.x;
   const size_t hg = (size_t)inst * g.Hkv + head;
-  if (chunk == 0 && hg == 0 && tid == 0) *status = 0;    // (these kernels have no wait to give up)
-  Chunk<T, NP> c;
-  c.load_keys(g, lay, k, chunk, head, inst);
+  if (blockIdx.x == 0 && hg == 0 && tid == 0) *status = 0;    // (these kernels have no wait to give up)
+  const int key_waves = WAVES / split, rg = (tid >> 6) / key_waves, kw = (tid >> 6) - rg * key_waves;
+  Chunk<T, NP, FULL> c;
+  c.load_keys(g, lay, k, (int)blockIdx.x * key_waves * 32 + kw * 32, head, inst);
   const T* qg = q + ((size_t)inst * g.Hq + (size_t)head * g.G) * g.W * g.d;
   const int ntile = g.Rpad / 32, tile_bytes = 32 * c.stride;
-  u32x4 v[Chunk<T, NP>::PER_THREAD];
-  auto constants = [&](int rt) {
-    if (rowc_all == nullptr) fold_rows(g, part + hg * g.nchunk * g.Rpad, rt, fold, rowc[rt & 1]);
-    else if (tid < 32) rowc[rt & 1][tid] = rowc_all[hg * g.Rpad + rt * 32 + tid];
+  u32x4 v[Chunk<T, NP, FULL>::PER_THREAD];
+  auto constants = [&](int turn, int rt) {
+#pragma unroll 1
+    for (int i = 0; i < split && rt + i < ntile; ++i) {
+      if (tid < 32) {
+        const int row = (rt + i) * 32 + tid;
+        last[turn][i][tid] = row < g.R ? last_visible_key(g, qp, row % g.W) : g.L - 1;
+      }
+      if (rowc_all == nullptr) fold_rows(g, part + hg * g.nchunk * g.Rpad, rt + i, fold, rowc[turn][i]);
+      else if (tid < 32) rowc[turn][i][tid] = rowc_all[hg * g.Rpad + (rt + i) * 32 + tid];
+    }
+  };
+  auto stage = [&](int turn, int rt) {                   // (the first of the next tiles is in v)
+    c.stage_rows(smem + turn * split * tile_bytes, v);
+#pragma unroll 1
+    for (int i = 1; i < split; ++i) {
+      c.fetch_rows(v, qg, g.R, rt + i);
+      c.stage_rows(smem + (turn * split + i) * tile_bytes, v);
+    }
+    constants(turn, rt);
   };
   c.fetch_rows(v, qg, g.R, 0);
-  c.stage_rows(smem, v);
-  constants(0);
-  const int k0 = c.j0 + c.wave * 32, key = k0 + c.n32;
-  const bool plain = k0 + 31 <= g.qmin;
+  stage(0, 0);
+  const int key = c.k0 + c.n32;
+  const bool plain = c.k0 + 31 <= g.qmin;
   float sum = 0.f;
-  for (int rt = 0; rt < ntile; ++rt) {
-    if (rt + 1 < ntile) c.fetch_rows(v, qg, g.R, rt + 1);
+  int turn = 0;
+  for (int rt = 0; rt < ntile; rt += split, turn ^= 1) {
+    if (rt + split < ntile) c.fetch_rows(v, qg, g.R, rt + split);
     __syncthreads();
-    f32x16 s = c.template product<false>(smem + (rt & 1) * tile_bytes);
-    if (!plain) {
+    if (rt + rg < ntile) {
+      f32x16 s = c.template product<false>(smem + (turn * split + rg) * tile_bytes);
+      if (!plain) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int row = rt * 32 + acc_row(i, c.hf);
-        if (key > (row < g.R ? last_visible_key(g, qp, row % g.W) : g.L - 1)) s[i] = -INFINITY;
+        for (int gq = 0; gq < 4; ++gq) {
+          const i32x4 lv = *reinterpret_cast<const i32x4*>(last[turn][rg] + 8 * gq + 4 * c.hf);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (key > lv[j]) s[4 * gq + j] = -INFINITY;
+        }
+      }
+      const float* rc = rowc[turn][rg];
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        const f32x4 cc = *reinterpret_cast<const f32x4*>(rc + 8 * gq + 4 * c.hf);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + j], g.scale2, -cc[j]));
       }
     }
-    const float* rc = rowc[rt & 1];
-#pragma unroll
-    for (int gq = 0; gq < 4; ++gq) {
-      const f32x4 cc = *reinterpret_cast<const f32x4*>(rc + 8 * gq + 4 * c.hf);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + j], g.scale2, -cc[j]));
-    }
-    if (rt + 1 < ntile) {
-      c.stage_rows(smem + ((rt + 1) & 1) * tile_bytes, v);
-      constants(rt + 1);
-    }
+    if (rt + split < ntile) stage(turn ^ 1, rt + split);
   }
   sum += __shfl_xor(sum, 32);
+  if (split > 1) {                                       // the row groups' sums, in their order
+    if (c.hf == 0) sums[c.wave][c.n32] = sum;
+    __syncthreads();
+    if (rg != 0) return;
+    for (int i = 1; i < split; ++i) sum += sums[kw + i * key_waves][c.n32];
+  }
   if (c.hf == 0 && key < g.L) raw[hg * g.L + key] = sum;
 }
 
@@ -280,48 +316,65 @@ __global__ __launch_bounds__(256) void pool_kernel(int L, int P, int half, bool 
   }
 }
 
-template <typename T, int NP>
+constexpr int MAX_LDS = 128 << 10;                       // of the staged score rows
+
+template <typename T, int NP, bool FULL>
 hipError_t launch_tile(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, const T* q, const T* k, float* raw,
                        const Workspace& ws, hipStream_t st) {
-  const dim3 grid(g.nchunk, g.Hkv, g.n_inst), block(THREADS);
-  const int bytes = 2 * 32 * q_stride(g.d * (int)sizeof(T));
-  hipLaunchKernelGGL((tile_stats_kernel<T, NP>), grid, block, bytes, st, g, qp, lay, q, k, ws.part);
+  const int bytes = 2 * 32 * q_stride(g.d * (int)sizeof(T)), ntile = g.Rpad / 32;
+  const long long units = (long long)g.nchunk * g.Hkv * g.n_inst;
+  int split = 1;                                         // (both kernels: the device's 256 compute units have one each then)
+  while (split < MAX_SPLIT && 2 * split <= ntile && units * split < 256) split *= 2;
+  hipLaunchKernelGGL((tile_stats_kernel<T, NP, FULL>), dim3(g.nchunk * split, g.Hkv, g.n_inst), dim3(THREADS), bytes, st, g, qp, lay, split, q,
+                     k, ws.part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const bool fold = g.nchunk <= FOLD_CHUNKS;
+  const bool fold = g.nchunk <= FOLD_CHUNKS && units <= FOLD_WORKGROUPS;
   if (!fold && (e = launch_row_constants(g, ws, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL((tile_score_kernel<T, NP>), grid, block, bytes, st, g, qp, lay, q, k, ws.part,
-                     fold ? (const float*)nullptr : ws.rowc, raw, ws.status);
+  if (split * bytes > MAX_LDS) split = 1;
+  const int keys = CHUNK_ROWS / split;
+  hipLaunchKernelGGL((tile_score_kernel<T, NP, FULL>), dim3((g.L + keys - 1) / keys, g.Hkv, g.n_inst), dim3(THREADS), split * bytes, st, g, qp, lay,
+                     split, q, k, ws.part, fold ? (const float*)nullptr : ws.rowc, raw, ws.status);
   return hipGetLastError();
 }
 
-template <typename T, int NP> hipError_t init_tile() {
-  const int bytes = 2 * 32 * (NP * 32 + 16);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_stats_kernel<T, NP>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+template <typename T, int NP, bool FULL> hipError_t init_tile() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_stats_kernel<T, NP, FULL>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_score_kernel<T, NP>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_score_kernel<T, NP, FULL>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, MAX_LDS);
 }
 
 }  // namespace
 
 hipError_t score_tile_init() {
   hipError_t e;
-  if ((e = init_tile<uint16_t, 8>()) != hipSuccess || (e = init_tile<uint16_t, 16>()) != hipSuccess) return e;
-  if ((e = init_tile<float, 8>()) != hipSuccess || (e = init_tile<float, 16>()) != hipSuccess) return e;
-  return init_tile<float, 32>();
+  if ((e = init_tile<uint16_t, 4, true>()) != hipSuccess || (e = init_tile<uint16_t, 8, true>()) != hipSuccess ||
+      (e = init_tile<uint16_t, 8, false>()) != hipSuccess || (e = init_tile<uint16_t, 16, true>()) != hipSuccess ||
+      (e = init_tile<uint16_t, 16, false>()) != hipSuccess || (e = init_tile<float, 8, true>()) != hipSuccess ||
+      (e = init_tile<float, 16, true>()) != hipSuccess || (e = init_tile<float, 16, false>()) != hipSuccess ||
+      (e = init_tile<float, 32, true>()) != hipSuccess)
+    return e;
+  return init_tile<float, 32, false>();
 }
 
 hipError_t launch_score_tile(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q, const void* k,
                              float* raw, const Workspace& ws, hipStream_t st) {
   if (dtype == LAQ_F32) {
     const float *qq = static_cast<const float*>(q), *kk = static_cast<const float*>(k);
-    if (g.d <= 64) return launch_tile<float, 8>(g, qp, lay, qq, kk, raw, ws, st);
-    if (g.d <= 128) return launch_tile<float, 16>(g, qp, lay, qq, kk, raw, ws, st);
-    return launch_tile<float, 32>(g, qp, lay, qq, kk, raw, ws, st);
+    if (g.d == 64) return launch_tile<float, 8, true>(g, qp, lay, qq, kk, raw, ws, st);
+    if (g.d == 128) return launch_tile<float, 16, true>(g, qp, lay, qq, kk, raw, ws, st);
+    if (g.d == 256) return launch_tile<float, 32, true>(g, qp, lay, qq, kk, raw, ws, st);
+    if (g.d < 128) return launch_tile<float, 16, false>(g, qp, lay, qq, kk, raw, ws, st);
+    return launch_tile<float, 32, false>(g, qp, lay, qq, kk, raw, ws, st);
   }
   const uint16_t *qq = static_cast<const uint16_t*>(q), *kk = static_cast<const uint16_t*>(k);
-  if (g.d <= 128) return launch_tile<uint16_t, 8>(g, qp, lay, qq, kk, raw, ws, st);
-  return launch_tile<uint16_t, 16>(g, qp, lay, qq, kk, raw, ws, st);
+  if (g.d == 64) return launch_tile<uint16_t, 4, true>(g, qp, lay, qq, kk, raw, ws, st);
+  if (g.d == 128) return launch_tile<uint16_t, 8, true>(g, qp, lay, qq, kk, raw, ws, st);
+  if (g.d == 256) return launch_tile<uint16_t, 16, true>(g, qp, lay, qq, kk, raw, ws, st);
+  if (g.d < 128) return launch_tile<uint16_t, 8, false>(g, qp, lay, qq, kk, raw, ws, st);
+  return launch_tile<uint16_t, 16, false>(g, qp, lay, qq, kk, raw, ws, st);
 }
 
 // pooled scores from raw ones, for the paths that do not pool where they score

@@ -382,6 +382,7 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
     const int ppr = fin.row_bytes >> 4, total = bk * ppr;
     const int64_t row0 = tab.first(li) + (int64_t)head * bk;
     const char *ks = fin.k + (size_t)head * fin.head_bytes, *vs = fin.v + (fin.v ? (size_t)head * fin.head_bytes : 0);
+#pragma unroll 2
     for (int p = tid; p < total; p += THREADS) {
       const int row = p / ppr, col = p - row * ppr, j = out[row];
       size_t so;

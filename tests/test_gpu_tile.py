@@ -1,0 +1,47 @@
+"""The one-chunk-per-workgroup scoring kernels and the finishing launch at the edges of their variants, against the
+oracle (needs an MI355X)."""
+import pytest
+import torch
+
+import oracle
+from parity_util import RTOL, check_index_row, check_scores, split_packed
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+F32, BF16 = torch.float32, torch.bfloat16
+
+# (dtype, n, Hq, Hkv, d, L, W, pool, pool_mode, budget): head sizes with half and missing pieces, one row tile and
+# several of them side by side (few chunks), chunk ends, prefixes around the longest one that is finished in
+# one launch, pooling wider than it does, all and no keys ranked
+CASES = [
+    (F32, 1, 8, 1, 64, 1536, 16, 7, "max", 1536), (F32, 1, 8, 1, 64, 1537, 16, 7, "avg", 200), (F32, 2, 4, 4, 8, 257, 3, 5, "max", 64),
+    (F32, 1, 6, 2, 200, 511, 9, 9, "avg", 77), (F32, 1, 2, 1, 256, 300, 40, 11, "max", 100), (F32, 1, 8, 8, 128, 8449, 4, 7, "max", 128),
+    (BF16, 1, 8, 1, 64, 700, 32, 7, "max", 32), (BF16, 1, 16, 2, 72, 1025, 16, 3, "max", 65), (BF16, 2, 8, 2, 96, 640, 24, 9, "max", 64),
+    (BF16, 1, 8, 2, 256, 769, 20, 7, "avg", 300), (BF16, 1, 8, 8, 128, 4096, 8, 7, "max", 128), (BF16, 1, 28, 4, 128, 1000, 32, 13, "max", 70),
+    (BF16, 1, 2, 1, 128, 16384 + 8, 8, 7, "max", 300), (BF16, 1, 2, 1, 128, 16385 + 8, 8, 7, "max", 300), (BF16, 1, 4, 1, 24, 9000, 70, 1, "max", 128),
+]
+
+
+@pytest.mark.parametrize("dtype,n,Hq,Hkv,d,L,W,pool,mode,budget", CASES)
+def test_small_and_fp32_evictions(dtype, n, Hq, Hkv, d, L, W, pool, mode, budget):
+    import paper_2505_20334_amd as laq
+    print("case:", dtype, n, Hq, Hkv, d, L, W, pool, mode, budget, flush=True)
+    g = torch.Generator().manual_seed(L + d)
+    q = (1.5 * torch.randn(n, Hq, W, d, generator=g)).to(dtype)
+    k, v = (torch.randn(n, Hkv, L, d, generator=g).to(dtype) for _ in range(2))
+    b = [budget - 3 * i for i in range(n)]
+    # one window of mixed positions (long ones travel in the workspace) and the trailing one
+    for pos, keep in ((None, None), ([(37 * w) % L if w % 3 else L + w for w in range(W)], min(5, budget))):
+        scores, idx, ko, vo = laq.laq_evict(q.to(DEV), k.to(DEV), v.to(DEV), b, pool, q_pos=pos, keep=keep, pool_mode=mode)
+        torch.cuda.synchronize()
+        parts, kp, vp = (split_packed(x.cpu(), b, Hkv, L) for x in (idx, ko, vo))
+        for i in range(n):
+            pooled, _, _, _ = oracle.evict(q[i], k[i], v[i], b[i], pool, q_pos=pos, keep=keep, pool_mode=mode)
+            check_scores(scores[i].cpu(), pooled, dtype, "scores")
+            kept = W if keep is None else keep
+            want = oracle.select(scores[i].cpu(), kept, b[i])
+            assert torch.equal(parts[i], want)
+            for h in range(Hkv):
+                check_index_row(parts[i][h].numpy(), pooled[h].float().numpy(), kept, b[i], RTOL[dtype], "list")
+            assert torch.equal(kp[i], oracle.compact(k[i], want)) and torch.equal(vp[i], oracle.compact(v[i], want))
