@@ -57,7 +57,7 @@ SCORE_STAGE_KERNELS = ("stream_kernel", "row_constants", "reset_counters", "pool
                        "fused_reset", "stats_generic_kernel", "norm_generic_kernel", "pool_kernel")
 
 
-DECODE_KERNELS = ("decode_kernel", "merge_parts_kernel")
+DECODE_KERNELS = ("decode_kernel",)
 LIVE_TRAFFIC_FAILED = []                   # why a profiled child run of this process failed, if one did
 
 
@@ -191,7 +191,7 @@ def bench_decode(args, torch, laq, cfg, budgets, dev):
                    "cache_copies_cycled": len(copies)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "traffic_source": traffic_source,
-                     "kernel": "decode_kernel + merge_parts_kernel (K' and V' rows read once, q read, out written)",
+                     "kernel": "decode_kernel (K' and V' rows read once, q read, out written)",
                      "algorithmic_bytes_per_launch": ab, "ms_per_launch": round(ms_kernel, 4)},
     }
     if not args.no_cpu_baseline:

@@ -315,8 +315,8 @@ int laq_qcache_store(const laq_shape *shape, const void *q_step, int32_t t, void
  *   out        fp32 [n_inst, Hq, d]
  *   ws / ws_bytes  optional device scratch (ws may be NULL).  With at least
  *              laq_decode_workspace_bytes(shape, budget) bytes, a call with few instances and
- *              heads spreads every cache of more than 512 rows over several workgroups and
- *              merges their partial results; LAQ_ERR_WORKSPACE if ws is given but too small.
+ *              heads spreads its longer caches over several workgroups and merges their
+ *              partial results; LAQ_ERR_WORKSPACE if ws is given but too small.
  *              Without it every cache is read by one workgroup.
  * Reads n_inst, Hq, Hkv, d, L, dtype, scale of the shape.  Partial sums are merged in a fixed
  * order: two runs of the same call give identical bits (with and without ws the last bits of

@@ -176,14 +176,6 @@ static void fill_compact_table(int Hkv, int L, int pieces_per_row, const int32_t
   *rows_after = row;
 }
 
-// The rows kept per KV head if that is the same number for instances i0 .. i0+n-1, else 0.
-static int uniform_rows(int L, const int32_t* budget, int i0, int n) {
-  const int bk = budget[i0] < L ? budget[i0] : L;
-  for (int i = 1; i < n; ++i)
-    if ((budget[i0 + i] < L ? budget[i0 + i] : L) != bk) return 0;
-  return bk;
-}
-
 static bool budgets_ok(const laq_shape* s, const ScoreGeom& g, const int32_t* budget) {
   if (!budget) return false;
   for (int i = 0; i < s->n_inst; ++i)
@@ -349,35 +341,10 @@ static int sink_recent_impl(int n_inst, int Hkv, int L, const int32_t* budget, i
   return LAQ_OK;
 }
 
-// Decode attention splits long caches over several workgroups when the call has few of them: a
-// cache of more than DECODE_SPLIT_ROWS rows becomes parts of at most that many rows, whose partial
-// results go through the workspace.  Without a workspace every cache is one part.
-constexpr int DECODE_SPLIT_ROWS = 512;
-constexpr int DECODE_SPLIT_BELOW_WORKGROUPS = 1024;
-
-static int decode_parts_of(int bk, bool split) {
-  if (!split) return 1;
-  const int s = (bk + DECODE_SPLIT_ROWS - 1) / DECODE_SPLIT_ROWS;
-  return s < MAX_PARTS_PER_LAUNCH ? s : MAX_PARTS_PER_LAUNCH;
-}
-
-static bool decode_would_split(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget) {
-  const int gb = decode_head_batch(g.Hq, g.Hkv), nbatch = (g.G + gb - 1) / gb;
-  if ((long long)g.Hkv * nbatch * g.n_inst >= DECODE_SPLIT_BELOW_WORKGROUPS) return false;
-  for (int i = 0; i < shape->n_inst; ++i)
-    if ((budget[i] < g.L ? budget[i] : g.L) > DECODE_SPLIT_ROWS) return true;
-  return false;
-}
-
-// bytes of partial results: one record of d + 2 floats per part, workgroup column and query-head slot,
-// for at most one launch's parts (launches reuse the area; they are ordered on the stream)
-static size_t decode_ws_bytes(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget) {
-  if (!decode_would_split(shape, g, budget)) return 0;
-  long long parts = 0;
-  for (int i = 0; i < shape->n_inst; ++i) parts += decode_parts_of(budget[i] < g.L ? budget[i] : g.L, true);
-  if (parts > MAX_PARTS_PER_LAUNCH) parts = MAX_PARTS_PER_LAUNCH;
-  const int gb = decode_head_batch(g.Hq, g.Hkv), nbatch = (g.G + gb - 1) / gb;
-  return round256((size_t)parts * g.Hkv * nbatch * gb * (g.d + 2) * sizeof(float));
+// bytes of partial results of a decode call that may cut its caches into parts
+static size_t decode_ws_bytes(const ScoreGeom& g, int dtype, const int32_t* budget) {
+  return round256(decode_partial_bytes(g.n_inst, g.L, g.Hq, g.Hkv, g.d, dtype, budget,
+                                       decode_part_rows(g.n_inst, g.L, g.Hq, g.Hkv, dtype, budget)));
 }
 
 static int decode_impl(const laq_shape* shape, const void* q, const void* kc, const void* vc,
@@ -389,60 +356,15 @@ static int decode_impl(const laq_shape* shape, const void* q, const void* kc, co
   for (int i = 0; i < shape->n_inst; ++i)
     if (budget[i] < 1) return LAQ_ERR_INVALID;
   if (g.Hkv > 65535) return LAQ_ERR_UNSUPPORTED;
-  const bool split = ws != nullptr && decode_would_split(shape, g, budget);
-  if (split && ws_bytes < decode_ws_bytes(shape, g, budget)) return LAQ_ERR_WORKSPACE;
-  float* partial = static_cast<float*>(ws);
-  if (!split) {                                      // every cache is one part: tables of whole instances
-    int64_t row = 0;
-    for (int i0 = 0; i0 < shape->n_inst; i0 += MAX_INST_PER_LAUNCH) {
-      const int n = shape->n_inst - i0 < MAX_INST_PER_LAUNCH ? shape->n_inst - i0 : MAX_INST_PER_LAUNCH;
-      DecodeWhole whole;
-      whole.inst0 = i0;
-      for (int i = 0; i < n; ++i) {
-        whole.bk[i] = budget[i0 + i] < g.L ? budget[i0 + i] : g.L;
-        whole.row0[i] = row;
-        row += (int64_t)g.Hkv * whole.bk[i];
-      }
-      if (launch_decode(n, g.Hq, g.Hkv, g.d, shape->dtype, g.scale2, whole, q, kc, vc, out, st) != hipSuccess)
-        return LAQ_ERR_DEVICE;
-    }
-    return LAQ_OK;
+  int part_rows = g.L;                     // without a workspace every cache is one part
+  if (ws != nullptr) {
+    if (ws_bytes < decode_ws_bytes(g, shape->dtype, budget)) return LAQ_ERR_WORKSPACE;
+    part_rows = decode_part_rows(g.n_inst, g.L, g.Hq, g.Hkv, shape->dtype, budget);
   }
-
-  DecodeParts tab;
-  int n_parts = 0;
-  bool any_split = false;
-  auto flush = [&]() -> bool {
-    if (n_parts == 0) return true;
-    if (launch_decode(n_parts, g.Hq, g.Hkv, g.d, shape->dtype, g.scale2, tab, q, kc, vc, out, partial, st) !=
-        hipSuccess)
-      return false;
-    if (any_split && launch_merge_parts(n_parts, g.Hq, g.Hkv, g.d, tab, partial, out, st) != hipSuccess) return false;
-    n_parts = 0;
-    any_split = false;
-    return true;
-  };
-  int64_t row = 0;
-  for (int i = 0; i < shape->n_inst; ++i) {
-    const int bk = budget[i] < g.L ? budget[i] : g.L;
-    const int S = decode_parts_of(bk, split);
-    if (n_parts + S > MAX_PARTS_PER_LAUNCH && !flush()) return LAQ_ERR_DEVICE;   // the parts of a cache stay together
-    const int per = (bk + S - 1) / S;
-    for (int p = 0; p < S; ++p) {
-      const int start = p * per;
-      tab.row0[n_parts] = row;
-      tab.bk[n_parts] = bk;
-      tab.start[n_parts] = start < bk ? start : bk;
-      tab.rows[n_parts] = start < bk ? (bk - start < per ? bk - start : per) : 0;
-      tab.inst[n_parts] = i;
-      tab.split[n_parts] = (int16_t)p;
-      tab.nsplit[n_parts] = (int16_t)S;
-      ++n_parts;
-    }
-    any_split = any_split || S > 1;
-    row += (int64_t)g.Hkv * bk;
-  }
-  return flush() ? LAQ_OK : LAQ_ERR_DEVICE;
+  return launch_decode(g.n_inst, g.L, g.Hq, g.Hkv, g.d, shape->dtype, g.scale2, part_rows, budget, q, kc, vc, out,
+                       ws, st) == hipSuccess
+             ? LAQ_OK
+             : LAQ_ERR_DEVICE;
 }
 
 // Whether the selection kernel can do the pooling and the gather of this call along with the selection (one
@@ -552,7 +474,7 @@ size_t laq_decode_workspace_bytes(const laq_shape* shape, const int32_t* budget)
   if (laq::make_geom(shape, &g) != LAQ_OK || !budget) return 0;
   for (int i = 0; i < shape->n_inst; ++i)
     if (budget[i] < 1) return 0;
-  return laq::decode_ws_bytes(shape, g, budget);
+  return laq::decode_ws_bytes(g, shape->dtype, budget);
 }
 
 int laq_decode_attention(const laq_shape* shape, const void* q, const void* k_c, const void* v_c,

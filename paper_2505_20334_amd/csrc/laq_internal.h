@@ -170,36 +170,13 @@ struct PairTable {
   int64_t row_a[MAX_PAIR_PER_LAUNCH], row_b[MAX_PAIR_PER_LAUNCH];     // first packed row of the instance
 };
 
-// Parts of compacted caches for decode attention, up to MAX_PARTS_PER_LAUNCH per launch: a cache
-// is one part, or several consecutive ones that are merged afterwards.
-constexpr int MAX_PARTS_PER_LAUNCH = 128;
-struct DecodeParts {
-  int64_t row0[MAX_PARTS_PER_LAUNCH];   // first packed row of the instance
-  int32_t bk[MAX_PARTS_PER_LAUNCH];     // rows per KV head of the instance
-  int32_t start[MAX_PARTS_PER_LAUNCH];  // first row of the part within a head's rows
-  int32_t rows[MAX_PARTS_PER_LAUNCH];   // rows of the part
-  int32_t inst[MAX_PARTS_PER_LAUNCH];   // instance
-  int16_t split[MAX_PARTS_PER_LAUNCH];  // index of the part within its cache
-  int16_t nsplit[MAX_PARTS_PER_LAUNCH]; // parts of its cache
-  __host__ __device__ int inst_of(int i) const { return inst[i]; }
-  __host__ __device__ int64_t base_row(int i) const { return row0[i]; }
-  __host__ __device__ int cache_rows(int i) const { return bk[i]; }
-  __host__ __device__ int first_row(int i) const { return start[i]; }
-  __host__ __device__ int part_rows(int i) const { return rows[i]; }
-  __host__ __device__ int parts(int i) const { return nsplit[i]; }
-};
-// The same view of a launch in which every cache is one part: instances inst0 .. of a call.
-struct DecodeWhole {
-  int64_t row0[MAX_INST_PER_LAUNCH];
-  int32_t bk[MAX_INST_PER_LAUNCH];
-  int32_t inst0;
-  __host__ __device__ int inst_of(int i) const { return inst0 + i; }
-  __host__ __device__ int64_t base_row(int i) const { return row0[i]; }
-  __host__ __device__ int cache_rows(int i) const { return bk[i]; }
-  __host__ __device__ int first_row(int) const { return 0; }
-  __host__ __device__ int part_rows(int i) const { return bk[i]; }
-  __host__ __device__ int parts(int) const { return 1; }
-};
+// The rows kept per KV head if that is the same number for instances i0 .. i0+n-1, else 0.
+inline int uniform_rows(int L, const int32_t* budget, int i0, int n) {
+  const int bk = budget[i0] < L ? budget[i0] : L;
+  for (int i = 1; i < n; ++i)
+    if ((budget[i0 + i] < L ? budget[i0 + i] : L) != bk) return 0;
+  return bk;
+}
 
 // launchers (each returns hipGetLastError() after its last launch); `raw` receives unpooled scores
 hipError_t launch_score_tile(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q,
@@ -236,13 +213,11 @@ hipError_t launch_sink_recent(int n_inst, int Hkv, int L, int n_sink, const Inst
                               hipStream_t st);
 hipError_t launch_recall(int n_inst, int inst0, int Hkv, const PairTable& tab, const int32_t* idx_pred,
                          const int32_t* idx_gold, int32_t* overlap, float* recall, hipStream_t st);
-int decode_head_batch(int Hq, int Hkv);   // query heads of a KV head that one decode workgroup serves
-hipError_t launch_decode(int n_parts, int Hq, int Hkv, int d, int dtype, float scale2, const DecodeParts& tab,
-                         const void* q, const void* kc, const void* vc, float* out, float* partial, hipStream_t st);
-hipError_t launch_decode(int n_inst, int Hq, int Hkv, int d, int dtype, float scale2, const DecodeWhole& tab,
-                         const void* q, const void* kc, const void* vc, float* out, hipStream_t st);
-hipError_t launch_merge_parts(int n_parts, int Hq, int Hkv, int d, const DecodeParts& tab, const float* partial,
-                              float* out, hipStream_t st);
+int decode_head_batch(int Hq, int Hkv, int dtype);   // query heads of a KV head that one decode workgroup serves
+int decode_part_rows(int n, int L, int Hq, int Hkv, int dtype, const int32_t* budget);   // rows per part of the caches of a call
+size_t decode_partial_bytes(int n, int L, int Hq, int Hkv, int d, int dtype, const int32_t* budget, int rows_per_part);
+hipError_t launch_decode(int n_inst, int L, int Hq, int Hkv, int d, int dtype, float scale2, int rows_per_part, const int32_t* budget,
+                         const void* q, const void* kc, const void* vc, float* out, void* ws, hipStream_t st);
 hipError_t launch_qcache_store(long long rows, int W, int t, int row_bytes, const void* q_step, void* q_cache,
                                hipStream_t st);
 constexpr int COMPACT_THREADS = 256;      // one 16-byte piece of an output row per thread

@@ -1,6 +1,5 @@
-// Helpers for kernels in which a group of adjacent lanes shares one row of d elements, 8 elements
-// (one 16- or 32-byte piece) per lane: loads of a piece, the product of two pieces, and the sum
-// over the lanes of a group.  Used by the decode-attention kernel and the generic scoring kernels.
+// Eight elements of a row of d as one lane of the decode-attention kernel holds them (one 16- or 32-byte piece): loads and the
+// product of two pieces.
 #ifndef LAQ_LANEGROUP_H
 #define LAQ_LANEGROUP_H
 
@@ -31,23 +30,6 @@ __device__ __forceinline__ void widen8(const Piece8BF16& x, float (&f)[8]) {   /
   f[6] = __uint_as_float(x.r.w << 16); f[7] = __uint_as_float(x.r.w & 0xffff0000u);
 }
 
-// Sum over the PP (8, 16 or 32) adjacent lanes of a group, result in every lane.  Data-parallel
-// lane permutations within a row of 16 lanes: swap neighbours, swap pairs, then mirror the 8 and
-// the 16 lanes (the halves already agree, so a mirror reaches the other half's sum).
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-template <int PP>
-__device__ __forceinline__ float group_sum(float x) {
-  x += dpp_move<0xB1>(x);                   // quad_perm [1,0,3,2]
-  x += dpp_move<0x4E>(x);                   // quad_perm [2,3,0,1]
-  x += dpp_move<0x141>(x);                  // row_half_mirror
-  if (PP >= 16) x += dpp_move<0x140>(x);    // row_mirror
-  if (PP >= 32) x += __shfl_xor(x, 16);
-  return x;
-}
-
 // Product of two 8-element pieces.  bf16: four two-element dot-product instructions on the raw
 // pairs (products and sums in fp32), no widening; fp32: eight fused multiply-adds.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -70,13 +52,6 @@ __device__ __forceinline__ float dot8(const Piece8F32& a, const Piece8F32& b) {
 template <typename T> struct PieceOf;
 template <> struct PieceOf<float> { using type = Piece8F32; };
 template <> struct PieceOf<uint16_t> { using type = Piece8BF16; };
-
-// lanes per row: the power of two (at least 8, at most 32) that covers the row's d / 8 pieces
-inline int lanes_per_row(int d) {
-  int pp = 8;
-  while (pp * 8 < d) pp <<= 1;
-  return pp;
-}
 
 }  // namespace laq
 #endif  // LAQ_LANEGROUP_H
