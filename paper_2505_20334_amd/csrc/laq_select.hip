@@ -161,7 +161,7 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
       return x;
     };
 #pragma unroll
-    for (int q4 = 0; q4 < ITEMS / 4; ++q4) v[q4] = quad_at(seg0 + q4 * 256 + lane * 4, -INFINITY);   // (below every score)
+    for (int q4 = 0; q4 < ITEMS / 4; ++q4) v[q4] = quad_at(seg0 + q4 * 256 + lane * 4, 0.f);
     if constexpr (FINISH) {
       if (fin.half > 0) {
         float* pooled = fin.pooled + ((size_t)(inst0 + li) * Hkv + head) * L;
@@ -205,10 +205,16 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
     for (int i = tid * 4; i < BINS * COPIES; i += THREADS * 4) *reinterpret_cast<int4*>(sh.first + i) = make_int4(0, 0, 0, 0);
 #pragma unroll
     for (int q4 = 0; q4 < ITEMS / 4; ++q4) {
-      key[4 * q4] = order_key(v[q4].x);
-      key[4 * q4 + 1] = order_key(v[q4].y);
-      key[4 * q4 + 2] = order_key(v[q4].z);
-      key[4 * q4 + 3] = order_key(v[q4].w);
+      const int pos = seg0 + q4 * 256 + lane * 4;
+      key[4 * q4] = max(order_key(v[q4].x), 1u);
+      key[4 * q4 + 1] = max(order_key(v[q4].y), 1u);
+      key[4 * q4 + 2] = max(order_key(v[q4].z), 1u);
+      key[4 * q4 + 3] = max(order_key(v[q4].w), 1u);
+      if (pos < 0 || pos + 3 >= P) {       // positions outside the prefix rank below every score, -inf too:
+#pragma unroll
+        for (int c = 0; c < 4; ++c)        // those before it would come first among equals
+          if (pos + c < 0 || pos + c >= P) key[4 * q4 + c] = 0u;
+      }
     }
   } else {
     for (int i = tid * 4; i < BINS * COPIES; i += THREADS * 4) *reinterpret_cast<int4*>(sh.first + i) = make_int4(0, 0, 0, 0);

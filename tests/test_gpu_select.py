@@ -22,7 +22,7 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("values", ["spread", "few", "equal", "plateaus"])
+@pytest.mark.parametrize("values", ["spread", "few", "equal", "plateaus", "masked"])
 @pytest.mark.parametrize("n,Hkv,L,W,budgets", CASES)
 def test_select_at_the_edges_of_its_variants(n, Hkv, L, W, budgets, values):
     import paper_2505_20334_amd as laq
@@ -34,6 +34,9 @@ def test_select_at_the_edges_of_its_variants(n, Hkv, L, W, budgets, values):
         s = torch.randint(0, 9, (n, Hkv, L), generator=g, device=DEV).float() / 7
     elif values == "equal":
         s = torch.full((n, Hkv, L), 0.25, device=DEV)
+    elif values == "masked":                # fewer scores than wanted keys: the others tie at -inf
+        s = torch.rand(n, Hkv, L, generator=g, device=DEV)
+        s.masked_fill_(torch.rand(n, Hkv, L, generator=g, device=DEV) < 0.999, float("-inf"))
     else:                                   # what the pooling makes of scores
         s = torch.exp(torch.randn(n * Hkv, 1, L, generator=g, device=DEV))
         s = torch.nn.functional.max_pool1d(s, 7, 1, 3).reshape(n, Hkv, L)
