@@ -180,9 +180,9 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
             float m = w[4 + c], sum = 0.f;
 #pragma unroll
             for (int o = -FINISH_MAX_HALF; o <= FINISH_MAX_HALF; ++o) {
-              const float x = abs(o) <= fin.half ? w[4 + c + o] : 0.f;
-              m = fmaxf(m, x);
-              sum += x;
+              const bool in = abs(o) <= fin.half;      // (no zero for those outside: it would hide a NaN)
+              m = in ? fmaxf(m, w[4 + c + o]) : m;
+              sum += in ? w[4 + c + o] : 0.f;
             }
             r[c] = fin.avg ? sum / kernel_size : m;
           }

@@ -45,3 +45,19 @@ def test_small_and_fp32_evictions(dtype, n, Hq, Hkv, d, L, W, pool, mode, budget
             for h in range(Hkv):
                 check_index_row(parts[i][h].numpy(), pooled[h].float().numpy(), kept, b[i], RTOL[dtype], "list")
             assert torch.equal(kp[i], oracle.compact(k[i], want)) and torch.equal(vp[i], oracle.compact(v[i], want))
+
+
+@pytest.mark.parametrize("mode", ["max", "avg"])
+@pytest.mark.parametrize("pool", [1, 5, 7, 9])
+def test_a_nan_shows_in_the_scores_of_one_launch_as_in_those_of_several(pool, mode):
+    """A key of NaNs makes the scores of its head NaN; the finishing launch pools them as laq_score does."""
+    import paper_2505_20334_amd as laq
+    g = torch.Generator().manual_seed(pool)
+    q, k, v = (torch.randn(1, h, r, 64, generator=g).to(DEV) for h, r in ((4, 8), (2, 601), (2, 601)))
+    k[0, 1, 77] = float("nan")
+    scores = laq.laq_evict(q, k, v, [64], pool, pool_mode=mode)[0]
+    want = laq.laq_score(q, k, pool, pool_mode=mode)
+    torch.cuda.synchronize()
+    half = pool // 2                        # (windows over either end of the prefix hold zeros, which a maximum takes over a NaN)
+    assert torch.isnan(want[0, 1, half:601 - 8 - half]).all() and not torch.isnan(want[0, 0]).any()
+    assert torch.equal(torch.isnan(scores), torch.isnan(want)) and torch.equal(scores[0, 0], want[0, 0])
