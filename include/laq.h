@@ -190,9 +190,10 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *          laq_score(p) + laq_select(1) and laq_score(1) + laq_select(p) give the same indices.
  *   ws / ws_bytes  device scratch of at least laq_workspace_bytes(shape)
  * Supported: dtype BF16 or F32; any Hq/Hkv/W/L within the limits of laq_shape;
- * pool_kernel odd, 1 <= pool_kernel <= 63.  BF16 with d = 64 or 128 and W <= 512 runs on the
- * matrix cores; everything else runs on a vector-ALU path with the same results to within the
- * rounding of its fp32 sums, several times slower per key.  q_win, k and scores must be 16-byte
+ * pool_kernel odd, 1 <= pool_kernel <= 63.  BF16 with d = 64 or 128, W <= 512 and more than 512
+ * chunks of 256 keys runs on kernels that stream the keys, everything else on kernels with one chunk
+ * per workgroup (score_choice overrides the number of chunks), with the same results to within the
+ * rounding of their fp32 sums; all of them on the matrix cores.  q_win, k and scores must be 16-byte
  * aligned.
  */
 int laq_score(const laq_shape *shape, const void *q_win, const void *k, int pool_kernel,
@@ -228,8 +229,9 @@ int laq_select_sink_recent(int32_t n_inst, int32_t Hkv, int32_t L, const int32_t
 /*
  * Which kernels laq_score (and laq_evict) take for this shape on the current device, for callers
  * that account for memory traffic (Sec. 4.3's scoring reads K once or twice accordingly):
- * LAQ_KERNEL_VECTOR (vector-ALU path, K streamed twice), LAQ_KERNEL_TWO_PASS (matrix cores, K
- * streamed twice) or LAQ_KERNEL_SINGLE_READ (matrix cores, K read once); a negative error code
+ * LAQ_KERNEL_VECTOR (fp32 caches, or a head size or window that the bf16 streaming kernels do not take: one
+ * chunk per workgroup, K read twice), LAQ_KERNEL_TWO_PASS (bf16, K read twice) or
+ * LAQ_KERNEL_SINGLE_READ (bf16, K read once); a negative error code
  * for an invalid shape.  The strides, the block table and the score_choice of `shape` are taken
  * into account like laq_score does.  Launches nothing.
  */

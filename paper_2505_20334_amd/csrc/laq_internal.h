@@ -65,11 +65,11 @@ struct QueryPos {                          // host side
 //   part:  float2 (m, z) per (instance, KV head, chunk, padded row): softmax statistics of a chunk
 //   rowc:  float c = M + log2(Z) per (instance, KV head, padded row)
 //   raw:   float per (instance, KV head, key): unpooled scores in front of a separate pooling
-//          kernel (generic path, average pool); the MFMA path with the max pool keeps the edge
-//          records of its chunk boundaries here instead
+//          kernel (one-chunk kernels, average pool); the streaming kernels with the max pool keep the edge
+//          records of their chunk boundaries here instead
 //   pooled: float per (instance, KV head, key): the hand-over plane between scoring and selection
 //          when laq_evict is called without a scores buffer
-//   ctr:   two work counters (one per streaming pass of the MFMA path), reset by every call
+//   ctr:   two work counters (one per streaming pass), reset by every call
 struct Workspace {
   float2* part;
   float* rowc;
