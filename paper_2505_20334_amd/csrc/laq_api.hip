@@ -221,8 +221,15 @@ static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g) {
 // three launches where the streaming ones need five.  laq_score, bf16, d = 128, 32 and 64 score rows, one against
 // the other: 128 chunks 18.9 : 21.3 and 17.4 : 20.2 us, 512 chunks 19.8 : 21.6 and 23.9 : 26.0; beyond that
 // nothing is gained and with many rows much is lost (1536 chunks, 64 rows 52.6 : 49.6, 128 rows 69.9 : 60.4).
+// Between 129 and 256 chunks a compute unit has one workgroup of them, which walks all row tiles alone; with several
+// groups of 128 rows, the last one more than half full, the streaming kernels are the faster ones (laq_evict, one
+// against the other: 256 rows, 192 and 256 chunks, d = 128 47.4 : 44.3 and 50.2 : 45.4 us, d = 64 40.8 : 35.6 and
+// 42.3 : 36.6; but 160 rows, d = 128 37.4 : 42.4 and 40.0 : 44.5; 256 rows, 128 and 384 chunks 36.2 : 40.9 and
+// 57.8 : 62.8).
 static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
-  return shape->score_choice == LAQ_CHOOSE_AUTO && (long long)g.n_inst * g.Hkv * g.nchunk <= 512;
+  const long long chunks = (long long)g.n_inst * g.Hkv * g.nchunk;
+  if (g.Rpad > 128 && (g.Rpad - 1) % 128 >= 64 && chunks > 128 && chunks <= 256) return false;
+  return shape->score_choice == LAQ_CHOOSE_AUTO && chunks <= 512;
 }
 
 // Scores of a validated call into `scores`: pooled, or, with pool == 1, raw.

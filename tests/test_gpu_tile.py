@@ -20,6 +20,9 @@ CASES = [
     (BF16, 1, 8, 1, 64, 700, 32, 7, "max", 32), (BF16, 1, 16, 2, 72, 1025, 16, 3, "max", 65), (BF16, 2, 8, 2, 96, 640, 24, 9, "max", 64),
     (BF16, 1, 8, 2, 256, 769, 20, 7, "avg", 300), (BF16, 1, 8, 8, 128, 4096, 8, 7, "max", 128), (BF16, 1, 28, 4, 128, 1000, 32, 13, "max", 70),
     (BF16, 1, 2, 1, 128, 16384 + 8, 8, 7, "max", 300), (BF16, 1, 2, 1, 128, 16385 + 8, 8, 7, "max", 300), (BF16, 1, 4, 1, 24, 9000, 70, 1, "max", 128),
+    # many score rows around 128 and 256 chunks
+    (BF16, 1, 64, 8, 64, 4096, 32, 7, "max", 200), (BF16, 1, 64, 8, 64, 4100, 32, 7, "max", 200),
+    (BF16, 1, 64, 8, 64, 8192, 20, 5, "avg", 96), (BF16, 1, 64, 8, 64, 8193, 20, 7, "max", 96),
 ]
 
 
