@@ -31,6 +31,7 @@ PyObject* get_device;      // torch._C._cuda_getDevice
 PyObject* get_stream;      // torch._C._cuda_getCurrentRawStream
 
 bool is_none(PyObject* o) { return o == Py_None; }
+bool is_text(PyObject* o, const char* text) { return PyUnicode_Check(o) && PyUnicode_CompareWithASCIIString(o, text) == 0; }
 
 // tensor on a GPU, or null
 const at::Tensor* gpu_tensor(PyObject* o) {
@@ -159,12 +160,12 @@ PyObject* evict(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
       sh.q_pos = pos.data();
     }
     if (!is_none(a[12]) && !as_int(a[12], &keep)) return none();
-    if (PyUnicode_CompareWithASCIIString(a[13], "max") == 0) sh.pool_mode = LAQ_POOL_MAX;
-    else if (PyUnicode_CompareWithASCIIString(a[13], "avg") == 0) sh.pool_mode = LAQ_POOL_AVG;
+    if (is_text(a[13], "max")) sh.pool_mode = LAQ_POOL_MAX;
+    else if (is_text(a[13], "avg")) sh.pool_mode = LAQ_POOL_AVG;
     else return none();
-    if (PyUnicode_CompareWithASCIIString(a[17], "auto") == 0) sh.score_choice = LAQ_CHOOSE_AUTO;
-    else if (PyUnicode_CompareWithASCIIString(a[17], "two-pass") == 0) sh.score_choice = LAQ_CHOOSE_TWO_PASS;
-    else if (PyUnicode_CompareWithASCIIString(a[17], "single-read") == 0) sh.score_choice = LAQ_CHOOSE_SINGLE_READ;
+    if (is_text(a[17], "auto")) sh.score_choice = LAQ_CHOOSE_AUTO;
+    else if (is_text(a[17], "two-pass")) sh.score_choice = LAQ_CHOOSE_TWO_PASS;
+    else if (is_text(a[17], "single-read")) sh.score_choice = LAQ_CHOOSE_SINGLE_READ;
     else return none();
     if (!PyBool_Check(a[14])) return none();
     if (v) {

@@ -1,0 +1,45 @@
+"""The compiled binding of the calls in a model's loop, on tensors without memory (no GPU needed): whatever it does
+not take must end in the Python binding's own exception.  Every case runs in a process of its own, since what
+these tests are about is a process that dies."""
+import subprocess
+import sys
+
+import pytest
+
+SETUP = """
+import ctypes
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+import paper_2505_20334_amd as laq
+from paper_2505_20334_amd import binding
+
+lib = laq.load_library()
+address = lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+# (no device here: a device and a stream number as a GPU would give them)
+binding._native.bind(address("laq_evict"), address("laq_workspace_bytes"), address("laq_decode_attention"),
+                     address("laq_decode_workspace_bytes"), address("laq_qcache_store"), lambda: 0, lambda device: 0)
+binding._stream = lambda stream: 0
+
+def made(*sizes):
+    return torch.empty(*sizes, dtype=torch.bfloat16, device="cuda")
+
+with FakeTensorMode():
+    q, k, step, rows = made(1, 8, 8, 128), made(1, 2, 512, 128), made(1, 8, 128), made(128, 128)
+    try:
+        %s
+        print("no exception")
+    except Exception as e:
+        print("raised", type(e).__name__, str(e).split(chr(10))[0])
+"""
+
+
+def outcome(call):
+    res = subprocess.run([sys.executable, "-c", SETUP % call], capture_output=True, text=True, timeout=110)
+    assert res.returncode == 0, "the process ended with %d: %s" % (res.returncode, res.stderr[-600:])
+    return res.stdout.strip().splitlines()[-1]
+
+
+@pytest.mark.parametrize("value", ["None", "b'max'"])
+@pytest.mark.parametrize("name", ["pool_mode", "choose"])
+def test_a_mode_that_is_no_text(name, value):
+    assert outcome("laq.laq_evict(q, k, k, [64], 7, %s=%s)" % (name, value)).startswith("raised ValueError")
