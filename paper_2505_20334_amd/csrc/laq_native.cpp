@@ -198,12 +198,15 @@ PyObject* evict(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     if (!out[4]) out[4] = &(made[4] = make({(int64_t)need}, at::kByte, *k));
     void* stream;
     if (!current_stream(&stream)) return nullptr;
+    // (a tensor without memory throws when it is asked for its address: not where the GIL is released)
     int rc;
     const size_t ws_bytes = out[4]->numel() * out[4]->element_size();
+    const void *qp = q->data_ptr(), *kp = k->data_ptr(), *vp = v ? v->data_ptr() : nullptr;
+    void* op[5];
+    for (int i = 0; i < 5; ++i) op[i] = out[i] ? out[i]->data_ptr() : nullptr;
     Py_BEGIN_ALLOW_THREADS;
-    rc = fn_evict(&sh, q->data_ptr(), k->data_ptr(), v ? v->data_ptr() : nullptr, budget.data(), (int)pool,
-                  out[0] ? static_cast<float*>(out[0]->data_ptr()) : nullptr, static_cast<int32_t*>(out[1]->data_ptr()),
-                  out[2]->data_ptr(), v ? out[3]->data_ptr() : nullptr, out[4]->data_ptr(), ws_bytes, stream);
+    rc = fn_evict(&sh, qp, kp, vp, budget.data(), (int)pool, static_cast<float*>(op[0]), static_cast<int32_t*>(op[1]), op[2],
+                  op[3], op[4], ws_bytes, stream);
     Py_END_ALLOW_THREADS;
     if (rc != LAQ_OK) return PyLong_FromLong(rc);
     PyObject* res = PyTuple_New(4);
@@ -261,9 +264,10 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     if (!current_stream(&stream)) return nullptr;
     int rc;
     const size_t ws_bytes = ws ? ws->numel() * ws->element_size() : 0;
+    const void *qp = q->data_ptr(), *kp = k->data_ptr(), *vp = v->data_ptr();
+    void *op = out->data_ptr(), *wp = ws ? ws->data_ptr() : nullptr;
     Py_BEGIN_ALLOW_THREADS;
-    rc = fn_decode_attention(&sh, q->data_ptr(), k->data_ptr(), v->data_ptr(), budget.data(), static_cast<float*>(out->data_ptr()),
-                             ws ? ws->data_ptr() : nullptr, ws_bytes, stream);
+    rc = fn_decode_attention(&sh, qp, kp, vp, budget.data(), static_cast<float*>(op), wp, ws_bytes, stream);
     Py_END_ALLOW_THREADS;
     if (rc != LAQ_OK) return PyLong_FromLong(rc);
     if (!is_none(a[7])) {

@@ -43,3 +43,12 @@ def outcome(call):
 @pytest.mark.parametrize("name", ["pool_mode", "choose"])
 def test_a_mode_that_is_no_text(name, value):
     assert outcome("laq.laq_evict(q, k, k, [64], 7, %s=%s)" % (name, value)).startswith("raised ValueError")
+
+
+BATCHED = {"evict": "laq.laq_evict(x, k, k, [64], 7), q", "decode": "laq.laq_decode_attention(x, rows, rows, [64], 2, 512), step"}
+
+
+@pytest.mark.parametrize("name", ["evict", "decode"])
+def test_a_tensor_without_an_address(name):
+    call, batch = BATCHED[name].rsplit(", ", 1)
+    assert outcome("torch.vmap(lambda x: %s)(%s.unsqueeze(0))" % (call, batch)).startswith("raised RuntimeError Cannot access data pointer")
