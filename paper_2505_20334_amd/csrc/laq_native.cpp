@@ -283,27 +283,34 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
 
 // qcache_store(q_cache, q_step, t) -> q_cache | error code | None
 PyObject* qcache_store(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
-  if (n_args != 3) return none();
-  const at::Tensor *c = gpu_tensor(a[0]), *q = gpu_tensor(a[1]);
-  long long t;
-  if (!c || !q || c->dim() != 4 || q->dim() != 3 || !c->is_contiguous() || !q->is_contiguous() || c->scalar_type() != q->scalar_type() ||
-      c->device() != q->device() || q->size(0) != c->size(0) || q->size(1) != c->size(1) || q->size(2) != c->size(3) || !as_int(a[2], &t))
-    return none();
-  const int dt = dtype_code(*c);
-  if (dt < 0 || c->size(0) < 1 || c->size(0) > INT32_MAX || c->size(1) > INT32_MAX || c->size(2) < 1 || c->size(2) > INT32_MAX) return none();
-  laq_shape sh;
-  memset(&sh, 0, sizeof sh);
-  sh.n_inst = (int32_t)c->size(0); sh.Hq = sh.Hkv = (int32_t)c->size(1); sh.d = (int32_t)c->size(3);
-  sh.L = sh.W = (int32_t)c->size(2); sh.dtype = dt;
-  void* stream;
-  if (!current_stream(&stream)) return nullptr;
-  int rc;
-  Py_BEGIN_ALLOW_THREADS;
-  rc = fn_qcache_store(&sh, q->data_ptr(), (int32_t)t, c->data_ptr(), stream);
-  Py_END_ALLOW_THREADS;
-  if (rc != LAQ_OK) return PyLong_FromLong(rc);
-  Py_INCREF(a[0]);
-  return a[0];
+  try {
+    if (n_args != 3) return none();
+    const at::Tensor *c = gpu_tensor(a[0]), *q = gpu_tensor(a[1]);
+    long long t;
+    if (!c || !q || c->dim() != 4 || q->dim() != 3 || !c->is_contiguous() || !q->is_contiguous() || c->scalar_type() != q->scalar_type() ||
+        c->device() != q->device() || q->size(0) != c->size(0) || q->size(1) != c->size(1) || q->size(2) != c->size(3) || !as_int(a[2], &t))
+      return none();
+    const int dt = dtype_code(*c);
+    if (dt < 0 || c->size(0) < 1 || c->size(0) > INT32_MAX || c->size(1) > INT32_MAX || c->size(2) < 1 || c->size(2) > INT32_MAX) return none();
+    laq_shape sh;
+    memset(&sh, 0, sizeof sh);
+    sh.n_inst = (int32_t)c->size(0); sh.Hq = sh.Hkv = (int32_t)c->size(1); sh.d = (int32_t)c->size(3);
+    sh.L = sh.W = (int32_t)c->size(2); sh.dtype = dt;
+    void* stream;
+    if (!current_stream(&stream)) return nullptr;
+    int rc;
+    const void* qp = q->data_ptr();
+    void* cp = c->data_ptr();
+    Py_BEGIN_ALLOW_THREADS;
+    rc = fn_qcache_store(&sh, qp, (int32_t)t, cp, stream);
+    Py_END_ALLOW_THREADS;
+    if (rc != LAQ_OK) return PyLong_FromLong(rc);
+    Py_INCREF(a[0]);
+    return a[0];
+  } catch (const std::exception& e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+    return nullptr;
+  }
 }
 
 // bind(addresses of laq_evict, laq_workspace_bytes, laq_decode_attention, laq_decode_workspace_bytes, laq_qcache_store,

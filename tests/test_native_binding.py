@@ -52,3 +52,8 @@ BATCHED = {"evict": "laq.laq_evict(x, k, k, [64], 7), q", "decode": "laq.laq_dec
 def test_a_tensor_without_an_address(name):
     call, batch = BATCHED[name].rsplit(", ", 1)
     assert outcome("torch.vmap(lambda x: %s)(%s.unsqueeze(0))" % (call, batch)).startswith("raised RuntimeError Cannot access data pointer")
+
+
+def test_a_tensor_without_an_address_in_the_query_cache():
+    call = "torch.vmap(lambda x: laq.laq_qcache_store(q, x, 0))(step.unsqueeze(0))"
+    assert outcome(call).startswith("raised RuntimeError Cannot access data pointer")
