@@ -7,8 +7,9 @@
 //
 // Every function takes exactly what its namesake in binding.py takes (positionally, defaults filled in
 // there) and returns None for anything out of the ordinary -- a tensor of another type, device or layout,
-// an argument that is not a plain number -- without having done anything: binding.py then walks its own
-// checks and raises what it always raised.  An error of the library comes back as its (negative) code.
+// an argument that is not a plain number, anything that throws (no memory for an output, a tensor without an
+// address) -- without having launched anything: binding.py then walks its own checks and raises what it always
+// raised, of the type it always had.  An error of the library comes back as its (negative) code.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -96,6 +97,8 @@ at::Tensor make(at::IntArrayRef sizes, at::ScalarType type, const at::Tensor& li
 }
 
 PyObject* none() { Py_RETURN_NONE; }
+// after a C++ exception: one that carries a Python exception (a dispatch mode raised it) leaves that set
+PyObject* thrown() { return PyErr_Occurred() ? nullptr : none(); }
 
 // rows of the packed outputs; false: a budget the library will refuse
 bool packed_rows(const std::vector<int32_t>& budget, int64_t Hkv, int64_t L, int64_t* rows) {
@@ -218,13 +221,16 @@ PyObject* evict(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         Py_INCREF(o);
       } else {
         o = THPVariable_Wrap(std::move(made[i]));
+        if (!o) {
+          Py_DECREF(res);
+          return nullptr;
+        }
       }
       PyTuple_SET_ITEM(res, i, o);
     }
     return res;
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
+  } catch (const std::exception&) {
+    return thrown();
   }
 }
 
@@ -275,9 +281,8 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
       return a[7];
     }
     return THPVariable_Wrap(std::move(made));
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
+  } catch (const std::exception&) {
+    return thrown();
   }
 }
 
@@ -307,9 +312,8 @@ PyObject* qcache_store(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     if (rc != LAQ_OK) return PyLong_FromLong(rc);
     Py_INCREF(a[0]);
     return a[0];
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
+  } catch (const std::exception&) {
+    return thrown();
   }
 }
 

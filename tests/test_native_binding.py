@@ -57,3 +57,20 @@ def test_a_tensor_without_an_address(name):
 def test_a_tensor_without_an_address_in_the_query_cache():
     call = "torch.vmap(lambda x: laq.laq_qcache_store(q, x, 0))(step.unsqueeze(0))"
     assert outcome(call).startswith("raised RuntimeError Cannot access data pointer")
+
+
+OUT_OF_MEMORY = """
+        from torch.utils._python_dispatch import TorchDispatchMode
+        class NoMemory(TorchDispatchMode):
+            def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+                if "empty" in str(func):
+                    raise torch.OutOfMemoryError("no memory")
+                return func(*args, **(kwargs or {}))
+        with NoMemory():
+            %s
+"""
+
+
+@pytest.mark.parametrize("call", ["laq.laq_evict(q, k, k, [64], 7)", "laq.laq_decode_attention(step, rows, rows, [64], 2, 512)"])
+def test_an_allocation_that_fails_raises_what_torch_raises(call):
+    assert outcome(OUT_OF_MEMORY % call) == "raised OutOfMemoryError no memory"
