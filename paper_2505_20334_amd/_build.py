@@ -80,7 +80,6 @@ def build(force: bool = True, verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(sources()) + 1)) as pool:
         native = pool.submit(compile_native)
         objs = list(pool.map(compile_one, sources()))
-        native.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     try:
         run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
@@ -89,6 +88,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         for o in objs:
             if os.path.exists(o):
                 os.remove(o)
+    native.result()                                # (the library is there even where its compiled binding does not build)
     return LIB
 
 

@@ -2,7 +2,7 @@
 
 The three calls that sit in a model's loop (laq_evict, laq_decode_attention, laq_qcache_store) are
 marshalled by the extension module ``_native`` (csrc/laq_native.cpp); ctypes serves the others, and
-these three where an argument is out of the ordinary.
+these three where an argument is out of the ordinary or the module cannot be loaded.
 
 Function names and argument meaning follow ``include/laq.h``.  Tensors are torch
 tensors that already live on the GPU (torch supplies device memory and the
@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -52,14 +53,15 @@ def load_library() -> ctypes.CDLL:
     global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH) or not os.path.exists(os.path.join(_PKG, "_native.so")):
+    if not os.path.exists(_LIB_PATH):
         # nothing built yet: build once (hipcc); there is no other way to run, so a failure is final
         try:
             from . import _build
             _build.build()
         except Exception as exc:
-            raise ImportError("liblaq.so is not built and building it failed (%s): run "
-                              "`python -c 'import __graft_entry__ as g; g.build()'`" % exc)
+            if not os.path.exists(_LIB_PATH):
+                raise ImportError("liblaq.so is not built and building it failed (%s): run "
+                                  "`python -c 'import __graft_entry__ as g; g.build()'`" % exc)
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
     sp = ctypes.POINTER(_Shape)
@@ -94,15 +96,18 @@ def load_library() -> ctypes.CDLL:
     lib.laq_workspace_status.restype = i32
     lib.laq_score_kernel.argtypes = [sp]
     lib.laq_score_kernel.restype = i32
-    from . import _native as native
+    try:
+        from . import _native as native
+    except ImportError as exc:          # not built, or built against another torch: ctypes serves every call
+        warnings.warn("the compiled binding _native cannot be loaded (%s): calls take about 10 us more on the host" % exc, RuntimeWarning)
+    else:
+        def address(name):
+            return ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
 
-    def address(name):
-        return ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
-
-    native.bind(address("laq_evict"), address("laq_workspace_bytes"), address("laq_decode_attention"),
-                address("laq_decode_workspace_bytes"), address("laq_qcache_store"),
-                torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
-    _native = native
+        native.bind(address("laq_evict"), address("laq_workspace_bytes"), address("laq_decode_attention"),
+                    address("laq_decode_workspace_bytes"), address("laq_qcache_store"),
+                    torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _native = native
     _lib = lib
     return lib
 
@@ -376,7 +381,7 @@ def laq_recall(idx_pred: torch.Tensor, budget_pred: Sequence[int], idx_gold: tor
 def laq_qcache_store(q_cache: torch.Tensor, q_step: torch.Tensor, t: int, stream=None) -> torch.Tensor:
     """q_cache [n, Hq, W, d] (updated in place: rows [.., t, :] = q_step [n, Hq, d]); returns q_cache."""
     lib = _lib or load_library()
-    if stream is None:
+    if stream is None and _native is not None:
         got = _native.qcache_store(q_cache, q_step, t)
         if got is not None:
             if got is not q_cache:
@@ -400,7 +405,7 @@ def laq_decode_attention(q: torch.Tensor, k_c: torch.Tensor, v_c: torch.Tensor, 
     token's attention over the retained rows of its KV head.  split: let the library spread long
     caches over several workgroups (a workspace of laq_decode_workspace_bytes is made if ws is None)."""
     lib = _lib or load_library()
-    if stream is None:
+    if stream is None and _native is not None:
         got = _native.decode(q, k_c, v_c, budget, Hkv, L, scale, out, ws, split)
         if got is not None:
             if type(got) is int:
@@ -480,7 +485,7 @@ def laq_evict(q_win: torch.Tensor, k: torch.Tensor, v: Optional[torch.Tensor], b
     None is returned in their place.  static_scratch=True calls laq_evict_static (the library's own scratch
     array instead of a workspace; every output buffer must then be passed in for the call to allocate nothing)."""
     lib = _lib or load_library()
-    if stream is None and not static_scratch:
+    if stream is None and not static_scratch and _native is not None:
         got = _native.evict(q_win, k, v, budget, pool_kernel, scale, scores, idx, k_out, v_out, ws, q_pos, keep, pool_mode,
                             want_scores, block_table, L, choose)
         if got is not None:

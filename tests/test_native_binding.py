@@ -39,6 +39,12 @@ def outcome(call):
     return res.stdout.strip().splitlines()[-1]
 
 
+def test_it_is_built_and_loads():
+    from paper_2505_20334_amd import binding
+    binding.load_library()
+    assert binding._native is not None
+
+
 @pytest.mark.parametrize("value", ["None", "b'max'"])
 @pytest.mark.parametrize("name", ["pool_mode", "choose"])
 def test_a_mode_that_is_no_text(name, value):
@@ -74,3 +80,16 @@ OUT_OF_MEMORY = """
 @pytest.mark.parametrize("call", ["laq.laq_evict(q, k, k, [64], 7)", "laq.laq_decode_attention(step, rows, rows, [64], 2, 512)"])
 def test_an_allocation_that_fails_raises_what_torch_raises(call):
     assert outcome(OUT_OF_MEMORY % call) == "raised OutOfMemoryError no memory"
+
+
+def test_calls_work_without_the_compiled_binding():
+    code = ("import sys, warnings\nsys.modules['paper_2505_20334_amd._native'] = None\nimport torch\nimport paper_2505_20334_amd as laq\n"
+            "with warnings.catch_warnings(record=True) as told:\n    warnings.simplefilter('always')\n    laq.load_library()\n"
+            "assert any('_native' in str(w.message) for w in told)\n"
+            "x = torch.zeros(1, 2, 64, 128)\n"
+            "for call in (lambda: laq.laq_evict(x, x, x, [8], 7), lambda: laq.laq_qcache_store(x, x[:, :, 0], 0),\n"
+            "             lambda: laq.laq_decode_attention(x[:, :, 0], x[0, 0], x[0, 0], [32], 2, 64)):\n"
+            "    try:\n        call()\n    except ValueError as e:\n        assert 'must live on the GPU' in str(e)\n"
+            "    else:\n        raise AssertionError\n")
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=110)
+    assert res.returncode == 0, res.stderr[-600:]
