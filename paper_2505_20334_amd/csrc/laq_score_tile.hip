@@ -193,7 +193,7 @@ __device__ __forceinline__ void fold_rows(const ScoreGeom& g, const float2* __re
     for (int w = 1; w < WAVES * 2; ++w) M = fmaxf(M, fold[w][tid].x);
 #pragma unroll 4
     for (int w = 0; w < WAVES * 2; ++w) Z = fmaf(fold[w][tid].y, __builtin_amdgcn_exp2f(fold[w][tid].x - M), Z);
-    rowc[tid] = rt * 32 + tid < g.R ? M + __builtin_amdgcn_logf(Z) : 1.0e30f;      // rows beyond R: probability 0
+    rowc[tid] = rt * 32 + tid < g.R ? M + __builtin_amdgcn_logf(Z) : 1.0e30f;      // (rows beyond R: any finite number)
   }
   __syncthreads();                                       // (`fold` may be written again)
 }
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(Sc
     for (int i = 0; i < split && rt + i < ntile; ++i) {
       if (tid < 32) {
         const int row = (rt + i) * 32 + tid;
-        last[turn][i][tid] = row < g.R ? last_visible_key(g, qp, row % g.W) : g.L - 1;
+        last[turn][i][tid] = row < g.R ? last_visible_key(g, qp, row % g.W) : -1;
       }
       if (rowc_all == nullptr) fold_rows(g, part + hg * g.nchunk * g.Rpad, rt + i, fold, rowc[turn][i]);
       else if (tid < 32) rowc[turn][i][tid] = rowc_all[hg * g.Rpad + (rt + i) * 32 + tid];
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(Sc
   c.fetch_rows(v, qg, g.R, 0);
   stage(0, 0);
   const int key = c.k0 + c.n32;
-  const bool plain = c.k0 + 31 <= g.qmin;
+  const bool seen = c.k0 + 31 <= g.qmin;
   float sum = 0.f;
   int turn = 0;
   for (int rt = 0; rt < ntile; rt += split, turn ^= 1) {
@@ -251,7 +251,8 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(Sc
     __syncthreads();
     if (rt + rg < ntile) {
       f32x16 s = c.template product<false>(smem + (turn * split + rg) * tile_bytes);
-      if (!plain) {
+      // rows beyond R see no key: their product with one that is not finite would be a NaN
+      if (!seen || (rt + rg + 1) * 32 > g.R) {
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
           const i32x4 lv = *reinterpret_cast<const i32x4*>(last[turn][rg] + 8 * gq + 4 * c.hf);

@@ -64,3 +64,45 @@ def test_a_nan_shows_in_the_scores_of_one_launch_as_in_those_of_several(pool, mo
     half = pool // 2                        # (windows over either end of the prefix hold zeros, which a maximum takes over a NaN)
     assert torch.isnan(want[0, 1, half:601 - 8 - half]).all() and not torch.isnan(want[0, 0]).any()
     assert torch.equal(torch.isnan(scores), torch.isnan(want)) and torch.equal(scores[0, 0], want[0, 0])
+
+
+# (dtype, Hq, Hkv, d, W): head sizes and types that always take these kernels and one that does in small calls; score rows that do
+# not fill a tile of 32, and that do
+ROWS = [(F32, 2, 2, 64, 8), (F32, 28, 4, 128, 4), (BF16, 8, 2, 96, 7), (BF16, 8, 2, 128, 2), (F32, 4, 1, 64, 8)]
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,W", ROWS)
+def test_keys_behind_every_query_do_not_matter(dtype, Hq, Hkv, d, W, bad):
+    """Rows of a buffer that no query sees (not yet written, say) have the score 0, whatever they hold."""
+    import paper_2505_20334_amd as laq
+    L, seen = 700, 590
+    g = torch.Generator().manual_seed(d)
+    q, k = (torch.randn(1, h, r, d, generator=g).to(dtype) for h, r in ((Hq, W), (Hkv, L)))
+    k[:, :, seen:] = 0.0
+    pos = [seen - 1 - 3 * w for w in range(W)]
+    pooled, want, _, _ = oracle.evict(q[0], k[0], k[0], 64, 1, q_pos=pos, keep=0)
+    k[:, :, seen:] = bad
+    scores, idx, _, _ = laq.laq_evict(q.to(DEV), k.to(DEV), k.to(DEV), [64], 1, q_pos=pos, keep=0)
+    torch.cuda.synchronize()
+    assert (scores[0, :, seen:] == 0).all()
+    check_scores(scores[0].cpu(), pooled, dtype, "scores")
+    assert torch.equal(idx.cpu().reshape(Hkv, 64), oracle.select(scores[0].cpu(), 0, 64)) and int(idx.max()) < seen
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,W", ROWS)
+def test_a_key_whose_logits_are_all_minus_infinity(dtype, Hq, Hkv, d, W):
+    import paper_2505_20334_amd as laq
+    L = 600
+    g = torch.Generator().manual_seed(d)
+    q, k = (torch.randn(1, h, r, d, generator=g).to(dtype) for h, r in ((Hq, W), (Hkv, L)))
+    q[..., 5] = -q[..., 5].abs() - 0.125
+    pos = [L + w for w in range(W)]
+    without = k.clone()
+    k[0, :, 100, 5] = float("inf")
+    without[0, :, 100, 5] = 1.0e4                          # a logit far enough below the others: probability 0 too
+    scores = laq.laq_score(q.to(DEV), k.to(DEV), 1, q_pos=pos, keep=0)
+    torch.cuda.synchronize()
+    pooled, _, _, _ = oracle.evict(q[0], without[0], without[0], 64, 1, q_pos=pos, keep=0)
+    assert (scores[0, :, 100] == 0).all()
+    check_scores(scores[0].cpu(), pooled, dtype, "scores")
