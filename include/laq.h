@@ -319,7 +319,8 @@ int laq_qcache_store(const laq_shape *shape, const void *q_step, int32_t t, void
  *              laq_decode_workspace_bytes(shape, budget) bytes, a call with few instances and
  *              heads spreads its longer caches over several workgroups and merges their
  *              partial results; LAQ_ERR_WORKSPACE if ws is given but too small.
- *              Without it every cache is read by one workgroup.
+ *              Without it every cache is read by one workgroup.  The bytes do not shrink as
+ *              budgets grow: a workspace for a shape's largest budgets serves its smaller ones.
  * Reads n_inst, Hq, Hkv, d, L, dtype, scale of the shape.  Partial sums are merged in a fixed
  * order: two runs of the same call give identical bits (with and without ws the last bits of
  * `out` may differ, the order of the sums being different).

@@ -352,8 +352,7 @@ static int sink_recent_impl(int n_inst, int Hkv, int L, const int32_t* budget, i
 
 // bytes of partial results of a decode call that may cut its caches into parts
 static size_t decode_ws_bytes(const ScoreGeom& g, int dtype, const int32_t* budget) {
-  return round256(decode_partial_bytes(g.n_inst, g.L, g.Hq, g.Hkv, g.d, dtype, budget,
-                                       decode_part_rows(g.n_inst, g.L, g.Hq, g.Hkv, dtype, budget)));
+  return round256(decode_partial_bytes(g.n_inst, g.L, g.Hq, g.Hkv, g.d, dtype, budget));
 }
 
 static int decode_impl(const laq_shape* shape, const void* q, const void* kc, const void* vc,

@@ -527,18 +527,23 @@ int decode_part_rows(int n, int L, int Hq, int Hkv, int dtype, const int32_t* bu
 // The area of the parts of a launch, in a workspace of any alignment: marks, then sums.
 static size_t part_slots(long long parts, int Hq, int Hkv, int dtype) { return (size_t)parts * decode_columns(Hq, Hkv, dtype) * decode_head_batch(Hq, Hkv, dtype); }
 
-// bytes of the parts of the largest launch (launches reuse the area; they are ordered on the stream)
-size_t decode_partial_bytes(int n, int L, int Hq, int Hkv, int d, int dtype, const int32_t* budget, int rows_per_part) {
+// Bytes that hold the parts of any launch of a call (launches reuse the area; they are ordered on the stream), and of any
+// other call of this shape whose caches are no longer: one workspace serves layers of different budgets.  A part has
+// at least DEC_PART_STEP rows and at least the longest cache's rows / DEC_MOST_PARTS, and more than rows * columns / DEC_WORKGROUPS
+// of the call's rows; each of the three bounds the number of parts and grows with every budget.  (The number itself does not: the
+// length of a part goes in steps, so that 2048 rows can have fewer parts than 1535.)
+size_t decode_partial_bytes(int n, int L, int Hq, int Hkv, int d, int dtype, const int32_t* budget) {
+  const long long columns = decode_columns(Hq, Hkv, dtype);
+  if (n * columns >= DEC_WHOLE_FROM || longest(n, L, budget) <= DEC_PART_STEP) return 0;
   long long parts = 0, most = 0;
-  bool split = false;
   for (int i = 0; i < n; ++i) {
-    const int s = parts_of(budget[i] < L ? budget[i] : L, rows_per_part);
-    split = split || s > 1;
     if (i % MAX_INST_PER_LAUNCH == 0) parts = 0;
-    parts += s;
+    const int s = parts_of(budget[i] < L ? budget[i] : L, DEC_PART_STEP);
+    parts += s < DEC_MOST_PARTS ? s : DEC_MOST_PARTS;
     if (parts > most) most = parts;
   }
-  return split ? 8 + part_slots(most, Hq, Hkv, dtype) * (2 * sizeof(unsigned long long) + d * sizeof(float)) : 0;
+  const long long by_rows = (n < MAX_INST_PER_LAUNCH ? n : MAX_INST_PER_LAUNCH) + DEC_WORKGROUPS / columns;
+  return 8 + part_slots(most < by_rows ? most : by_rows, Hq, Hkv, dtype) * (2 * sizeof(unsigned long long) + d * sizeof(float));
 }
 
 hipError_t launch_decode(int n_inst, int L, int Hq, int Hkv, int d, int dtype, float scale2, int rows_per_part, const int32_t* budget,

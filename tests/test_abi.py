@@ -2,6 +2,7 @@
 rejects bad arguments synchronously (these calls return before anything touches a GPU)."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -179,6 +180,28 @@ def test_decode_side_calls_are_checked_without_a_gpu():
     assert lib.laq_qcache_store(ctypes.byref(sh), fake, -1, fake, None) == INVALID
     assert lib.laq_qcache_store(ctypes.byref(sh), fake, 8, fake, None) == INVALID      # W = 8 slots: 0..7
     assert lib.laq_qcache_store(ctypes.byref(_shape(d=12)), fake, 0, fake, None) == INVALID
+
+
+@pytest.mark.parametrize("n,Hq,Hkv,d", [(1, 32, 32, 128), (1, 32, 8, 128), (3, 8, 8, 64), (40, 8, 2, 128), (300, 9, 1, 256), (127, 8, 8, 64)])
+def test_decode_workspace_grows_with_the_budgets(n, Hq, Hkv, d):
+    """A workspace for the largest budgets of a shape serves every smaller one."""
+    lib = laq.load_library()
+
+    def need(budgets, dtype):
+        sh = _shape(n_inst=n, Hq=Hq, Hkv=Hkv, d=d, L=1 << 20, keep=0, dtype=dtype)
+        return lib.laq_decode_workspace_bytes(ctypes.byref(sh), (ctypes.c_int32 * n)(*budgets))
+
+    rng = random.Random(n + Hq)
+    for dtype in (binding.LAQ_F32, binding.LAQ_BF16):
+        sizes = [need([r] * n, dtype) for r in list(range(1, 300)) + list(range(300, 8200, 37)) + [9000, 50000]]
+        assert sizes[0] == 0 and sizes[-1] > 0 and all(a <= b for a, b in zip(sizes, sizes[1:]))
+        budgets = [rng.randint(1, 400) for _ in range(n)]
+        before = need(budgets, dtype)
+        for _ in range(60):
+            budgets[rng.randrange(n)] += rng.randint(1, 900)
+            now = need(budgets, dtype)
+            assert now >= before
+            before = now
 
 
 def test_key_value_strides_are_checked_without_a_gpu():
