@@ -430,13 +430,21 @@ __global__ __launch_bounds__(256) void sink_recent_kernel(int Hkv, int L, int n_
   for (int t = threadIdx.x; t < bk; t += 256) out[t] = t < s ? t : t + shift;
 }
 
+// How many scores the rows of a launch start behind a 16-byte boundary, at most.  Only where they do does a variant hold
+// fewer keys than its registers: 32768 keys of aligned rows taken for 32771 went to the kernel that holds none (8, 256, 2048
+// heads: 43.6, 51.0 and 366 us against 15.6, 17.1 and 116 for 32764), 2048 of them to the next larger one (2048
+// heads: 27.8 us against 10.5 for 2044).
+int row_shift(const float* scores, int L) {
+  return L % 4 == 0 ? (int)(reinterpret_cast<uintptr_t>(scores) / sizeof(float) % 4) : 3;
+}
+
 template <typename TAB>
 hipError_t launch_for(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores, const TAB& tab,
                       int32_t* idx, hipStream_t st) {
-  // The fewest registers that hold the prefix (a row may start three positions behind a 16-byte boundary).
+  // The fewest registers that hold the prefix.
   // With many heads in the launch, small workgroups of which several share a compute unit: while one
   // waits at a barrier or for its scores, another one works.
-  const int P = L - keep, most = P + (pool == 1 ? 3 : 0);
+  const int most = L - keep + (pool == 1 ? row_shift(scores, L) : 0);
   auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, NoFinish{}, st); };
   if (pool == 1) {
     if ((long long)Hkv * n_inst >= SEL_MANY_WORKGROUPS) {
@@ -459,7 +467,7 @@ hipError_t launch_for(int n_inst, int inst0, int Hkv, int L, int keep, int pool,
 template <typename TAB>
 hipError_t finish_for(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const TAB& tab, int32_t* idx,
                       const FinishArgs& fin, hipStream_t st) {
-  const int most = L - keep + 3;
+  const int most = L - keep + row_shift(raw, L);
   auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, 1, false, raw, tab, idx, fin, st); };
   if (most <= 256 * 8) return at(launch_one<256, 8, true, TAB, FinishArgs>);
   if (most <= 1024 * 4) return at(launch_one<1024, 4, true, TAB, FinishArgs>);

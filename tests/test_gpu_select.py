@@ -19,6 +19,9 @@ CASES = [
     (400, 2, 2045 + 4, 4, [4 + 255, 4 + 2044]), (400, 2, 2046 + 4, 4, [4 + 256, 4 + 513]),
     (400, 2, 8189 + 4, 4, [4 + 300, 4 + 4000]), (400, 2, 8190 + 4, 4, [4 + 512, 4 + 1100]),
     (384, 2, 32765, 0, [512, 1500]), (384, 2, 32766, 0, [700, 2100]),
+    # aligned rows: these fill a variant's registers exactly
+    (1, 3, 4096, 0, [1024]), (1, 3, 16384 + 4, 4, [4 + 1024]), (1, 3, 32768, 0, [1024]), (1, 3, 32772, 4, [4 + 2048]),
+    (400, 2, 2048, 0, [256, 2040]), (400, 2, 8192, 0, [512, 1100]), (384, 2, 32768, 0, [700, 2100]),
 ]
 
 
@@ -47,3 +50,27 @@ def test_select_at_the_edges_of_its_variants(n, Hkv, L, W, budgets, values):
     parts = split_packed(idx.cpu(), b, Hkv, L)
     for i in sorted({0, 1, n // 2, n - 1} & set(range(n))):
         assert torch.equal(parts[i], oracle.select(s[i].cpu(), W, b[i])), i
+
+
+def test_a_prefix_of_a_variants_size_takes_that_variant():
+    """32768 aligned scores per head fit the registers; the kernel that re-reads longer prefixes takes three times as long."""
+    import paper_2505_20334_amd as laq
+
+    def fastest(L):
+        s = torch.rand(32, 8, L, device=DEV)
+        idx = laq.laq_select(s, [512] * 32, 1, 0)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                laq.laq_select(s, [512] * 32, 1, 0, idx=idx)
+        best = float("inf")
+        for _ in range(20):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            graph.replay()
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        return best
+
+    assert fastest(32768) < 2 * fastest(32764)
