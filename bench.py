@@ -123,7 +123,7 @@ SCORE_KERNEL_TEXT = {
     "single-read": "laq_score stage: fused_reset_kernel + fused_kernel (K read once; the unnormalised probabilities "
                    "stay in registers until the softmax denominators are known) + pool_boundaries_kernel",
     "two-pass": "laq_score stage: stream_kernel<pass 1> + row_constants_mfma_kernel + stream_kernel<pass 2> + "
-                "pool_boundaries_kernel, or tile_stats_kernel + tile_score_kernel where a call has at most 512 "
+                "pool_boundaries_kernel, or tile_stats_kernel + tile_score_kernel in most calls of at most 512 "
                 "chunks of 256 keys (K counted once in the algorithmic bytes, read twice)",
     "vector": "laq_score stage: tile_stats_kernel + tile_score_kernel (K counted once in the algorithmic bytes, read twice)",
 }

@@ -125,8 +125,9 @@ typedef struct laq_shape {
    * Which scoring kernels to take where more than one applies (laq_score_choice; 0 = LAQ_CHOOSE_AUTO:
    * the single-read kernel for at most 64 score rows per KV head from 128 MiB of keys per call on,
    * otherwise the two streaming passes, whose launches cost less and which are the faster ones with
-   * more rows).  A choice that does not apply to the shape is ignored; laq_score_kernel()
-   * tells what a call will run.
+   * more rows, or, in calls of at most 512 chunks of 256 keys, the kernels that take one chunk per
+   * workgroup where those are faster).  A choice that does not apply to the shape is ignored;
+   * laq_score_kernel() tells what a call will run.
    */
   int32_t score_choice;
 } laq_shape;
@@ -190,10 +191,11 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *          laq_score(p) + laq_select(1) and laq_score(1) + laq_select(p) give the same indices.
  *   ws / ws_bytes  device scratch of at least laq_workspace_bytes(shape)
  * Supported: dtype BF16 or F32; any Hq/Hkv/W/L within the limits of laq_shape;
- * pool_kernel odd, 1 <= pool_kernel <= 63.  BF16 with d = 64 or 128, W <= 512 and more than 512
- * chunks of 256 keys runs on kernels that stream the keys, everything else on kernels with one chunk
- * per workgroup (score_choice overrides the number of chunks), with the same results to within the
- * rounding of their fp32 sums; all of them on the matrix cores.  q_win, k and scores must be 16-byte
+ * pool_kernel odd, 1 <= pool_kernel <= 63.  BF16 with d = 64 or 128 and W <= 512 runs on kernels that
+ * stream the keys -- calls of at most 512 chunks of 256 keys on kernels with one chunk per workgroup
+ * where these are faster, which is most of them (score_choice LAQ_CHOOSE_TWO_PASS: never) --, everything else
+ * on kernels with one chunk per workgroup, with the same results to within the rounding of their fp32
+ * sums; all of them on the matrix cores.  q_win, k and scores must be 16-byte
  * aligned.
  */
 int laq_score(const laq_shape *shape, const void *q_win, const void *k, int pool_kernel,

@@ -218,18 +218,29 @@ static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g) {
 }
 
 // Few enough chunks that each gets a workgroup of its own at once: the kernels that take one chunk each need
-// three launches where the streaming ones need five.  laq_score, bf16, d = 128, 32 and 64 score rows, one against
-// the other: 128 chunks 18.9 : 21.3 and 17.4 : 20.2 us, 512 chunks 19.8 : 21.6 and 23.9 : 26.0; beyond that
-// nothing is gained and with many rows much is lost (1536 chunks, 64 rows 52.6 : 49.6, 128 rows 69.9 : 60.4).
-// Between 129 and 256 chunks a compute unit has one workgroup of them, which walks all row tiles alone; with several
-// groups of 128 rows, the last one more than half full, the streaming kernels are the faster ones (laq_evict, one
-// against the other: 256 rows, 192 and 256 chunks, d = 128 47.4 : 44.3 and 50.2 : 45.4 us, d = 64 40.8 : 35.6 and
-// 42.3 : 36.6; but 160 rows, d = 128 37.4 : 42.4 and 40.0 : 44.5; 256 rows, 128 and 384 chunks 36.2 : 40.9 and
-// 57.8 : 62.8).
+// three launches where the streaming ones need five (four where the selection launch pools).  They walk the row tiles of
+// 32 one after the other, a streaming workgroup takes four at a time: up to so many quarter tiles per group of four
+// they are the faster ones.  laq_score and (laq_evict), one against the other, us, d = 128, rows x chunks:
+//    64 x 128  18.7 : 19.5 (23.8 : 25.7)     128 x 128  23.2 : 22.4 (28.0 : 30.1)     256 x 128  32.3 : 32.9 (37.1 : 40.1)
+//    96 x 256  23.7 : 23.7 (31.5 : 34.7)     128 x 256  27.6 : 25.0 (35.3 : 35.0)     192 x 256  33.5 : 34.1 (41.8 : 43.1)
+//   224 x 256  37.2 : 35.0 (45.8 : 45.6)     288 x 256  44.3 : 44.1 (52.9 : 54.2)     448 x 256  61.1 : 54.4 (69.6 : 64.6)
+//    64 x 512  26.0 : 28.3 (41.4 : 45.2)     128 x 384  31.0 : 30.5 (45.5 : 47.0)     512 x 512  62.9 : 67.1 (79.2 : 84.5)
+// and d = 64, where the streaming ones lead more often:
+//   128 x 64   17.7 : 17.3 (23.2 : 23.8)     224 x 128  25.8 : 24.7 (30.1 : 30.5)     256 x 128  27.7 : 24.9 (31.8 : 30.8)
+//    64 x 256  16.3 : 15.9 (23.5 : 24.6)      96 x 256  19.2 : 17.6 (26.4 : 27.4)     160 x 192  24.8 : 24.5 (31.1 : 32.4)
+//   352 x 384  40.3 : 39.8 (52.8 : 54.4)     128 x 384  24.8 : 22.6 (38.4 : 38.2)     384 x 384  42.6 : 40.5 (55.9 : 56.0)
+//    64 x 288  19.2 : 17.4 (31.1 : 31.1)      96 x 512  22.9 : 22.8 (38.0 : 40.2)     288 x 288  34.6 : 37.4 (46.5 : 51.7)
+// Beyond 512 chunks nothing is gained and with many rows much is lost (d = 128, 1536 chunks, 64 rows 52.6 : 49.6, 128
+// rows 69.9 : 60.4).  Up to 64 and 128 chunks four and two workgroups share a chunk's row tiles; up to 256 every
+// compute unit has one workgroup, which is alone with all of them; beyond that there are two.
 static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
   const long long chunks = (long long)g.n_inst * g.Hkv * g.nchunk;
-  if (g.Rpad > 128 && (g.Rpad - 1) % 128 >= 64 && chunks > 128 && chunks <= 256) return false;
-  return shape->score_choice == LAQ_CHOOSE_AUTO && chunks <= 512;
+  if (shape->score_choice != LAQ_CHOOSE_AUTO || chunks > 512) return false;
+  const int tiles = g.Rpad / 32, groups = (tiles + 3) / 4;
+  int quarters = 16;
+  if (g.d == 64 && chunks > 64) quarters = chunks <= 128 ? 14 : chunks <= 256 ? 10 : 15;
+  if (g.d == 128 && chunks > 128 && chunks <= 256) quarters = 12;
+  return 4 * tiles <= quarters * groups;
 }
 
 // Scores of a validated call into `scores`: pooled, or, with pool == 1, raw.

@@ -23,6 +23,10 @@ CASES = [
     # many score rows around 128 and 256 chunks
     (BF16, 1, 64, 8, 64, 4096, 32, 7, "max", 200), (BF16, 1, 64, 8, 64, 4100, 32, 7, "max", 200),
     (BF16, 1, 64, 8, 64, 8192, 20, 5, "avg", 96), (BF16, 1, 64, 8, 64, 8193, 20, 7, "max", 96),
+    # either side of the line to the streaming kernels: row tiles that fill the streaming kernels' groups of four, and one less
+    (BF16, 1, 32, 8, 128, 4097, 32, 7, "max", 100), (BF16, 1, 32, 8, 128, 8193, 32, 7, "max", 100), (BF16, 1, 32, 8, 128, 4200, 24, 7, "avg", 100),
+    (BF16, 1, 64, 8, 128, 4097, 36, 7, "max", 100), (BF16, 1, 64, 8, 128, 4097, 40, 7, "max", 100),
+    (BF16, 1, 32, 8, 64, 2048, 32, 7, "max", 100), (BF16, 1, 32, 8, 64, 2049, 32, 7, "avg", 100), (BF16, 1, 32, 8, 64, 8200, 24, 7, "max", 100),
 ]
 
 
