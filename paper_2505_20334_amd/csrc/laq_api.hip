@@ -388,8 +388,8 @@ static int decode_impl(const laq_shape* shape, const void* q, const void* kc, co
 
 // Whether the selection kernel can do the pooling and the gather of this call along with the selection (one
 // workgroup per head: worth it where that is less work than the launches it saves).
-static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, int row_bytes) {
-  if ((pool - 1) / 2 > FINISH_MAX_HALF || g.P > FINISH_MAX_KEYS || (long long)g.n_inst * g.Hkv > FINISH_MAX_HEADS ||
+static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, const float* raw, int row_bytes) {
+  if ((pool - 1) / 2 > FINISH_MAX_HALF || g.P + row_shift(raw, g.L) > FINISH_MAX_KEYS || (long long)g.n_inst * g.Hkv > FINISH_MAX_HEADS ||
       shape->n_inst > MAX_INST_PER_LAUNCH)
     return false;
   int most = 0;
@@ -541,8 +541,8 @@ static int evict_impl(const laq_shape* shape, const void* q_win, const void* k, 
   const laq::Workspace w = laq::carve_workspace(g, ws);
   if (!scores) scores = w.pooled;        // the hand-over plane between the stages
   const int row_bytes = g.d * (shape->dtype == LAQ_F32 ? 4 : 2);
-  if (laq::finish_wanted(shape, g, budget, pool_kernel, row_bytes)) {
-    float* raw = pool_kernel > 1 ? w.raw : scores;
+  float* raw = pool_kernel > 1 ? w.raw : scores;
+  if (laq::finish_wanted(shape, g, budget, pool_kernel, raw, row_bytes)) {
     const int rc = laq::score_checked(shape, g, qp, lay, q_win, k, 1, raw, ws, st);
     if (rc != LAQ_OK) return rc;
     return laq::finish_checked(shape, g, lay, k, v, budget, pool_kernel, raw, scores, idx, k_out, v_out, st);

@@ -430,14 +430,6 @@ __global__ __launch_bounds__(256) void sink_recent_kernel(int Hkv, int L, int n_
   for (int t = threadIdx.x; t < bk; t += 256) out[t] = t < s ? t : t + shift;
 }
 
-// How many scores the rows of a launch start behind a 16-byte boundary, at most.  Only where they do does a variant hold
-// fewer keys than its registers: 32768 keys of aligned rows taken for 32771 went to the kernel that holds none (8, 256, 2048
-// heads: 43.6, 51.0 and 366 us against 15.6, 17.1 and 116 for 32764), 2048 of them to the next larger one (2048
-// heads: 27.8 us against 10.5 for 2044).
-int row_shift(const float* scores, int L) {
-  return L % 4 == 0 ? (int)(reinterpret_cast<uintptr_t>(scores) / sizeof(float) % 4) : 3;
-}
-
 template <typename TAB>
 hipError_t launch_for(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores, const TAB& tab,
                       int32_t* idx, hipStream_t st) {
@@ -471,10 +463,9 @@ hipError_t finish_for(int n_inst, int inst0, int Hkv, int L, int keep, const flo
   auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, 1, false, raw, tab, idx, fin, st); };
   if (most <= 256 * 8) return at(launch_one<256, 8, true, TAB, FinishArgs>);
   if (most <= 1024 * 4) return at(launch_one<1024, 4, true, TAB, FinishArgs>);
-  if (most <= 1024 * 8) return at(launch_one<1024, 8, true, TAB, FinishArgs>);
-  return at(launch_one<1024, 20, true, TAB, FinishArgs>);
+  return at(launch_one<1024, 8, true, TAB, FinishArgs>);
 }
-static_assert(FINISH_MAX_KEYS + 3 <= 1024 * 20, "");
+static_assert(FINISH_MAX_KEYS == 1024 * 8, "the largest variant above; finish_wanted() counts the shift of the rows too");
 
 }  // namespace
 

@@ -12,7 +12,7 @@ DEV = "cuda:0"
 F32, BF16 = torch.float32, torch.bfloat16
 
 # (dtype, n, Hq, Hkv, d, L, W, pool, pool_mode, budget): head sizes with half and missing pieces, one row tile and
-# several of them side by side (few chunks), chunk ends, prefixes around the longest one that is finished in
+# several of them side by side (few chunks), chunk ends, prefixes and kept rows around the most that are finished in
 # one launch, pooling wider than it does, all and no keys ranked
 CASES = [
     (F32, 1, 8, 1, 64, 1536, 16, 7, "max", 1536), (F32, 1, 8, 1, 64, 1537, 16, 7, "avg", 200), (F32, 2, 4, 4, 8, 257, 3, 5, "max", 64),
@@ -20,6 +20,8 @@ CASES = [
     (BF16, 1, 8, 1, 64, 700, 32, 7, "max", 32), (BF16, 1, 16, 2, 72, 1025, 16, 3, "max", 65), (BF16, 2, 8, 2, 96, 640, 24, 9, "max", 64),
     (BF16, 1, 8, 2, 256, 769, 20, 7, "avg", 300), (BF16, 1, 8, 8, 128, 4096, 8, 7, "max", 128), (BF16, 1, 28, 4, 128, 1000, 32, 13, "max", 70),
     (BF16, 1, 2, 1, 128, 16384 + 8, 8, 7, "max", 300), (BF16, 1, 2, 1, 128, 16385 + 8, 8, 7, "max", 300), (BF16, 1, 4, 1, 24, 9000, 70, 1, "max", 128),
+    (BF16, 1, 2, 1, 128, 8192 + 8, 8, 7, "max", 256), (BF16, 1, 2, 1, 128, 8192 + 8, 8, 5, "avg", 257), (BF16, 1, 2, 1, 128, 8193 + 8, 8, 7, "max", 256),
+    (BF16, 1, 2, 1, 128, 8189 + 8, 8, 9, "avg", 256), (BF16, 1, 2, 1, 128, 8190 + 8, 8, 7, "max", 256), (F32, 2, 2, 1, 128, 4096 + 8, 8, 7, "max", 131),
     # many score rows around 128 and 256 chunks
     (BF16, 1, 64, 8, 64, 4096, 32, 7, "max", 200), (BF16, 1, 64, 8, 64, 4100, 32, 7, "max", 200),
     (BF16, 1, 64, 8, 64, 8192, 20, 5, "avg", 96), (BF16, 1, 64, 8, 64, 8193, 20, 7, "max", 96),
