@@ -36,6 +36,9 @@ constexpr int WAVES = CHUNK_ROWS / 32, THREADS = WAVES * 64;
 // Row tiles of a chunk that are worked on side by side where there are too few chunks to fill the device.
 constexpr int MAX_SPLIT = 4;
 constexpr int FOLD_CHUNKS = 32, FOLD_WORKGROUPS = 512;
+// The exponential instruction returns 0 below 2^-126, where fp32 still tells scores apart: what it lost is added to a tile's sum
+// that is below TINY (above it, 32 such terms are less than a rounding).
+constexpr float TINY = 0x1p-90f;
 
 // Row index (0..31) of accumulator register i for a lane in half hf of the 32x32 output layout.
 __device__ __forceinline__ int acc_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
@@ -55,6 +58,20 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 acc, float) {
   return acc;
 }
 
+// (in a scalar register: what follows from it costs none of the vector registers, of which these kernels have none to spare)
+__device__ __forceinline__ int wave_number() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// The thread's number; TIGHT: by a way that keeps what is computed from it inside the loop that uses it.  (Kept in registers
+// over the loop, it cost waves, or pushed keys out to memory, and waiting for those is waiting for the score rows asked for
+// before them too.  64 score rows, 64 heads x 8191 keys: fp32, d = 128 201.5 -> 189.6 us, bf16, d = 96 55.1 -> 49.8, d = 256 126.5 ->
+// 108; fp32, d = 256, which has two waves and registers left, 114.5 -> 117.)
+template <bool TIGHT>
+__device__ __forceinline__ int thread_here() {
+  int t = threadIdx.x;
+  if (TIGHT) asm volatile("" : "+v"(t));
+  return t;
+}
+
 // What both kernels do around their products.  NP: pairs of 16-byte pieces a row may have (32 bytes each); FULL:
 // it has exactly that many.
 template <typename T, int NP, bool FULL> struct Chunk {
@@ -68,7 +85,7 @@ template <typename T, int NP, bool FULL> struct Chunk {
   __device__ __forceinline__ void load_keys(const ScoreGeom& g, const KvLayout& lay, const T* __restrict__ k, int first,
                                             int head, int inst) {
     const int tid = threadIdx.x;
-    lane = tid & 63; hf = lane >> 5; n32 = lane & 31; wave = tid >> 6;
+    lane = tid & 63; hf = lane >> 5; n32 = lane & 31; wave = wave_number();
     row_bytes = FULL ? NP * 32 : g.d * (int)sizeof(T);
     stride = q_stride(row_bytes);
     np = FULL ? NP : (row_bytes + 31) / 32;
@@ -87,20 +104,20 @@ template <typename T, int NP, bool FULL> struct Chunk {
   // score rows rt * 32 .. + 31 of the group (rows beyond R: zeros), memory -> registers -> LDS
   static constexpr int PER_THREAD = (32 * NP * 2 + THREADS - 1) / THREADS;
   __device__ __forceinline__ void fetch_rows(u32x4 (&v)[PER_THREAD], const T* __restrict__ qg, int R, int rt) const {
-    const int per_row = 2 * np;
+    const int per_row = 2 * np, tid = thread_here<(NP <= 16)>();
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
-      const int p = threadIdx.x + i * THREADS, row = p / per_row, col = p - row * per_row;
+      const int p = tid + i * THREADS, row = p / per_row, col = p - row * per_row;
       v[i] = u32x4{0u, 0u, 0u, 0u};
       if (row < 32 && rt * 32 + row < R && col * 16 < row_bytes)
         v[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(qg) + (size_t)(rt * 32 + row) * row_bytes + col * 16);
     }
   }
   __device__ __forceinline__ void stage_rows(char* lds, const u32x4 (&v)[PER_THREAD]) const {
-    const int per_row = 2 * np;
+    const int per_row = 2 * np, tid = thread_here<(NP <= 16)>();
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
-      const int p = threadIdx.x + i * THREADS, row = p / per_row, col = p - row * per_row;
+      const int p = tid + i * THREADS, row = p / per_row, col = p - row * per_row;
       if (row < 32) *reinterpret_cast<u32x4*>(lds + row * stride + col * 16) = v[i];
     }
   }
@@ -131,7 +148,7 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_stats_kernel(Sc
   __shared__ float2 stat[WAVES][32];
   const int chunk = blockIdx.x / split, first = blockIdx.x - chunk * split, head = blockIdx.y, inst = blockIdx.z, tid = threadIdx.x;
   Chunk<T, NP, FULL> c;
-  c.load_keys(g, lay, k, chunk * CHUNK_ROWS + (tid >> 6) * 32, head, inst);
+  c.load_keys(g, lay, k, chunk * CHUNK_ROWS + wave_number() * 32, head, inst);
   const T* qg = q + ((size_t)inst * g.Hq + (size_t)head * g.G) * g.W * g.d;
   float2* out = part + (((size_t)inst * g.Hkv + head) * g.nchunk + chunk) * g.Rpad;
   const int ntile = g.Rpad / 32, tile_bytes = 32 * c.stride;
@@ -175,8 +192,9 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_stats_kernel(Sc
 
 // c = M + log2 Z of the score rows rt * 32 .. + 31 from the statistics of all chunks of the head: thread
 // (sub, row) takes the chunks sub, sub + WAVES * 2, ...; fixed order.
+template <bool TIGHT>
 __device__ __forceinline__ void fold_rows(const ScoreGeom& g, const float2* __restrict__ part, int rt, float2 (*fold)[32], float* rowc) {
-  const int tid = threadIdx.x, row = tid & 31, sub = tid >> 5;
+  const int tid = thread_here<TIGHT>(), row = tid & 31, sub = tid >> 5;
   float M = NEG_BIG, Z = 0.f;
 #pragma unroll 1
   for (int ch = sub; ch < g.nchunk; ch += WAVES * 2) {
@@ -214,20 +232,21 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(Sc
   const int head = blockIdx.y, inst = blockIdx.z, tid = threadIdx.x;
   const size_t hg = (size_t)inst * g.Hkv + head;
   if (blockIdx.x == 0 && hg == 0 && tid == 0) *status = 0;    // (these kernels have no wait to give up)
-  const int key_waves = WAVES / split, rg = (tid >> 6) / key_waves, kw = (tid >> 6) - rg * key_waves;
+  const int key_waves = WAVES / split, rg = wave_number() / key_waves, kw = wave_number() - rg * key_waves;
   Chunk<T, NP, FULL> c;
   c.load_keys(g, lay, k, (int)blockIdx.x * key_waves * 32 + kw * 32, head, inst);
   const T* qg = q + ((size_t)inst * g.Hq + (size_t)head * g.G) * g.W * g.d;
   const int ntile = g.Rpad / 32, tile_bytes = 32 * c.stride;
   u32x4 v[Chunk<T, NP, FULL>::PER_THREAD];
   auto constants = [&](int turn, int rt) {
+    const int tid = thread_here<(NP <= 16)>();
 #pragma unroll 1
     for (int i = 0; i < split && rt + i < ntile; ++i) {
       if (tid < 32) {
         const int row = (rt + i) * 32 + tid;
         last[turn][i][tid] = row < g.R ? last_visible_key(g, qp, row % g.W) : -1;
       }
-      if (rowc_all == nullptr) fold_rows(g, part + hg * g.nchunk * g.Rpad, rt + i, fold, rowc[turn][i]);
+      if (rowc_all == nullptr) fold_rows<(NP <= 16)>(g, part + hg * g.nchunk * g.Rpad, rt + i, fold, rowc[turn][i]);
       else if (tid < 32) rowc[turn][i][tid] = rowc_all[hg * g.Rpad + (rt + i) * 32 + tid];
     }
   };
@@ -262,12 +281,25 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(Sc
         }
       }
       const float* rc = rowc[turn][rg];
+      float tile_sum = 0.f;
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
         const f32x4 cc = *reinterpret_cast<const f32x4*>(rc + 8 * gq + 4 * c.hf);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + j], g.scale2, -cc[j]));
+        for (int j = 0; j < 4; ++j) tile_sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + j], g.scale2, -cc[j]));
       }
+      if (__builtin_expect(__any(tile_sum < TINY), 0)) {
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+          const f32x4 cc = *reinterpret_cast<const f32x4*>(rc + 8 * gq + 4 * c.hf);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float x = fmaf(s[4 * gq + j], g.scale2, -cc[j]);
+            if (x < -126.f) tile_sum = fmaf(__builtin_amdgcn_exp2f(x + 64.f), 0x1p-64f, tile_sum);
+          }
+        }
+      }
+      sum += tile_sum;
     }
     if (rt + split < ntile) stage(turn ^ 1, rt + split);
   }

@@ -112,3 +112,25 @@ def test_a_key_whose_logits_are_all_minus_infinity(dtype, Hq, Hkv, d, W):
     pooled, _, _, _ = oracle.evict(q[0], without[0], without[0], 64, 1, q_pos=pos, keep=0)
     assert (scores[0, :, 100] == 0).all()
     check_scores(scores[0].cpu(), pooled, dtype, "scores")
+
+
+@pytest.mark.parametrize("dtype,d,W", [(F32, 64, 5), (F32, 128, 20), (F32, 200, 16), (BF16, 96, 20)])
+def test_probabilities_below_the_smallest_normal_number_stay_apart(dtype, d, W):
+    """Logits 0, -1/4, -1/2, ... -119.75 (exact in either type): a list that ends among the denormal scores."""
+    import paper_2505_20334_amd as laq
+    Hq, Hkv, L, budget = 4, 2, 480, 400              # 2^-126 lies at key 349, 2^-149 at 413
+    g = torch.Generator().manual_seed(d)
+    rank = torch.randperm(L, generator=g)
+    q, k = torch.zeros(1, Hq, W, d), torch.zeros(1, Hkv, L, d)
+    q[..., :2] = 1.0
+    k[..., 0], k[..., 1] = -8.0 * (rank // 32), -0.25 * (rank % 32)
+    q, k = q.to(dtype), k.to(dtype)
+    pos = [L + w for w in range(W)]
+    scores, idx, _, _ = laq.laq_evict(q.to(DEV), k.to(DEV), None, [budget], 1, scale=1.0, q_pos=pos, keep=0)
+    torch.cuda.synchronize()
+    assert torch.equal(idx.cpu().reshape(Hkv, budget), torch.nonzero(rank < budget).flatten().int().expand(Hkv, budget))
+    want = oracle.raw_scores(q[0], k[0], 1.0, q_pos=pos)
+    # an exponent of up to 173 is rounded twice (by half of 2^-16, and the factor log2 e by 2^-25 of it): relative error
+    # ln 2 * (2^-17 + 173 * 2^-25) = 9e-6, and the instruction's own 1e-7; every term and sum to half of 2^-149
+    rows = Hq // Hkv * W
+    assert ((scores[0].cpu().double() - want).abs() <= 1.2e-5 * want + rows * 2.0 ** -149).all()
