@@ -22,17 +22,17 @@ def laq():
     return m
 
 
-def run_and_check(laq, q, k, v, budgets, pool, what, heads=None, scale=0.0, exact_expected=None):
+def run_and_check(laq, q, k, v, budgets, pool, what, heads=None, scale=0.0, exact_expected=None, choose="auto"):
     """q [n,Hq,W,d], k/v [n,Hkv,L,d] on the GPU.  Runs laq_evict and the three calls, compares with
     the oracle instance by instance (optionally only some KV heads)."""
     n, Hq, W, d = q.shape
     _, Hkv, L, _ = k.shape
     G = Hq // Hkv
-    print("case:", what, "n=%d Hq=%d Hkv=%d d=%d L=%d W=%d pool=%d" % (n, Hq, Hkv, d, L, W, pool), flush=True)
-    scores, idx, ko, vo = laq.laq_evict(q, k, v, budgets, pool, scale=scale)
+    print("case:", what, "n=%d Hq=%d Hkv=%d d=%d L=%d W=%d pool=%d %s" % (n, Hq, Hkv, d, L, W, pool, choose), flush=True)
+    scores, idx, ko, vo = laq.laq_evict(q, k, v, budgets, pool, scale=scale, choose=choose)
     torch.cuda.synchronize()
     # the three-call sequence gives the same bits
-    s3 = laq.laq_score(q, k, pool, scale=scale)
+    s3 = laq.laq_score(q, k, pool, scale=scale, choose=choose)
     i3 = laq.laq_select(s3, budgets, 1, W)
     k3, v3 = laq.laq_compact(k, v, i3, budgets, W)
     torch.cuda.synchronize()
@@ -40,7 +40,7 @@ def run_and_check(laq, q, k, v, budgets, pool, what, heads=None, scale=0.0, exac
     if v is not None:
         assert torch.equal(v3, vo)
     # ... and so does pooling inside laq_select instead of inside laq_score
-    s_raw = laq.laq_score(q, k, 1, scale=scale)
+    s_raw = laq.laq_score(q, k, 1, scale=scale, choose=choose)
     i_alt = laq.laq_select(s_raw, budgets, pool, W)
     torch.cuda.synchronize()
     assert torch.equal(i_alt, idx)
@@ -190,17 +190,23 @@ EDGE = [
 ]
 
 
+# calls this small take the one-chunk kernels by themselves and the streaming ones on request
+BOTH = pytest.mark.parametrize("choose", ["auto", "two-pass"])
+
+
+@BOTH
 @pytest.mark.parametrize("name,dtype,Hq,Hkv,d,L,W,pool,budget", EDGE, ids=[e[0] for e in EDGE])
-def test_edge_cases(laq, name, dtype, Hq, Hkv, d, L, W, pool, budget):
+def test_edge_cases(laq, name, dtype, Hq, Hkv, d, L, W, pool, budget, choose):
     g = torch.Generator().manual_seed(len(name) * 1000 + L)
     n = 2
     q = (torch.randn(n, Hq, W, d, generator=g) * 1.5).to(dtype).to(DEV)
     k = torch.randn(n, Hkv, L, d, generator=g).to(dtype).to(DEV)
     v = torch.randn(n, Hkv, L, d, generator=g).to(dtype).to(DEV)
-    run_and_check(laq, q, k, v, [budget, max(W, budget - 3)], pool, name)
+    run_and_check(laq, q, k, v, [budget, max(W, budget - 3)], pool, name, choose=choose)
 
 
-def test_peaks_on_chunk_boundaries_spread_to_both_sides(laq):
+@BOTH
+def test_peaks_on_chunk_boundaries_spread_to_both_sides(laq, choose):
     # keys aligned with the window queries right before and after every 256-key boundary: their
     # pooled plateau must reach across the boundary in both directions
     g = torch.Generator().manual_seed(5)
@@ -212,7 +218,7 @@ def test_peaks_on_chunk_boundaries_spread_to_both_sides(laq):
         k[0, 1, b] = q[0, 4].mean(0) * 3.0
     q, k = q.bfloat16().to(DEV), k.bfloat16().to(DEV)
     v = torch.randn(1, Hkv, L, d, generator=g).bfloat16().to(DEV)
-    sc = run_and_check(laq, q, k, v, [80], 7, "boundary-peaks")[0].cpu()
+    sc = run_and_check(laq, q, k, v, [80], 7, "boundary-peaks", choose=choose)[0].cpu()
     for b in (256, 512, 768, 1024):
         assert (sc[0, 0, b - 4:b + 3] == sc[0, 0, b - 1]).all()       # plateau of key b-1
         assert (sc[0, 1, b - 3:b + 4] == sc[0, 1, b]).all()           # plateau of key b
@@ -359,17 +365,17 @@ def test_explicit_scale(laq):
 
 
 # ---- general observation window (Eq. 5): explicit query positions, independent keep count ----
-def run_general(laq, q, k, v, budgets, pool, q_pos, keep, what, heads=None, pool_mode="max"):
+def run_general(laq, q, k, v, budgets, pool, q_pos, keep, what, heads=None, pool_mode="max", choose="auto"):
     n, Hq, W, d = q.shape
     _, Hkv, L, _ = k.shape
     G = Hq // Hkv
-    print("case:", what, "n=%d Hq=%d Hkv=%d d=%d L=%d W=%d pool=%d(%s) keep=%d" % (
-        n, Hq, Hkv, d, L, W, pool, pool_mode, keep), flush=True)
-    scores, idx, ko, vo = laq.laq_evict(q, k, v, budgets, pool, q_pos=q_pos, keep=keep, pool_mode=pool_mode)
-    s3 = laq.laq_score(q, k, pool, q_pos=q_pos, keep=keep, pool_mode=pool_mode)
+    print("case:", what, "n=%d Hq=%d Hkv=%d d=%d L=%d W=%d pool=%d(%s) keep=%d %s" % (
+        n, Hq, Hkv, d, L, W, pool, pool_mode, keep, choose), flush=True)
+    scores, idx, ko, vo = laq.laq_evict(q, k, v, budgets, pool, q_pos=q_pos, keep=keep, pool_mode=pool_mode, choose=choose)
+    s3 = laq.laq_score(q, k, pool, q_pos=q_pos, keep=keep, pool_mode=pool_mode, choose=choose)
     i3 = laq.laq_select(s3, budgets, 1, keep, pool_mode=pool_mode)
     k3, v3 = laq.laq_compact(k, v, i3, budgets, keep)
-    raw = laq.laq_score(q, k, 1, q_pos=q_pos, keep=keep, pool_mode=pool_mode)
+    raw = laq.laq_score(q, k, 1, q_pos=q_pos, keep=keep, pool_mode=pool_mode, choose=choose)
     i_alt = laq.laq_select(raw, budgets, pool, keep, pool_mode=pool_mode)
     torch.cuda.synchronize()
     assert torch.equal(s3, scores) and torch.equal(i3, idx) and torch.equal(k3, ko) and torch.equal(v3, vo)
@@ -414,13 +420,17 @@ GENERAL = [
      lambda L, W: [L - 8 + i for i in range(8)] + [L - 1] * 8),
     ("keep-everything", torch.bfloat16, 8, 2, 128, 300, 8, 7, 300, 300, lambda L, W: [L] * W),
     ("many-queries-more-than-keys", torch.bfloat16, 4, 2, 128, 40, 64, 3, 20, 0, lambda L, W: [w % 40 for w in range(W)]),
+    # more positions than travel in the launch arguments
+    ("long-window-scattered", torch.bfloat16, 4, 2, 128, 900, 40, 7, 100, 5, lambda L, W: [(101 * w) % (L + 60) for w in range(W)]),
+    ("long-window-lookahead-d64", torch.bfloat16, 6, 2, 64, 1300, 33, 5, 100, 0, lambda L, W: [L - 20 + w for w in range(W)]),
 ]
 
 
+@pytest.mark.parametrize("choose", ["auto", "two-pass", "single-read"])
 @pytest.mark.parametrize("name,dtype,Hq,Hkv,d,L,W,pool,budget,keep,pos", GENERAL, ids=[e[0] for e in GENERAL])
-def test_general_window(laq, name, dtype, Hq, Hkv, d, L, W, pool, budget, keep, pos):
+def test_general_window(laq, name, dtype, Hq, Hkv, d, L, W, pool, budget, keep, pos, choose):
     q, k, v = _qkv(len(name) * 77 + L, 2, Hq, Hkv, d, L, W, dtype)
-    run_general(laq, q, k, v, [budget, max(keep, budget - 3, 1)], pool, pos(L, W), keep, name)
+    run_general(laq, q, k, v, [budget, max(keep, budget - 3, 1)], pool, pos(L, W), keep, name, choose=choose)
 
 
 def test_explicit_trailing_positions_give_the_default_bits(laq):
@@ -802,17 +812,18 @@ STRIDED = [
 ]
 
 
+@BOTH
 @pytest.mark.parametrize("name,dtype,Hq,Hkv,d,L,W,pool,budget", STRIDED, ids=[e[0] for e in STRIDED])
-def test_strided_caches_give_the_dense_bits(laq, name, dtype, Hq, Hkv, d, L, W, pool, budget):
+def test_strided_caches_give_the_dense_bits(laq, name, dtype, Hq, Hkv, d, L, W, pool, budget, choose):
     q, k, v = _qkv(len(name) * 7 + L, 2, Hq, Hkv, d, L, W, dtype)
     budgets = [budget, max(W, budget - 5)]
-    dense = laq.laq_evict(q, k, v, budgets, pool)
+    dense = laq.laq_evict(q, k, v, budgets, pool, choose=choose)
     for how, view in (("token-major", _token_major_view), ("padded-rows", _padded_rows_view)):
         print("case:", name, how, flush=True)
         kv, vv = view(k), view(v)
         assert not kv.is_contiguous() and torch.equal(kv, k)
-        got = laq.laq_evict(q, kv, vv, budgets, pool)
-        s3 = laq.laq_score(q, kv, pool)
+        got = laq.laq_evict(q, kv, vv, budgets, pool, choose=choose)
+        s3 = laq.laq_score(q, kv, pool, choose=choose)
         k3, v3 = laq.laq_compact(kv, vv, dense[1], budgets, W)
         torch.cuda.synchronize()
         for a, b in zip(got, dense):
@@ -901,15 +912,16 @@ def _random_case(rng):
                 pool_mode="avg" if rng.random() < 0.2 else "max", strided=bool(rng.random() < 0.25))
 
 
+@BOTH
 @pytest.mark.parametrize("seed", range(24))
-def test_random_shapes_against_the_oracle(laq, seed):
+def test_random_shapes_against_the_oracle(laq, seed, choose):
     c = _random_case(np.random.default_rng(1000 + seed))
     q, k, v = _qkv(seed, 2, c["Hq"], c["Hkv"], c["d"], c["L"], c["W"], c["dtype"])
     if c["strided"]:
         k, v = _token_major_view(k), _token_major_view(v)
     name = "random-%d d=%d G=%d mode=%s strided=%s dtype=%s" % (seed, c["d"], c["Hq"] // c["Hkv"], c["pool_mode"],
                                                                c["strided"], c["dtype"])
-    run_general(laq, q, k, v, c["budgets"], c["pool"], c["pos"], c["keep"], name, pool_mode=c["pool_mode"])
+    run_general(laq, q, k, v, c["budgets"], c["pool"], c["pos"], c["keep"], name, pool_mode=c["pool_mode"], choose=choose)
 
 
 def test_three_stage_flow_with_synthetic_queries(laq):
