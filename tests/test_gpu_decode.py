@@ -46,19 +46,23 @@ def test_decode_variants(dtype, Hq, Hkv, d, budgets):
 
 @pytest.mark.parametrize("offset", [0, 4])
 def test_captured_decode_in_parts(offset):
-    # replays with the workspace left alone and overwritten in between; a workspace of any alignment
+    # replays with new inputs (sums left over from the replay before would show), the workspace left alone and overwritten in
+    # between; a workspace of any alignment
     import paper_2505_20334_amd as laq
     n, Hq, Hkv, d, L, budgets = 3, 8, 2, 128, 1500, [1500, 700, 64]
     q, kc, vc = (x.to(DEV) for x in _inputs(BF16, n, Hq, Hkv, d, L, budgets))
     need = laq.laq_decode_workspace_bytes(n, Hq, Hkv, d, L, BF16, budgets)
     area = torch.randint(0, 256, (need + 8,), dtype=torch.uint8, device=DEV)
     ws, out = area[offset:offset + need], torch.empty(n, Hq, d, device=DEV)
-    want = laq.laq_decode_attention(q, kc, vc, budgets, Hkv, L, ws=ws).clone()
+    laq.laq_decode_attention(q, kc, vc, budgets, Hkv, L, ws=ws)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         laq.laq_decode_attention(q, kc, vc, budgets, Hkv, L, out=out, ws=ws)
     for replay in range(6):
         out.fill_(7.0)
+        for x in (q, kc, vc):
+            x.normal_()
+        want = laq.laq_decode_attention(q, kc, vc, budgets, Hkv, L)           # (in a workspace of its own)
         if replay % 3 == 2:
             area[: need // 2].random_(0, 256)
         graph.replay()
