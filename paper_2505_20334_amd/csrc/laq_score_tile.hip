@@ -288,15 +288,15 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(Sc
 #pragma unroll
         for (int j = 0; j < 4; ++j) tile_sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + j], g.scale2, -cc[j]));
       }
-      if (__builtin_expect(__any(tile_sum < TINY), 0)) {
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const f32x4 cc = *reinterpret_cast<const f32x4*>(rc + 8 * gq + 4 * c.hf);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float x = fmaf(s[4 * gq + j], g.scale2, -cc[j]);
-            if (x < -126.f) tile_sum = fmaf(__builtin_amdgcn_exp2f(x + 64.f), 0x1p-64f, tile_sum);
-          }
+      // (over both lanes' rows: one lane's may all pad, or not see the key)
+      const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(tile_sum), __float_as_uint(tile_sum), false, false);
+      const float both = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+      if (__builtin_expect(__any(both < TINY && key < g.L), 0)) {
+#pragma unroll 1
+        for (int i = 0; i < 16; ++i) {                   // (few instructions: what follows them is fetched sooner)
+          const float x = fmaf(s[0], g.scale2, -rc[acc_row(i, c.hf)]);
+          if (x < -126.f) tile_sum = fmaf(__builtin_amdgcn_exp2f(x + 64.f), 0x1p-64f, tile_sum);
+          s = __builtin_shufflevector(s, s, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 0);
         }
       }
       sum += tile_sum;
