@@ -386,18 +386,35 @@ static int decode_impl(const laq_shape* shape, const void* q, const void* kc, co
              : LAQ_ERR_DEVICE;
 }
 
-// Whether the selection kernel can do the pooling and the gather of this call along with the selection (one
-// workgroup per head: worth it where that is less work than the launches it saves).
+// Whether the selection kernel can do the pooling and the gather of this call along with the selection, and that is faster than
+// pooling where the scores are made and launches of their own for selection and gather.  One workgroup works for a head, so with
+// few heads its pass over the keys and its copies (K rows kept per head: `gather`) soon take longer than the launches they save; with a
+// workgroup for most compute units they do not.  laq_evict, bf16, d = 128, pool 7, one launch : several, us:
+//   keys <= 2048 (256 threads a head)   32 KiB: 8, 256 heads 21.4 : 22.6, 69.3 : 71.2;  64 KiB: 25.4 : 22.6, 81.5 : 77.7
+//   4096 keys   8, 128 heads   32 KiB 21.2 : 24.8, 62.6 : 68.4;  96 KiB 24.6 : 25.3, 72.7 : 74.9;  128 KiB 24.5 : 24.2, 77.9 : 78.2
+//   8001 keys   8, 64, 128 heads   32 KiB 24.6 : 25.8, 67.0 : 66.1, 95.1 : 98.4;  64 KiB 27.4 : 26.3, 71.1 : 68.5, 101.2 : 103.7;
+//               128 heads 96 KiB 106.4 : 106.8, 128 KiB 111.9 : 111.0
+//   16384 keys  8, 128 heads, 32 KiB 39.4 : 35.2, 158.9 : 155.2;  64 score rows, 128, 160, 256 heads 162.5 : 163.6, 191.3 : 193.9,
+//               273.7 : 282.1, 128 KiB 178.3 : 174.5, 208.6 : 207.6, 298.0 : 303.9
+//   160 heads, 128 KiB: 4096 keys 90.2 : 93.1, 8001 128.4 : 128.7;  256 heads 120.7 : 126.7, 178.2 : 181.1
+//   more heads than compute units, 8001 keys: 384, 1024 heads 218.8 : 215.5, 522 : 505
+// (With at most 32 score rows the single-read kernel pools 16384 keys for less: 256 heads 264.6 : 261.4; the mean pool, which has a
+// launch of its own, 264.8 : 273.8.)
 static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, const float* raw, int row_bytes) {
-  if ((pool - 1) / 2 > FINISH_MAX_HALF || g.P + row_shift(raw, g.L) > FINISH_MAX_KEYS || (long long)g.n_inst * g.Hkv > FINISH_MAX_HEADS ||
-      shape->n_inst > MAX_INST_PER_LAUNCH)
-    return false;
+  const long long heads = (long long)g.n_inst * g.Hkv;
+  const int keys = g.P + row_shift(raw, g.L);
+  if ((pool - 1) / 2 > FINISH_MAX_HALF || keys > FINISH_MAX_KEYS || heads > 256 || shape->n_inst > MAX_INST_PER_LAUNCH) return false;
+  int gather = 0;
+  if (keys <= 2048) gather = 32 << 10;
+  else if (heads >= 160) gather = 128 << 10;
+  else if (keys <= 4096 || (keys <= 8192 && heads >= 128)) gather = 96 << 10;
+  else if (keys <= 8192) gather = 32 << 10;
   int most = 0;
   for (int i = 0; i < shape->n_inst; ++i) {
     const int bk = budget[i] < g.L ? budget[i] : g.L;
     if (bk > most) most = bk;
   }
-  return (long long)most * row_bytes <= FINISH_MAX_GATHER;
+  return (long long)most * row_bytes <= gather;
 }
 
 // Pooling, selection and gather of a small call, from the raw scores.

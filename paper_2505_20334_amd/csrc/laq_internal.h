@@ -132,20 +132,8 @@ struct FinishArgs {
   int32_t half, avg;
   KvLayout lay;
 };
-// Up to which sizes one launch is faster than pooling where the scores are made, selection and gather launches of their own
-// (laq_evict, bf16, d = 128, 32 score rows, pool 7, us, one launch : several):
-//   keys    8 heads, 128 rows kept: 4104 21.0 : 24.0, 8200 30.6 : 31.9, 12296 37.7 : 34.6, 16392 46.0 : 40.1 (one
-//           workgroup pools a head); 128 heads: 4096 67.2 : 73.0, 8001 95.8 : 98.9, 16384 159 : 155
-//   heads   8001 keys: 256 heads 153.8 : 156.2, 384 218.8 : 215.5, 1024 522 : 505 (4096 keys: 1024 heads 283 : 294)
-//   gather  4096 keys, 8 and 64 heads: 64 KiB per head 22.5 : 24.2 and 49.6 : 49.4, 128 KiB 27.1 : 25.2 and 56.9 : 53.4, 256 KiB
-//           34.5 : 26.2 and 71.3 : 58.9; fp32: 64 KiB 33.9 : 35.8 and 91.7 : 93.7, 128 KiB 37.3 : 35.6 and 99.6 : 97.4 (one compute unit
-//           copies a head's rows)
-//   half    the neighbours that two loads beside a lane's own four scores bring; pools up to that width, 4096 keys
-//           20.9 : 23.5
-constexpr int FINISH_MAX_HALF = 4;
-constexpr int FINISH_MAX_KEYS = 8 * 1024;
-constexpr int FINISH_MAX_HEADS = 256;
-constexpr int FINISH_MAX_GATHER = 64 << 10;    // bytes of K rows per head
+constexpr int FINISH_MAX_HALF = 4;              // widest pooling it does: what two loads beside a lane's own four scores bring
+constexpr int FINISH_MAX_KEYS = 16 * 1024;      // longest prefix
 // How many scores the rows of a launch start behind a 16-byte boundary, at most.  Only where they do does a variant of the
 // selection kernel hold fewer keys than its registers: 32768 keys of aligned rows taken for 32771 went to the kernel that holds
 // none (8, 256, 2048 heads: 43.6, 51.0 and 366 us against 15.6, 17.1 and 116 for 32764), 2048 of them to the next

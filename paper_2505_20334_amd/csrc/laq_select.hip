@@ -463,9 +463,10 @@ hipError_t finish_for(int n_inst, int inst0, int Hkv, int L, int keep, const flo
   auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, 1, false, raw, tab, idx, fin, st); };
   if (most <= 256 * 8) return at(launch_one<256, 8, true, TAB, FinishArgs>);
   if (most <= 1024 * 4) return at(launch_one<1024, 4, true, TAB, FinishArgs>);
-  return at(launch_one<1024, 8, true, TAB, FinishArgs>);
+  if (most <= 1024 * 8) return at(launch_one<1024, 8, true, TAB, FinishArgs>);
+  return at(launch_one<1024, 16, true, TAB, FinishArgs>);
 }
-static_assert(FINISH_MAX_KEYS == 1024 * 8, "the largest variant above; finish_wanted() counts the shift of the rows too");
+static_assert(FINISH_MAX_KEYS == 1024 * 16, "the largest variant above; finish_wanted() counts the shift of the rows too");
 
 }  // namespace
 

@@ -20,8 +20,9 @@ CASES = [
     (BF16, 1, 8, 1, 64, 700, 32, 7, "max", 32), (BF16, 1, 16, 2, 72, 1025, 16, 3, "max", 65), (BF16, 2, 8, 2, 96, 640, 24, 9, "max", 64),
     (BF16, 1, 8, 2, 256, 769, 20, 7, "avg", 300), (BF16, 1, 8, 8, 128, 4096, 8, 7, "max", 128), (BF16, 1, 28, 4, 128, 1000, 32, 13, "max", 70),
     (BF16, 1, 2, 1, 128, 16384 + 8, 8, 7, "max", 300), (BF16, 1, 2, 1, 128, 16385 + 8, 8, 7, "max", 300), (BF16, 1, 4, 1, 24, 9000, 70, 1, "max", 128),
-    (BF16, 1, 2, 1, 128, 8192 + 8, 8, 7, "max", 256), (BF16, 1, 2, 1, 128, 8192 + 8, 8, 5, "avg", 257), (BF16, 1, 2, 1, 128, 8193 + 8, 8, 7, "max", 256),
-    (BF16, 1, 2, 1, 128, 8189 + 8, 8, 9, "avg", 256), (BF16, 1, 2, 1, 128, 8190 + 8, 8, 7, "max", 256), (F32, 2, 2, 1, 128, 4096 + 8, 8, 7, "max", 131),
+    (BF16, 1, 2, 1, 128, 8192 + 8, 8, 7, "max", 128), (BF16, 1, 2, 1, 128, 8192 + 8, 8, 5, "avg", 129), (BF16, 1, 2, 1, 128, 8193 + 8, 8, 7, "max", 128),
+    (BF16, 1, 2, 1, 128, 8189 + 8, 8, 9, "avg", 128), (BF16, 1, 2, 1, 128, 8190 + 8, 8, 7, "max", 128), (F32, 2, 2, 1, 128, 2048 + 8, 8, 7, "max", 67),
+    (BF16, 1, 2, 1, 128, 4096 + 8, 8, 7, "max", 384), (BF16, 1, 2, 1, 128, 4096 + 8, 8, 5, "avg", 385), (BF16, 1, 2, 1, 128, 4094 + 8, 8, 7, "max", 384),
     # many score rows around 128 and 256 chunks
     (BF16, 1, 64, 8, 64, 4096, 32, 7, "max", 200), (BF16, 1, 64, 8, 64, 4100, 32, 7, "max", 200),
     (BF16, 1, 64, 8, 64, 8192, 20, 5, "avg", 96), (BF16, 1, 64, 8, 64, 8193, 20, 7, "max", 96),
@@ -134,3 +135,28 @@ def test_probabilities_below_the_smallest_normal_number_stay_apart(dtype, d, W):
     # ln 2 * (2^-17 + 173 * 2^-25) = 9e-6, and the instruction's own 1e-7; every term and sum to half of 2^-149
     rows = Hq // Hkv * W
     assert ((scores[0].cpu().double() - want).abs() <= 1.2e-5 * want + rows * 2.0 ** -149).all()
+
+
+# (heads, KV rows kept in KiB, keys): with a workgroup for most compute units the finishing launch takes longer prefixes and more rows
+MANY = [(128, 96, 8192), (128, 97, 8192), (159, 128, 8193), (160, 128, 16384), (160, 129, 16384), (160, 128, 16381), (160, 128, 16382), (256, 128, 9001)]
+
+
+@pytest.mark.parametrize("mode", ["max", "avg"])
+@pytest.mark.parametrize("heads,kib,keys", MANY)
+def test_one_launch_for_many_heads_gives_the_bits_of_several(heads, kib, keys, mode):
+    import paper_2505_20334_amd as laq
+    print("case:", heads, kib, keys, mode, flush=True)
+    d, W = 32, 2
+    n, Hkv = (heads // 8, 8) if heads % 8 == 0 else (heads, 1)
+    budgets = [kib * 1024 // (2 * d)] * n
+    g = torch.Generator(device=DEV).manual_seed(heads + keys)
+    q, k, v = (torch.randn(n, Hkv, r, d, generator=g, device=DEV).to(BF16) for r in (W, keys + W, keys + W))
+    got = laq.laq_evict(q, k, v, budgets, 7, pool_mode=mode)
+    scores = laq.laq_score(q, k, 7, pool_mode=mode)
+    idx = laq.laq_select(scores, budgets, 1, W)
+    rows = laq.laq_compact(k, v, idx, budgets, W)
+    torch.cuda.synchronize()
+    for x, y in zip(got, (scores, idx) + tuple(rows)):
+        assert torch.equal(x, y)
+    for i, h in ((0, 0), (n - 1, Hkv - 1)):
+        assert torch.equal(split_packed(idx.cpu(), budgets, Hkv, keys + W)[i][h], oracle.select(scores[i, h:h + 1].cpu(), W, budgets[0])[0])
