@@ -229,12 +229,13 @@ int laq_select_sink_recent(int32_t n_inst, int32_t Hkv, int32_t L, const int32_t
                            int32_t n_sink, int32_t *idx, void *stream);
 
 /*
- * Which kernels laq_score (and laq_evict) take for this shape on the current device, for callers
+ * How laq_score (and laq_evict) read K for this shape on the current device, for callers
  * that account for memory traffic (Sec. 4.3's scoring reads K once or twice accordingly):
- * LAQ_KERNEL_VECTOR (fp32 caches, or a head size or window that the bf16 streaming kernels do not take: one
- * chunk per workgroup, K read twice), LAQ_KERNEL_TWO_PASS (bf16, K read twice) or
- * LAQ_KERNEL_SINGLE_READ (bf16, K read once); a negative error code
- * for an invalid shape.  The strides, the block table and the score_choice of `shape` are taken
+ * LAQ_KERNEL_VECTOR (fp32 caches, or a head size or window that the bf16 streaming kernels do not take: always one
+ * chunk per workgroup, K read twice), LAQ_KERNEL_TWO_PASS (bf16, K read twice: by the streaming kernels, or,
+ * in calls of at most 512 chunks that leave the choice to the library, by the one-chunk kernels where
+ * these are faster) or LAQ_KERNEL_SINGLE_READ (bf16, K read once); a negative error code
+ * for an invalid shape.  (The first name is older than its kernels, which work on the matrix cores.)  The strides, the block table and the score_choice of `shape` are taken
  * into account like laq_score does.  Launches nothing.
  */
 enum { LAQ_KERNEL_VECTOR = 0, LAQ_KERNEL_TWO_PASS = 1, LAQ_KERNEL_SINGLE_READ = 2 };

@@ -28,8 +28,7 @@ constexpr int MAX_QPOS = 512;              // explicit query positions a call ma
 // device at once that the exchange memory of a workspace is sized for.
 constexpr int FUSED_ROWS = 512;
 constexpr int FUSED_MAX_RESIDENT = 1024;
-// Whether scoring takes the single-read kernel where it applies (it is slower than the two streaming
-// passes on the shapes measured so far; the parity tests run with it switched on).
+// Whether scoring may take the single-read kernel at all (single_read_wanted() tells where it is the faster one).
 constexpr bool SINGLE_READ_ENABLED = true;
 
 struct ScoreGeom {

@@ -4,7 +4,7 @@
 // the streaming kernels' set-up, combine and pooling launches would bound.
 //
 // Two kernels: (1) per-row softmax statistics (m, z) of each chunk, (2) after folding the statistics of a
-// head's chunks (by every workgroup itself when they are few, else by row_constants_kernel), the sum over
+// head's chunks (by every workgroup itself when they are few, else by row_constants_mfma_kernel), the sum over
 // the rows of exp2(s - c): raw scores.  Also here: the sequence pooling over raw scores.
 //
 // A wave holds 32 key rows in registers in operand layout (lane l: row l % 32, the 16-byte pieces 2t + l / 32)
@@ -16,7 +16,7 @@
 //
 // What bounds it: for fp32 the matrix cores (157 TFLOP/s dense), which do the product twice; the vector ALU
 // kernels that stood here took 8 us per (million keys x score row) and pass pair, these about 1.  64 heads x
-// 8191 keys, d = 128, 64 score rows, fp32: 1018 -> 216 us.
+// 8191 keys, d = 128, 64 score rows, fp32: 1018 -> 211 us.
 #include "laq_internal.h"
 
 namespace laq {
@@ -31,10 +31,10 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float NEG_BIG = -1.0e30f;   // finite "minus infinity" for running maxima
 constexpr int WAVES = CHUNK_ROWS / 32, THREADS = WAVES * 64;
-// Every workgroup of the second kernel folds the statistics of its head itself where that is little next to
-// its keys and the workgroups are few (one launch less); otherwise row_constants_mfma_kernel does it once.
 // Row tiles of a chunk that are worked on side by side where there are too few chunks to fill the device.
 constexpr int MAX_SPLIT = 4;
+// Every workgroup of the second kernel folds the statistics of its head itself where that is little next to
+// its keys and the workgroups are few (one launch less); otherwise row_constants_mfma_kernel does it once.
 constexpr int FOLD_CHUNKS = 32, FOLD_WORKGROUPS = 512;
 // The exponential instruction returns 0 below 2^-126, where fp32 still tells scores apart: what it lost is added to a tile's sum
 // that is below TINY (above it, 32 such terms are less than a rounding).

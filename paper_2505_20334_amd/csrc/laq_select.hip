@@ -1,14 +1,14 @@
 // Per-KV-head selection: the "ArgSort(...)[:B]" of Eq. 4 done as a radix select (no sort).
 //
-// One workgroup of 16 waves ranks the prefix scores of one (instance, KV head).  Scores are mapped to
+// One workgroup of 4, 8 or 16 waves ranks the prefix scores of one (instance, KV head).  Scores are mapped to
 // order-preserving 32-bit keys, which live in registers for prefixes up to 32768 (longer ones re-read the
 // scores from memory in every sweep).
 //   1. A lower bound of the k-th largest key: the keys are cut into at least k groups (a thread's, or halves
 //      or quarters of them); the k-th largest of the groups' maxima is such a bound, and only one key per
-//      group is counted for it (by its 11 leading bits; the bound is the lower edge of a bin).  Few more
+//      group is counted for it (by its 9, 10 or 11 leading bits -- two bins per thread; the bound is the lower edge of a bin).  Few more
 //      than k keys are left above it.  (Short prefixes with many keys wanted: every key is a group.)
-//   2. These are counted by their distance from the bound, 2048 bins up to the largest key, and the bin of
-//      the k-th one is refined, 11 bits at a time, until its keys are all wanted or so few (CANDIDATES)
+//   2. These are counted by their distance from the bound, in as many bins up to the largest key, and the bin of
+//      the k-th one is refined, as many bits at a time, until its keys are all wanted or so few (CANDIDATES)
 //      that comparing all pairs tells the key T of the k-th largest and how many keys equal to T still
 //      fit (ties go to the lower position).
 //   3. A last sweep emits, in ascending position order, every key above T plus the first `want` keys equal to
