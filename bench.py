@@ -53,8 +53,9 @@ def read_traffic(workload):
     return None, "%s holds no traffic figure for the kernels of this build (see the note at its top)" % rel
 
 
-SCORE_STAGE_KERNELS = ("stream_kernel", "row_constants", "reset_counters", "pool_boundaries", "fused_kernel",
-                       "fused_reset", "window_table_kernel", "tile_stats_kernel", "tile_score_kernel", "pool_kernel")
+SCORE_STAGE_KERNELS = ("wave_stats_kernel", "wave_score_kernel", "row_constants", "pool_boundaries", "fused_kernel",
+                       "fused_reset", "window_table_kernel", "tile_stats_kernel", "tile_score_kernel", "pool_kernel",
+                       "pool_quads_kernel")
 
 
 DECODE_KERNELS = ("decode_kernel",)
@@ -122,10 +123,10 @@ def live_traffic(args, cfg_id, kernels=SCORE_STAGE_KERNELS):
 SCORE_KERNEL_TEXT = {
     "single-read": "laq_score stage: fused_reset_kernel + fused_kernel (K read once; the unnormalised probabilities "
                    "stay in registers until the softmax denominators are known) + pool_boundaries_kernel",
-    "two-pass": "laq_score stage: stream_kernel<pass 1> + row_constants_mfma_kernel + stream_kernel<pass 2> + "
-                "pool_boundaries_kernel, or tile_stats_kernel + tile_score_kernel in most calls of at most 512 "
-                "chunks of 256 keys (K counted once in the algorithmic bytes, read twice)",
-    "vector": "laq_score stage: tile_stats_kernel + tile_score_kernel (K counted once in the algorithmic bytes, read twice)",
+    "two-pass": "laq_score stage: wave_stats_kernel + wave_score_kernel + pool_quads_kernel, or tile_stats_kernel + "
+                "tile_score_kernel + pool_quads_kernel in small calls (K counted once in the algorithmic bytes, read twice)",
+    "vector": "laq_score stage: wave_stats_kernel + wave_score_kernel, or tile_stats_kernel + tile_score_kernel in small calls, + "
+              "pool_quads_kernel (K counted once in the algorithmic bytes, read twice)",
 }
 
 

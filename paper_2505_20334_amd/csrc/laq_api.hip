@@ -97,12 +97,9 @@ static int make_layout(const laq_shape* s, const ScoreGeom& g, KvLayout* lay) {
 
 static size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// chunks per head under the finest chunking any scoring path uses
-static size_t max_chunks(const ScoreGeom& g) { return ((size_t)g.L + MIN_CHUNK_ROWS - 1) / MIN_CHUNK_ROWS; }
-
 size_t workspace_bytes(const ScoreGeom& g) {
   const size_t heads = (size_t)g.n_inst * g.Hkv;
-  return round256(heads * max_chunks(g) * g.Rpad * sizeof(float2)) + round256(heads * g.Rpad * sizeof(float)) +
+  return round256(heads * g.nchunk * g.Rpad * sizeof(float2)) + round256(heads * g.Rpad * sizeof(float)) +
          2 * round256(heads * g.L * sizeof(float)) + round256(fused_sync_bytes(g)) + 256;
 }
 
@@ -111,7 +108,7 @@ Workspace carve_workspace(const ScoreGeom& g, void* ws) {
   char* base = static_cast<char*>(ws);
   Workspace w;
   w.part = reinterpret_cast<float2*>(base);
-  base += round256(heads * max_chunks(g) * g.Rpad * sizeof(float2));
+  base += round256(heads * g.nchunk * g.Rpad * sizeof(float2));
   w.rowc = reinterpret_cast<float*>(base);
   base += round256(heads * g.Rpad * sizeof(float));
   w.raw = reinterpret_cast<float*>(base);
@@ -121,8 +118,7 @@ Workspace carve_workspace(const ScoreGeom& g, void* ws) {
   w.fused = base;
   base += round256(fused_sync_bytes(g));
   w.window = reinterpret_cast<int32_t*>(base - MAX_QPOS * sizeof(int32_t));   // (the end of that area, see make_plan() of the single-read kernel)
-  w.ctr = reinterpret_cast<int*>(base);
-  w.status = w.ctr + 8;
+  w.status = reinterpret_cast<int*>(base) + 8;
   return w;
 }
 
@@ -197,15 +193,22 @@ static int init_current_device(int* dev_out) {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return LAQ_ERR_DEVICE;
   if (dev_out) *dev_out = dev;
   if (scratch_of[dev].load(std::memory_order_acquire)) return LAQ_OK;
-  if (score_mfma_init(dev) != hipSuccess || score_fused_init(dev) != hipSuccess || score_tile_init() != hipSuccess) return LAQ_ERR_DEVICE;
+  if (score_fused_init(dev) != hipSuccess || score_tile_init() != hipSuccess || score_wave_init() != hipSuccess) return LAQ_ERR_DEVICE;
   void* ptr = nullptr;
   if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return LAQ_ERR_DEVICE;
   scratch_of[dev].store(ptr, std::memory_order_release);
   return LAQ_OK;
 }
 
+// bf16 and one of the head sizes 64 and 128, with byte offsets inside a head (or block) that fit 31 bits: what laq_score_kernel
+// tells apart from the other shapes.
+static bool usual_shape(const ScoreGeom& g, const KvLayout& lay, int dtype) {
+  return dtype == LAQ_BF16 && (g.d == 128 || g.d == 64) && g.W <= MAX_QPOS && g.n_inst * (long long)g.Hkv <= 0x7fffffff &&
+         ((long long)(lay.table ? lay.block_rows : g.L) + CHUNK_ROWS) * lay.row_bytes < 0x7fffffffLL;
+}
+
 // The single-read kernel's cooperative launch and its serial start cost about 15 us more than the
-// launches of the two streaming passes; measured on an MI355X it is the faster one from 128 MiB of
+// launches of the two passes; measured on an MI355X it is the faster one from 128 MiB of
 // keys per call on (21-27 % at 1 GiB and more).
 static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g) {
   if (shape->score_choice == LAQ_CHOOSE_SINGLE_READ) return true;
@@ -217,30 +220,40 @@ static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g) {
   return g.Rpad <= 64 && key_bytes >= (128LL << 20);
 }
 
-// Few enough chunks that each gets a workgroup of its own at once: the kernels that take one chunk each need
-// three launches where the streaming ones need five (four where the selection launch pools).  They walk the row tiles of
-// 32 one after the other, a streaming workgroup takes four at a time: up to so many quarter tiles per group of four
-// they are the faster ones.  laq_score and (laq_evict), one against the other, us, d = 128, rows x chunks:
-//    64 x 128  18.7 : 19.5 (23.8 : 25.7)     128 x 128  23.2 : 22.4 (28.0 : 30.1)     256 x 128  32.3 : 32.9 (37.1 : 40.1)
-//    96 x 256  23.7 : 23.7 (31.5 : 34.7)     128 x 256  27.6 : 25.0 (35.3 : 35.0)     192 x 256  33.5 : 34.1 (41.8 : 43.1)
-//   224 x 256  37.2 : 35.0 (45.8 : 45.6)     288 x 256  44.3 : 44.1 (52.9 : 54.2)     448 x 256  61.1 : 54.4 (69.6 : 64.6)
-//    64 x 512  26.0 : 28.3 (41.4 : 45.2)     128 x 384  31.0 : 30.5 (45.5 : 47.0)     512 x 512  62.9 : 67.1 (79.2 : 84.5)
-// and d = 64, where the streaming ones lead more often:
-//   128 x 64   17.7 : 17.3 (23.2 : 23.8)     224 x 128  25.8 : 24.7 (30.1 : 30.5)     256 x 128  27.7 : 24.9 (31.8 : 30.8)
-//    64 x 256  16.3 : 15.9 (23.5 : 24.6)      96 x 256  19.2 : 17.6 (26.4 : 27.4)     160 x 192  24.8 : 24.5 (31.1 : 32.4)
-//   352 x 384  40.3 : 39.8 (52.8 : 54.4)     128 x 384  24.8 : 22.6 (38.4 : 38.2)     384 x 384  42.6 : 40.5 (55.9 : 56.0)
-//    64 x 288  19.2 : 17.4 (31.1 : 31.1)      96 x 512  22.9 : 22.8 (38.0 : 40.2)     288 x 288  34.6 : 37.4 (46.5 : 51.7)
-// Beyond 512 chunks nothing is gained and with many rows much is lost (d = 128, 1536 chunks, 64 rows 52.6 : 49.6, 128
-// rows 69.9 : 60.4).  Up to 64 and 128 chunks four and two workgroups share a chunk's row tiles; up to 256 every
-// compute unit has one workgroup, which is alone with all of them; beyond that there are two.
+// Which kernels score a call.  The single-read kernel pools (maximum) where it scores, the others leave raw scores.
+enum class ScorePath { single_read, tile, wave };
+
+// The kernels that give every 256-key chunk a workgroup of its own, where they are the faster ones.  They work on up to four row tiles of a
+// chunk side by side where chunks are few, and hold all of a chunk's keys at once; the others have their score rows in LDS
+// once for many keys and no barrier after that.  laq_evict, these : the others, us, by row tiles x chunks:
+//   bf16, d = 128   1 x 32 17.5 : 18.7, 1 x 128 21.1 : 22.1, 1 x 288 26.7 : 28.7, 1 x 512 30.0 : 33.0; 1 x 280, 344 in 8 heads 31.0 : 27.9, 32.9 : 29.6
+//                   2 x 16 20.4 : 19.5, 2 x 64 23.6 : 21.4, 2 x 256 31.9 : 30.5, 2 x 480 36.0 : 32.2
+//                   4 x 39 27.8 : 29.5, 7 x 60 32.8 : 33.8, 4 x 65 26.5 : 25.7, 4 x 192 36.9 : 30.4, 4 x 399 38.5 : 32.4, 8 x 228 50.5 : 45.2
+//   bf16, d = 64    1 x 96 21.8 : 22.6, 1 x 464 23.4 : 26.6, 2 x 192 21.9 : 19.3, 2 x 480 28.0 : 26.4, 4 x 48 22.0 : 22.6, 4 x 192 33.7 : 25.7
+//   bf16, d = 256   1 x 48 26.0 : 28.7, 1 x 3752 212 : 216, 2 x 396 45.6 : 47.6, 2 x 4360 307 : 292, 4 x 140 39.9 : 36.2
+//   fp32            1 x 72 24.9 : 25.2, 1 x 256 46.5 : 45.7, 2 x 38 34.2 : 36.3, 2 x 148 45.4 : 40.1, 4 x 24 28.3 : 32.7, 4 x 268 114.1 : 96.5
+// fp32 with d > 128 always (the others have no registers for the parts of 32 such keys).
 static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
+  if (!score_wave_supported(g, shape->dtype)) return true;
+  if (shape->score_choice != LAQ_CHOOSE_AUTO && shape->dtype == LAQ_BF16 && (g.d == 64 || g.d == 128)) return false;
   const long long chunks = (long long)g.n_inst * g.Hkv * g.nchunk;
-  if (shape->score_choice != LAQ_CHOOSE_AUTO || chunks > 512) return false;
-  const int tiles = g.Rpad / 32, groups = (tiles + 3) / 4;
-  int quarters = 16;
-  if (g.d == 64 && chunks > 64) quarters = chunks <= 128 ? 14 : chunks <= 256 ? 10 : 15;
-  if (g.d == 128 && chunks > 128 && chunks <= 256) quarters = 12;
-  return 4 * tiles <= quarters * groups;
+  const int tiles = g.Rpad / 32;
+  if (shape->dtype == LAQ_F32) return chunks <= 128;
+  if (g.d > 128) return tiles == 1 || (tiles == 2 && chunks <= 512) || chunks <= 64;
+  if (tiles == 1) return chunks <= 512 && g.nchunk <= 32;
+  return tiles > 2 && chunks <= 64;
+}
+
+static ScorePath score_path(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay) {
+  if (SINGLE_READ_ENABLED && usual_shape(g, lay, shape->dtype) && score_fused_supported(g, lay, shape->dtype) && single_read_wanted(shape, g))
+    return ScorePath::single_read;
+  return tile_wanted(shape, g) ? ScorePath::tile : ScorePath::wave;
+}
+
+// Whether scores that are to be pooled come raw from the kernels that make them.
+static bool leaves_raw(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay) {
+  const ScorePath path = score_path(shape, g, lay);
+  return path != ScorePath::single_read || pool_avg(shape);
 }
 
 // Scores of a validated call into `scores`: pooled, or, with pool == 1, raw.
@@ -254,27 +267,19 @@ static int score_checked(const laq_shape* shape, const ScoreGeom& g, const Query
   WindowPos qp;
   hipError_t e = window_positions(g, positions, w, st, &qp);
   if (e != hipSuccess) return LAQ_ERR_DEVICE;
-  const bool avg = pool_avg(shape) && pool > 1;
-  const bool mfma = score_mfma_supported(g, lay, shape->dtype);
-  const bool fused = SINGLE_READ_ENABLED && score_fused_supported(g, lay, shape->dtype) && single_read_wanted(shape, g);
-  const bool tile = !mfma || (!fused && tile_wanted(shape, g));
-  // matrix cores: the single-read kernel where a team of workgroups can hold a head, else the two
-  // streaming passes; both fuse the max pooling, the average goes through the raw-score plane
-  auto score_on_matrix_cores = [&](int p, float* dst) -> hipError_t {
+  const ScorePath path = score_path(shape, g, lay);
+  if (path == ScorePath::single_read) {
+    const bool apart = pool > 1 && pool_avg(shape);
     bool done = false;
-    if (fused) {
-      const hipError_t ef = launch_score_fused(g, qp, lay, p, q_win, k, dst, w, st, &done);
-      if (ef != hipSuccess || done) return ef;
-    }
-    return launch_score_mfma(g, qp, lay, p, q_win, k, dst, w, st);
-  };
-  if (!tile && !avg) {
-    e = score_on_matrix_cores(pool, scores);
-  } else {
-    float* raw = pool > 1 ? w.raw : scores;
-    e = tile ? launch_score_tile(g, qp, lay, shape->dtype, q_win, k, raw, w, st) : score_on_matrix_cores(1, raw);
-    if (e == hipSuccess && pool > 1) e = launch_pool(g, pool, avg, raw, scores, st);
+    e = launch_score_fused(g, qp, lay, apart ? 1 : pool, q_win, k, apart ? w.raw : scores, w, st, &done);
+    if (e == hipSuccess && done && apart) e = launch_pool(g, pool, true, w.raw, scores, st);
+    if (e != hipSuccess || done) return e == hipSuccess ? LAQ_OK : LAQ_ERR_DEVICE;
+    // (a team of its workgroups does not fit this device: the two passes)
   }
+  float* raw = pool > 1 ? w.raw : scores;
+  e = path == ScorePath::tile ? launch_score_tile(g, qp, lay, shape->dtype, q_win, k, raw, w, st)
+                              : launch_score_wave(g, qp, lay, shape->dtype, q_win, k, raw, w, st);
+  if (e == hipSuccess && pool > 1) e = launch_pool(g, pool, pool_avg(shape), raw, scores, st);
   return e == hipSuccess ? LAQ_OK : LAQ_ERR_DEVICE;
 }
 
@@ -292,24 +297,28 @@ static int score_impl(const laq_shape* shape, const void* q_win, const void* k, 
 }
 
 static int select_impl(const laq_shape* shape, const float* scores, const int32_t* budget, int pool,
-                       int32_t* idx, hipStream_t st) {
+                       int32_t* idx, hipStream_t st, const PoolArgs* pooling = nullptr) {
   ScoreGeom g;
   const int rc = make_geom(shape, &g);
   if (rc != LAQ_OK) return rc;
   if (!pool_ok(pool) || !scores || !idx || !budgets_ok(shape, g, budget)) return LAQ_ERR_INVALID;
   if (g.Hkv > 65535) return LAQ_ERR_UNSUPPORTED;
+  auto launch = [&](int n, int i0, const auto& tab) {
+    return pooling ? launch_select_pooling(n, i0, g.Hkv, g.L, g.keep, scores, tab, idx, *pooling, st)
+                   : launch_select(n, i0, g.Hkv, g.L, g.keep, pool, pool_avg(shape), scores, tab, idx, st);
+  };
   int64_t row = 0;
   for (int i0 = 0; i0 < shape->n_inst; i0 += MAX_INST_PER_LAUNCH) {
     const int n = shape->n_inst - i0 < MAX_INST_PER_LAUNCH ? shape->n_inst - i0 : MAX_INST_PER_LAUNCH;
     hipError_t e;
     if (const int bk = uniform_rows(g.L, budget, i0, n)) {
       const UniformInst u{bk, row, (int64_t)g.Hkv * bk};
-      e = launch_select(n, i0, g.Hkv, g.L, g.keep, pool, pool_avg(shape), scores, u, idx, st);
+      e = launch(n, i0, u);
       row += n * u.per_inst;
     } else {
       InstTable tab;
       fill_table(g.Hkv, g.L, budget, i0, n, row, &tab, &row);
-      e = launch_select(n, i0, g.Hkv, g.L, g.keep, pool, pool_avg(shape), scores, tab, idx, st);
+      e = launch(n, i0, tab);
     }
     if (e != hipSuccess) return LAQ_ERR_DEVICE;
   }
@@ -403,7 +412,7 @@ static int decode_impl(const laq_shape* shape, const void* q, const void* kc, co
 static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, const float* raw, int row_bytes) {
   const long long heads = (long long)g.n_inst * g.Hkv;
   const int keys = g.P + row_shift(raw, g.L);
-  if ((pool - 1) / 2 > FINISH_MAX_HALF || keys > FINISH_MAX_KEYS || heads > 256 || shape->n_inst > MAX_INST_PER_LAUNCH) return false;
+  if ((pool - 1) / 2 > SELECT_POOL_MAX_HALF || keys > FINISH_MAX_KEYS || heads > 256 || shape->n_inst > MAX_INST_PER_LAUNCH) return false;
   int gather = 0;
   if (keys <= 2048) gather = 32 << 10;
   else if (heads >= 160) gather = 128 << 10;
@@ -415,6 +424,13 @@ static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const int3
     if (bk > most) most = bk;
   }
   return (long long)most * row_bytes <= gather;
+}
+
+// Whether the selection kernel pools the raw scores of this call on the way: a launch, a read and a write of the scores less.
+static bool select_pools(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, int pool, const float* raw) {
+  const int keys = g.P + row_shift(raw, g.L);
+  return pool > 1 && (pool - 1) / 2 <= SELECT_POOL_MAX_HALF && keys <= SELECT_POOL_MAX_KEYS &&
+         (keys <= SELECT_POOL_MANY_KEYS || (long long)g.n_inst * g.Hkv < SELECT_MANY_HEADS) && leaves_raw(shape, g, lay);
 }
 
 // Pooling, selection and gather of a small call, from the raw scores.
@@ -564,9 +580,17 @@ static int evict_impl(const laq_shape* shape, const void* q_win, const void* k, 
     if (rc != LAQ_OK) return rc;
     return laq::finish_checked(shape, g, lay, k, v, budget, pool_kernel, raw, scores, idx, k_out, v_out, st);
   }
-  int rc = laq::score_checked(shape, g, qp, lay, q_win, k, pool_kernel, scores, ws, st);
-  if (rc != LAQ_OK) return rc;
-  rc = laq::select_impl(shape, scores, budget, 1, idx, st);
+  int rc;
+  if (laq::select_pools(shape, g, lay, pool_kernel, raw)) {
+    rc = laq::score_checked(shape, g, qp, lay, q_win, k, 1, raw, ws, st);
+    if (rc != LAQ_OK) return rc;
+    const laq::PoolArgs pooling{scores, (pool_kernel - 1) / 2, laq::pool_avg(shape) ? 1 : 0};
+    rc = laq::select_impl(shape, raw, budget, 1, idx, st, &pooling);
+  } else {
+    rc = laq::score_checked(shape, g, qp, lay, q_win, k, pool_kernel, scores, ws, st);
+    if (rc != LAQ_OK) return rc;
+    rc = laq::select_impl(shape, scores, budget, 1, idx, st);
+  }
   if (rc != LAQ_OK) return rc;
   return laq::compact_impl(shape, k, v, idx, budget, k_out, v_out, st);
 }
@@ -592,7 +616,7 @@ int laq_score_kernel(const laq_shape* shape) {
   if (rc != LAQ_OK) return rc;
   laq::KvLayout lay;
   if (laq::make_layout(shape, g, &lay) != LAQ_OK) return LAQ_ERR_INVALID;
-  if (!laq::score_mfma_supported(g, lay, shape->dtype)) return LAQ_KERNEL_VECTOR;
+  if (!laq::usual_shape(g, lay, shape->dtype)) return LAQ_KERNEL_VECTOR;
   bool single = false;
   if (laq::SINGLE_READ_ENABLED && laq::single_read_wanted(shape, g) &&
       laq::score_fused_applies(g, lay, shape->dtype, &single) != hipSuccess)

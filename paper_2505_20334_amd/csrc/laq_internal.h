@@ -10,16 +10,9 @@
 
 namespace laq {
 
-// Each scoring workgroup stages CHUNK_ROWS consecutive key rows of one KV head; a head is
-// covered by nchunk = ceil(L / CHUNK_ROWS) chunks.
+// The one-chunk scoring kernels give every workgroup CHUNK_ROWS consecutive key rows of one KV head; a head is
+// covered by nchunk = ceil(L / CHUNK_ROWS) chunks.  The other two-pass kernels cut a head into at most as many segments.
 constexpr int CHUNK_ROWS = 256;
-// The matrix-core path stages MFMA_ROWS key rows per workgroup (its own, finer chunking of the
-// same per-chunk statistics); the workspace is sized for the finer of the two.
-#ifndef LAQ_MFMA_ROWS
-#define LAQ_MFMA_ROWS 256
-#endif
-constexpr int MFMA_ROWS = LAQ_MFMA_ROWS;
-constexpr int MIN_CHUNK_ROWS = MFMA_ROWS < CHUNK_ROWS ? MFMA_ROWS : CHUNK_ROWS;
 constexpr int MAX_POOL = 63;
 constexpr int MAX_INST_PER_LAUNCH = 256;   // size of the per-instance tables passed as kernel arguments
 
@@ -61,21 +54,18 @@ struct QueryPos {                          // host side
 };
 
 // Workspace carving: [partials | row constants | raw scores]
-//   part:  float2 (m, z) per (instance, KV head, chunk, padded row): softmax statistics of a chunk
+//   part:  float2 (m, z) per (instance, KV head, chunk, padded row): softmax statistics of a chunk or segment
 //   rowc:  float c = M + log2(Z) per (instance, KV head, padded row)
-//   raw:   float per (instance, KV head, key): unpooled scores in front of a separate pooling
-//          kernel (one-chunk kernels, average pool); the streaming kernels with the max pool keep the edge
-//          records of their chunk boundaries here instead
+//   raw:   float per (instance, KV head, key): unpooled scores in front of a pooling or selecting kernel; the single-read
+//          kernel with the max pool keeps the edge records of its workgroups' boundaries here instead
 //   pooled: float per (instance, KV head, key): the hand-over plane between scoring and selection
 //          when laq_evict is called without a scores buffer
-//   ctr:   two work counters (one per streaming pass), reset by every call
 struct Workspace {
   float2* part;
   float* rowc;
   float* raw;
   float* pooled;
   void* fused;      // exchange memory of the single-read kernel (fused_sync_bytes)
-  int* ctr;
   int32_t* window;  // position table of a window longer than WINDOW_INLINE (MAX_QPOS entries)
   int* status;      // != 0 after a call whose single-read kernel gave up a wait (results invalid)
 };
@@ -119,20 +109,25 @@ struct CompactTable {
   int64_t row0[MAX_INST_PER_LAUNCH];
   int32_t blk0[MAX_INST_PER_LAUNCH + 1];
 };
-// What the selection kernel does besides where it finishes a small eviction in one launch: it pools the raw
-// scores (max or mean over half positions to either side), writes the pooled ones and gathers the rows it
-// has selected.
-struct FinishArgs {
+// What the selection kernel does besides: it pools the raw scores it is given (max or mean over half positions to either
+// side) and writes the pooled ones; and, where it finishes a small eviction in one launch, it gathers the rows it has
+// selected.
+struct PoolArgs {
   float* pooled;
+  int32_t half, avg;
+};
+struct FinishArgs : PoolArgs {
   const char *k, *v;
   char *k_out, *v_out;
   int64_t inst_bytes, head_bytes;
   int32_t row_bytes, src_row_bytes, elem_bytes;
-  int32_t half, avg;
   KvLayout lay;
 };
-constexpr int FINISH_MAX_HALF = 4;              // widest pooling it does: what two loads beside a lane's own four scores bring
-constexpr int FINISH_MAX_KEYS = 16 * 1024;      // longest prefix
+constexpr int SELECT_POOL_MAX_HALF = 8;         // widest pooling it does: two quads of scores beside a lane's own on either side
+constexpr int SELECT_POOL_MAX_KEYS = 32 * 1024; // longest prefix it pools
+constexpr int SELECT_MANY_HEADS = 768;          // heads of a launch from which on several workgroups share a compute unit,
+constexpr int SELECT_POOL_MANY_KEYS = 8 * 1024; // and the longest prefix it pools there (a longer one leaves no registers for it)
+constexpr int FINISH_MAX_KEYS = 16 * 1024;      // longest prefix of a finishing launch
 // How many scores the rows of a launch start behind a 16-byte boundary, at most.  Only where they do does a variant of the
 // selection kernel hold fewer keys than its registers: 32768 keys of aligned rows taken for 32771 went to the kernel that holds
 // none (8, 256, 2048 heads: 43.6, 51.0 and 366 us against 15.6, 17.1 and 116 for 32764), 2048 of them to the next
@@ -186,11 +181,13 @@ inline int uniform_rows(int L, const int32_t* budget, int i0, int n) {
 hipError_t launch_score_tile(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q,
                              const void* k, float* raw, const Workspace& ws, hipStream_t st);
 hipError_t score_tile_init();
+bool score_wave_supported(const ScoreGeom& g, int dtype);
+hipError_t launch_score_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q,
+                             const void* k, float* raw, const Workspace& ws, hipStream_t st);
+hipError_t score_wave_init();
 hipError_t launch_row_constants(const ScoreGeom& g, const Workspace& ws, hipStream_t st);
-bool score_mfma_supported(const ScoreGeom& g, const KvLayout& lay, int dtype);
-// kernel attributes and residency of every matrix-core scoring kernel on device `dev`, which must be
+// kernel attributes and residency of the single-read scoring kernel on device `dev`, which must be
 // the current device; idempotent
-hipError_t score_mfma_init(int dev);
 hipError_t score_fused_init(int dev);
 size_t fused_sync_bytes(const ScoreGeom& g);
 bool score_fused_supported(const ScoreGeom& g, const KvLayout& lay, int dtype);
@@ -202,13 +199,16 @@ hipError_t launch_score_fused(const ScoreGeom& g, const WindowPos& qp, const KvL
 // from the chunks' edge records
 hipError_t launch_pool_boundaries(const ScoreGeom& g, int half, int nchunk, int chunk_rows, const float* edge,
                                   float* scores, hipStream_t st);
-hipError_t launch_score_mfma(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const void* q,
-                             const void* k, float* scores, const Workspace& ws, hipStream_t st);
 hipError_t launch_pool(const ScoreGeom& g, int pool, bool avg, const float* raw, float* pooled, hipStream_t st);
 hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
                          const InstTable& tab, int32_t* idx, hipStream_t st);
 hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
                          const UniformInst& tab, int32_t* idx, hipStream_t st);
+// the same from raw scores, pooled on the way
+hipError_t launch_select_pooling(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const InstTable& tab, int32_t* idx,
+                                 const PoolArgs& pool, hipStream_t st);
+hipError_t launch_select_pooling(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const UniformInst& tab, int32_t* idx,
+                                 const PoolArgs& pool, hipStream_t st);
 hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const InstTable& tab, int32_t* idx,
                          const FinishArgs& fin, hipStream_t st);
 hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const UniformInst& tab, int32_t* idx,

@@ -5,8 +5,7 @@
 //
 // Two kernels: (1) per-row softmax statistics (m, z) of each chunk, (2) after folding the statistics of a
 // head's chunks (by every workgroup itself when they are few, else by row_constants_mfma_kernel), the sum over
-// the rows of exp2(s - c): raw scores.  Also here: the sequence pooling over raw scores.
-//
+// the rows of exp2(s - c): raw scores.  //
 // A wave holds 32 key rows in registers in operand layout (lane l: row l % 32, the 16-byte pieces 2t + l / 32)
 // and walks the score rows in tiles of 32 that the workgroup stages in LDS, one tile ahead.  The reduction
 // index of a product may run in any order as long as both operands agree, so fp32 takes the four elements
@@ -313,42 +312,6 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(Sc
   if (c.hf == 0 && key < g.L) raw[hg * g.L + key] = sum;
 }
 
-// pooled[j] = max (or mean) of raw[i], |i - j| <= half, 0 <= i < P, for prefix keys; the kept
-// trailing columns are copied.  A workgroup stages POOL_TILE scores plus the window margins in
-// LDS, with zeros for positions outside the prefix: the scores are sums of probabilities, never
-// negative, so a zero leaves a maximum alone, and it leaves the ascending fp32 sum of the average
-// bit-identical to pool_window()'s sum over the clipped window.  grid.x walks the (instance, KV
-// head) pairs.
-constexpr int POOL_TILE = 1024;
-__global__ __launch_bounds__(256) void pool_kernel(int L, int P, int half, bool avg, const float* __restrict__ raw,
-                                                   float* __restrict__ pooled) {
-  __shared__ float tile[POOL_TILE + MAX_POOL - 1];
-  const float* r = raw + (size_t)blockIdx.x * L;
-  float* out = pooled + (size_t)blockIdx.x * L;
-  const int j0 = blockIdx.y * POOL_TILE;
-  for (int t = threadIdx.x; t < POOL_TILE + 2 * half; t += 256) {
-    const int i = j0 - half + t;
-    tile[t] = (i >= 0 && i < P) ? r[i] : 0.f;
-  }
-  __syncthreads();
-  const float kernel_size = (float)(2 * half + 1);
-  for (int t = threadIdx.x; t < POOL_TILE && j0 + t < L; t += 256) {
-    const int j = j0 + t;
-    float v;
-    if (j >= P) {
-      v = r[j];
-    } else if (avg) {
-      float acc = 0.f;
-      for (int o = 0; o <= 2 * half; ++o) acc += tile[t + o];
-      v = acc / kernel_size;
-    } else {
-      v = tile[t + half];
-      for (int o = 0; o <= 2 * half; ++o) v = fmaxf(v, tile[t + o]);
-    }
-    out[j] = v;
-  }
-}
-
 constexpr int MAX_LDS = 128 << 10;                       // of the staged score rows
 
 template <typename T, int NP, bool FULL>
@@ -411,13 +374,6 @@ hipError_t launch_score_tile(const ScoreGeom& g, const WindowPos& qp, const KvLa
   if (g.d == 256) return launch_tile<uint16_t, 16, true>(g, qp, lay, qq, kk, raw, ws, st);
   if (g.d < 128) return launch_tile<uint16_t, 8, false>(g, qp, lay, qq, kk, raw, ws, st);
   return launch_tile<uint16_t, 16, false>(g, qp, lay, qq, kk, raw, ws, st);
-}
-
-// pooled scores from raw ones, for the paths that do not pool where they score
-hipError_t launch_pool(const ScoreGeom& g, int pool, bool avg, const float* raw, float* pooled, hipStream_t st) {
-  dim3 grid(g.n_inst * g.Hkv, (g.L + POOL_TILE - 1) / POOL_TILE);
-  hipLaunchKernelGGL(pool_kernel, grid, dim3(256), 0, st, g.L, g.P, (pool - 1) / 2, avg, raw, pooled);
-  return hipGetLastError();
 }
 
 }  // namespace laq

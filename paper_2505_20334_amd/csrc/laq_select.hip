@@ -20,12 +20,14 @@
 #include <type_traits>
 
 #include "laq_internal.h"
+#include "laq_pool.h"
 
 namespace laq {
 
 namespace {
 
-constexpr int SEL_MANY_WORKGROUPS = 768;   // heads of a launch from which on several workgroups share a compute unit
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // (a native vector: arrays of it stay in registers)
+
 constexpr int COPIES = 8;                  // histograms of the first pass
 constexpr int CANDIDATES = 128;            // keys that are ranked by comparing all pairs
 
@@ -51,6 +53,11 @@ __device__ __forceinline__ int wave_scan(int x) {
   x += dpp_or_zero<0x142, 0xa>(x);         // lane 15 of a row to the next row
   x += dpp_or_zero<0x143, 0xc>(x);         // lane 31 to the upper half
   return x;
+}
+
+__device__ __forceinline__ float4 quad_of_lane(float4 x, int l) {
+  return make_float4(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x.x), l)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x.y), l)),
+                     __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x.z), l)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x.w), l)));
 }
 
 // Sizes that follow from the threads of a workgroup: two bins per thread.
@@ -108,14 +115,14 @@ __device__ __forceinline__ void find_bin(Sel<THREADS>& sh, const int* hist, int 
 // QUADS (scores that are final: no pooling here): register 4q + c of a lane holds position
 // seg0 + 256 q + 4 lane + c - shift, where shift (0 .. 3) is how far the row starts behind a 16-byte boundary,
 // fetched with one load per q.  Otherwise register i holds position seg0 + 64 i + lane.
-// FIN = FinishArgs: the scores are raw ones, see there; NoFinish: nothing of that.
+// FIN = PoolArgs, FinishArgs: the scores are raw ones, see there; NoFinish: nothing of that.
 struct NoFinish {};
 template <int THREADS, int ITEMS, bool QUADS, typename TAB, typename FIN>
 __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int keep, int pool, bool avg,
                                                              const float* __restrict__ scores, TAB tab,
                                                              int inst0, int32_t* __restrict__ idx, FIN fin) {
-  constexpr bool FINISH = std::is_same<FIN, FinishArgs>::value;
-  static_assert(!FINISH || QUADS, "four neighbours per lane");
+  constexpr bool FINISH = std::is_same<FIN, FinishArgs>::value, POOLS = std::is_base_of<PoolArgs, FIN>::value;
+  static_assert(!POOLS || QUADS, "four neighbours per lane");
   __shared__ __align__(16) Sel<THREADS> sh;
   constexpr int BINS = Sel<THREADS>::BINS, BITS = Sel<THREADS>::BITS, TOP = 32 - BITS;
 
@@ -131,7 +138,7 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
   const bool all = ksel >= P, ranked = ksel > 0 && !all;
   if (all)
     for (int j = tid; j < P; j += THREADS) out[j] = j;
-  if constexpr (!FINISH) {
+  if constexpr (!POOLS) {
     if (!ranked) return;
   } else if (fin.pooled != scores) {
     float* pooled = fin.pooled + ((size_t)(inst0 + li) * Hkv + head) * L;
@@ -162,40 +169,53 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
     };
 #pragma unroll
     for (int q4 = 0; q4 < ITEMS / 4; ++q4) v[q4] = quad_at(seg0 + q4 * 256 + lane * 4, 0.f);
-    if constexpr (FINISH) {
+    if constexpr (POOLS) {
       if (fin.half > 0) {
         float* pooled = fin.pooled + ((size_t)(inst0 + li) * Hkv + head) * L;
-        const float kernel_size = (float)(2 * fin.half + 1);
+        // The quads around a lane's own come from its neighbours' registers; around the first and the last of the wave's
+        // from memory.
+        constexpr int NQ = ITEMS / 4;
+        const float4 none = make_float4(0.f, 0.f, 0.f, 0.f);
+        const bool wide = fin.half > 4;
+        const int end = seg0 + NQ * 256;
+        float4 before1 = none, before2 = none, after1 = none, after2 = none;
+        if (lane == 0 || lane == 63) {
+          before1 = quad_at(lane == 0 ? seg0 - 4 : end, 0.f);
+          if (wide) before2 = quad_at(lane == 0 ? seg0 - 8 : end + 4, 0.f);
+          after1 = before1;
+          after2 = before2;
+        }
 #pragma unroll
-        for (int q4 = 0; q4 < ITEMS / 4; ++q4) {
+        for (int q4 = 0; q4 < NQ; ++q4) {
           const int pos = seg0 + q4 * 256 + lane * 4;
-          if (pos + 3 < 0 || pos >= P) continue;
-          // the neighbours (scores are never negative: a zero stands for "not in the window", and leaves an
-          // ascending sum as it is)
-          const float4 lo = quad_at(pos - 4, 0.f), mid = quad_at(pos, 0.f), hi = quad_at(pos + 4, 0.f);
-          const float w[12] = {lo.x, lo.y, lo.z, lo.w, mid.x, mid.y, mid.z, mid.w, hi.x, hi.y, hi.z, hi.w};
-          float r[4];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            float m = w[4 + c], sum = 0.f;
-#pragma unroll
-            for (int o = -FINISH_MAX_HALF; o <= FINISH_MAX_HALF; ++o) {
-              const bool in = abs(o) <= fin.half;      // (no zero for those outside: it would hide a NaN)
-              m = in ? fmaxf(m, w[4 + c + o]) : m;
-              sum += in ? w[4 + c + o] : 0.f;
-            }
-            r[c] = fin.avg ? sum / kernel_size : m;
+          float4 q[5];
+          q[2] = v[q4];
+          float4 n1 = after1, n2 = after2;     // what lies behind the last lane's quad
+          if (q4 + 1 < NQ) {
+            n1 = quad_of_lane(v[q4 + 1 < NQ ? q4 + 1 : 0], 0);
+            if (wide) n2 = quad_of_lane(v[q4 + 1 < NQ ? q4 + 1 : 0], 1);
           }
+          q[1] = lane_before(before1, q[2]);
+          q[3] = lane_after(n1, q[2]);
+          q[0] = q[4] = none;
+          if (wide) {
+            q[0] = lane_before(before2, q[1]);
+            q[4] = lane_after(n2, q[3]);
+          }
+          before1 = quad_of_lane(q[2], 63);
+          if (wide) before2 = quad_of_lane(q[2], 62);
+          const float4 r = pool_quad(q, fin.half, fin.avg != 0);
           if (pos >= 0 && pos + 3 < P) {
-            *reinterpret_cast<float4*>(pooled + pos) = make_float4(r[0], r[1], r[2], r[3]);
-            v[q4] = make_float4(r[0], r[1], r[2], r[3]);
-          } else {
+            *reinterpret_cast<float4*>(pooled + pos) = r;
+            v[q4] = r;
+          } else if (pos + 3 >= 0 && pos < P) {
             float* e = &v[q4].x;
+            const float* x = &r.x;
 #pragma unroll
             for (int c = 0; c < 4; ++c)
               if (pos + c >= 0 && pos + c < P) {
-                pooled[pos + c] = r[c];
-                e[c] = r[c];
+                pooled[pos + c] = x[c];
+                e[c] = x[c];
               }
           }
         }
@@ -226,7 +246,7 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
       }
     }
   }
-  if (FINISH ? ranked : true) {
+  if (POOLS ? ranked : true) {
   auto key_of = [&](int i) -> uint32_t {
     if (ITEMS > 0) return key[i];
     const int pos = seg0 + i * 64 + lane;
@@ -388,24 +408,45 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
     const int ppr = fin.row_bytes >> 4, total = bk * ppr;
     const int64_t row0 = tab.first(li) + (int64_t)head * bk;
     const char *ks = fin.k + (size_t)head * fin.head_bytes, *vs = fin.v + (fin.v ? (size_t)head * fin.head_bytes : 0);
-#pragma unroll 2
-    for (int p = tid; p < total; p += THREADS) {
-      const int row = p / ppr, col = p - row * ppr, j = out[row];
-      size_t so;
-      if (fin.lay.table) {
-        int r;
-        so = (size_t)paged_block_offset(fin.lay, inst0 + li, j, &r) * fin.elem_bytes + (size_t)r * fin.src_row_bytes;
-      } else {
-        so = (size_t)(inst0 + li) * fin.inst_bytes + (size_t)j * fin.src_row_bytes;
+    // several pieces per thread and turn, so that their list entries and then their rows are on the way together
+    constexpr int TURN = 4;
+    const int drow = THREADS / ppr, dcol = THREADS - drow * ppr;
+    int row = tid / ppr, col = tid - row * ppr;
+    for (int p = tid; p < total; p += THREADS * TURN) {
+      int j[TURN];
+      size_t from[TURN], to[TURN];
+#pragma unroll
+      for (int u = 0; u < TURN; ++u) {
+        const bool in = p + u * THREADS < total;
+        j[u] = out[in ? row : 0];
+        from[u] = (size_t)col * 16;
+        to[u] = (size_t)(row0 + row) * fin.row_bytes + (size_t)col * 16;
+        row += drow;
+        col += dcol;
+        if (col >= ppr) {
+          col -= ppr;
+          ++row;
+        }
       }
-      so += (size_t)col * 16;
-      const size_t dof = (size_t)(row0 + row) * fin.row_bytes + (size_t)col * 16;
-      const uint4 x = *reinterpret_cast<const uint4*>(ks + so);
-      if (fin.v) {
-        const uint4 y = *reinterpret_cast<const uint4*>(vs + so);
-        *reinterpret_cast<uint4*>(fin.v_out + dof) = y;
+      u32x4 x[TURN], y[TURN];
+#pragma unroll
+      for (int u = 0; u < TURN; ++u) {
+        if (fin.lay.table) {
+          int r;
+          from[u] += (size_t)paged_block_offset(fin.lay, inst0 + li, j[u], &r) * fin.elem_bytes + (size_t)r * fin.src_row_bytes;
+        } else {
+          from[u] += (size_t)(inst0 + li) * fin.inst_bytes + (size_t)j[u] * fin.src_row_bytes;
+        }
+        x[u] = *reinterpret_cast<const u32x4*>(ks + from[u]);
+        if (fin.v) y[u] = *reinterpret_cast<const u32x4*>(vs + from[u]);
       }
-      *reinterpret_cast<uint4*>(fin.k_out + dof) = x;
+#pragma unroll
+      for (int u = 0; u < TURN; ++u) {
+        if (p + u * THREADS < total) {
+          *reinterpret_cast<u32x4*>(fin.k_out + to[u]) = x[u];
+          if (fin.v) *reinterpret_cast<u32x4*>(fin.v_out + to[u]) = y[u];
+        }
+      }
     }
   }
 }
@@ -430,31 +471,36 @@ __global__ __launch_bounds__(256) void sink_recent_kernel(int Hkv, int L, int n_
   for (int t = threadIdx.x; t < bk; t += 256) out[t] = t < s ? t : t + shift;
 }
 
-template <typename TAB>
+template <typename TAB, typename FIN>
 hipError_t launch_for(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores, const TAB& tab,
-                      int32_t* idx, hipStream_t st) {
+                      int32_t* idx, const FIN& fin, hipStream_t st) {
   // The fewest registers that hold the prefix.
   // With many heads in the launch, small workgroups of which several share a compute unit: while one
   // waits at a barrier or for its scores, another one works.
   const int most = L - keep + (pool == 1 ? row_shift(scores, L) : 0);
-  auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, NoFinish{}, st); };
+  auto at = [&](auto launch) { return launch(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, fin, st); };
   if (pool == 1) {
-    if ((long long)Hkv * n_inst >= SEL_MANY_WORKGROUPS) {
-      if (most <= 256 * 8) return at(launch_one<256, 8, true, TAB, NoFinish>);
-      if (most <= 256 * 32) return at(launch_one<256, 32, true, TAB, NoFinish>);
-      if (most <= 512 * 64) return at(launch_one<512, 64, true, TAB, NoFinish>);
+    if ((long long)Hkv * n_inst >= SELECT_MANY_HEADS) {
+      if (most <= 256 * 8) return at(launch_one<256, 8, true, TAB, FIN>);
+      if (most <= 256 * 32) return at(launch_one<256, 32, true, TAB, FIN>);
+      if constexpr (std::is_same<FIN, NoFinish>::value)
+        if (most <= 512 * 64) return at(launch_one<512, 64, true, TAB, FIN>);
     }
-    if (most <= 1024 * 4) return at(launch_one<1024, 4, true, TAB, NoFinish>);
-    if (most <= 1024 * 8) return at(launch_one<1024, 8, true, TAB, NoFinish>);
-    if (most <= 1024 * 16) return at(launch_one<1024, 16, true, TAB, NoFinish>);
-    if (most <= 1024 * 32) return at(launch_one<1024, 32, true, TAB, NoFinish>);
-    return at(launch_one<1024, 0, false, TAB, NoFinish>);
+    if (most <= 1024 * 4) return at(launch_one<1024, 4, true, TAB, FIN>);
+    if (most <= 1024 * 8) return at(launch_one<1024, 8, true, TAB, FIN>);
+    if (most <= 1024 * 16) return at(launch_one<1024, 16, true, TAB, FIN>);
+    if (most <= 1024 * 32) return at(launch_one<1024, 32, true, TAB, FIN>);
   }
-  if (most <= 1024 * 2) return at(launch_one<1024, 2, false, TAB, NoFinish>);
-  if (most <= 1024 * 8) return at(launch_one<1024, 8, false, TAB, NoFinish>);
-  if (most <= 1024 * 32) return at(launch_one<1024, 32, false, TAB, NoFinish>);
-  return at(launch_one<1024, 0, false, TAB, NoFinish>);
+  if constexpr (std::is_same<FIN, NoFinish>::value) {
+    if (pool == 1) return at(launch_one<1024, 0, false, TAB, FIN>);
+    if (most <= 1024 * 2) return at(launch_one<1024, 2, false, TAB, FIN>);
+    if (most <= 1024 * 8) return at(launch_one<1024, 8, false, TAB, FIN>);
+    if (most <= 1024 * 32) return at(launch_one<1024, 32, false, TAB, FIN>);
+    return at(launch_one<1024, 0, false, TAB, FIN>);
+  }
+  return hipErrorInvalidValue;             // (the callers pool longer prefixes before)
 }
+static_assert(SELECT_POOL_MAX_KEYS == 1024 * 32 && SELECT_POOL_MAX_HALF == POOL_QUAD_MAX_HALF, "");
 
 template <typename TAB>
 hipError_t finish_for(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const TAB& tab, int32_t* idx,
@@ -478,11 +524,19 @@ hipError_t launch_sink_recent(int n_inst, int Hkv, int L, int n_sink, const Inst
 
 hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
                          const InstTable& tab, int32_t* idx, hipStream_t st) {
-  return launch_for(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st);
+  return launch_for(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, NoFinish{}, st);
 }
 hipError_t launch_select(int n_inst, int inst0, int Hkv, int L, int keep, int pool, bool avg, const float* scores,
                          const UniformInst& tab, int32_t* idx, hipStream_t st) {
-  return launch_for(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, st);
+  return launch_for(n_inst, inst0, Hkv, L, keep, pool, avg, scores, tab, idx, NoFinish{}, st);
+}
+hipError_t launch_select_pooling(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const InstTable& tab, int32_t* idx,
+                                 const PoolArgs& pool, hipStream_t st) {
+  return launch_for(n_inst, inst0, Hkv, L, keep, 1, false, raw, tab, idx, pool, st);
+}
+hipError_t launch_select_pooling(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const UniformInst& tab, int32_t* idx,
+                                 const PoolArgs& pool, hipStream_t st) {
+  return launch_for(n_inst, inst0, Hkv, L, keep, 1, false, raw, tab, idx, pool, st);
 }
 hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const InstTable& tab, int32_t* idx,
                          const FinishArgs& fin, hipStream_t st) {

@@ -1,0 +1,116 @@
+"""The scoring kernels that walk a segment of keys without a barrier, and the pooling in the selection kernel, at the
+edges of their variants, against the oracle and the separate launches (needs an MI355X)."""
+import pytest
+import torch
+
+import oracle
+from parity_util import check_scores
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+F32, BF16 = torch.float32, torch.bfloat16
+
+# (dtype, n, Hq, Hkv, d, L, W): tiles of 32 keys and blocks of 128 with remainders, waves without a tile, segments of one and
+# several blocks (their statistics folded by the second kernel, or by a launch in between: more than 32), row tiles up to
+# the four that are staged together and beyond, head sizes with half and missing pieces.  fp32 and the head sizes other than 64
+# and 128 take these kernels from 129 and 65 chunks of 256 keys on.
+CASES = [
+    (BF16, 1, 2, 1, 128, 31, 3), (BF16, 1, 2, 1, 128, 33, 16), (BF16, 2, 4, 2, 64, 127, 17), (BF16, 1, 8, 2, 128, 129, 32),
+    (BF16, 1, 8, 1, 64, 1025, 33), (BF16, 1, 8, 1, 128, 8200, 16), (BF16, 1, 2, 1, 128, 20011, 8), (BF16, 130, 2, 1, 64, 160, 16),
+    (BF16, 17, 12, 4, 96, 257, 33), (BF16, 17, 12, 4, 256, 300, 33), (BF16, 17, 8, 4, 40, 260, 50), (BF16, 17, 8, 4, 200, 511, 50),
+    (F32, 65, 4, 2, 64, 65, 8), (F32, 33, 8, 4, 96, 130, 33), (F32, 33, 8, 4, 128, 97, 24), (F32, 43, 3, 3, 8, 140, 33),
+    (F32, 33, 8, 4, 104, 129, 12), (F32, 1, 2, 1, 128, 33000, 20), (F32, 1, 3, 1, 128, 33100, 70),
+]
+
+
+@pytest.mark.parametrize("dtype,n,Hq,Hkv,d,L,W", CASES)
+def test_scores_against_the_oracle(dtype, n, Hq, Hkv, d, L, W):
+    import paper_2505_20334_amd as laq
+    print("case:", dtype, n, Hq, Hkv, d, L, W, flush=True)
+    g = torch.Generator().manual_seed(L + d)
+    q = (1.5 * torch.randn(n, Hq, W, d, generator=g)).to(dtype)
+    k = torch.randn(n, Hkv, L, d, generator=g).to(dtype)
+    for pos, keep in ((None, None), ([(37 * w) % L if w % 3 else L + w for w in range(W)], 0)):
+        if pos is None and W > L:
+            continue
+        got = laq.laq_score(q.to(DEV), k.to(DEV), 1, q_pos=pos, keep=keep, choose="two-pass").cpu()
+        # rows of a wider cache: the same bits
+        wide = torch.zeros(n, Hkv, L, d + 16, dtype=dtype, device=DEV)
+        wide[..., :d] = k.to(DEV)
+        again = laq.laq_score(q.to(DEV), wide[..., :d], 1, q_pos=pos, keep=keep, choose="two-pass").cpu()
+        assert torch.equal(got, again)
+        for i in sorted({0, n // 2, n - 1}):
+            want, _, _, _ = oracle.evict(q[i], k[i], k[i], max(1, W if keep is None else keep), 1, q_pos=pos, keep=keep)
+            check_scores(got[i], want, dtype, "instance %d" % i)
+
+
+@pytest.mark.parametrize("d", [64, 104, 128])
+def test_fp32_infinities_and_nans_are_those_of_whole_products(d):
+    """A float is taken apart into three for the products; an infinity leaves NaNs, and the tile is scored from whole
+    floats instead.  A key whose logits are all -inf gets the score 0 and leaves the others alone; one whose logits are +inf, or
+    that holds a NaN, makes the scores of its head NaN, and only those."""
+    import paper_2505_20334_amd as laq
+    L, W = 33200, 4                          # 130 chunks
+    g = torch.Generator().manual_seed(d)
+    q, k = torch.randn(1, 2, W, d, generator=g).abs(), torch.randn(1, 1, L, d, generator=g)
+    pos = [L + w for w in range(W)]
+    k[0, 0, 777, 3] = -float("inf")
+    got = laq.laq_score(q.to(DEV), k.to(DEV), 1, q_pos=pos, keep=0).cpu()
+    k[0, 0, 777] = k[0, 0, 778]
+    other = torch.cat([k[:, :, :777], k[:, :, 778:]], 2)
+    want, _, _, _ = oracle.evict(q[0], other[0], other[0], 64, 1, q_pos=[p - 1 for p in pos], keep=0)
+    assert got[0, 0, 777] == 0
+    check_scores(torch.cat([got[0, :, :777], got[0, :, 778:]], 1), want, F32, "scores")
+    for bad in (float("inf"), float("nan")):
+        two = torch.cat([k, torch.randn(1, 1, L, d, generator=g)])
+        two[0, 0, L - 1, 0] = bad
+        got = laq.laq_score(torch.cat([q, q]).to(DEV), two.to(DEV), 1, q_pos=pos, keep=0).cpu()
+        assert got[0].isnan().all() and not got[1].isnan().any()
+
+
+def test_fp32_products_of_parts_are_no_further_from_64_bits():
+    """Logits of a standard deviation of 4, 2-norm of the error of the scores over 130 heads x 250 keys, 64 score rows: an
+    fp32 sum of 128 products q k rounded to 2^-24 of the running sum at every one is off by about 2^-24 * sqrt(128 / 3) of a
+    logit's deviation, 1.6e-6 of an exponent, and the fp32 instruction measured 7 to 13e-7; the left-out products are 2^-24 of
+    the whole ones.  A product of parts more left out (2^-16) would show as 6e-5."""
+    import paper_2505_20334_amd as laq
+    g = torch.Generator().manual_seed(5)
+    n, W, L, d = 130, 16, 250, 128
+    q, k = 4.0 * torch.randn(n, 4, W, d, generator=g), torch.randn(n, 1, L, d, generator=g)
+    got = laq.laq_score(q.to(DEV), k.to(DEV), 1, q_pos=[L + w for w in range(W)], keep=0).cpu().double()
+    s = q.double().reshape(n, 4 * W, d) @ k[:, 0].double().transpose(1, 2) / d ** 0.5
+    want = torch.softmax(s, -1).sum(1).unsqueeze(1)
+    assert ((got - want).norm() / want.norm()).item() < 7e-7
+
+
+# (n, Hkv, L, keep): prefixes around the sizes at which a variant of the selection kernel ends, rows of any alignment
+@pytest.mark.parametrize("n,Hkv,L,keep", [(1, 3, 300, 5), (3, 3, 4093, 0), (2, 3, 8193, 3), (2, 3, 16385, 8), (1, 3, 32767, 2), (1, 2, 32768, 0),
+                                          (1, 2, 32777, 1), (400, 2, 2046, 4), (400, 2, 2501, 9), (400, 2, 8199, 4)])
+def test_pooling_and_selection_in_one_launch_are_those_of_two(n, Hkv, L, keep):
+    """laq_evict pools raw scores where it selects; laq_score pools them in a launch of its own, laq_select takes those: the
+    same bits, for every width and both kinds."""
+    import paper_2505_20334_amd as laq
+    g = torch.Generator(device=DEV).manual_seed(L)
+    q = torch.randn(n, 2 * Hkv, 5, 64, generator=g, device=DEV).bfloat16()
+    k, v = (torch.randn(n, Hkv, L, 64, generator=g, device=DEV).bfloat16() for _ in range(2))
+    pos = [L + w for w in range(5)]
+    budgets = [min(L, 40 + keep + 300 * (i % 3)) for i in range(n)]
+    for pool, mode in ((3, "max"), (5, "avg"), (7, "max"), (9, "avg"), (11, "max"), (13, "avg"), (15, "max"), (17, "avg"), (17, "max"), (19, "max")):
+        raw = laq.laq_score(q, k, 1, q_pos=pos, keep=keep)
+        pooled = laq.laq_score(q, k, pool, q_pos=pos, keep=keep, pool_mode=mode)
+        scores, idx, ko, vo = laq.laq_evict(q, k, v, budgets, pool, q_pos=pos, keep=keep, pool_mode=mode)
+        assert torch.equal(scores, pooled)
+        P, half = L - keep, pool // 2
+        win = torch.nn.functional.pad(raw[..., :P].cpu(), (half, half)).unfold(-1, pool, 1)
+        if mode == "max":
+            want = win.amax(-1)
+        else:
+            want = torch.zeros_like(win[..., 0])
+            for o in range(pool):
+                want = want + win[..., o]
+            want = want / torch.full((1,), float(pool))    # (a tensor: by a number torch may multiply with the reciprocal)
+        assert torch.equal(pooled[..., :P].cpu(), want) and torch.equal(pooled[..., P:], raw[..., P:])
+        assert torch.equal(idx, laq.laq_select(pooled, budgets, 1, keep))
+        for a, b in zip((ko, vo), laq.laq_compact(k, v, idx, budgets, keep)):
+            assert torch.equal(a, b)
