@@ -193,7 +193,7 @@ static int init_current_device(int* dev_out) {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return LAQ_ERR_DEVICE;
   if (dev_out) *dev_out = dev;
   if (scratch_of[dev].load(std::memory_order_acquire)) return LAQ_OK;
-  if (score_fused_init(dev) != hipSuccess || score_tile_init() != hipSuccess || score_wave_init() != hipSuccess) return LAQ_ERR_DEVICE;
+  if (score_fused_init(dev) != hipSuccess || score_tile_init() != hipSuccess || score_wave_init() != hipSuccess || head_init() != hipSuccess) return LAQ_ERR_DEVICE;
   void* ptr = nullptr;
   if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return LAQ_ERR_DEVICE;
   scratch_of[dev].store(ptr, std::memory_order_release);
@@ -220,8 +220,12 @@ static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g) {
   return g.Rpad <= 64 && key_bytes >= (128LL << 20);
 }
 
-// Which kernels score a call.  The single-read kernel pools (maximum) where it scores, the others leave raw scores.
-enum class ScorePath { single_read, tile, wave };
+// Heads of a call from which on their gather is spread over enough compute units with a workgroup each.
+constexpr int HEAD_MANY = 72;
+
+// Which kernels score a call.  The single-read kernel pools (maximum) where it scores; the one-workgroup kernel pools, selects and gathers
+// too; the others leave raw scores.
+enum class ScorePath { single_read, head, tile, wave };
 
 // The kernels that give every 256-key chunk a workgroup of its own, where they are the faster ones.  They work on up to four row tiles of a
 // chunk side by side where chunks are few, and hold all of a chunk's keys at once; the others have their score rows in LDS
@@ -244,7 +248,23 @@ static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
   return tiles > 2 && chunks <= 64;
 }
 
+// A workgroup for each head, with all its keys in registers.  Against the launches of the other kernels (laq_evict, us, the others : this one):
+//   up to 512 keys always: bf16, d = 128, 24 heads 20.3 : 10.1 (d = 64), 64 heads 21.1 : 16.3, 576 heads 47.3 : 25.8, 2000 heads, 128 rows 314 : 226,
+//   6016 heads 392 : 285; fp32, d = 64, 192 heads 30.2 : 24.9; but fp32 of more than 64 elements in few heads 6 heads 32.7 : 39.7, 16 heads 33.6 : 35.1,
+//   80 heads 39.2 : 35.3; and many score rows in few 13 heads, 256 rows 42.2 : 53.4
+//   up to 1024 keys (two tiles per wave, one workgroup per compute unit): 72 heads 32.5 : 28.7, 160 heads 33.8 : 25.3, 216 heads 45.0 : 28.9, 600 heads
+//   81.9 : 63.6; 992 heads 56.9 : 63.9, 1488 heads 111.9 : 121.3, 6912 heads 464 : 568; few heads, one or two row tiles 24 heads x 560 keys 20.1 : 13.3,
+//   16 x 768 22.2 : 19.7, 16 x 1024 24.4 : 27.2, 56 x 1024 23.9 : 25.6; more row tiles 64 x 714 32.7 : 34.5, 8 x 1024 26.0 : 32.1
+static bool head_wanted(const laq_shape* shape, const ScoreGeom& g) {
+  if (shape->score_choice != LAQ_CHOOSE_AUTO || !head_supported(g, shape->dtype)) return false;
+  const long long heads = (long long)g.n_inst * g.Hkv;
+  if (shape->dtype == LAQ_F32 && ((g.d > 64 && heads <= 16) || (g.Rpad > 128 && heads < HEAD_MANY))) return false;
+  if (g.L <= 512) return true;
+  return heads >= HEAD_MANY ? heads <= 768 : g.L <= 768 && g.Rpad <= 64;
+}
+
 static ScorePath score_path(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay) {
+  if (head_wanted(shape, g)) return ScorePath::head;
   if (SINGLE_READ_ENABLED && usual_shape(g, lay, shape->dtype) && score_fused_supported(g, lay, shape->dtype) && single_read_wanted(shape, g))
     return ScorePath::single_read;
   return tile_wanted(shape, g) ? ScorePath::tile : ScorePath::wave;
@@ -253,7 +273,7 @@ static ScorePath score_path(const laq_shape* shape, const ScoreGeom& g, const Kv
 // Whether scores that are to be pooled come raw from the kernels that make them.
 static bool leaves_raw(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay) {
   const ScorePath path = score_path(shape, g, lay);
-  return path != ScorePath::single_read || pool_avg(shape);
+  return path == ScorePath::tile || path == ScorePath::wave || (path == ScorePath::single_read && pool_avg(shape));
 }
 
 // Scores of a validated call into `scores`: pooled, or, with pool == 1, raw.
@@ -276,6 +296,17 @@ static int score_checked(const laq_shape* shape, const ScoreGeom& g, const Query
     if (e != hipSuccess || done) return e == hipSuccess ? LAQ_OK : LAQ_ERR_DEVICE;
     // (a team of its workgroups does not fit this device: the two passes)
   }
+  if (path == ScorePath::head) {
+    const bool apart = (pool - 1) / 2 > SELECT_POOL_MAX_HALF;
+    FinishArgs fin;
+    memset(&fin, 0, sizeof fin);
+    fin.pooled = apart ? w.raw : scores;
+    fin.half = apart ? 0 : (pool - 1) / 2;
+    fin.avg = pool_avg(shape) ? 1 : 0;
+    e = launch_head(g, qp, lay, shape->dtype, false, q_win, k, g.n_inst, 0, UniformInst{1, 0, 0}, nullptr, fin, w.status, st);
+    if (e == hipSuccess && apart) e = launch_pool(g, pool, pool_avg(shape), w.raw, scores, st);
+    return e == hipSuccess ? LAQ_OK : LAQ_ERR_DEVICE;
+  }
   float* raw = pool > 1 ? w.raw : scores;
   e = path == ScorePath::tile ? launch_score_tile(g, qp, lay, shape->dtype, q_win, k, raw, w, st)
                               : launch_score_wave(g, qp, lay, shape->dtype, q_win, k, raw, w, st);
@@ -296,20 +327,12 @@ static int score_impl(const laq_shape* shape, const void* q_win, const void* k, 
   return score_checked(shape, g, qp, lay, q_win, k, pool, scores, ws, st);
 }
 
-static int select_impl(const laq_shape* shape, const float* scores, const int32_t* budget, int pool,
-                       int32_t* idx, hipStream_t st, const PoolArgs* pooling = nullptr) {
-  ScoreGeom g;
-  const int rc = make_geom(shape, &g);
-  if (rc != LAQ_OK) return rc;
-  if (!pool_ok(pool) || !scores || !idx || !budgets_ok(shape, g, budget)) return LAQ_ERR_INVALID;
-  if (g.Hkv > 65535) return LAQ_ERR_UNSUPPORTED;
-  auto launch = [&](int n, int i0, const auto& tab) {
-    return pooling ? launch_select_pooling(n, i0, g.Hkv, g.L, g.keep, scores, tab, idx, *pooling, st)
-                   : launch_select(n, i0, g.Hkv, g.L, g.keep, pool, pool_avg(shape), scores, tab, idx, st);
-  };
+// launch(n, i0, table) for runs of at most MAX_INST_PER_LAUNCH instances
+template <typename LAUNCH>
+static int for_instances(const ScoreGeom& g, const int32_t* budget, LAUNCH launch) {
   int64_t row = 0;
-  for (int i0 = 0; i0 < shape->n_inst; i0 += MAX_INST_PER_LAUNCH) {
-    const int n = shape->n_inst - i0 < MAX_INST_PER_LAUNCH ? shape->n_inst - i0 : MAX_INST_PER_LAUNCH;
+  for (int i0 = 0; i0 < g.n_inst; i0 += MAX_INST_PER_LAUNCH) {
+    const int n = g.n_inst - i0 < MAX_INST_PER_LAUNCH ? g.n_inst - i0 : MAX_INST_PER_LAUNCH;
     hipError_t e;
     if (const int bk = uniform_rows(g.L, budget, i0, n)) {
       const UniformInst u{bk, row, (int64_t)g.Hkv * bk};
@@ -323,6 +346,20 @@ static int select_impl(const laq_shape* shape, const float* scores, const int32_
     if (e != hipSuccess) return LAQ_ERR_DEVICE;
   }
   return LAQ_OK;
+}
+
+static int select_impl(const laq_shape* shape, const float* scores, const int32_t* budget, int pool,
+                       int32_t* idx, hipStream_t st, const PoolArgs* pooling = nullptr) {
+  ScoreGeom g;
+  const int rc = make_geom(shape, &g);
+  if (rc != LAQ_OK) return rc;
+  if (!pool_ok(pool) || !scores || !idx || !budgets_ok(shape, g, budget)) return LAQ_ERR_INVALID;
+  if (g.Hkv > 65535) return LAQ_ERR_UNSUPPORTED;
+  auto launch = [&](int n, int i0, const auto& tab) {
+    return pooling ? launch_select_pooling(n, i0, g.Hkv, g.L, g.keep, scores, tab, idx, *pooling, st)
+                   : launch_select(n, i0, g.Hkv, g.L, g.keep, pool, pool_avg(shape), scores, tab, idx, st);
+  };
+  return for_instances(g, budget, launch);
 }
 
 static int compact_impl(const laq_shape* shape, const void* k, const void* v, const int32_t* idx,
@@ -433,30 +470,47 @@ static bool select_pools(const laq_shape* shape, const ScoreGeom& g, const KvLay
          (keys <= SELECT_POOL_MANY_KEYS || (long long)g.n_inst * g.Hkv < SELECT_MANY_HEADS) && leaves_raw(shape, g, lay);
 }
 
-// Pooling, selection and gather of a small call, from the raw scores.
-static int finish_checked(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const void* k, const void* v,
-                          const int32_t* budget, int pool, const float* raw, float* scores, int32_t* idx, void* k_out, void* v_out,
-                          hipStream_t st) {
+static FinishArgs finish_args(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const void* k, const void* v, int pool, float* scores,
+                              void* k_out, void* v_out) {
   const int eb = shape->dtype == LAQ_F32 ? 4 : 2;
   FinishArgs fin;
   fin.pooled = scores;
+  fin.half = (pool - 1) / 2; fin.avg = pool_avg(shape) ? 1 : 0;
   fin.k = static_cast<const char*>(k); fin.v = static_cast<const char*>(v);
   fin.k_out = static_cast<char*>(k_out); fin.v_out = static_cast<char*>(v_out);
   fin.inst_bytes = lay.inst * eb; fin.head_bytes = lay.head * eb;
   fin.row_bytes = g.d * eb; fin.src_row_bytes = lay.row_bytes; fin.elem_bytes = eb;
-  fin.half = (pool - 1) / 2; fin.avg = pool_avg(shape) ? 1 : 0;
   fin.lay = lay;
-  hipError_t e;
-  const int n = shape->n_inst;
-  if (const int bk = uniform_rows(g.L, budget, 0, n)) {
-    e = launch_finish(n, 0, g.Hkv, g.L, g.keep, raw, UniformInst{bk, 0, (int64_t)g.Hkv * bk}, idx, fin, st);
-  } else {
-    InstTable tab;
-    int64_t row = 0;
-    fill_table(g.Hkv, g.L, budget, 0, n, 0, &tab, &row);
-    e = launch_finish(n, 0, g.Hkv, g.L, g.keep, raw, tab, idx, fin, st);
-  }
-  return e == hipSuccess ? LAQ_OK : LAQ_ERR_DEVICE;
+  return fin;
+}
+
+// Pooling, selection and gather of a small call, from the raw scores.
+static int finish_checked(const ScoreGeom& g, const FinishArgs& fin, const int32_t* budget, const float* raw, int32_t* idx, hipStream_t st) {
+  return for_instances(g, budget, [&](int n, int i0, const auto& tab) { return launch_finish(n, i0, g.Hkv, g.L, g.keep, raw, tab, idx, fin, st); });
+}
+
+// Whether the kernel that scores short heads selects and gathers too: one workgroup copies a head's rows, which takes longer than a
+// launch that spreads them where heads are few and rows many (8 heads x 1017 keys, 688 rows kept 26.3 us, 20.3 with the old launches).
+static bool head_gathers(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, int row_bytes) {
+  if ((pool - 1) / 2 > SELECT_POOL_MAX_HALF) return false;
+  if (g.L <= 512 || (long long)g.n_inst * g.Hkv >= HEAD_MANY) return true;
+  int most = 0;
+  for (int i = 0; i < shape->n_inst; ++i) most = budget[i] > most ? budget[i] : most;
+  return (long long)(most < g.L ? most : g.L) * row_bytes <= 128 << 10;
+}
+
+// All of a call of short heads.
+static int head_checked(const laq_shape* shape, const ScoreGeom& g, const QueryPos& positions, const KvLayout& lay, const FinishArgs& fin,
+                        const void* q_win, const void* k, const int32_t* budget, int32_t* idx, void* ws, hipStream_t st) {
+  if (g.Hkv > 65535 || g.n_inst > 65535 || (long long)g.Hkv * g.n_inst > 0x7fffffffLL) return LAQ_ERR_UNSUPPORTED;
+  const int rc_init = init_current_device(nullptr);
+  if (rc_init != LAQ_OK) return rc_init;
+  const Workspace w = carve_workspace(g, ws);
+  WindowPos qp;
+  if (window_positions(g, positions, w, st, &qp) != hipSuccess) return LAQ_ERR_DEVICE;
+  return for_instances(g, budget, [&](int n, int i0, const auto& tab) {
+    return launch_head(g, qp, lay, shape->dtype, true, q_win, k, n, i0, tab, idx, fin, w.status, st);
+  });
 }
 
 static int qcache_store_impl(const laq_shape* shape, const void* q_step, int t, void* q_cache, hipStream_t st) {
@@ -575,10 +629,13 @@ static int evict_impl(const laq_shape* shape, const void* q_win, const void* k, 
   if (!scores) scores = w.pooled;        // the hand-over plane between the stages
   const int row_bytes = g.d * (shape->dtype == LAQ_F32 ? 4 : 2);
   float* raw = pool_kernel > 1 ? w.raw : scores;
-  if (laq::finish_wanted(shape, g, budget, pool_kernel, raw, row_bytes)) {
+  const laq::ScorePath path = laq::score_path(shape, g, lay);
+  if (path == laq::ScorePath::head && laq::head_gathers(shape, g, budget, pool_kernel, row_bytes))
+    return laq::head_checked(shape, g, qp, lay, laq::finish_args(shape, g, lay, k, v, pool_kernel, scores, k_out, v_out), q_win, k, budget, idx, ws, st);
+  if (path != laq::ScorePath::head && laq::finish_wanted(shape, g, budget, pool_kernel, raw, row_bytes)) {
     const int rc = laq::score_checked(shape, g, qp, lay, q_win, k, 1, raw, ws, st);
     if (rc != LAQ_OK) return rc;
-    return laq::finish_checked(shape, g, lay, k, v, budget, pool_kernel, raw, scores, idx, k_out, v_out, st);
+    return laq::finish_checked(g, laq::finish_args(shape, g, lay, k, v, pool_kernel, scores, k_out, v_out), budget, raw, idx, st);
   }
   int rc;
   if (laq::select_pools(shape, g, lay, pool_kernel, raw)) {

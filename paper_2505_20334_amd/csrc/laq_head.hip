@@ -1,0 +1,387 @@
+// A whole head in one workgroup: scores, pooling, selection and gather of a short cache in one launch.
+//
+// A workgroup of 4, 8 or 16 waves holds all keys of one KV head in registers (operand layout, up to two tiles of 32
+// per wave), K is read once, and nothing leaves the workgroup between the steps:
+//   (m, z) of every score row per wave -> LDS -> c = M + log2 Z -> products again, sum of exp2(s - c) over the rows ->
+//   raw scores in LDS -> one position per thread: pooled, ranked (counted in bins), listed -> gather.
+// What bounds it: the latency of one workgroup -- two trips to memory (keys; the rows of V) and a dozen barriers.
+#include <algorithm>
+#include <type_traits>
+
+#include "laq_internal.h"
+#include "laq_products.h"
+#include "laq_rank.h"
+
+namespace laq {
+
+namespace {
+
+constexpr int MAX_TILES = 4;                 // 32-row tiles of score rows that are staged together
+constexpr int MAX_ROWS = 256;                // score rows of a head
+constexpr int MARGIN = SELECT_POOL_MAX_HALF;
+
+struct HeadPlan {
+  int group_tiles, groups;   // row tiles staged together
+  int off_stat;              // bytes of the staged rows
+};
+
+// the product of 32 keys held as they lie in memory
+template <typename T, int NP, bool FULL, bool KEYS_AS_ROWS>
+__device__ __forceinline__ f32x16 product_raw(u32x4 (&key)[NP], const char* lds, int plane, int steps) {
+  f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if constexpr (is_f32(T())) {
+#pragma unroll
+    for (int u = 0; u < (NP + 1) / 2; ++u) {
+      if (FULL || u < steps) {
+        const u32x4 none = {0u, 0u, 0u, 0u};
+        // (taken apart here, for every product: the registers do not hold the parts)
+        asm volatile("" : "+v"(key[2 * u]));
+        if (2 * u + 1 < NP) asm volatile("" : "+v"(key[2 * u + 1 < NP ? 2 * u + 1 : 0]));
+        const Split s = split8(key[2 * u], 2 * u + 1 < NP ? key[2 * u + 1 < NP ? 2 * u + 1 : 0] : none);
+        const u32x4 q0 = *reinterpret_cast<const u32x4*>(lds + u * 32);
+        acc = mm<KEYS_AS_ROWS>(s.p[2], q0, acc);
+        const u32x4 q2 = *reinterpret_cast<const u32x4*>(lds + 2 * plane + u * 32);
+        acc = mm<KEYS_AS_ROWS>(s.p[0], q2, acc);
+        const u32x4 q1 = *reinterpret_cast<const u32x4*>(lds + plane + u * 32);
+        acc = mm<KEYS_AS_ROWS>(s.p[1], q1, acc);
+        acc = mm<KEYS_AS_ROWS>(s.p[0], q1, acc);
+        acc = mm<KEYS_AS_ROWS>(s.p[1], q0, acc);
+        acc = mm<KEYS_AS_ROWS>(s.p[0], q0, acc);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      if (FULL || u < steps) acc = mm<KEYS_AS_ROWS>(key[u], *reinterpret_cast<const u32x4*>(lds + u * 32), acc);
+      if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  return acc;
+}
+
+// `gather`: with selection and gather (laq_evict), else scores only.  fin.half: pooling of the scores, 0 for none.
+template <typename T, int NP, bool FULL, int WAVES, int TPW, typename TAB>
+__global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 4) void head_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, HeadPlan pl, bool gather,
+                                                              const T* __restrict__ q, const T* __restrict__ k, TAB tab,
+                                                              int inst0, int32_t* __restrict__ idx, FinishArgs fin, int* __restrict__ status) {
+  constexpr int THREADS = WAVES * 64;
+  extern __shared__ __align__(16) char smem[];
+  __shared__ __align__(16) float rowc[MAX_ROWS];
+  __shared__ __align__(16) int last[MAX_ROWS];           // last key the rows see
+  __shared__ float raw[MARGIN + THREADS + MARGIN];       // raw scores of the prefix, zeros around them
+  __shared__ int list[THREADS];
+  __shared__ RankScratch<WAVES> rank;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, n32 = lane & 31;
+  const int head = blockIdx.x, li = blockIdx.y, inst = inst0 + li;
+  const size_t hg = (size_t)inst * g.Hkv + head;
+  if (head == 0 && inst == 0 && tid == 0) *status = 0;   // (no wait to give up here)
+  const int row_bytes = FULL ? NP * 32 : g.d * (int)sizeof(T);
+  const int plane = plane_bytes(row_bytes / (int)sizeof(T)), stride = row_stride<T>(row_bytes / (int)sizeof(T));
+  const char* head_rows = reinterpret_cast<const char*>(q + hg * g.R * g.d);
+  auto key_row = [&](int key0) {
+    int r0 = key0;
+    const char* p = reinterpret_cast<const char*>(k + (lay.table ? 0 : (int64_t)inst * lay.inst) + (int64_t)head * lay.head);
+    if (lay.table) p += paged_block_offset(lay, inst, key0, &r0) * (int64_t)sizeof(T);
+    return p + (int64_t)(r0 + min(n32, g.L - 1 - key0)) * lay.row_bytes;     // (keys beyond the last one are masked: any row will do)
+  };
+  const int tiles = g.Rpad / 32;
+  float2* stat = reinterpret_cast<float2*>(smem + pl.off_stat);            // [row tile][wave][row]
+  u32x4 key[TPW][NP];
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) {
+    const int key0 = (i * WAVES + wave) * 32;
+    if (key0 < g.L) {
+      const char* p = key_row(key0) + hf * 16;
+#pragma unroll
+      for (int t = 0; t < NP; ++t) {
+        if (!FULL) key[i][t] = u32x4{0u, 0u, 0u, 0u};
+        if (FULL || (2 * t + hf) * 16 < row_bytes) key[i][t] = *reinterpret_cast<const u32x4*>(p + t * 32);
+      }
+    }
+  }
+  for (int r = tid; r < tiles * 32; r += THREADS) last[r] = last_visible_key(g, qp, min(r, g.R - 1) % g.W);
+  for (int i = tid; i < THREADS + 2 * MARGIN; i += THREADS) raw[i] = 0.f;
+  rank.bins[tid] = 0;
+  stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, 0, min(pl.group_tiles, tiles) * 32);
+  __syncthreads();
+  const char* rows = smem + n32 * stride + hf * 16;
+  // ---- statistics ----
+#pragma unroll 1
+  for (int rt0 = 0; rt0 < tiles; rt0 += pl.group_tiles) {
+    const int ntile = min(pl.group_tiles, tiles - rt0);
+    if (rt0 > 0) {
+      __syncthreads();
+      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32);
+      __syncthreads();
+    }
+#pragma unroll 1
+    for (int rt = 0; rt < ntile; ++rt) {
+      float M = NEG_BIG, Z = 0.f;
+#pragma unroll
+      for (int i = 0; i < TPW; ++i) {
+        const int key0 = (i * WAVES + wave) * 32;
+        if (key0 >= g.L) continue;
+        float m, z;
+        f32x16 s = product_raw<T, NP, FULL, true>(key[i], rows + rt * 32 * stride, plane, plane / 32);
+#pragma unroll 1
+        for (bool again = false;; again = true) {
+          if (key0 + 31 > g.qmin) {
+            const int seen = last[(rt0 + rt) * 32 + n32] - key0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              if (acc_row(e, hf) > seen) s[e] = -INFINITY;
+          }
+          m = s[0];
+#pragma unroll
+          for (int e = 1; e < 16; ++e) m = fmaxf(m, s[e]);
+          const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+          m = fmaxf(M, fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1])) * g.scale2);     // (the logit scale is positive)
+          z = 0.f;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) z += __builtin_amdgcn_exp2f(fmaf(s[e], g.scale2, -m));
+          const auto zh = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
+          z = __uint_as_float(zh[0]) + __uint_as_float(zh[1]);
+          if (!is_f32(T()) || again || __builtin_expect(!__any(z != z), 1)) break;
+          s = product_f32<true>(key_row(key0), head_rows + (size_t)min((rt0 + rt) * 32 + n32, g.R - 1) * row_bytes, hf, row_bytes);
+        }
+        Z = fmaf(Z, __builtin_amdgcn_exp2f(M - m), z);
+        M = m;
+      }
+      if (hf == 0) stat[((rt0 + rt) * WAVES + wave) * 32 + n32] = make_float2(M, Z);
+    }
+  }
+  __syncthreads();
+  for (int r = tid; r < tiles * 32; r += THREADS) {
+    const float2* s = stat + (r >> 5) * WAVES * 32 + (r & 31);
+    float M = NEG_BIG, Z = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) M = fmaxf(M, s[w * 32].x);
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) Z = fmaf(s[w * 32].y, __builtin_amdgcn_exp2f(s[w * 32].x - M), Z);
+    rowc[r] = r < g.R ? M + __builtin_amdgcn_logf(Z) : INFINITY;
+  }
+  __syncthreads();
+  // ---- raw scores ----
+  float sum[TPW];
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) sum[i] = 0.f;
+  auto masked = [&](f32x16 s, int row0, int key0) {
+    if (key0 + 31 > g.qmin) {
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        const i32x4 lv = *reinterpret_cast<const i32x4*>(last + row0 + 8 * gq + 4 * hf);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (key0 + n32 > lv[e]) s[4 * gq + e] = -INFINITY;
+      }
+    }
+    return s;
+  };
+#pragma unroll 1
+  for (int rt0 = 0; rt0 < tiles; rt0 += pl.group_tiles) {
+    const int ntile = min(pl.group_tiles, tiles - rt0);
+    if (pl.groups > 1) {
+      __syncthreads();
+      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32);
+      __syncthreads();
+    }
+#pragma unroll 1
+    for (int rt = 0; rt < ntile; ++rt) {
+#pragma unroll
+      for (int i = 0; i < TPW; ++i) {
+        const int key0 = (i * WAVES + wave) * 32;
+        if (key0 >= g.L) continue;
+        const f32x16 s = masked(product_raw<T, NP, FULL, false>(key[i], rows + rt * 32 * stride, plane, plane / 32), (rt0 + rt) * 32, key0);
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+          const f32x4 c = *reinterpret_cast<const f32x4*>(rowc + (rt0 + rt) * 32 + 8 * gq + 4 * hf);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[i] += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + e], g.scale2, -c[e]));
+        }
+      }
+    }
+  }
+  float* scores = fin.pooled + hg * g.L;
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) {
+    const int key0 = (i * WAVES + wave) * 32, j = key0 + n32;
+    if (key0 >= g.L) continue;
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[i]), __float_as_uint(sum[i]), false, false);
+    float both = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+    if (__builtin_expect(__any((both < TINY || (is_f32(T()) && both != both)) && j < g.L), 0)) {
+      // (score rows and keys from memory: the staged rows may be another group's)
+      float x_sum = 0.f;
+#pragma unroll 1
+      for (int rt = 0; rt < tiles; ++rt) {
+        const char *kr = key_row(key0), *qr = head_rows + (size_t)min(rt * 32 + n32, g.R - 1) * row_bytes;
+        f32x16 s;
+        if constexpr (is_f32(T())) {
+          s = product_f32<false>(kr, qr, hf, row_bytes);
+        } else {
+          s = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int o = hf * 16; o < row_bytes + hf * 16; o += 32) {
+            u32x4 x = {0u, 0u, 0u, 0u}, y = x;
+            if (o < row_bytes) {
+              x = *reinterpret_cast<const u32x4*>(kr + o);
+              y = *reinterpret_cast<const u32x4*>(qr + o);
+            }
+            s = mm<false>(x, y, s);
+          }
+        }
+        s = masked(s, rt * 32, key0);
+#pragma unroll 1
+        for (int e = 0; e < 16; ++e) {
+          const float x = fmaf(s[0], g.scale2, -rowc[rt * 32 + acc_row(e, hf)]);
+          x_sum += x < -126.f ? __builtin_amdgcn_exp2f(x + 64.f) * 0x1p-64f : __builtin_amdgcn_exp2f(x);
+          s = __builtin_shufflevector(s, s, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 0);
+        }
+      }
+      both = x_sum + __shfl_xor(x_sum, 32);
+    }
+    if (hf == 0 && j < g.L) {
+      if (j < g.P) raw[MARGIN + j] = both;
+      else scores[j] = both;
+    }
+  }
+  __syncthreads();
+  // ---- pooling: position tid ----
+  const int P = g.P, half = fin.half;
+  float v = raw[MARGIN + tid];
+  if (half > 0) {
+    const float* w = raw + MARGIN + tid;
+    if (fin.avg) {
+      float acc = 0.f;
+      for (int o = -half; o <= half; ++o) acc += w[o];
+      v = acc / (float)(2 * half + 1);
+    } else {
+      for (int o = -half; o <= half; ++o) v = fmaxf(v, w[o]);
+    }
+  }
+  if (tid < P) scores[tid] = v;
+  if (!gather) return;
+  // ---- selection ----
+  const int bk = tab.rows(li), ksel = bk - g.keep;
+  const int64_t row0 = tab.first(li) + (int64_t)head * bk;
+  int32_t* out = idx + row0;
+  for (int w = tid; w < g.keep; w += THREADS) {
+    list[ksel + w] = P + w;
+    out[ksel + w] = P + w;
+  }
+  if (ksel >= P) {
+    if (tid < P) {
+      list[tid] = tid;
+      out[tid] = tid;
+    }
+  } else if (ksel > 0) {
+    const int at = rank_position<WAVES>(rank, tid < P ? max(order_key(v), 1u) : 0u, ksel, lane, wave);
+    if (at >= 0) {
+      list[at] = tid;
+      out[at] = tid;
+    }
+  }
+  __syncthreads();
+  gather_rows<THREADS>(fin, inst, head, bk, row0, [&](int r) { return list[r]; });
+}
+
+template <typename T, int NP, bool FULL, int WAVES, int TPW, typename TAB>
+hipError_t launch_one(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, bool gather, const T* q, const T* k, int n, int inst0,
+                      const TAB& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
+  const int stride = row_stride<T>(g.d), tiles = g.Rpad / 32;
+  HeadPlan pl;
+  const int stat = tiles * WAVES * 32 * (int)sizeof(float2), most = ((WAVES == 16 ? 150 : 74) << 10) - stat - 12 * 1024;
+  pl.group_tiles = std::max(1, std::min(std::min(tiles, MAX_TILES), most / (32 * stride)));
+  pl.groups = (tiles + pl.group_tiles - 1) / pl.group_tiles;
+  pl.off_stat = pl.group_tiles * 32 * stride;
+  hipLaunchKernelGGL((head_kernel<T, NP, FULL, WAVES, TPW, TAB>), dim3(g.Hkv, n), dim3(WAVES * 64), pl.off_stat + stat, st, g, qp, lay, pl, gather, q, k,
+                     tab, inst0, idx, fin, status);
+  return hipGetLastError();
+}
+
+template <typename T, int NP, bool FULL, bool SHORT, typename TAB>
+hipError_t launch_for_keys(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, bool gather, const T* q, const T* k, int n, int inst0,
+                           const TAB& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
+  if (g.L <= 512) {
+    // one tile of keys per wave: the shortest way through one head; two per wave, half the waves: two heads per compute unit
+    if (SHORT || (long long)g.n_inst * g.Hkv <= 256)
+      return launch_one<T, NP, FULL, 16, 1, TAB>(g, qp, lay, gather, q, k, n, inst0, tab, idx, fin, status, st);
+    if constexpr (!SHORT) return launch_one<T, NP, FULL, 8, 2, TAB>(g, qp, lay, gather, q, k, n, inst0, tab, idx, fin, status, st);
+  }
+  if constexpr (!SHORT) return launch_one<T, NP, FULL, 16, 2, TAB>(g, qp, lay, gather, q, k, n, inst0, tab, idx, fin, status, st);
+  return hipErrorInvalidValue;
+}
+
+template <typename TAB>
+hipError_t launch_for(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, bool gather, const void* q, const void* k, int n, int inst0,
+                      const TAB& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
+  if (dtype == LAQ_F32) {
+    const float *qq = static_cast<const float*>(q), *kk = static_cast<const float*>(k);
+    if (g.d == 64) return launch_for_keys<float, 8, true, false>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+    if (g.d == 128) return launch_for_keys<float, 16, true, true>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+    return launch_for_keys<float, 16, false, true>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+  }
+  const uint16_t *qq = static_cast<const uint16_t*>(q), *kk = static_cast<const uint16_t*>(k);
+  if (g.d == 64) return launch_for_keys<uint16_t, 4, true, false>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+  if (g.d == 128) return launch_for_keys<uint16_t, 8, true, false>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+  if (g.d < 128) return launch_for_keys<uint16_t, 8, false, false>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+  if (g.d == 256) return launch_for_keys<uint16_t, 16, true, true>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+  return launch_for_keys<uint16_t, 16, false, true>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+}
+
+}  // namespace
+
+bool head_supported(const ScoreGeom& g, int dtype) {
+  const bool two_tiles = dtype == LAQ_F32 ? g.d == 64 : g.d <= 128;      // that a wave has registers for
+  return g.R <= MAX_ROWS && g.d <= (dtype == LAQ_F32 ? 128 : 256) && g.L <= (two_tiles ? 1024 : 512);
+}
+
+hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, bool gather, const void* q, const void* k, int n, int inst0,
+                       const InstTable& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
+  return launch_for(g, qp, lay, dtype, gather, q, k, n, inst0, tab, idx, fin, status, st);
+}
+hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, bool gather, const void* q, const void* k, int n, int inst0,
+                       const UniformInst& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
+  return launch_for(g, qp, lay, dtype, gather, q, k, n, inst0, tab, idx, fin, status, st);
+}
+
+hipError_t head_init() {
+  hipError_t e;
+  for (const void* f : {
+           (const void*)&head_kernel<float, 8, true, 16, 1, InstTable>,
+           (const void*)&head_kernel<float, 8, true, 16, 1, UniformInst>,
+           (const void*)&head_kernel<float, 8, true, 8, 2, InstTable>,
+           (const void*)&head_kernel<float, 8, true, 8, 2, UniformInst>,
+           (const void*)&head_kernel<float, 8, true, 16, 2, InstTable>,
+           (const void*)&head_kernel<float, 8, true, 16, 2, UniformInst>,
+           (const void*)&head_kernel<float, 16, true, 16, 1, InstTable>,
+           (const void*)&head_kernel<float, 16, true, 16, 1, UniformInst>,
+           (const void*)&head_kernel<float, 16, false, 16, 1, InstTable>,
+           (const void*)&head_kernel<float, 16, false, 16, 1, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 4, true, 16, 1, InstTable>,
+           (const void*)&head_kernel<uint16_t, 4, true, 16, 1, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 4, true, 8, 2, InstTable>,
+           (const void*)&head_kernel<uint16_t, 4, true, 8, 2, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 4, true, 16, 2, InstTable>,
+           (const void*)&head_kernel<uint16_t, 4, true, 16, 2, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 8, true, 16, 1, InstTable>,
+           (const void*)&head_kernel<uint16_t, 8, true, 16, 1, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 8, true, 8, 2, InstTable>,
+           (const void*)&head_kernel<uint16_t, 8, true, 8, 2, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 8, true, 16, 2, InstTable>,
+           (const void*)&head_kernel<uint16_t, 8, true, 16, 2, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 8, false, 16, 1, InstTable>,
+           (const void*)&head_kernel<uint16_t, 8, false, 16, 1, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 8, false, 8, 2, InstTable>,
+           (const void*)&head_kernel<uint16_t, 8, false, 8, 2, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 8, false, 16, 2, InstTable>,
+           (const void*)&head_kernel<uint16_t, 8, false, 16, 2, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 16, true, 16, 1, InstTable>,
+           (const void*)&head_kernel<uint16_t, 16, true, 16, 1, UniformInst>,
+           (const void*)&head_kernel<uint16_t, 16, false, 16, 1, InstTable>,
+           (const void*)&head_kernel<uint16_t, 16, false, 16, 1, UniformInst>})
+    if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 144 << 10)) != hipSuccess) return e;
+  return hipSuccess;
+}
+
+}  // namespace laq

@@ -1,0 +1,107 @@
+// Products of key rows and score rows on the matrix cores, for the kernels that hold 32 key rows per wave in operand layout
+// (lane l: row l % 32, the 16-byte pieces 2t + l / 32) and the score rows in LDS.
+//
+// fp32 takes six bf16 products: a float is the sum of three bf16 (split8), and the three products of parts that lie below
+// 2^-24 of the whole are left out.
+#pragma once
+
+#include "laq_internal.h"
+
+namespace laq {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+constexpr float NEG_BIG = -1.0e30f;   // finite "minus infinity" for running maxima
+// The exponential instruction returns 0 below 2^-126, where fp32 still tells scores apart: a score below TINY is summed again
+// with the exponents of its terms raised (above it, what is lost is less than a rounding).
+constexpr float TINY = 0x1p-90f;
+
+
+// Row index (0..31) of accumulator register i for a lane in half hf of the 32x32 output layout.
+__device__ __forceinline__ int acc_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
+
+// Eight floats as the sums of three bf16 each (8 bits of the mantissa, cut off, so that nothing is lost).
+struct Split { u32x4 p[3]; };
+__device__ __forceinline__ Split split8(u32x4 a, u32x4 b) {
+  unsigned x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  Split s;
+#pragma unroll
+  for (int pl = 0; pl < 3; ++pl) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s.p[pl][i] = __builtin_amdgcn_perm(x[2 * i + 1], x[2 * i], 0x07060302u);
+    if (pl < 2) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = __float_as_uint(__uint_as_float(x[i]) - __uint_as_float(x[i] & 0xffff0000u));
+    }
+  }
+  return s;
+}
+__device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 acc) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+
+constexpr bool is_f32(float) { return true; }
+constexpr bool is_f32(uint16_t) { return false; }
+
+// bytes of d staged bf16 (32 bytes for a product step), and from one staged score row to the next: bf16 as it is, fp32 as three rows
+// of bf16; and 16 more, so that 128-bit reads of 16 consecutive rows fall on distinct banks
+__host__ __device__ inline int plane_bytes(int d) { return (d + 15) / 16 * 32; }
+template <typename T> __host__ __device__ inline int row_stride(int d) { return (is_f32(T()) ? 3 : 1) * plane_bytes(d) + 16; }
+
+// The product of fp32 rows by the fp32 instruction, from memory: where the split one holds a NaN (a part of an infinity is one).
+template <bool KEYS_AS_ROWS>
+__device__ __forceinline__ f32x16 product_f32(const char* key, const char* q, int hf, int row_bytes) {
+  f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int o = hf * 16; o < row_bytes + hf * 16; o += 32) {     // (both halves as often: the last piece of the upper one may be missing)
+    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+    if (o < row_bytes) {
+      x = *reinterpret_cast<const f32x4*>(key + o);
+      y = *reinterpret_cast<const f32x4*>(q + o);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      acc = KEYS_AS_ROWS ? __builtin_amdgcn_mfma_f32_32x32x2f32(x[j], y[j], acc, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x2f32(y[j], x[j], acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+template <bool KEYS_AS_ROWS>
+__device__ __forceinline__ f32x16 mm(u32x4 key, u32x4 q, f32x16 acc) { return KEYS_AS_ROWS ? mfma(key, q, acc) : mfma(q, key, acc); }
+
+__device__ __forceinline__ void merge_stat(float& M, float& Z, float2 p) {
+  const float Mn = fmaxf(M, p.x);
+  Z = Z * __builtin_amdgcn_exp2f(M - Mn) + p.y * __builtin_amdgcn_exp2f(p.x - Mn);
+  M = Mn;
+}
+
+// Score rows r0 .. r0 + n - 1 of a head to LDS, `stride` bytes apart (rows beyond R: the last one again).
+template <typename T, bool FULL, int THREADS>
+__device__ __forceinline__ void stage_rows(char* lds, const char* head_rows, int row_bytes, int plane, int stride, int R, int r0, int n) {
+  const int tid = threadIdx.x, per = plane / 16, total = n * per;
+#pragma unroll(is_f32(T()) ? 2 : 4)
+  for (int p = tid; p < total; p += THREADS) {
+    const int row = p / per, col = p - row * per;
+    const char* src = head_rows + (size_t)min(r0 + row, R - 1) * row_bytes;
+    if constexpr (!is_f32(T())) {
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (FULL || col * 16 < row_bytes) v = *reinterpret_cast<const u32x4*>(src + col * 16);
+      *reinterpret_cast<u32x4*>(lds + row * stride + col * 16) = v;
+    } else {
+      // 8 elements as the key side has them: pieces 2t + hf and 2(t + 1) + hf
+      const int a = (col >> 1) * 4 + (col & 1);
+      u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u};
+      if (FULL || a * 16 < row_bytes) x = *reinterpret_cast<const u32x4*>(src + a * 16);
+      if (FULL || (a + 2) * 16 < row_bytes) y = *reinterpret_cast<const u32x4*>(src + (a + 2) * 16);
+      const Split s = split8(x, y);
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(lds + row * stride + pl * plane + col * 16) = s.p[pl];
+    }
+  }
+}
+
+}  // namespace laq

@@ -21,39 +21,14 @@
 
 #include "laq_internal.h"
 #include "laq_pool.h"
+#include "laq_rank.h"
 
 namespace laq {
 
 namespace {
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // (a native vector: arrays of it stay in registers)
-
 constexpr int COPIES = 8;                  // histograms of the first pass
 constexpr int CANDIDATES = 128;            // keys that are ranked by comparing all pairs
-
-__device__ __forceinline__ uint32_t order_key(float f) {
-  const uint32_t b = __float_as_uint(f);
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);   // larger float <=> larger key
-}
-
-__device__ __forceinline__ int lanes_below(uint64_t m) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-}
-
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_or_zero(int x) {
-  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
-}
-// inclusive sum over the lanes of a wave
-__device__ __forceinline__ int wave_scan(int x) {
-  x += dpp_or_zero<0x111, 0xf>(x);         // row_shr 1, 2, 4, 8 within 16 lanes
-  x += dpp_or_zero<0x112, 0xf>(x);
-  x += dpp_or_zero<0x114, 0xf>(x);
-  x += dpp_or_zero<0x118, 0xf>(x);
-  x += dpp_or_zero<0x142, 0xa>(x);         // lane 15 of a row to the next row
-  x += dpp_or_zero<0x143, 0xc>(x);         // lane 31 to the upper half
-  return x;
-}
 
 __device__ __forceinline__ float4 quad_of_lane(float4 x, int l) {
   return make_float4(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x.x), l)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x.y), l)),
@@ -405,49 +380,7 @@ __global__ __launch_bounds__(THREADS, 4) void select_kernel(int Hkv, int L, int 
   if constexpr (FINISH) {
     // ---- gather: this workgroup's own list, complete behind the barrier ----
     __syncthreads();
-    const int ppr = fin.row_bytes >> 4, total = bk * ppr;
-    const int64_t row0 = tab.first(li) + (int64_t)head * bk;
-    const char *ks = fin.k + (size_t)head * fin.head_bytes, *vs = fin.v + (fin.v ? (size_t)head * fin.head_bytes : 0);
-    // several pieces per thread and turn, so that their list entries and then their rows are on the way together
-    constexpr int TURN = 4;
-    const int drow = THREADS / ppr, dcol = THREADS - drow * ppr;
-    int row = tid / ppr, col = tid - row * ppr;
-    for (int p = tid; p < total; p += THREADS * TURN) {
-      int j[TURN];
-      size_t from[TURN], to[TURN];
-#pragma unroll
-      for (int u = 0; u < TURN; ++u) {
-        const bool in = p + u * THREADS < total;
-        j[u] = out[in ? row : 0];
-        from[u] = (size_t)col * 16;
-        to[u] = (size_t)(row0 + row) * fin.row_bytes + (size_t)col * 16;
-        row += drow;
-        col += dcol;
-        if (col >= ppr) {
-          col -= ppr;
-          ++row;
-        }
-      }
-      u32x4 x[TURN], y[TURN];
-#pragma unroll
-      for (int u = 0; u < TURN; ++u) {
-        if (fin.lay.table) {
-          int r;
-          from[u] += (size_t)paged_block_offset(fin.lay, inst0 + li, j[u], &r) * fin.elem_bytes + (size_t)r * fin.src_row_bytes;
-        } else {
-          from[u] += (size_t)(inst0 + li) * fin.inst_bytes + (size_t)j[u] * fin.src_row_bytes;
-        }
-        x[u] = *reinterpret_cast<const u32x4*>(ks + from[u]);
-        if (fin.v) y[u] = *reinterpret_cast<const u32x4*>(vs + from[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < TURN; ++u) {
-        if (p + u * THREADS < total) {
-          *reinterpret_cast<u32x4*>(fin.k_out + to[u]) = x[u];
-          if (fin.v) *reinterpret_cast<u32x4*>(fin.v_out + to[u]) = y[u];
-        }
-      }
-    }
+    gather_rows<THREADS>(fin, inst0 + li, head, bk, tab.first(li) + (int64_t)head * bk, [&](int r) { return out[r]; });
   }
 }
 
