@@ -40,19 +40,15 @@ __global__ __launch_bounds__(THREADS) void pool_quads_kernel(int L, int P, int h
 #pragma unroll
   for (int t = 0; t < TURNS; ++t) {
     const int pos = (first + t * WAVE_QUADS) * 4 - shift;
-    float4 q[5];
-    q[2] = x[t];
+    float4 own = x[t];
     if (pos + 3 >= P) {                    // what lies behind the prefix is in no window
-      if (pos >= P) q[2].x = 0.f;
-      if (pos + 1 >= P) q[2].y = 0.f;
-      if (pos + 2 >= P) q[2].z = 0.f;
-      q[2].w = 0.f;
+      if (pos >= P) own.x = 0.f;
+      if (pos + 1 >= P) own.y = 0.f;
+      if (pos + 2 >= P) own.z = 0.f;
+      own.w = 0.f;
     }
-    q[1] = lane_before(q[2], q[2]);
-    q[3] = lane_after(q[2], q[2]);
-    q[0] = lane_before(q[1], q[1]);
-    q[4] = lane_after(q[3], q[3]);
-    const float4 p = pool_quad(q, half, avg);
+    float4 p;
+    for_half(half, [&](auto h) { p = pool_quad_of<decltype(h)::value>(own, own, own, own, own, avg); });
     if (lane < 2 || lane >= 62) continue;
     const float v[4] = {pos < P ? p.x : x[t].x, pos + 1 < P ? p.y : x[t].y, pos + 2 < P ? p.z : x[t].z, pos + 3 < P ? p.w : x[t].w};
     if (out_shift == shift && pos >= 0 && pos + 3 < L) {

@@ -52,6 +52,29 @@ def test_select_at_the_edges_of_its_variants(n, Hkv, L, W, budgets, values):
         assert torch.equal(parts[i], oracle.select(s[i].cpu(), W, b[i])), i
 
 
+# (n, P, waves): the variants with lists; a wave's list holds 204 quads of neighbouring keys
+@pytest.mark.parametrize("n,P,waves", [(1, 32768, 16), (1, 16388, 16), (768, 8192, 4), (768, 32768, 8)])
+@pytest.mark.parametrize("crowded", [64, 203, 204, 205, 512])
+def test_select_where_one_waves_part_is_crowded(n, P, waves, crowded):
+    """`crowded` quads of the first wave's part hold a high score, and one of every lane of the others."""
+    import paper_2505_20334_amd as laq
+    print("case:", n, P, waves, crowded, flush=True)
+    part = 64 * 64 if waves == 8 else 64 * 32
+    g = torch.Generator(device=DEV).manual_seed(crowded)
+    s = torch.rand(n, 1, P, generator=g, device=DEV) * 1e-3
+    for w in range(-(-P // part)):
+        quads = torch.arange(crowded) if w == 0 else torch.arange(64) + 64 * (torch.arange(64) * 7 % (part // 256))
+        pos = w * part + 4 * quads + quads % 4
+        pos = pos[pos < P].to(DEV)
+        s[:, 0, pos] = 1 + torch.randint(0, 50, (n, len(pos)), generator=g, device=DEV).float() / 64
+    high = int((s[0, 0] >= 1).sum())
+    budgets = [min(high - 5, P // 40), 37, high]
+    b = [budgets[i % 3] for i in range(n)]
+    parts = split_packed(laq.laq_select(s, b, 1, 0).cpu(), b, 1, P)
+    for i in sorted({0, 1 % n, 2 % n, n - 1}):
+        assert torch.equal(parts[i], oracle.select(s[i].cpu(), 0, b[i])), i
+
+
 def test_a_prefix_of_a_variants_size_takes_that_variant():
     """32768 aligned scores per head fit the registers; the kernel that re-reads longer prefixes takes three times as long."""
     import paper_2505_20334_amd as laq
