@@ -124,9 +124,9 @@ typedef struct laq_shape {
   /*
    * Which scoring kernels to take where more than one applies (laq_score_choice; 0 = LAQ_CHOOSE_AUTO:
    * the single-read kernel for at most 64 score rows per KV head from 128 MiB of keys per call on,
-   * otherwise the two streaming passes, whose launches cost less and which are the faster ones with
-   * more rows, or, in calls of at most 512 chunks of 256 keys, the kernels that take one chunk per
-   * workgroup where those are faster).  A choice that does not apply to the shape is ignored;
+   * otherwise two passes over the keys, which are the faster ones with more rows, in small calls of
+   * bf16 with one chunk of 256 keys per workgroup, or, for heads of at most 512 keys and many of at most
+   * 1024, a whole head in one workgroup).  A choice that does not apply to the shape is ignored;
    * laq_score_kernel() tells what a call will run.
    */
   int32_t score_choice;
@@ -191,12 +191,12 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *          laq_score(p) + laq_select(1) and laq_score(1) + laq_select(p) give the same indices.
  *   ws / ws_bytes  device scratch of at least laq_workspace_bytes(shape)
  * Supported: dtype BF16 or F32; any Hq/Hkv/W/L within the limits of laq_shape;
- * pool_kernel odd, 1 <= pool_kernel <= 63.  BF16 with d = 64 or 128 and W <= 512 runs on kernels that
- * stream the keys -- calls of at most 512 chunks of 256 keys on kernels with one chunk per workgroup
- * where these are faster, which is most of them (score_choice LAQ_CHOOSE_TWO_PASS: never) --, everything else
- * on kernels with one chunk per workgroup, with the same results to within the rounding of their fp32
- * sums; all of them on the matrix cores.  q_win, k and scores must be 16-byte
- * aligned.
+ * pool_kernel odd, 1 <= pool_kernel <= 63.  Short heads are scored by one workgroup each, K read once;
+ * small calls by one workgroup per chunk of 256 keys, larger ones by workgroups that walk a segment of a head's
+ * keys (BF16 with d = 64 or 128, W <= 512 and score_choice LAQ_CHOOSE_TWO_PASS: always these), with the same
+ * results to within the rounding of their fp32 sums; all of them on the matrix cores (F32: as six products of
+ * bf16 parts, with no larger error than the fp32 instruction, or with that instruction).  q_win, k and scores
+ * must be 16-byte aligned.
  */
 int laq_score(const laq_shape *shape, const void *q_win, const void *k, int pool_kernel,
               float *scores, void *ws, size_t ws_bytes, void *stream);
@@ -231,11 +231,11 @@ int laq_select_sink_recent(int32_t n_inst, int32_t Hkv, int32_t L, const int32_t
 /*
  * How laq_score (and laq_evict) read K for this shape on the current device, for callers
  * that account for memory traffic (Sec. 4.3's scoring reads K once or twice accordingly):
- * LAQ_KERNEL_VECTOR (fp32 caches, or a head size or window that the bf16 streaming kernels do not take: always one
- * chunk per workgroup, K read twice), LAQ_KERNEL_TWO_PASS (bf16, K read twice: by the streaming kernels, or,
- * in calls of at most 512 chunks that leave the choice to the library, by the one-chunk kernels where
- * these are faster) or LAQ_KERNEL_SINGLE_READ (bf16, K read once); a negative error code
- * for an invalid shape.  (The first name is older than its kernels, which work on the matrix cores.)  The strides, the block table and the score_choice of `shape` are taken
+ * LAQ_KERNEL_VECTOR (fp32 caches, head sizes other than 64 and 128, W > 512: K read twice), LAQ_KERNEL_TWO_PASS
+ * (bf16, d = 64 or 128, K read twice) or LAQ_KERNEL_SINGLE_READ (bf16, K read once by teams of workgroups); a
+ * negative error code for an invalid shape.  Calls of the first two kinds whose heads fit a workgroup (at most
+ * 1024 keys) and that leave the choice to the library read K once.  (The first name is older than its kernels,
+ * which work on the matrix cores.)  The strides, the block table and the score_choice of `shape` are taken
  * into account like laq_score does.  Launches nothing.
  */
 enum { LAQ_KERNEL_VECTOR = 0, LAQ_KERNEL_TWO_PASS = 1, LAQ_KERNEL_SINGLE_READ = 2 };

@@ -139,9 +139,9 @@ SCORE_KERNELS = ("vector", "two-pass", "single-read")
 def laq_score_kernel(n_inst: int, Hq: int, Hkv: int, d: int, L: int, W: int, dtype: torch.dtype,
                      q_pos: Optional[Sequence[int]] = None, keep: Optional[int] = None,
                      kv_strides: Tuple[int, int, int] = (0, 0, 0), paged=None, choose: str = "auto") -> str:
-    """How laq_score reads K for this shape on the current device: "vector" (fp32 and the head sizes that
-    only the one-chunk kernels take, K read twice), "two-pass" (bf16, K read twice: the streaming kernels, or the
-    one-chunk kernels in small automatic calls) or "single-read" (K read once)."""
+    """How laq_score reads K for this shape on the current device: "vector" (fp32 and head sizes other than 64
+    and 128, K read twice), "two-pass" (bf16, K read twice) or "single-read" (bf16, K read once by teams of
+    workgroups).  Heads of at most 1024 keys that a workgroup holds whole are read once in any case."""
     code = LAQ_F32 if dtype == torch.float32 else LAQ_BF16
     sh = _shape(n_inst, Hq, Hkv, d, L, W, code, 0.0, q_pos, keep, "max", kv_strides, paged, choose)
     rc = int(load_library().laq_score_kernel(ctypes.byref(sh)))

@@ -1,11 +1,12 @@
 // Scoring, one 256-key chunk per workgroup: every head size up to 256 and any number of score rows, fp32 or
 // bf16, on the matrix cores (v_mfma_f32_32x32x2_f32, v_mfma_f32_32x32x16_bf16: products of the stored values,
-// fp32 sums).  Used for fp32 caches and head sizes other than 64 and 128, and for small bf16 calls, which
-// the streaming kernels' set-up, combine and pooling launches would bound.
+// fp32 sums).  Used for small calls: a workgroup per chunk, and up to four for its row tiles, fill the device where the
+// segments of laq_score_wave.hip would not.
 //
 // Two kernels: (1) per-row softmax statistics (m, z) of each chunk, (2) after folding the statistics of a
-// head's chunks (by every workgroup itself when they are few, else by row_constants_mfma_kernel), the sum over
-// the rows of exp2(s - c): raw scores.  //
+// head's chunks (by every workgroup itself when they are few, else by row_constants_kernel), the sum over
+// the rows of exp2(s - c): raw scores.
+//
 // A wave holds 32 key rows in registers in operand layout (lane l: row l % 32, the 16-byte pieces 2t + l / 32)
 // and walks the score rows in tiles of 32 that the workgroup stages in LDS, one tile ahead.  The reduction
 // index of a product may run in any order as long as both operands agree, so fp32 takes the four elements
@@ -13,9 +14,8 @@
 //   (1) D = K * Q^T: lane = score row, registers = 16 keys: maximum and sum in registers.
 //   (2) D = Q * K^T: lane = key, registers = 16 rows: the sum over the rows in registers.
 //
-// What bounds it: for fp32 the matrix cores (157 TFLOP/s dense), which do the product twice; the vector ALU
-// kernels that stood here took 8 us per (million keys x score row) and pass pair, these about 1.  64 heads x
-// 8191 keys, d = 128, 64 score rows, fp32: 1018 -> 211 us.
+// What bounds it: latency, of two launches and of load -> LDS -> products -> reduction in each (8 heads x 4096 keys, bf16: 5.3 + 6.6 us);
+// fp32 pays the fp32 instruction's rate for both products, which larger calls do not (laq_score_wave.hip).
 #include "laq_internal.h"
 
 namespace laq {
@@ -33,7 +33,7 @@ constexpr int WAVES = CHUNK_ROWS / 32, THREADS = WAVES * 64;
 // Row tiles of a chunk that are worked on side by side where there are too few chunks to fill the device.
 constexpr int MAX_SPLIT = 4;
 // Every workgroup of the second kernel folds the statistics of its head itself where that is little next to
-// its keys and the workgroups are few (one launch less); otherwise row_constants_mfma_kernel does it once.
+// its keys and the workgroups are few (one launch less); otherwise row_constants_kernel does it once.
 constexpr int FOLD_CHUNKS = 32, FOLD_WORKGROUPS = 512;
 // The exponential instruction returns 0 below 2^-126, where fp32 still tells scores apart: what it lost is added to a tile's sum
 // that is below TINY (above it, 32 such terms are less than a rounding).
