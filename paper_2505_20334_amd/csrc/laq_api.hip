@@ -444,14 +444,18 @@ static int decode_impl(const laq_shape* shape, const void* q, const void* kc, co
 //               273.7 : 282.1, 128 KiB 178.3 : 174.5, 208.6 : 207.6, 298.0 : 303.9
 //   160 heads, 128 KiB: 4096 keys 90.2 : 93.1, 8001 128.4 : 128.7;  256 heads 120.7 : 126.7, 178.2 : 181.1
 //   more heads than compute units, 8001 keys: 384, 1024 heads 218.8 : 215.5, 522 : 505
-// (With at most 32 score rows the single-read kernel pools 16384 keys for less: 256 heads 264.6 : 261.4; the mean pool, which has a
-// launch of its own, 264.8 : 273.8.)
-static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, const float* raw, int row_bytes) {
+// Where the single-read kernel would pool the maximum (in launches of its own beside the selection and the gather), more is saved, and the
+// line is one by heads.  32 and 64 rows, 6000 to 16380 keys, several : one:   64 heads 64, 96, 128 KiB 1.03-1.06, 1.01-1.04, .99-1.00
+//   96 heads 96, 128, 192 KiB 1.01-1.04, 1.00-1.02, .95-.98;  128 heads 128, 192 KiB 1.00-1.03, .99-1.00;  160 heads 128, 192 KiB 1.02-1.04, 1.01-1.03
+//   256 heads 128, 192, 256 KiB 1.01-1.04; with rows 2 KiB apart 192 heads x 3867 keys, 217 KiB .97
+static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const int32_t* budget, int pool, const float* raw,
+                          int row_bytes) {
   const long long heads = (long long)g.n_inst * g.Hkv;
   const int keys = g.P + row_shift(raw, g.L);
   if ((pool - 1) / 2 > SELECT_POOL_MAX_HALF || keys > FINISH_MAX_KEYS || heads > 256 || shape->n_inst > MAX_INST_PER_LAUNCH) return false;
-  int gather = 0;
+  long long gather = 0;
   if (keys <= 2048) gather = 32 << 10;
+  else if (pool > 1 && !leaves_raw(shape, g, lay)) gather = heads < 128 ? heads * 1280 : 160 << 10;
   else if (heads >= 160) gather = 128 << 10;
   else if (keys <= 4096 || (keys <= 8192 && heads >= 128)) gather = 96 << 10;
   else if (keys <= 8192) gather = 32 << 10;
@@ -632,7 +636,7 @@ static int evict_impl(const laq_shape* shape, const void* q_win, const void* k, 
   const laq::ScorePath path = laq::score_path(shape, g, lay);
   if (path == laq::ScorePath::head && laq::head_gathers(shape, g, budget, pool_kernel, row_bytes))
     return laq::head_checked(shape, g, qp, lay, laq::finish_args(shape, g, lay, k, v, pool_kernel, scores, k_out, v_out), q_win, k, budget, idx, ws, st);
-  if (path != laq::ScorePath::head && laq::finish_wanted(shape, g, budget, pool_kernel, raw, row_bytes)) {
+  if (path != laq::ScorePath::head && laq::finish_wanted(shape, g, lay, budget, pool_kernel, raw, row_bytes)) {
     const int rc = laq::score_checked(shape, g, qp, lay, q_win, k, 1, raw, ws, st);
     if (rc != LAQ_OK) return rc;
     return laq::finish_checked(g, laq::finish_args(shape, g, lay, k, v, pool_kernel, scores, k_out, v_out), budget, raw, idx, st);

@@ -114,3 +114,20 @@ def test_pooling_and_selection_in_one_launch_are_those_of_two(n, Hkv, L, keep):
         assert torch.equal(idx, laq.laq_select(pooled, budgets, 1, keep))
         for a, b in zip((ko, vo), laq.laq_compact(k, v, idx, budgets, keep)):
             assert torch.equal(a, b)
+
+
+# the last list that the finishing launch takes after the single-read kernel, and the first that it leaves: heads * 1280 bytes of
+# K rows, from 128 heads on 160 KiB; one more layer, shorter heads, the two budgets in one call
+@pytest.mark.parametrize("n,L,budgets", [(8, 8300, [320]), (8, 8300, [321]), (8, 8300, [17, 320]), (17, 3900, [640]), (17, 3900, [641])])
+def test_gather_after_the_single_read_kernel_is_that_of_the_stages(n, L, budgets):
+    import paper_2505_20334_amd as laq
+    g = torch.Generator(device=DEV).manual_seed(L)
+    q = torch.randn(n, 16, 8, 128, generator=g, device=DEV).bfloat16()
+    k, v = (torch.randn(n, 8, L, 128, generator=g, device=DEV).bfloat16() for _ in range(2))
+    assert laq.laq_score_kernel(n, 16, 8, 128, L, 8, BF16) == "single-read"
+    b = [budgets[i % len(budgets)] for i in range(n)]
+    scores, idx, ko, vo = laq.laq_evict(q, k, v, b, 7)
+    assert torch.equal(scores, laq.laq_score(q, k, 7))
+    assert torch.equal(idx, laq.laq_select(scores, b, 1, 8))
+    for x, y in zip((ko, vo), laq.laq_compact(k, v, idx, b, 8)):
+        assert torch.equal(x, y)
