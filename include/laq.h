@@ -194,9 +194,11 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  * pool_kernel odd, 1 <= pool_kernel <= 63.  Short heads are scored by one workgroup each, K read once;
  * small calls by one workgroup per chunk of 256 keys, larger ones by workgroups that walk a segment of a head's
  * keys (BF16 with d = 64 or 128, W <= 512 and score_choice LAQ_CHOOSE_TWO_PASS: always these), with the same
- * results to within the rounding of their fp32 sums; all of them on the matrix cores (F32: as six products of
- * bf16 parts, with no larger error than the fp32 instruction, or with that instruction).  q_win, k and scores
- * must be 16-byte aligned.
+ * results to within the rounding of their fp32 sums; all of them on the matrix cores.  F32: with the fp32
+ * instruction, or as six products of bf16 parts, which give the product of two elements to within 2^-24 of it, summed in
+ * fp32; dot products of dense rows are closer to their value than the instruction's, those of rows with a single
+ * element that is not 0 may be off by up to 2^-22.5 where the instruction's are by 2^-24.  q_win, k and scores must be
+ * 16-byte aligned.
  */
 int laq_score(const laq_shape *shape, const void *q_win, const void *k, int pool_kernel,
               float *scores, void *ws, size_t ws_bytes, void *stream);

@@ -13,10 +13,11 @@
 //   (2) D = Q * K^T: lane = key, registers = 16 rows: the sum over the rows in registers.
 // Score rows beyond R repeat the last one and get c = inf, so that they add nothing.
 //
-// fp32 takes six bf16 products: a float is the sum of three bf16 (split8), and the three products of parts that lie below
-// 2^-24 of the whole are left out.  The sums are fp32, those of the small products apart from those of the large ones: fewer
-// roundings than the fp32 instruction makes.  Error against 64 bits (2-norm of the scores, d = 64, 96, 128, logits of standard deviation
-// 1 / 4): 1.8-2.6e-7 / 3.9-6.0e-7, with the fp32 instruction 1.8-2.8e-7 / 7-13e-7; and 2.7 times its rate.
+// fp32 takes six bf16 products: a float is the sum of three bf16 (split8), and the three products of parts that together reach
+// 2^-24 of the whole at most are left out.  The sums are fp32, those of the small products apart from those of the large ones: fewer
+// roundings than the fp32 instruction makes.  Error against 64 bits (2-norm of the scores, d = 64, 96, 104, 128, logits of standard
+// deviation 1 / 4): 1.85-1.9e-7 / 4.5-4.9e-7, with the fp32 instruction 1.9e-7 / 7.9-9.7e-7; and 2.7 times its rate.  Rows of a single
+// element (no sum, one rounding) are where it is not the closer one: 2.34e-8 of a logit rms, 9e-8 at most, against 2.31e-8 and 6e-8.
 //
 // What bounds it: for up to 64 score rows the two reads of K (64 heads x 8192 to 16384 keys: 5.6 TB/s of 6.2), with 128 the
 // matrix cores and the exponentials at the clock they leave, for fp32 the matrix cores.  Scoring, us, before : now: the streaming kernels

@@ -69,19 +69,87 @@ def test_fp32_infinities_and_nans_are_those_of_whole_products(d):
         assert got[0].isnan().all() and not got[1].isnan().any()
 
 
-def test_fp32_products_of_parts_are_no_further_from_64_bits():
-    """Logits of a standard deviation of 4, 2-norm of the error of the scores over 130 heads x 250 keys, 64 score rows: an
-    fp32 sum of 128 products q k rounded to 2^-24 of the running sum at every one is off by about 2^-24 * sqrt(128 / 3) of a
+@pytest.mark.parametrize("n,L,d", [(130, 250, 128), (65, 600, 128), (65, 1100, 64)])
+def test_fp32_products_of_parts_are_no_further_from_64_bits(n, L, d):
+    """Logits of a standard deviation of 4, 2-norm of the error of the scores, 64 score rows; a workgroup per head, and the kernels
+    that walk a segment: an fp32 sum of 128 products q k rounded to 2^-24 of the running sum at every one is off by about 2^-24 * sqrt(128 / 3) of a
     logit's deviation, 1.6e-6 of an exponent, and the fp32 instruction measured 7 to 13e-7; the left-out products are 2^-24 of
     the whole ones.  A product of parts more left out (2^-16) would show as 6e-5."""
     import paper_2505_20334_amd as laq
     g = torch.Generator().manual_seed(5)
-    n, W, L, d = 130, 16, 250, 128
+    W = 16
     q, k = 4.0 * torch.randn(n, 4, W, d, generator=g), torch.randn(n, 1, L, d, generator=g)
     got = laq.laq_score(q.to(DEV), k.to(DEV), 1, q_pos=[L + w for w in range(W)], keep=0).cpu().double()
     s = q.double().reshape(n, 4 * W, d) @ k[:, 0].double().transpose(1, 2) / d ** 0.5
     want = torch.softmax(s, -1).sum(1).unsqueeze(1)
     assert ((got - want).norm() / want.norm()).item() < 7e-7
+
+
+# (heads, keys, d): fp32 calls that a workgroup per head takes, and calls of the kernels that walk a segment
+F32_SHORT = [(24, 500, 64), (300, 300, 64), (80, 1000, 64), (80, 300, 128)]
+F32_LONG = [(65, 1100, 64), (65, 600, 96), (65, 600, 104), (65, 600, 128)]
+
+
+def _logit_errors(q, k):
+    """One query row per head and logits near 1024: errors of the logits over 1024, from the scores.  A constant of the head is lost
+    in the softmax: it is taken so that the median over the keys `k[:, 0, ::2]` is 0."""
+    import paper_2505_20334_amd as laq
+    got = laq.laq_score(q.to(DEV), k.to(DEV), 1, scale=1.0, q_pos=[k.shape[2]], keep=0).cpu().double()[:, 0]
+    s = (q.double()[:, 0] @ k.double()[:, 0].transpose(1, 2))[:, 0]
+    assert (s - 1024).abs().max() < 32         # (exponents of up to 92, rounded by 2^-18)
+    e = torch.log(got) - torch.log_softmax(s, -1)
+    return (e - e[:, ::2].median(-1, keepdim=True)[0]) / 1024
+
+
+def _low_bits(x, bits):
+    return ((x.view(torch.int32) & ~0xffff) | bits).view(torch.float32)
+
+
+@pytest.mark.parametrize("n,L,d", F32_SHORT + F32_LONG)
+def test_fp32_single_products(n, L, d):
+    """Rows of one element that is not 0, so that a logit is one product.  Left out of it are the products of second and third
+    parts: 2 * 2^-8 * 2^-17 = 2^-24 at most of a logit (below 1056).  The sum of the small products and the large one is rounded
+    once, 2^-24 more; where a workgroup takes a head the matrix instruction adds them, which may cut off a whole unit, 2^-23.
+    Every second key has 8 bits of mantissa, of which nothing is left out: their errors are the rounding alone, and their median
+    is 0 but for the sampling (1.25 * 2^-24 / sqrt(3 * L / 2), four times that).  The exponents are rounded by 2^-18."""
+    g = torch.Generator().manual_seed(d)
+    for bits in (0xffff, 0x7fff, 0x8000, 0x8080, 0x7f7f, 0x0180, None):
+        q, k = torch.zeros(n, 1, 1, d), torch.zeros(n, 1, L, d)
+        a = 1 + 2.0 ** -7 * torch.randint(0, 128, (n,), generator=g)
+        b = (1021 + 6 * torch.rand(n, L, generator=g)) / a[:, None]
+        if bits is not None:
+            a, b = _low_bits(a, bits), _low_bits(b, bits)
+        else:
+            a = a + 2.0 ** -7 * torch.rand(n, generator=g)
+        b[:, ::2] = _low_bits(b[:, ::2].contiguous(), 0)
+        q[:, 0, 0, d // 3], k[:, 0, :, d // 3] = a, b
+        rounding = 2.0 ** (-23 if (n, L, d) in F32_SHORT else -24)
+        bound = (2.0 ** -24 + rounding) * 1056 / 1024 + 4 * 1.25 * 2.0 ** -24 / (1.5 * L) ** 0.5 + 2.0 ** -28
+        worst = _logit_errors(q, k).abs().max().item()
+        assert worst <= bound, "low bits %s: %.3g of %.3g" % (bits if bits is None else hex(bits), worst, bound)
+
+
+@pytest.mark.parametrize("n,L,d", F32_SHORT + F32_LONG)
+def test_fp32_products_are_not_off_to_one_side(n, L, d):
+    """Rows of positive elements whose mantissas end in ones, or in zeros (8 bits: nothing is left out): the roundings of the sums
+    go to both sides in both, and on the average over all keys of all heads there is no difference: less than half a unit of
+    a logit, 2^-24 (left-out parts that follow the sign of the product are 1 to 2.5e-7)."""
+    g = torch.Generator().manual_seed(d)
+    for signs in (False, True):
+        q, k = 1 + torch.rand(n, 1, 1, d, generator=g), 1 + torch.rand(n, 1, L, d, generator=g)
+        k = k * (1022 + 4 * torch.rand(n, 1, L, 1, generator=g)) / (q * k).sum(-1, keepdim=True)
+        q, ones, zeros = _low_bits(q, 0xffff), _low_bits(k, 0xffff), _low_bits(k, 0)
+        ones[:, :, ::2] = zeros[:, :, ::2]
+        # (the shortened keys' logits are up to 2^-7 smaller: brought back by an element of a bf16 value)
+        s = (q.double() * ones.double()).sum(-1, keepdim=True)
+        fix = ((1024 - s) / q[..., :1].double()).float().bfloat16().float()
+        ones[..., :1] = _low_bits((ones[..., :1] + fix).contiguous(), 0)
+        if signs:
+            sg = 1 - 2.0 * torch.randint(0, 2, (n, 1, 1, d), generator=g)
+            q, ones = q * sg, ones * sg
+        e = _logit_errors(q, ones)
+        off = (e[:, 1::2].mean() - e[:, ::2].mean()).abs().item()
+        assert off <= 2.0 ** -24, off
 
 
 # (n, Hkv, L, keep): prefixes around the sizes at which a variant of the selection kernel ends, rows of any alignment
