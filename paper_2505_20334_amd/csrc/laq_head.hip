@@ -103,7 +103,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 4) void head_kernel(Sc
   for (int r = tid; r < tiles * 32; r += THREADS) last[r] = last_visible_key(g, qp, min(r, g.R - 1) % g.W);
   for (int i = tid; i < THREADS + 2 * MARGIN; i += THREADS) raw[i] = 0.f;
   rank.bins[tid] = 0;
-  stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, 0, min(pl.group_tiles, tiles) * 32);
+  stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, 0, min(pl.group_tiles, tiles) * 32, g.shift);
   __syncthreads();
   const char* rows = smem + n32 * stride + hf * 16;
   // ---- statistics ----
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 4) void head_kernel(Sc
     const int ntile = min(pl.group_tiles, tiles - rt0);
     if (rt0 > 0) {
       __syncthreads();
-      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32);
+      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32, g.shift);
       __syncthreads();
     }
 #pragma unroll 1
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 4) void head_kernel(Sc
       for (int i = 0; i < TPW; ++i) {
         const int key0 = (i * WAVES + wave) * 32;
         if (key0 >= g.L) continue;
-        float m, z;
+        float m, z, scale = g.shifted_scale2;
         f32x16 s = product_raw<T, NP, FULL, true>(key[i], rows + rt * 32 * stride, plane, plane / 32);
 #pragma unroll 1
         for (bool again = false;; again = true) {
@@ -136,14 +136,15 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 4) void head_kernel(Sc
 #pragma unroll
           for (int e = 1; e < 16; ++e) m = fmaxf(m, s[e]);
           const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-          m = fmaxf(M, fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1])) * g.scale2);     // (the logit scale is positive)
+          m = fmaxf(M, fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1])) * scale);     // (the logit scale is positive)
           z = 0.f;
 #pragma unroll
-          for (int e = 0; e < 16; ++e) z += __builtin_amdgcn_exp2f(fmaf(s[e], g.scale2, -m));
+          for (int e = 0; e < 16; ++e) z += __builtin_amdgcn_exp2f(fmaf(s[e], scale, -m));
           const auto zh = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
           z = __uint_as_float(zh[0]) + __uint_as_float(zh[1]);
           if (!is_f32(T()) || again || __builtin_expect(!__any(z != z), 1)) break;
           s = product_f32<true>(key_row(key0), head_rows + (size_t)min((rt0 + rt) * 32 + n32, g.R - 1) * row_bytes, hf, row_bytes);
+          scale = g.scale2;
         }
         Z = fmaf(Z, __builtin_amdgcn_exp2f(M - m), z);
         M = m;
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 4) void head_kernel(Sc
     const int ntile = min(pl.group_tiles, tiles - rt0);
     if (pl.groups > 1) {
       __syncthreads();
-      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32);
+      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32, g.shift);
       __syncthreads();
     }
 #pragma unroll 1
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 4) void head_kernel(Sc
         for (int gq = 0; gq < 4; ++gq) {
           const f32x4 c = *reinterpret_cast<const f32x4*>(rowc + (rt0 + rt) * 32 + 8 * gq + 4 * hf);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sum[i] += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + e], g.scale2, -c[e]));
+          for (int e = 0; e < 4; ++e) sum[i] += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + e], g.shifted_scale2, -c[e]));
         }
       }
     }

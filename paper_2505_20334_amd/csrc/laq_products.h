@@ -91,9 +91,11 @@ __device__ __forceinline__ void merge_stat(float& M, float& Z, float2 p) {
   M = Mn;
 }
 
-// Score rows r0 .. r0 + n - 1 of a head to LDS, `stride` bytes apart (rows beyond R: the last one again).
+// Score rows r0 .. r0 + n - 1 of a head to LDS, `stride` bytes apart (rows beyond R: the last one again); fp32: times
+// 2^shift (ScoreGeom::shift).
 template <typename T, bool FULL, int THREADS>
-__device__ __forceinline__ void stage_rows(char* lds, const char* head_rows, int row_bytes, int plane, int stride, int R, int r0, int n) {
+__device__ __forceinline__ void stage_rows(char* lds, const char* head_rows, int row_bytes, int plane, int stride, int R, int r0, int n,
+                                           int shift) {
   const int tid = threadIdx.x, per = plane / 16, total = n * per;
 #pragma unroll(is_f32(T()) ? 2 : 4)
   for (int p = tid; p < total; p += THREADS) {
@@ -109,6 +111,11 @@ __device__ __forceinline__ void stage_rows(char* lds, const char* head_rows, int
       u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u};
       if (FULL || a * 16 < row_bytes) x = *reinterpret_cast<const u32x4*>(src + a * 16);
       if (FULL || (a + 2) * 16 < row_bytes) y = *reinterpret_cast<const u32x4*>(src + (a + 2) * 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[i] = __float_as_uint(__builtin_amdgcn_ldexpf(__uint_as_float(x[i]), shift));
+        y[i] = __float_as_uint(__builtin_amdgcn_ldexpf(__uint_as_float(y[i]), shift));
+      }
       const Split s = split8(x, y);
 #pragma unroll
       for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(lds + row * stride + pl * plane + col * 16) = s.p[pl];

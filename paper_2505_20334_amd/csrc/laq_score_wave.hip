@@ -201,7 +201,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
   const Wave<T, NP, FULL> w(g, lay, q, k, seg, pl.seg_blocks);
   u32x4 key[NP];
   if (w.some) w.load(key, g, lay, w.first);
-  stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32);
+  stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, g.shift);
   float2* stat = reinterpret_cast<float2*>(smem + pl.group_tiles * 32 * w.stride);       // [row tile][wave][row]
   for (int i = threadIdx.x; i < ntile * WAVES * 32; i += THREADS) stat[i] = make_float2(NEG_BIG, 0.f);
   __syncthreads();
@@ -214,6 +214,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
       const float2 old = *mine;
       float m, z;
       f32x16 s = op.template product<true>(rows, w.plane, w.plane / 32);
+      float scale = g.shifted_scale2;
 #pragma unroll 1
       for (bool again = false;; again = true) {
         if (!plain) {
@@ -228,14 +229,15 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
 #pragma unroll
         for (int i = 1; i < 16; ++i) m = fmaxf(m, s[i]);
         const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-        m = fmaxf(old.x, fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1])) * g.scale2);    // (the logit scale is positive)
+        m = fmaxf(old.x, fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1])) * scale);    // (the logit scale is positive)
         z = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f(fmaf(s[i], g.scale2, -m));
+        for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f(fmaf(s[i], scale, -m));
         const auto zh = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
         z = __uint_as_float(zh[0]) + __uint_as_float(zh[1]);
         if (!is_f32(T()) || again || __builtin_expect(!__any(z != z), 1)) break;
         s = product_f32<true>(w.key_row(g, lay, key0), w.score_row(g, rt0 + rt), w.hf, w.row_bytes);
+        scale = g.scale2;
       }
       *mine = make_float2(m, fmaf(old.y, __builtin_amdgcn_exp2f(old.x - m), z));
       rows += 32 * w.stride;
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
     const int ntile = min(pl.group_tiles, g.Rpad / 32 - rt0);
     if (w.some) w.load(key, g, lay, w.first);
     if (rt0 > 0) __syncthreads();
-    stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32);
+    stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, g.shift);
     if (tid < ntile * 32) {
       const int row = rt0 * 32 + tid;
       last[tid] = last_visible_key(g, qp, min(row, g.R - 1) % g.W);
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
         for (int gq = 0; gq < 4; ++gq) {
           const f32x4 c = *reinterpret_cast<const f32x4*>(rowc + rt * 32 + 8 * gq + 4 * w.hf);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + i], g.scale2, -c[i]));
+          for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + i], g.shifted_scale2, -c[i]));
         }
       }
       const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);

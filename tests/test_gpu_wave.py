@@ -152,6 +152,22 @@ def test_fp32_products_are_not_off_to_one_side(n, L, d):
         assert off <= 2.0 ** -24, off
 
 
+@pytest.mark.parametrize("n,L,d", F32_SHORT + F32_LONG)
+def test_fp32_keys_and_queries_of_any_magnitude(n, L, d):
+    """Queries times a power of two and keys divided by it, also by way of the scale: parts of small numbers that bf16 does not hold
+    are not lost from the logits."""
+    import paper_2505_20334_amd as laq
+    g = torch.Generator().manual_seed(L)
+    q, k = 1.5 * torch.randn(n, 2, 5, d, generator=g), torch.randn(n, 1, L, d, generator=g)
+    q[:, 0, 0] = 0.0                          # (a row of zeros is one of ordinary numbers)
+    pos = [L - 3 * w for w in range(5)]
+    for eq, ek, es in ((110, -110, 0), (122, -122, 0), (-110, 110, 0), (-122, 122, 0), (60, -120, 60), (-120, 60, 60), (100, 20, -120)):
+        scaled, kk, scale = q * 2.0 ** eq, k * 2.0 ** ek, d ** -0.5 * 2.0 ** es
+        got = laq.laq_score(scaled.to(DEV), kk.to(DEV), 1, scale=scale, q_pos=pos, keep=0).cpu()
+        for i in (0, n - 1):
+            check_scores(got[i], oracle.raw_scores(scaled[i], kk[i], scale, q_pos=pos), F32, "2^%d 2^%d 2^%d" % (eq, ek, es))
+
+
 # (n, Hkv, L, keep): prefixes around the sizes at which a variant of the selection kernel ends, rows of any alignment
 @pytest.mark.parametrize("n,Hkv,L,keep", [(1, 3, 300, 5), (3, 3, 4093, 0), (2, 3, 8193, 3), (2, 3, 16385, 8), (1, 3, 32767, 2), (1, 2, 32768, 0),
                                           (1, 2, 32777, 1), (400, 2, 2046, 4), (400, 2, 2501, 9), (400, 2, 8199, 4)])
