@@ -173,7 +173,8 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *                               The library takes that kernel by itself with at most 64 score
  *                               rows and at least 128 MiB of keys in the call, where it is the
  *                               faster one; shape.score_choice asks for it or against it.
- *                               Otherwise K is streamed twice (laq_score_kernel() says which).
+ *                               Heads of at most 1024 keys that one workgroup holds are read once
+ *                               too.  Otherwise K is streamed twice (laq_score_kernel() says which).
  *                               The single-read kernel is started with a cooperative launch,
  *                               which keeps a team of workgroups on the device together; with
  *                               LAQ_COOPERATIVE_LAUNCH=0 in the environment (read at the first
@@ -234,13 +235,13 @@ int laq_select_sink_recent(int32_t n_inst, int32_t Hkv, int32_t L, const int32_t
  * How laq_score (and laq_evict) read K for this shape on the current device, for callers
  * that account for memory traffic (Sec. 4.3's scoring reads K once or twice accordingly):
  * LAQ_KERNEL_VECTOR (fp32 caches, head sizes other than 64 and 128, W > 512: K read twice), LAQ_KERNEL_TWO_PASS
- * (bf16, d = 64 or 128, K read twice) or LAQ_KERNEL_SINGLE_READ (bf16, K read once by teams of workgroups); a
- * negative error code for an invalid shape.  Calls of the first two kinds whose heads fit a workgroup (at most
- * 1024 keys) and that leave the choice to the library read K once.  (The first name is older than its kernels,
+ * (bf16, d = 64 or 128, K read twice), LAQ_KERNEL_SINGLE_READ (bf16, K read once by teams of workgroups) or
+ * LAQ_KERNEL_WHOLE_HEAD (heads of at most 1024 keys, K read once by a workgroup per head; only where the choice is
+ * left to the library); a negative error code for an invalid shape.  (The first name is older than its kernels,
  * which work on the matrix cores.)  The strides, the block table and the score_choice of `shape` are taken
  * into account like laq_score does.  Launches nothing.
  */
-enum { LAQ_KERNEL_VECTOR = 0, LAQ_KERNEL_TWO_PASS = 1, LAQ_KERNEL_SINGLE_READ = 2 };
+enum { LAQ_KERNEL_VECTOR = 0, LAQ_KERNEL_TWO_PASS = 1, LAQ_KERNEL_SINGLE_READ = 2, LAQ_KERNEL_WHOLE_HEAD = 3 };
 typedef enum { LAQ_CHOOSE_AUTO = 0, LAQ_CHOOSE_TWO_PASS = 1, LAQ_CHOOSE_SINGLE_READ = 2 } laq_score_choice;
 int laq_score_kernel(const laq_shape *shape);
 

@@ -133,18 +133,23 @@ def laq_workspace_status(ws: torch.Tensor, n_inst: int, Hq: int, Hkv: int, d: in
                                                    _stream(stream)))
 
 
-SCORE_KERNELS = ("vector", "two-pass", "single-read")
+SCORE_KERNELS = ("vector", "two-pass", "single-read", "whole-head")
 
 
 def laq_score_kernel(n_inst: int, Hq: int, Hkv: int, d: int, L: int, W: int, dtype: torch.dtype,
                      q_pos: Optional[Sequence[int]] = None, keep: Optional[int] = None,
-                     kv_strides: Tuple[int, int, int] = (0, 0, 0), paged=None, choose: str = "auto") -> str:
+                     kv_strides: Tuple[int, int, int] = (0, 0, 0), paged=None, choose: str = "auto",
+                     whole_heads: bool = False) -> str:
     """How laq_score reads K for this shape on the current device: "vector" (fp32 and head sizes other than 64
     and 128, K read twice), "two-pass" (bf16, K read twice) or "single-read" (bf16, K read once by teams of
-    workgroups).  Heads of at most 1024 keys that a workgroup holds whole are read once in any case."""
+    workgroups); with whole_heads also "whole-head" (heads of at most 1024 keys, K read once by a workgroup per
+    head).  Without, such a call has the name of the kernels that read its K twice, which choose="two-pass" takes."""
     code = LAQ_F32 if dtype == torch.float32 else LAQ_BF16
     sh = _shape(n_inst, Hq, Hkv, d, L, W, code, 0.0, q_pos, keep, "max", kv_strides, paged, choose)
     rc = int(load_library().laq_score_kernel(ctypes.byref(sh)))
+    if SCORE_KERNELS[max(rc, 0)] == "whole-head" and not whole_heads:
+        sh.score_choice = 1                # two-pass
+        rc = int(load_library().laq_score_kernel(ctypes.byref(sh)))
     if rc < 0:
         raise LaqError(rc, "laq_score_kernel")
     return SCORE_KERNELS[rc]

@@ -681,6 +681,7 @@ int laq_score_kernel(const laq_shape* shape) {
   if (rc != LAQ_OK) return rc;
   laq::KvLayout lay;
   if (laq::make_layout(shape, g, &lay) != LAQ_OK) return LAQ_ERR_INVALID;
+  if (laq::head_wanted(shape, g)) return LAQ_KERNEL_WHOLE_HEAD;
   if (!laq::usual_shape(g, lay, shape->dtype)) return LAQ_KERNEL_VECTOR;
   bool single = false;
   if (laq::SINGLE_READ_ENABLED && laq::single_read_wanted(shape, g) &&

@@ -282,3 +282,24 @@ def test_bench_refuses_more_than_one_gpu(repo_root):
                          text=True, timeout=120)
     assert res.returncode == 2
     assert "single-GPU" in res.stderr and res.stdout.strip() == ""
+
+
+def test_which_calls_a_workgroup_per_head_takes():
+    """laq_score_kernel follows the choice that laq_score makes: either side of the longest heads by type and head size, of the
+    numbers of heads and of score rows, and a call of enough keys for the single-read kernel."""
+    bf, f32 = torch.bfloat16, torch.float32
+
+    def names(*shape, **kw):
+        return tuple(laq.laq_score_kernel(*shape, whole_heads=whole, **kw) for whole in (True, False))
+
+    taken, two, vector = ("whole-head", "two-pass"), ("two-pass", "two-pass"), ("vector", "vector")
+    assert names(1, 8, 2, 128, 512, 8, bf) == taken and names(1, 8, 2, 128, 769, 8, bf) == two
+    assert names(1, 8, 8, 64, 768, 8, bf) == taken and names(1, 8, 1, 64, 768, 9, bf) == two                 # 64, 72 score rows
+    assert names(9, 8, 8, 128, 1024, 8, bf) == taken and names(9, 8, 8, 128, 1025, 8, bf) == two
+    assert names(96, 8, 8, 64, 1024, 8, bf) == taken and names(769, 1, 1, 64, 1000, 8, bf) == two
+    assert names(256, 32, 8, 128, 512, 8, bf) == taken                                                      # 256 MiB of keys
+    assert names(256, 32, 8, 128, 512, 8, bf, choose="two-pass") == two
+    assert names(1, 4, 2, 64, 512, 8, f32) == ("whole-head", "vector") and names(1, 4, 2, 64, 800, 8, f32) == vector
+    assert names(17, 1, 1, 128, 512, 8, f32) == ("whole-head", "vector") and names(16, 1, 1, 128, 512, 8, f32) == vector
+    assert names(1, 8, 1, 256, 512, 32, bf) == ("whole-head", "vector") and names(1, 8, 1, 256, 512, 33, bf) == vector
+    assert names(1, 8, 2, 256, 513, 8, bf) == vector
