@@ -55,7 +55,7 @@ def read_traffic(workload):
 
 SCORE_STAGE_KERNELS = ("wave_stats_kernel", "wave_score_kernel", "row_constants", "pool_boundaries", "fused_kernel",
                        "fused_reset", "window_table_kernel", "tile_stats_kernel", "tile_score_kernel", "pool_kernel",
-                       "pool_quads_kernel")
+                       "pool_quads_kernel", "head_kernel")
 
 
 DECODE_KERNELS = ("decode_kernel",)
@@ -65,7 +65,7 @@ LIVE_TRAFFIC_FAILED = []                   # why a profiled child run of this pr
 def live_traffic(args, cfg_id, kernels=SCORE_STAGE_KERNELS):
     """(HBM bytes per score-stage launch, source) measured now, or (None, why not).  Two short runs of this
     script as child processes under rocprofv3 (--pmc FETCH_SIZE, then WRITE_SIZE: one counter per run, 3
-    steps each, same workload flags), each counter scaled by what it reads in the same run for a 1 GiB
+    steps each, same workload flags, --score-only: laq_evict's launches of the same kernels may do more), each counter scaled by what it reads in the same run for a 1 GiB
     device-to-device copy; per kernel the average over its dispatches, summed over the kernels of the
     score stage.  The child runs start the single-read kernel with an ordinary launch
     (LAQ_COOPERATIVE_LAUNCH=0): a process profiled by rocprofv3 does not survive a cooperative one."""
@@ -91,7 +91,7 @@ def live_traffic(args, cfg_id, kernels=SCORE_STAGE_KERNELS):
             out_dir = os.path.join(tmp, counter)
             cmd = ["rocprofv3", "--pmc", counter, "--output-format", "csv", "-d", out_dir, "-o", "t", "--",
                    sys.executable, os.path.abspath(__file__), "--no-cpu-baseline", "--no-probe", "--no-extra",
-                   "--calibrate-copy", "--steps", "3", "--warmup", "1"] + flags
+                   "--calibrate-copy", "--score-only", "--steps", "3", "--warmup", "1"] + flags
             try:
                 res = subprocess.run(cmd, cwd="/tmp", env=env, capture_output=True, text=True, timeout=100)
             except (subprocess.TimeoutExpired, OSError) as err:
@@ -127,6 +127,7 @@ SCORE_KERNEL_TEXT = {
                 "tile_score_kernel + pool_quads_kernel in small calls (K counted once in the algorithmic bytes, read twice)",
     "vector": "laq_score stage: wave_stats_kernel + wave_score_kernel, or tile_stats_kernel + tile_score_kernel in small calls, + "
               "pool_quads_kernel (K counted once in the algorithmic bytes, read twice)",
+    "whole-head": "laq_score stage: head_kernel (a workgroup per head, K read once, the maximum pooled on the way)",
 }
 
 
@@ -247,6 +248,8 @@ def main():
                          "roofline.traffic -- (keeps profiler runs to the timed kernels)")
     ap.add_argument("--no-live-traffic", action="store_true",
                     help="take roofline.traffic from the committed counter summary instead of measuring it now")
+    ap.add_argument("--score-only", action="store_true",
+                    help="a step is laq_score alone (for counting the traffic of its kernels; not the benchmark)")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run one 1 GiB device-to-device tensor copy (a kernel of known traffic, "
                          "for scaling rocprofv3 FETCH_SIZE / WRITE_SIZE readings)")
@@ -344,9 +347,12 @@ def measure_evict(args, torch, laq, cfg, budgets, dev, steps, warmup, primary):
     keep_rows = cfg.W if keep is None else keep
     strides = (0, 0, 0) if k.is_contiguous() else (k.stride(0), k.stride(1), k.stride(2))
     score_kernel = laq.laq_score_kernel(n, cfg.Hq, cfg.Hkv, cfg.d, cfg.L, cfg.W, dt, q_pos, keep, strides,
-                                        paged=(paged["block_table"], 256, k_in.stride(0)) if paged else None)
+                                        paged=(paged["block_table"], 256, k_in.stride(0)) if paged else None, whole_heads=True)
 
     def step():
+        if args.score_only:
+            laq.laq_score(q, k_in, cfg.pool, scores=scores, ws=ws, q_pos=q_pos, keep=keep, pool_mode=args.pool_mode, **paged)
+            return
         laq.laq_evict(q, k_in, v_in, budgets, cfg.pool, scores=scores, idx=idx, k_out=k_out, v_out=v_out, ws=ws,
                       q_pos=q_pos, keep=keep, pool_mode=args.pool_mode, **paged)
 
