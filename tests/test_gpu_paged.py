@@ -4,8 +4,8 @@ oracle on the gathered dense cache (needs an MI355X).
 The library reads paged caches in laq_score, laq_compact and laq_evict; the oracle side gathers the
 cache into its dense form first (oracle.gather_paged, pinned on the CPU against an independent
 scatter).  Cases: a permuted table, a ragged last block, blocks shared between instances, blocks of
-several sizes, token-major blocks, fp32 and bf16 (the one-chunk kernels, the two streaming
-passes and the single-read kernel), and the dense call on the gathered cache as a bit-exact
+several sizes, token-major blocks, fp32 and bf16 (the kernels of small calls, the two
+passes over segments and the single-read kernel), and the dense call on the gathered cache as a bit-exact
 cross-check of scores, indices and rows.
 """
 import numpy as np
@@ -102,7 +102,7 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("choose", ["auto", "two-pass"])        # the one-chunk and the streaming kernels
+@pytest.mark.parametrize("choose", ["auto", "two-pass"])        # the kernels of small calls, and those that walk a segment
 @pytest.mark.parametrize("name,n,Hkv,G,L,W,d,block_rows,dtype,pool,tm,share", CASES, ids=[c[0] for c in CASES])
 def test_paged_cache(laq, name, n, Hkv, G, L, W, d, block_rows, dtype, pool, tm, share, choose):
     budgets = [min(L, 64 + 40 * i) for i in range(n)]
@@ -148,7 +148,7 @@ def test_paged_single_read_gives_the_dense_single_read_bits(laq):
 
 
 def test_paged_equals_dense_bit_for_bit_on_the_two_pass_kernels(laq):
-    # 128 score rows: dense and paged both take the two streaming passes, in the same order of sums
+    # 128 score rows: dense and paged both take the two passes, in the same order of sums
     n, Hkv, G, L, W, d = 2, 2, 4, 1800, 32, 128
     budgets = [200, 333]
     q, k, v, scores, idx, ko, vo = run_paged(laq, n, Hkv, G, L, W, d, 512, torch.bfloat16, 7, budgets, "paged-vs-dense",

@@ -190,7 +190,7 @@ EDGE = [
 ]
 
 
-# calls this small take the one-chunk kernels by themselves and the streaming ones on request
+# by themselves calls this small take a workgroup per head or per 256-key chunk; on request the kernels that walk a segment
 BOTH = pytest.mark.parametrize("choose", ["auto", "two-pass"])
 
 
@@ -234,11 +234,12 @@ def test_very_long_sequence(laq):
     run_and_check(laq, q, k, v, [1024], 7, "L131k")
 
 
-def test_many_heads_dynamic_runs_and_one_unit_tail(laq):
-    # 513 short heads = 8721 units per pass: enough for the streaming kernels to hand out the tail of
-    # the work in runs of 4 through their counter, and 8721 - 512*10 = 4*900 + 1 leaves a last run of
-    # one unit (on a device that holds 512 workgroups).  Sampled heads against the oracle, invariants
-    # on everything, and the same bits on a second call.
+@BOTH
+def test_many_heads_dynamic_runs_and_one_unit_tail(laq, choose):
+    # 513 heads of 33 blocks of 128 keys, 540 MB of keys: the single-read kernel's teams take many heads each, the last
+    # one alone (auto); 16929 blocks are enough for the two passes to cut heads by a number of blocks per segment rather than
+    # to fit the resident workgroups, the last segment shorter (two-pass).  Sampled heads against the oracle,
+    # invariants on everything, and the same bits on a second call.
     n, Hq, Hkv, d, L, W, pool, budget = 57, 18, 9, 128, 4100, 16, 7, 300
     G = Hq // Hkv
     gen = torch.Generator(device=DEV).manual_seed(2024)
@@ -246,9 +247,10 @@ def test_many_heads_dynamic_runs_and_one_unit_tail(laq):
     k = torch.randn(n, Hkv, L, d, generator=gen, device=DEV).bfloat16()
     v = torch.randn(n, Hkv, L, d, generator=gen, device=DEV).bfloat16()
     budgets = [budget] * n
-    scores, idx, ko, vo = laq.laq_evict(q, k, v, budgets, pool)
-    raw = laq.laq_score(q, k, 1)
-    again = laq.laq_evict(q, k, v, budgets, pool)
+    assert laq.laq_score_kernel(n, Hq, Hkv, d, L, W, k.dtype, choose=choose) == ("single-read" if choose == "auto" else choose)
+    scores, idx, ko, vo = laq.laq_evict(q, k, v, budgets, pool, choose=choose)
+    raw = laq.laq_score(q, k, 1, choose=choose)
+    again = laq.laq_evict(q, k, v, budgets, pool, choose=choose)
     torch.cuda.synchronize()
     for x, y in zip((scores, idx, ko, vo), again):
         assert torch.equal(x, y)
@@ -256,7 +258,7 @@ def test_many_heads_dynamic_runs_and_one_unit_tail(laq):
     assert (scores >= raw).all() and (raw >= 0).all()
     idx_l = split_packed(idx.cpu(), budgets, Hkv, L)
     ko_l = split_packed(ko.cpu(), budgets, Hkv, L)
-    for (i, g) in [(0, 0), (22, 4), (39, 8), (56, 8)]:       # first, middle (static / claimed runs), very last head
+    for (i, g) in [(0, 0), (22, 4), (39, 8), (56, 8)]:       # first, middle, very last head
         print("many-heads sample", i, g, flush=True)
         qc, kc = q[i, g * G:(g + 1) * G].cpu(), k[i, g:g + 1].cpu()
         r = oracle.raw_scores(qc, kc)

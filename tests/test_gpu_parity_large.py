@@ -2,7 +2,7 @@
 
 The kernels pick different instantiations by the size of a call: the selection kernel built for
 two workgroups per compute unit from 768 (instance, KV head) pairs on, the one-workgroup-per-cache
-decode kernel from 1024 workgroups on, the streaming kernels' claimed runs with thousands of units.
+decode kernel from 1024 workgroups on, the two passes over segments with thousands of blocks.
 These cases reach them at their real sizes: oracle comparison on a spread of (instance, head)
 pairs, and on every head the properties that hold at any size.
 """
