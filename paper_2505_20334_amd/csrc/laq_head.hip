@@ -1,6 +1,6 @@
 // A whole head in one workgroup: scores, pooling, selection and gather of a short cache in one launch.
 //
-// A workgroup of 4, 8 or 16 waves holds all keys of one KV head in registers (operand layout, up to two tiles of 32
+// A workgroup of 8 or 16 waves holds all keys of one KV head in registers (operand layout, up to two tiles of 32
 // per wave), K is read once, and nothing leaves the workgroup between the steps:
 //   (m, z) of every score row per wave -> LDS -> c = M + log2 Z -> products again, sum of exp2(s - c) over the rows ->
 //   raw scores in LDS -> one position per thread: pooled, ranked (counted in bins), listed -> gather.
@@ -62,7 +62,7 @@ __device__ __forceinline__ f32x16 product_raw(u32x4 (&key)[NP], const char* lds,
 
 // `gather`: with selection and gather (laq_evict), else scores only.  fin.half: pooling of the scores, 0 for none.
 template <typename T, int NP, bool FULL, int WAVES, int TPW, typename TAB>
-__global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 4) void head_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, HeadPlan pl, bool gather,
+__global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, HeadPlan pl, bool gather,
                                                               const T* __restrict__ q, const T* __restrict__ k, TAB tab,
                                                               int inst0, int32_t* __restrict__ idx, FinishArgs fin, int* __restrict__ status) {
   constexpr int THREADS = WAVES * 64;

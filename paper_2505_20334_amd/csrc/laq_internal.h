@@ -130,7 +130,7 @@ struct FinishArgs : PoolArgs {
   int32_t row_bytes, src_row_bytes, elem_bytes;
   KvLayout lay;
 };
-constexpr int SELECT_POOL_MAX_HALF = 8;         // widest pooling it does: two quads of scores beside a lane's own on either side
+constexpr int SELECT_POOL_MAX_HALF = 8;         // widest pooling it does (laq_pool.h): two quads of scores beside a lane's own on either side
 constexpr int SELECT_POOL_MAX_KEYS = 32 * 1024; // longest prefix it pools
 constexpr int SELECT_MANY_HEADS = 768;          // heads of a launch from which on several workgroups share a compute unit,
 constexpr int SELECT_POOL_MANY_KEYS = 8 * 1024; // and the longest prefix it pools there (a longer one leaves no registers for it)

@@ -7,9 +7,8 @@
 
 namespace laq {
 
-// Scores are never negative: a zero stands for "not in the window", and leaves a maximum and an ascending sum as they are.
-constexpr int POOL_QUAD_MAX_HALF = 8;            // widest window: two quads beside a lane's own on either side
-
+// Windows of up to SELECT_POOL_MAX_HALF scores to either side.  Scores are never negative: a zero stands for "not in the window",
+// and leaves a maximum and an ascending sum as they are.
 __device__ __forceinline__ float lane_before(float old, float x) {       // lane l: x of lane l - 1; lane 0: old
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), 0x138, 0xf, 0xf, false));
 }

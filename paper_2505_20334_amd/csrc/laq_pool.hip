@@ -135,7 +135,7 @@ hipError_t launch_pool_boundaries(const ScoreGeom& g, int half, int nchunk, int 
 hipError_t launch_pool(const ScoreGeom& g, int pool, bool avg, const float* raw, float* pooled, hipStream_t st) {
   const int half = (pool - 1) / 2;
   const unsigned heads = (unsigned)(g.n_inst * g.Hkv);
-  if (half <= POOL_QUAD_MAX_HALF) {
+  if (half <= SELECT_POOL_MAX_HALF) {
     hipLaunchKernelGGL(pool_quads_kernel, dim3(heads, (g.L + 3 + WORKGROUP_KEYS - 1) / WORKGROUP_KEYS), dim3(THREADS), 0, st, g.L, g.P, half, avg,
                        raw, pooled);
   } else {

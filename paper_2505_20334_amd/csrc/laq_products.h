@@ -22,7 +22,6 @@ constexpr float NEG_BIG = -1.0e30f;   // finite "minus infinity" for running max
 // with the exponents of its terms raised (above it, what is lost is less than a rounding).
 constexpr float TINY = 0x1p-90f;
 
-
 // Row index (0..31) of accumulator register i for a lane in half hf of the 32x32 output layout.
 __device__ __forceinline__ int acc_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
 

@@ -54,7 +54,7 @@ template <int WAVES> struct RankScratch {
 // 5.2 us in one wave, 3 to 7 us with sixteen waves and a barrier per four bits.)
 template <int WAVES>
 __device__ __forceinline__ int rank_position(RankScratch<WAVES>& sh, uint32_t key, int want, int lane, int wave) {
-  constexpr int THREADS = WAVES * 64, BITS = WAVES == 16 ? 10 : WAVES == 8 ? 9 : 8;
+  constexpr int THREADS = WAVES * 64, BITS = WAVES == 16 ? 10 : 9;
   static_assert(1 << BITS == THREADS, "one bin per thread");
   const int tid = threadIdx.x;
   {

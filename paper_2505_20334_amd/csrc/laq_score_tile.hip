@@ -17,39 +17,24 @@
 // What bounds it: latency, of two launches and of load -> LDS -> products -> reduction in each (8 heads x 4096 keys, bf16: 5.3 + 6.6 us);
 // fp32 pays the fp32 instruction's rate for both products, which larger calls do not (laq_score_wave.hip).
 #include "laq_internal.h"
+#include "laq_products.h"
 
 namespace laq {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
-constexpr float NEG_BIG = -1.0e30f;   // finite "minus infinity" for running maxima
 constexpr int WAVES = CHUNK_ROWS / 32, THREADS = WAVES * 64;
 // Row tiles of a chunk that are worked on side by side where there are too few chunks to fill the device.
 constexpr int MAX_SPLIT = 4;
 // Every workgroup of the second kernel folds the statistics of its head itself where that is little next to
 // its keys and the workgroups are few (one launch less); otherwise row_constants_kernel does it once.
 constexpr int FOLD_CHUNKS = 32, FOLD_WORKGROUPS = 512;
-// The exponential instruction returns 0 below 2^-126, where fp32 still tells scores apart: what it lost is added to a tile's sum
-// that is below TINY (above it, 32 such terms are less than a rounding).
-constexpr float TINY = 0x1p-90f;
-
-// Row index (0..31) of accumulator register i for a lane in half hf of the 32x32 output layout.
-__device__ __forceinline__ int acc_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
-
 // bytes between rows of the staged score rows: pairs of 16-byte pieces (the second half of the last one may be
 // padding, zeros) and one more, so that 128-bit reads of 16 consecutive rows fall on distinct banks
 __host__ __device__ inline int q_stride(int row_bytes) { return (row_bytes + 31) / 32 * 32 + 16; }
 
 // acc += A * B over one piece (16 bytes) per lane of either operand
-__device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 acc, uint16_t) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-}
+__device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 acc, uint16_t) { return mfma(a, b, acc); }
 __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 acc, float) {
   const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
 #pragma unroll
@@ -290,7 +275,7 @@ __global__ __launch_bounds__(THREADS, NP > 16 ? 2 : 4) void tile_score_kernel(Sc
       // (over both lanes' rows: one lane's may all pad, or not see the key)
       const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(tile_sum), __float_as_uint(tile_sum), false, false);
       const float both = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
-      if (__builtin_expect(__any(both < TINY && key < g.L), 0)) {
+      if (__builtin_expect(__any(both < TINY && key < g.L), 0)) {      // (what the exponential lost is added)
 #pragma unroll 1
         for (int i = 0; i < 16; ++i) {                   // (few instructions: what follows them is fetched sooner)
           const float x = fmaf(s[0], g.scale2, -rc[acc_row(i, c.hf)]);

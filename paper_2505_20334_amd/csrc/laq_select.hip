@@ -515,7 +515,7 @@ hipError_t launch_for(int n_inst, int inst0, int Hkv, int L, int keep, int pool,
   }
   return hipErrorInvalidValue;             // (the callers pool longer prefixes before)
 }
-static_assert(SELECT_POOL_MAX_KEYS == 1024 * 32 && SELECT_POOL_MAX_HALF == POOL_QUAD_MAX_HALF, "");
+static_assert(SELECT_POOL_MAX_KEYS == 1024 * 32, "");
 
 template <typename TAB>
 hipError_t finish_for(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const TAB& tab, int32_t* idx,
