@@ -399,7 +399,10 @@ __global__ __launch_bounds__(256) void row_constants_kernel(ScoreGeom g, const f
 // How a call's keys are cut into segments.  A segment costs its blocks and about three more (the score rows' way to LDS, the first keys'
 // to the registers).  Where a workgroup has few blocks, the cut with the least of that over the rounds of resident workgroups it takes
 // (and a little per segment, which the second kernel folds, or a launch that does): 64 heads x 8191 keys, fp32, 512 resident workgroups: 8, 16,
-// 32 segments (1, 2, 4 rounds) 122, 144, 169 us.  Where it has many, segments of 10 to 16 blocks, so that workgroups which get ahead of
+// 32 segments (1, 2, 4 rounds) 122, 144, 169 us.  More score rows than are staged together are other workgroups' in the first kernel, but
+// in the second the same one takes a group after the other: its rounds count that often (laq_evict, counted as in the first : so, 448 rows: bf16, d = 256,
+// 64 heads x 4000 284 : 207, d = 64 99.7 : 85.1, 300 x 1030 125 : 107; fp32, d = 96, 16 x 8000 220 : 173; 256 rows, d = 128, 64 x 4000 333 : 232).
+// Where a workgroup has many, segments of 10 to 16 blocks, so that workgroups which get ahead of
 // others take more of them: 1800 heads x 20259 keys, d = 64: 1, 3, 5, 16, 80 segments 2047, 1936, 1862, 1844, 2102 us.
 WavePlan plan_of(const ScoreGeom& g, int resident, int lds, int stride) {
   WavePlan pl;
@@ -419,8 +422,8 @@ WavePlan plan_of(const ScoreGeom& g, int resident, int lds, int stride) {
     for (const double share : {0.0, 0.25, 0.35, 0.5, 0.7, 1.0, 1.5, 2.0, 3.0}) {
       const int s = std::max(1, std::min(most, (int)(share * resident / heads)));
       const int sb = (blocks + s - 1) / s, used = (blocks + sb - 1) / sb;
-      const long long rounds = (heads * used * pl.groups + resident - 1) / resident;
-      const double cost = rounds * (sb + 3.0) + 0.1 * sb + 0.12 * used + (used > FOLD_SEGMENTS ? 3.0 : 0.0);
+      const long long first = (heads * used * pl.groups + resident - 1) / resident, second = (heads * used + resident - 1) / resident * pl.groups;
+      const double cost = 0.5 * (first + second) * (sb + 3.0) + 0.1 * sb + 0.12 * used + (used > FOLD_SEGMENTS ? 3.0 : 0.0);
       if (cost < least) { least = cost; best = s; }
     }
   }

@@ -21,6 +21,8 @@ CASES = [
     (BF16, 17, 12, 4, 96, 257, 33), (BF16, 17, 12, 4, 256, 300, 33), (BF16, 17, 8, 4, 40, 260, 50), (BF16, 17, 8, 4, 200, 511, 50),
     (F32, 65, 4, 2, 64, 65, 8), (F32, 33, 8, 4, 96, 130, 33), (F32, 33, 8, 4, 128, 97, 24), (F32, 43, 3, 3, 8, 140, 33),
     (F32, 33, 8, 4, 104, 129, 12), (F32, 1, 2, 1, 128, 33000, 20), (F32, 1, 3, 1, 128, 33100, 70),
+    # several groups of row tiles: as many segments as the second kernel, which takes one group after the other, has use for
+    (F32, 100, 4, 2, 64, 600, 65), (F32, 65, 4, 2, 128, 400, 100), (BF16, 200, 4, 2, 64, 400, 65),
 ]
 
 
