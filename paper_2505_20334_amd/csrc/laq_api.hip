@@ -241,13 +241,31 @@ enum class ScorePath { single_read, head, tile, wave };
 //   bf16, d = 256   1 x 48 26.0 : 28.7, 1 x 3752 212 : 216, 2 x 396 45.6 : 47.6, 2 x 4360 307 : 292, 4 x 140 39.9 : 36.2
 //   fp32            1 x 72 24.9 : 25.2, 1 x 256 46.5 : 45.7, 2 x 38 34.2 : 36.3, 2 x 148 45.4 : 40.1, 4 x 24 28.3 : 32.7, 4 x 268 114.1 : 96.5
 // fp32 with d > 128 always (the others have no registers for the parts of 32 such keys).
+// Long heads, so few that a workgroup per chunk is one round of them, by row tiles x chunks in 4 heads: fp32, d = 128   1 x 252 38 : 45,
+//   4 x 252 67 : 74; 1, 4 x 268 .96, 1.16 (these over the others); d = 96   1 x 252 34 : 38; d = 256   1 x 376 .87, 4 x 252 41 : 47, 4 x 376 .91;
+//   in 8 heads 4 x 264 1.15.  More than eight row tiles, d = 256: 96 to 8000 chunks .82-.95.
+// The other head sizes share one variant of the others for up to 256 (fp32: 128) elements; these have eight.  These over the others:
+//   bf16, d = 8 to 112   1, 2 tiles .74-1.06, 4 .67-1.07, 8 .70-1.13, 14 .76-1.08; but heads of half a chunk, 4 and 14 tiles, 100 heads and more 1.0-1.28
+//   bf16, d = 136 to 232   1 tile, up to 1500 chunks .77-1.07; 2, 4 tiles, up to 320 chunks .66-1.05, 512 .83-.94, 640 to 1500 .97-1.20 (900 heads of one chunk .83-.95), 8000 1.1-1.28;
+//                   7, 8 tiles, up to 1024 chunks .66-1.08, 8000 1.02-1.17; 14 tiles .73-1.07; half a chunk, 4 and 14 tiles, d = 136 .89-1.25, 232 .82-1.04
+//   fp32, d = 8, 16   .71-1.10, half a chunk and 4, 14 tiles .93-1.62;  d = 40   1 tile .69-1.04, 2 tiles 8 heads x 288 .97, 640 on 1.03-1.14, 4 tiles 4 heads
+//                   x 256 .72, 8 heads x 192, 288 1.05, 1.06, 640 on 1.16-1.34;  d = 88, 112   1 tile, up to 512 chunks .74-1.06, 640 on 1.02-1.15; 2 tiles and
+//                   more, 8 heads and more x 192 on 1.02-1.5;  1 to 6 heads, all types, up to 500 chunks .66-.98, 512 to 564 .75-.96, 780 to 940 .80-1.16,
+//                   1096 on .92-1.14
 static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
   if (!score_wave_supported(g, shape->dtype)) return true;
-  if (shape->score_choice != LAQ_CHOOSE_AUTO && shape->dtype == LAQ_BF16 && (g.d == 64 || g.d == 128)) return false;
-  const long long chunks = (long long)g.n_inst * g.Hkv * g.nchunk;
+  const bool f32 = shape->dtype == LAQ_F32;
+  if (shape->score_choice != LAQ_CHOOSE_AUTO && !f32 && (g.d == 64 || g.d == 128)) return false;
+  const long long heads = (long long)g.n_inst * g.Hkv, chunks = heads * g.nchunk;
   const int tiles = g.Rpad / 32;
-  if (shape->dtype == LAQ_F32) return chunks <= 128;
-  if (g.d > 128) return tiles == 1 || (tiles == 2 && chunks <= 512) || chunks <= 64;
+  const bool half = 2 * g.L <= CHUNK_ROWS;               // (half of a workgroup's waves have no keys)
+  if (!score_wave_own_size(g, shape->dtype) && !(half && tiles > 2 && (f32 || g.d < 200))) {
+    if (heads < 8 && chunks <= 1024) return true;
+    if (f32 && (g.d <= 32 || (tiles == 1 && (g.d < 64 || chunks <= 512)))) return true;
+    if (!f32 && (g.d < 128 || tiles > 8 || g.nchunk == 1 || chunks <= (tiles > 4 ? 4096 : 512))) return true;
+  }
+  if (f32) return chunks <= 128 || (heads < 8 && chunks > 192 && chunks <= 256 && (tiles <= 4 || g.d > 96));
+  if (g.d > 128) return tiles == 1 || (tiles > 8 && !half) || chunks <= 64 || (chunks <= 512 && (tiles == 2 || heads < 8));
   if (tiles == 1) return chunks <= 512 && g.nchunk <= 32;
   return tiles > 2 && chunks <= 64;
 }

@@ -189,6 +189,7 @@ hipError_t launch_score_tile(const ScoreGeom& g, const WindowPos& qp, const KvLa
                              const void* k, float* raw, const Workspace& ws, hipStream_t st);
 hipError_t score_tile_init();
 bool score_wave_supported(const ScoreGeom& g, int dtype);
+bool score_wave_own_size(const ScoreGeom& g, int dtype);      // a head size that these kernels have a variant of its own for
 hipError_t launch_score_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q,
                              const void* k, float* raw, const Workspace& ws, hipStream_t st);
 hipError_t score_wave_init();

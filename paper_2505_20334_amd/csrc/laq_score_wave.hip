@@ -485,6 +485,10 @@ hipError_t score_wave_init() {
 
 bool score_wave_supported(const ScoreGeom& g, int dtype) { return dtype == LAQ_BF16 || g.d <= 128; }
 
+bool score_wave_own_size(const ScoreGeom& g, int dtype) {
+  return g.d == 64 || g.d == 96 || g.d == 128 || (dtype == LAQ_BF16 && g.d == 256);
+}
+
 hipError_t launch_score_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q, const void* k,
                              float* raw, const Workspace& ws, hipStream_t st) {
   if (dtype == LAQ_F32) {

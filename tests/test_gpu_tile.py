@@ -34,8 +34,12 @@ CASES = [
     # more than 128 elements, two row tiles and 512 chunks, three and 64; fp32 and 128 chunks
     (BF16, 1, 32, 8, 128, 8192, 8, 7, "max", 100), (BF16, 1, 32, 8, 128, 8193, 8, 7, "max", 100), (BF16, 8, 8, 8, 64, 2048, 8, 7, "max", 100),
     (BF16, 9, 8, 8, 64, 2048, 8, 7, "avg", 100), (BF16, 8, 8, 8, 136, 2048, 33, 7, "max", 100), (BF16, 8, 8, 8, 136, 2049, 33, 7, "max", 100),
-    (BF16, 1, 8, 8, 136, 2048, 70, 7, "max", 100), (BF16, 1, 8, 8, 136, 2049, 70, 7, "max", 100), (F32, 1, 8, 8, 128, 4096, 4, 7, "max", 100),
+    (BF16, 1, 8, 8, 256, 2048, 70, 7, "max", 100), (BF16, 1, 8, 8, 256, 2049, 70, 7, "max", 100), (F32, 1, 8, 8, 128, 4096, 4, 7, "max", 100),
     (F32, 1, 8, 8, 128, 4097, 4, 7, "max", 100),
+    # long heads, so few that a workgroup per chunk is one round of them; more than eight row tiles of 256 elements
+    (F32, 1, 1, 1, 128, 49152, 4, 7, "max", 100), (F32, 1, 1, 1, 128, 49153, 4, 7, "avg", 100), (F32, 1, 1, 1, 128, 65536, 4, 7, "max", 100),
+    (F32, 1, 1, 1, 128, 65537, 4, 7, "max", 100), (BF16, 1, 1, 1, 256, 131072, 65, 7, "max", 100), (BF16, 1, 1, 1, 256, 131073, 65, 7, "max", 100),
+    (BF16, 1, 8, 8, 256, 2049, 256, 7, "max", 260), (BF16, 1, 8, 8, 256, 2049, 257, 7, "max", 260), (BF16, 9, 24, 8, 256, 127, 87, 7, "max", 120),
 ]
 
 
@@ -83,12 +87,12 @@ def test_a_nan_shows_in_the_scores_of_one_launch_as_in_those_of_several(pool, mo
 
 # (dtype, n, Hq, Hkv, d, W, choose), 480 to 700 keys; score rows that do not fill a tile of 32, and that do.  The first five take a
 # workgroup per head or (fp32, d = 128 beyond 512 keys) per chunk, the next four one per chunk, and the others the kernels that walk
-# a segment: d = 64 and 128 on request, the others with more than 128 chunks (fp32), 64 (d = 200, four row tiles) or two row
+# a segment: d = 64 and 128 on request, the others with more than 128 chunks (fp32), 512 (d = 104 and 200) or two row
 # tiles (d = 96); with 160 score rows, a second group of them
 ROWS = [(F32, 1, 2, 2, 64, 8, "auto"), (F32, 1, 28, 4, 128, 4, "auto"), (BF16, 1, 8, 2, 96, 7, "auto"), (BF16, 1, 8, 2, 128, 2, "auto"), (F32, 1, 4, 1, 64, 8, "auto"),
         (F32, 1, 2, 2, 64, 8, "two-pass"), (F32, 1, 4, 1, 200, 20, "two-pass"), (BF16, 1, 8, 2, 96, 7, "two-pass"), (BF16, 1, 8, 2, 200, 5, "two-pass"),
-        (BF16, 1, 8, 2, 64, 7, "two-pass"), (BF16, 2, 8, 2, 128, 40, "two-pass"), (BF16, 1, 8, 2, 96, 10, "two-pass"), (BF16, 17, 8, 2, 200, 25, "two-pass"),
-        (F32, 33, 4, 2, 64, 8, "two-pass"), (F32, 33, 4, 2, 104, 5, "two-pass"), (F32, 33, 8, 2, 128, 40, "two-pass"), (F32, 33, 8, 2, 96, 10, "two-pass")]
+        (BF16, 1, 8, 2, 64, 7, "two-pass"), (BF16, 2, 8, 2, 128, 40, "two-pass"), (BF16, 1, 8, 2, 96, 10, "two-pass"), (BF16, 86, 8, 2, 200, 25, "two-pass"),
+        (F32, 33, 4, 2, 64, 8, "two-pass"), (F32, 86, 4, 2, 104, 5, "two-pass"), (F32, 33, 8, 2, 128, 40, "two-pass"), (F32, 33, 8, 2, 96, 10, "two-pass")]
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
@@ -134,7 +138,7 @@ def test_a_key_whose_logits_are_all_minus_infinity(dtype, n, Hq, Hkv, d, W, choo
 # kernels that walk a segment, with one group of score rows and two
 @pytest.mark.parametrize("dtype,d,W,n,choose", [
     (F32, 64, 5, 1, "auto"), (F32, 128, 20, 1, "auto"), (F32, 200, 16, 1, "auto"), (BF16, 96, 20, 1, "auto"), (F32, 64, 5, 1, "two-pass"), (BF16, 96, 7, 1, "two-pass"),
-    (BF16, 64, 5, 1, "two-pass"), (BF16, 128, 20, 1, "two-pass"), (BF16, 128, 80, 1, "two-pass"), (BF16, 96, 20, 1, "two-pass"), (BF16, 200, 50, 17, "two-pass"),
+    (BF16, 64, 5, 1, "two-pass"), (BF16, 128, 20, 1, "two-pass"), (BF16, 128, 80, 1, "two-pass"), (BF16, 96, 20, 1, "two-pass"), (BF16, 200, 50, 130, "two-pass"),
     (F32, 64, 5, 33, "two-pass"), (F32, 104, 20, 33, "two-pass"), (F32, 128, 80, 33, "two-pass")])
 def test_probabilities_below_the_smallest_normal_number_stay_apart(dtype, d, W, n, choose):
     """Logits 0, -1/4, -1/2, ... -119.75 (exact in either type): a list that ends among the denormal scores."""

@@ -18,11 +18,16 @@ F32, BF16 = torch.float32, torch.bfloat16
 CASES = [
     (BF16, 1, 2, 1, 128, 31, 3), (BF16, 1, 2, 1, 128, 33, 16), (BF16, 2, 4, 2, 64, 127, 17), (BF16, 1, 8, 2, 128, 129, 32),
     (BF16, 1, 8, 1, 64, 1025, 33), (BF16, 1, 8, 1, 128, 8200, 16), (BF16, 1, 2, 1, 128, 20011, 8), (BF16, 130, 2, 1, 64, 160, 16),
-    (BF16, 17, 12, 4, 96, 257, 33), (BF16, 17, 12, 4, 256, 300, 33), (BF16, 17, 8, 4, 40, 260, 50), (BF16, 17, 8, 4, 200, 511, 50),
-    (F32, 65, 4, 2, 64, 65, 8), (F32, 33, 8, 4, 96, 130, 33), (F32, 33, 8, 4, 128, 97, 24), (F32, 43, 3, 3, 8, 140, 33),
-    (F32, 33, 8, 4, 104, 129, 12), (F32, 1, 2, 1, 128, 33000, 20), (F32, 1, 3, 1, 128, 33100, 70),
+    (BF16, 17, 12, 4, 96, 257, 33), (BF16, 17, 12, 4, 256, 300, 33), (BF16, 17, 8, 4, 40, 127, 50), (BF16, 65, 8, 4, 200, 511, 50),
+    (F32, 65, 4, 2, 64, 65, 8), (F32, 33, 8, 4, 96, 130, 33), (F32, 33, 8, 4, 128, 97, 24), (F32, 43, 3, 3, 8, 100, 70),
+    (F32, 33, 8, 4, 104, 129, 20), (F32, 1, 2, 1, 128, 33000, 20), (F32, 1, 3, 1, 128, 33100, 70),
     # several groups of row tiles: as many segments as the second kernel, which takes one group after the other, has use for
     (F32, 100, 4, 2, 64, 600, 65), (F32, 65, 4, 2, 128, 400, 100), (BF16, 200, 4, 2, 64, 400, 65),
+    # head sizes without a variant of their own, either side of the lines up to which a workgroup takes a chunk instead: short heads of three row tiles;
+    # fp32 from 33 elements and two row tiles on; one row tile and 64 elements, and bf16 of more than 128, from 513 chunks; five row tiles
+    (BF16, 17, 4, 4, 72, 128, 65), (BF16, 17, 4, 4, 72, 129, 65), (BF16, 17, 4, 4, 200, 128, 65), (F32, 33, 4, 4, 16, 128, 65), (F32, 33, 4, 4, 16, 129, 65),
+    (F32, 17, 8, 8, 32, 200, 65), (F32, 17, 8, 8, 40, 200, 65), (F32, 1, 7, 7, 72, 5000, 33), (F32, 1, 8, 8, 72, 4800, 33), (F32, 171, 1, 1, 72, 600, 5),
+    (F32, 170, 1, 1, 72, 600, 5), (BF16, 171, 1, 1, 136, 600, 70), (BF16, 170, 1, 1, 136, 600, 70), (BF16, 513, 1, 1, 136, 250, 70), (BF16, 171, 1, 1, 136, 600, 140),
 ]
 
 
@@ -53,7 +58,7 @@ def test_fp32_infinities_and_nans_are_those_of_whole_products(d):
     floats instead.  A key whose logits are all -inf gets the score 0 and leaves the others alone; one whose logits are +inf, or
     that holds a NaN, makes the scores of its head NaN, and only those."""
     import paper_2505_20334_amd as laq
-    L, W = 33200, 4                          # 130 chunks
+    L, W = (262400 if d == 104 else 33200), 4      # 1025, 130 chunks
     g = torch.Generator().manual_seed(d)
     q, k = torch.randn(1, 2, W, d, generator=g).abs(), torch.randn(1, 1, L, d, generator=g)
     pos = [L + w for w in range(W)]
@@ -89,7 +94,7 @@ def test_fp32_products_of_parts_are_no_further_from_64_bits(n, L, d):
 
 # (heads, keys, d): fp32 calls that a workgroup per head takes, and calls of the kernels that walk a segment
 F32_SHORT = [(24, 500, 64), (300, 300, 64), (80, 1000, 64), (80, 300, 128)]
-F32_LONG = [(65, 1100, 64), (65, 600, 96), (65, 600, 104), (65, 600, 128)]
+F32_LONG = [(65, 1100, 64), (65, 600, 96), (172, 600, 104), (65, 600, 128)]
 
 
 def _logit_errors(q, k):
