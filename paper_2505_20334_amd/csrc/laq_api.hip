@@ -273,16 +273,19 @@ static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
 // A workgroup for each head, with all its keys in registers.  Against the launches of the other kernels (laq_evict, us, the others : this one):
 //   up to 512 keys always: bf16, d = 128, 24 heads 20.3 : 10.1 (d = 64), 64 heads 21.1 : 16.3, 576 heads 47.3 : 25.8, 2000 heads, 128 rows 314 : 226,
 //   6016 heads 392 : 285; fp32, d = 64, 192 heads 30.2 : 24.9; but fp32 of more than 64 elements in few heads 6 heads 32.7 : 39.7, 16 heads 33.6 : 35.1,
-//   80 heads 39.2 : 35.3; and many score rows in few 13 heads, 256 rows 42.2 : 53.4
+//   80 heads 39.2 : 35.3; and many score rows in few 13 heads, 256 rows 42.2 : 53.4; 128 rows, 4 to 24 heads x 330 1.03, 395 and 512 .87-.89, 40 heads x
+//   395 1.03 (the others over this one)
 //   up to 1024 keys (two tiles per wave, one workgroup per compute unit): 72 heads 32.5 : 28.7, 160 heads 33.8 : 25.3, 216 heads 45.0 : 28.9, 600 heads
 //   81.9 : 63.6; 992 heads 56.9 : 63.9, 1488 heads 111.9 : 121.3, 6912 heads 464 : 568; few heads, one or two row tiles 24 heads x 560 keys 20.1 : 13.3,
-//   16 x 768 22.2 : 19.7, 16 x 1024 24.4 : 27.2, 56 x 1024 23.9 : 25.6; more row tiles 64 x 714 32.7 : 34.5, 8 x 1024 26.0 : 32.1
+//   16 x 768 22.2 : 19.7, 16 x 1024 24.4 : 27.2, 56 x 1024 23.9 : 25.6; more row tiles 64 x 714 32.7 : 34.5, 8 x 1024 26.0 : 32.1; fp32, 2 to 64 heads, one
+//   row tile 600 keys 1.09-1.16, 768 .98-1.06; two 600 .92-.94, 768 .82-.85
 static bool head_wanted(const laq_shape* shape, const ScoreGeom& g) {
   if (shape->score_choice != LAQ_CHOOSE_AUTO || !head_supported(g, shape->dtype)) return false;
   const long long heads = (long long)g.n_inst * g.Hkv;
-  if (shape->dtype == LAQ_F32 && ((g.d > 64 && heads <= 16) || (g.Rpad > 128 && heads < HEAD_MANY))) return false;
+  const bool f32 = shape->dtype == LAQ_F32;
+  if (f32 && ((g.d > 64 && heads <= 16) || (g.Rpad > 128 && heads < HEAD_MANY) || (g.Rpad > 96 && heads < 40 && g.L > 384))) return false;
   if (g.L <= 512) return true;
-  return heads >= HEAD_MANY ? heads <= 768 : g.L <= 768 && g.Rpad <= 64;
+  return heads >= HEAD_MANY ? heads <= 768 : g.L <= 768 && g.Rpad <= (f32 ? 32 : 64);
 }
 
 static ScorePath score_path(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay) {

@@ -303,3 +303,6 @@ def test_which_calls_a_workgroup_per_head_takes():
     assert names(17, 1, 1, 128, 512, 8, f32) == ("whole-head", "vector") and names(16, 1, 1, 128, 512, 8, f32) == vector
     assert names(1, 8, 1, 256, 512, 32, bf) == ("whole-head", "vector") and names(1, 8, 1, 256, 512, 33, bf) == vector
     assert names(1, 8, 2, 256, 513, 8, bf) == vector
+    assert names(1, 8, 1, 64, 384, 16, f32) == ("whole-head", "vector") and names(1, 8, 1, 64, 385, 16, f32) == vector      # 128 score rows
+    assert names(40, 8, 1, 64, 512, 16, f32) == ("whole-head", "vector") and names(39, 8, 1, 64, 512, 16, f32) == vector
+    assert names(1, 8, 2, 64, 768, 8, f32) == ("whole-head", "vector") and names(1, 8, 2, 64, 513, 9, f32) == vector          # 32, 36
