@@ -124,8 +124,8 @@ typedef struct laq_shape {
   /*
    * Which scoring kernels to take where more than one applies (laq_score_choice; 0 = LAQ_CHOOSE_AUTO:
    * the single-read kernel for at most 64 score rows per KV head from 128 MiB of keys per call on,
-   * otherwise two passes over the keys, which are the faster ones with more rows, in small calls of
-   * bf16 with one chunk of 256 keys per workgroup, or, for heads of at most 512 keys and many of at most
+   * otherwise two passes over the keys, which are the faster ones with more rows, in small calls and for unusual
+   * head sizes with one chunk of 256 keys per workgroup, or, for heads of at most 512 keys and many of at most
    * 1024, a whole head in one workgroup).  A choice that does not apply to the shape is ignored;
    * laq_score_kernel() tells what a call will run.
    */
@@ -193,8 +193,8 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *   ws / ws_bytes  device scratch of at least laq_workspace_bytes(shape)
  * Supported: dtype BF16 or F32; any Hq/Hkv/W/L within the limits of laq_shape;
  * pool_kernel odd, 1 <= pool_kernel <= 63.  Short heads are scored by one workgroup each, K read once;
- * small calls by one workgroup per chunk of 256 keys, larger ones by workgroups that walk a segment of a head's
- * keys (BF16 with d = 64 or 128, W <= 512 and score_choice LAQ_CHOOSE_TWO_PASS: always these), with the same
+ * small calls, and most calls of other head sizes than 64, 96, 128 and (BF16) 256, by one workgroup per chunk of 256 keys, larger
+ * ones by workgroups that walk a segment of a head's keys (BF16 with d = 64 or 128, W <= 512 and score_choice LAQ_CHOOSE_TWO_PASS: always these), with the same
  * results to within the rounding of their fp32 sums; all of them on the matrix cores.  F32: with the fp32
  * instruction, or as six products of bf16 parts, which give the product of two elements to within 2^-24 of it, summed in
  * fp32; dot products of dense rows are closer to their value than the instruction's, those of rows with a single

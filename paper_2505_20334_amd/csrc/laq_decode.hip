@@ -31,10 +31,11 @@ namespace {
 
 constexpr float DEC_NEG_BIG = -1.0e30f;
 constexpr int DEC_THREADS = 256, DEC_WAVES = DEC_THREADS / 64;
-// Parts: as many workgroups as the device holds at once, three per compute unit (more make a second wave of workgroups and
-// longer folding: 128 caches of 2048 rows, 8 heads, take 41 us in 768 workgroups and 46 in 1408), but no parts
+// Parts: for about three workgroups per compute unit, which is what it holds of most kernels here (110 to 136 registers: three or four)
+// and fewer than make the folding long (128 caches of 2048 rows, 8 heads, take 41 us in 768 workgroups and 46 in 1408), but no parts
 // shorter than a turn of the workgroup's lane groups; at most DEC_MOST_PARTS of one cache, since one
-// workgroup folds them.
+// workgroup folds them.  The parts of a call have one length, and what remains of a cache is a part too: 32 caches of 2048 to
+// 128 rows, 8 heads, make 856 workgroups of 5 to 384 rows.
 constexpr long long DEC_WORKGROUPS = 768;
 constexpr int DEC_PART_STEP = 64;
 constexpr int DEC_MOST_PARTS = 128;

@@ -96,8 +96,8 @@ __global__ __launch_bounds__(256) void pool_kernel(int L, int P, int half, bool 
   }
 }
 
-// Pooled scores of the prefix keys whose pooling window crosses a boundary between two chunks of
-// the scoring kernels, from the edge records (per chunk: raw scores of its first 2*half rows, then of its last
+// Pooled scores of the prefix keys whose pooling window crosses a boundary between two workgroups (`chunks` of chunk_rows keys) of
+// the single-read scoring kernel, from the edge records (per chunk: raw scores of its first 2*half rows, then of its last
 // 2*half rows).  The boundary before chunk c lies at key b = c * chunk_rows and the keys
 // b-half .. b+half-1 are pooled here, one per thread; blockIdx.x is the head.
 __global__ __launch_bounds__(256) void pool_boundaries_kernel(int L, int P, int half, int nchunk, int chunk_rows,

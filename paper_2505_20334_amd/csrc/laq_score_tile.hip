@@ -1,7 +1,8 @@
 // Scoring, one 256-key chunk per workgroup: every head size up to 256 and any number of score rows, fp32 or
 // bf16, on the matrix cores (v_mfma_f32_32x32x2_f32, v_mfma_f32_32x32x16_bf16: products of the stored values,
 // fp32 sums).  Used for small calls: a workgroup per chunk, and up to four for its row tiles, fill the device where the
-// segments of laq_score_wave.hip would not.
+// segments of laq_score_wave.hip would not; and for most calls of head sizes that those kernels have no variant of their own for
+// (tile_wanted() has both sides' times).
 //
 // Two kernels: (1) per-row softmax statistics (m, z) of each chunk, (2) after folding the statistics of a
 // head's chunks (by every workgroup itself when they are few, else by row_constants_kernel), the sum over
