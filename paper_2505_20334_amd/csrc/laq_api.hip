@@ -46,10 +46,6 @@ static int make_geom(const laq_shape* s, ScoreGeom* g, QueryPos* qp = nullptr) {
   g->nchunk = (s->L + CHUNK_ROWS - 1) / CHUNK_ROWS;
   const float sc = s->scale > 0.f ? s->scale : 1.0f / sqrtf((float)s->d);
   g->scale2 = sc * 1.44269504088896340736f;
-  int exponent = 0;
-  frexpf(g->scale2, &exponent);
-  g->shift = s->dtype == LAQ_F32 ? 27 + exponent : 0;
-  g->shifted_scale2 = ldexpf(g->scale2, -g->shift);
   return LAQ_OK;
 }
 

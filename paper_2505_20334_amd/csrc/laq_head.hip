@@ -79,6 +79,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
   const int row_bytes = FULL ? NP * 32 : g.d * (int)sizeof(T);
   const int plane = plane_bytes(row_bytes / (int)sizeof(T)), stride = row_stride<T>(row_bytes / (int)sizeof(T));
   const char* head_rows = reinterpret_cast<const char*>(q + hg * g.R * g.d);
+  const RowScale<T> row_scale(g.scale2);
   auto key_row = [&](int key0) {
     int r0 = key0;
     const char* p = reinterpret_cast<const char*>(k + (lay.table ? 0 : (int64_t)inst * lay.inst) + (int64_t)head * lay.head);
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
   for (int r = tid; r < tiles * 32; r += THREADS) last[r] = last_visible_key(g, qp, min(r, g.R - 1) % g.W);
   for (int i = tid; i < THREADS + 2 * MARGIN; i += THREADS) raw[i] = 0.f;
   rank.bins[tid] = 0;
-  stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, 0, min(pl.group_tiles, tiles) * 32, g.shift);
+  stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, 0, min(pl.group_tiles, tiles) * 32, row_scale.shift);
   __syncthreads();
   const char* rows = smem + n32 * stride + hf * 16;
   // ---- statistics ----
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
     const int ntile = min(pl.group_tiles, tiles - rt0);
     if (rt0 > 0) {
       __syncthreads();
-      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32, g.shift);
+      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
       __syncthreads();
     }
 #pragma unroll 1
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
       for (int i = 0; i < TPW; ++i) {
         const int key0 = (i * WAVES + wave) * 32;
         if (key0 >= g.L) continue;
-        float m, z, scale = g.shifted_scale2;
+        float m, z, scale = row_scale.scale2;
         f32x16 s = product_raw<T, NP, FULL, true>(key[i], rows + rt * 32 * stride, plane, plane / 32);
 #pragma unroll 1
         for (bool again = false;; again = true) {
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
     const int ntile = min(pl.group_tiles, tiles - rt0);
     if (pl.groups > 1) {
       __syncthreads();
-      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32, g.shift);
+      stage_rows<T, FULL, THREADS>(smem, head_rows, row_bytes, plane, stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
       __syncthreads();
     }
 #pragma unroll 1
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
         for (int gq = 0; gq < 4; ++gq) {
           const f32x4 c = *reinterpret_cast<const f32x4*>(rowc + (rt0 + rt) * 32 + 8 * gq + 4 * hf);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sum[i] += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + e], g.shifted_scale2, -c[e]));
+          for (int e = 0; e < 4; ++e) sum[i] += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + e], row_scale.scale2, -c[e]));
         }
       }
     }

@@ -35,13 +35,6 @@ struct ScoreGeom {
   int explicit_pos;   // 1: positions come from the QueryPos table instead
   int qmin;      // smallest last-visible key over the W queries: keys up to here need no mask
   float scale2;  // scale * log2(e): logits are kept in base-2 units
-  // fp32 score rows are split into bf16 parts times 2^shift; their products then take shifted_scale2 = scale2 * 2^-shift, which is 2^-28
-  // to 2^-27.  The parts of a float below 2^-103 reach numbers that bf16 does not hold or the matrix cores take for 0: an element loses
-  // less than 2^-126.  Times that scale and the other factor, a key or a staged element below 2^128, it is less than 2^-25 of an
-  // exponent whatever the magnitudes of keys, queries and scale.  What is larger is infinite, and taken from whole floats; the
-  // products become infinite at exponents from 2^100 on, beyond the smallest maximum the kernels know.  bf16: 0 and scale2.
-  int shift;
-  float shifted_scale2;
 };
 
 // Last key each window query sees, where positions are explicit (already clamped to L-1); passed by value

@@ -90,8 +90,25 @@ __device__ __forceinline__ void merge_stat(float& M, float& Z, float2 p) {
   M = Mn;
 }
 
+// fp32 score rows are split into bf16 parts times 2^shift; their products then take scale2 * 2^-shift, which is 2^-28
+// to 2^-27.  The parts of a float below 2^-103 reach numbers that bf16 does not hold or the matrix cores take for 0: an element loses
+// less than 2^-126.  Times that scale and the other factor, a key or a staged element below 2^128, it is less than 2^-25 of an
+// exponent whatever the magnitudes of keys, queries and scale.  What is larger is infinite, and taken from whole floats; the
+// products become infinite at exponents from 2^100 on, beyond the smallest maximum the kernels know.  bf16: 0 and scale2.
+// (Made here from scale2: two more kernel arguments for all move the others' addresses, and the single-read kernel took 2 us of 289 longer.)
+template <typename T> struct RowScale {
+  int shift;
+  float scale2;
+  __device__ __forceinline__ explicit RowScale(float s) : shift(0), scale2(s) {
+    if constexpr (is_f32(T())) {
+      shift = 27 + __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(s));
+      scale2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(__builtin_amdgcn_frexp_mantf(s) * 0x1p-27f)));
+    }
+  }
+};
+
 // Score rows r0 .. r0 + n - 1 of a head to LDS, `stride` bytes apart (rows beyond R: the last one again); fp32: times
-// 2^shift (ScoreGeom::shift).
+// 2^shift (RowScale).
 template <typename T, bool FULL, int THREADS>
 __device__ __forceinline__ void stage_rows(char* lds, const char* head_rows, int row_bytes, int plane, int stride, int R, int r0, int n,
                                            int shift) {

@@ -199,9 +199,10 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
   const int group = blockIdx.x / pl.segs, seg = blockIdx.x - group * pl.segs;
   const int rt0 = group * pl.group_tiles, ntile = min(pl.group_tiles, g.Rpad / 32 - rt0);
   const Wave<T, NP, FULL> w(g, lay, q, k, seg, pl.seg_blocks);
+  const RowScale<T> row_scale(g.scale2);
   u32x4 key[NP];
   if (w.some) w.load(key, g, lay, w.first);
-  stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, g.shift);
+  stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
   float2* stat = reinterpret_cast<float2*>(smem + pl.group_tiles * 32 * w.stride);       // [row tile][wave][row]
   for (int i = threadIdx.x; i < ntile * WAVES * 32; i += THREADS) stat[i] = make_float2(NEG_BIG, 0.f);
   __syncthreads();
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
       const float2 old = *mine;
       float m, z;
       f32x16 s = op.template product<true>(rows, w.plane, w.plane / 32);
-      float scale = g.shifted_scale2;
+      float scale = row_scale.scale2;
 #pragma unroll 1
       for (bool again = false;; again = true) {
         if (!plain) {
@@ -301,6 +302,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
   const size_t hg = (size_t)blockIdx.z * g.Hkv + blockIdx.y;
   if (blockIdx.x == 0 && hg == 0 && tid == 0) *status = 0;    // (these kernels have no wait to give up)
   const Wave<T, NP, FULL> w(g, lay, q, k, blockIdx.x, pl.seg_blocks);
+  const RowScale<T> row_scale(g.scale2);
   float* out = raw + hg * g.L;
   u32x4 key[NP];
 #pragma unroll 1
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
     const int ntile = min(pl.group_tiles, g.Rpad / 32 - rt0);
     if (w.some) w.load(key, g, lay, w.first);
     if (rt0 > 0) __syncthreads();
-    stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, g.shift);
+    stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
     if (tid < ntile * 32) {
       const int row = rt0 * 32 + tid;
       last[tid] = last_visible_key(g, qp, min(row, g.R - 1) % g.W);
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
         for (int gq = 0; gq < 4; ++gq) {
           const f32x4 c = *reinterpret_cast<const f32x4*>(rowc + rt * 32 + 8 * gq + 4 * w.hf);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + i], g.shifted_scale2, -c[i]));
+          for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + i], row_scale.scale2, -c[i]));
         }
       }
       const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
