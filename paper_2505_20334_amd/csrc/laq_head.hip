@@ -23,6 +23,7 @@ constexpr int MARGIN = SELECT_POOL_MAX_HALF;
 struct HeadPlan {
   int group_tiles, groups;   // row tiles staged together
   int off_stat;              // bytes of the staged rows
+  RowScale row_scale;
 };
 
 // the product of 32 keys held as they lie in memory
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
   const int row_bytes = FULL ? NP * 32 : g.d * (int)sizeof(T);
   const int plane = plane_bytes(row_bytes / (int)sizeof(T)), stride = row_stride<T>(row_bytes / (int)sizeof(T));
   const char* head_rows = reinterpret_cast<const char*>(q + hg * g.R * g.d);
-  const RowScale<T> row_scale(g.scale2);
+  const RowScale row_scale = pl.row_scale;
   auto key_row = [&](int key0) {
     int r0 = key0;
     const char* p = reinterpret_cast<const char*>(k + (lay.table ? 0 : (int64_t)inst * lay.inst) + (int64_t)head * lay.head);
@@ -296,6 +297,7 @@ hipError_t launch_one(const ScoreGeom& g, const WindowPos& qp, const KvLayout& l
   pl.group_tiles = std::max(1, std::min(std::min(tiles, MAX_TILES), most / (32 * stride)));
   pl.groups = (tiles + pl.group_tiles - 1) / pl.group_tiles;
   pl.off_stat = pl.group_tiles * 32 * stride;
+  pl.row_scale = row_scale_of<T>(g.scale2);
   hipLaunchKernelGGL((head_kernel<T, NP, FULL, WAVES, TPW, TAB>), dim3(g.Hkv, n), dim3(WAVES * 64), pl.off_stat + stat, st, g, qp, lay, pl, gather, q, k,
                      tab, inst0, idx, fin, status);
   return hipGetLastError();

@@ -5,6 +5,8 @@
 // 2^-24 of the whole at most are left out.
 #pragma once
 
+#include <cmath>
+
 #include "laq_internal.h"
 
 namespace laq {
@@ -95,17 +97,18 @@ __device__ __forceinline__ void merge_stat(float& M, float& Z, float2 p) {
 // less than 2^-126.  Times that scale and the other factor, a key or a staged element below 2^128, it is less than 2^-25 of an
 // exponent whatever the magnitudes of keys, queries and scale.  What is larger is infinite, and taken from whole floats; the
 // products become infinite at exponents from 2^100 on, beyond the smallest maximum the kernels know.  bf16: 0 and scale2.
-// (Made here from scale2: two more kernel arguments for all move the others' addresses, and the single-read kernel took 2 us of 289 longer.)
-template <typename T> struct RowScale {
+// (An argument of its own: as members of the geometry they move the arguments of all kernels, and the single-read one took 2 us of 289 longer;
+// made in the kernels it costs registers, 800 fp32 heads of 300 keys 60 us instead of 57.)
+struct RowScale {
   int shift;
   float scale2;
-  __device__ __forceinline__ explicit RowScale(float s) : shift(0), scale2(s) {
-    if constexpr (is_f32(T())) {
-      shift = 27 + __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(s));
-      scale2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(__builtin_amdgcn_frexp_mantf(s) * 0x1p-27f)));
-    }
-  }
 };
+template <typename T> RowScale row_scale_of(float scale2) {
+  int exponent = 0;
+  if (is_f32(T())) frexpf(scale2, &exponent);
+  const int shift = is_f32(T()) ? 27 + exponent : 0;
+  return RowScale{shift, ldexpf(scale2, -shift)};
+}
 
 // Score rows r0 .. r0 + n - 1 of a head to LDS, `stride` bytes apart (rows beyond R: the last one again); fp32: times
 // 2^shift (RowScale).

@@ -185,6 +185,7 @@ struct WavePlan {
   int seg_blocks;          // blocks of BLOCK_KEYS keys each of them takes
   int group_tiles;         // row tiles staged together
   int groups;
+  RowScale row_scale;
 };
 
 // Waves per SIMD the kernels are built for: as many as their registers (and 32 of the score rows per workgroup in LDS) allow.
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
   const int group = blockIdx.x / pl.segs, seg = blockIdx.x - group * pl.segs;
   const int rt0 = group * pl.group_tiles, ntile = min(pl.group_tiles, g.Rpad / 32 - rt0);
   const Wave<T, NP, FULL> w(g, lay, q, k, seg, pl.seg_blocks);
-  const RowScale<T> row_scale(g.scale2);
+  const RowScale row_scale = pl.row_scale;
   u32x4 key[NP];
   if (w.some) w.load(key, g, lay, w.first);
   stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
@@ -302,7 +303,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
   const size_t hg = (size_t)blockIdx.z * g.Hkv + blockIdx.y;
   if (blockIdx.x == 0 && hg == 0 && tid == 0) *status = 0;    // (these kernels have no wait to give up)
   const Wave<T, NP, FULL> w(g, lay, q, k, blockIdx.x, pl.seg_blocks);
-  const RowScale<T> row_scale(g.scale2);
+  const RowScale row_scale = pl.row_scale;
   float* out = raw + hg * g.L;
   u32x4 key[NP];
 #pragma unroll 1
@@ -441,7 +442,8 @@ hipError_t launch_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& 
                        const Workspace& ws, hipStream_t st) {
   constexpr int per_simd = waves_per_simd<T, NP>();
   const int stride = row_stride<T>(g.d);
-  const WavePlan pl = plan_of(g, 256 * per_simd, (MAX_LDS / per_simd - STATIC_LDS) & ~255, stride);
+  WavePlan pl = plan_of(g, 256 * per_simd, (MAX_LDS / per_simd - STATIC_LDS) & ~255, stride);
+  pl.row_scale = row_scale_of<T>(g.scale2);
   const int rows = pl.group_tiles * 32;
   hipLaunchKernelGGL((wave_stats_kernel<T, NP, FULL>), dim3(pl.segs * pl.groups, g.Hkv, g.n_inst), dim3(THREADS),
                      rows * (stride + WAVES * (int)sizeof(float2)), st, g, qp, lay, pl, q, k, ws.part);
