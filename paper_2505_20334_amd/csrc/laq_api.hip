@@ -239,7 +239,8 @@ enum class ScorePath { single_read, head, tile, wave };
 // fp32 with d > 128 always (the others have no registers for the parts of 32 such keys).
 // Long heads, so few that a workgroup per chunk is one round of them, by row tiles x chunks in 4 heads: fp32, d = 128   1 x 252 38 : 45,
 //   4 x 252 67 : 74; 1, 4 x 268 .96, 1.16 (these over the others); d = 96   1 x 252 34 : 38; d = 256   1 x 376 .87, 4 x 252 41 : 47, 4 x 376 .91;
-//   in 8 heads 4 x 264 1.15.  More than eight row tiles, d = 256: 96 to 8000 chunks .82-.95.
+//   in 8 heads 4 x 264 1.15.  More than eight row tiles, d = 256: 96 to 8000 chunks .82-.95; five (a
+//   second group of one or two): up to 640 chunks .97-1.08, 768 to 3600 .86-.95.
 // The other head sizes share one variant of the others for up to 256 (fp32: 128) elements; these have eight.  These over the others:
 //   bf16, d = 8 to 112   1, 2 tiles .74-1.06, 4 .67-1.07, 8 .70-1.13, 14 .76-1.08; but heads of half a chunk, 4 and 14 tiles, 100 heads and more 1.0-1.28
 //   bf16, d = 136 to 232   1 tile, up to 1500 chunks .77-1.07; 2, 4 tiles, up to 320 chunks .66-1.05, 512 .83-.94, 640 to 1500 .97-1.20 (900 heads of one chunk .83-.95), 8000 1.1-1.28;
@@ -261,7 +262,7 @@ static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
     if (!f32 && (g.d < 128 || tiles > 8 || g.nchunk == 1 || chunks <= (tiles > 4 ? 4096 : 512))) return true;
   }
   if (f32) return chunks <= 128 || (heads < 8 && chunks > 192 && chunks <= 256 && (tiles <= 4 || g.d > 96));
-  if (g.d > 128) return tiles == 1 || (tiles > 8 && !half) || chunks <= 64 || (chunks <= 512 && (tiles == 2 || heads < 8));
+  if (g.d > 128) return tiles == 1 || (tiles > 8 && !half) || (tiles == 5 && chunks > 640) || chunks <= 64 || (chunks <= 512 && (tiles == 2 || heads < 8));
   if (tiles == 1) return chunks <= 512 && g.nchunk <= 32;
   return tiles > 2 && chunks <= 64;
 }

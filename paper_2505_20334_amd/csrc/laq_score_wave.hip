@@ -26,6 +26,7 @@
 // d = 96, 64 rows, 1656 heads x 796 keys 145 : 85; d = 96, 128 rows, 264 x 5815 194 : 135; fp32, d = 128, 64 rows, 64 x 8191 195 : 122;
 // d = 96, 128 rows, 368 x 1255 264 : 141.
 #include <algorithm>
+#include <cmath>
 
 #include "laq_internal.h"
 #include "laq_products.h"
@@ -402,12 +403,14 @@ __global__ __launch_bounds__(256) void row_constants_kernel(ScoreGeom g, const f
 // How a call's keys are cut into segments.  A segment costs its blocks and about three more (the score rows' way to LDS, the first keys'
 // to the registers).  Where a workgroup has few blocks, the cut with the least of that over the rounds of resident workgroups it takes
 // (and a little per segment, which the second kernel folds, or a launch that does): 64 heads x 8191 keys, fp32, 512 resident workgroups: 8, 16,
-// 32 segments (1, 2, 4 rounds) 122, 144, 169 us.  More score rows than are staged together are other workgroups' in the first kernel, but
-// in the second the same one takes a group after the other: its rounds count that often (laq_evict, counted as in the first : so, 448 rows: bf16, d = 256,
-// 64 heads x 4000 284 : 207, d = 64 99.7 : 85.1, 300 x 1030 125 : 107; fp32, d = 96, 16 x 8000 220 : 173; 256 rows, d = 128, 64 x 4000 333 : 232).
-// Where a workgroup has many, segments of 10 to 16 blocks, so that workgroups which get ahead of
+// 32 segments (1, 2, 4 rounds) 122, 144, 169 us.  Where a workgroup has many, segments of 10 to 16 blocks, so that workgroups which get ahead of
 // others take more of them: 1800 heads x 20259 keys, d = 64: 1, 3, 5, 16, 80 segments 2047, 1936, 1862, 1844, 2102 us.
-WavePlan plan_of(const ScoreGeom& g, int resident, int lds, int stride) {
+// More score rows than are staged together are other workgroups' in the first kernel, but in the second the same one takes a group after the other.
+// Its rounds count that often; but where not all workgroups that fit are there, those that are get on faster: a share `enough` of them
+// does what all do (bf16 1.25 waves per SIMD, fp32 2), though never less than the first kernel's.  laq_evict, the second counted as the first : so, us: fp32, 256 rows, d = 128, 64 heads x 3300 285 : 212,
+// 16 x 4000 114.5 : 87.9, 300 x 3000 866 : 787; 448 rows, d = 96, 16 x 8000 220 : 173.  With all the workgroups that fit counted as needed: bf16, 160 rows,
+// d = 128, 256 x 1500 81 : 91; 224 rows, d = 256, 128 x 1100 80 : 91.
+WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int stride) {
   WavePlan pl;
   const int ntile = g.Rpad / 32, blocks = (g.L + BLOCK_KEYS - 1) / BLOCK_KEYS;
   const long long heads = (long long)g.n_inst * g.Hkv;
@@ -425,7 +428,12 @@ WavePlan plan_of(const ScoreGeom& g, int resident, int lds, int stride) {
     for (const double share : {0.0, 0.25, 0.35, 0.5, 0.7, 1.0, 1.5, 2.0, 3.0}) {
       const int s = std::max(1, std::min(most, (int)(share * resident / heads)));
       const int sb = (blocks + s - 1) / s, used = (blocks + sb - 1) / sb;
-      const long long first = (heads * used * pl.groups + resident - 1) / resident, second = (heads * used + resident - 1) / resident * pl.groups;
+      const long long first = (heads * used * pl.groups + resident - 1) / resident;
+      double second = first;
+      if (pl.groups > 1) {
+        const double load = (double)(heads * used) / resident;
+        second = std::max(second, pl.groups * (load <= 1.0 ? std::max(load, enough) : std::ceil(load)));
+      }
       const double cost = 0.5 * (first + second) * (sb + 3.0) + 0.1 * sb + 0.12 * used + (used > FOLD_SEGMENTS ? 3.0 : 0.0);
       if (cost < least) { least = cost; best = s; }
     }
@@ -442,7 +450,7 @@ hipError_t launch_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& 
                        const Workspace& ws, hipStream_t st) {
   constexpr int per_simd = waves_per_simd<T, NP>();
   const int stride = row_stride<T>(g.d);
-  WavePlan pl = plan_of(g, 256 * per_simd, (MAX_LDS / per_simd - STATIC_LDS) & ~255, stride);
+  WavePlan pl = plan_of(g, 256 * per_simd, (is_f32(T()) ? 2.0 : 1.25) / per_simd, (MAX_LDS / per_simd - STATIC_LDS) & ~255, stride);
   pl.row_scale = row_scale_of<T>(g.scale2);
   const int rows = pl.group_tiles * 32;
   hipLaunchKernelGGL((wave_stats_kernel<T, NP, FULL>), dim3(pl.segs * pl.groups, g.Hkv, g.n_inst), dim3(THREADS),

@@ -28,6 +28,7 @@ CASES = [
     (BF16, 17, 4, 4, 72, 128, 65), (BF16, 17, 4, 4, 72, 129, 65), (BF16, 17, 4, 4, 200, 128, 65), (F32, 33, 4, 4, 16, 128, 65), (F32, 33, 4, 4, 16, 129, 65),
     (F32, 17, 8, 8, 32, 200, 65), (F32, 17, 8, 8, 40, 200, 65), (F32, 1, 7, 7, 72, 5000, 33), (F32, 1, 8, 8, 72, 4800, 33), (F32, 171, 1, 1, 72, 600, 5),
     (F32, 170, 1, 1, 72, 600, 5), (BF16, 171, 1, 1, 136, 600, 70), (BF16, 170, 1, 1, 136, 600, 70), (BF16, 513, 1, 1, 136, 250, 70), (BF16, 171, 1, 1, 136, 600, 140),
+    (BF16, 80, 8, 2, 256, 1000, 40), (BF16, 81, 8, 2, 256, 1000, 40),
 ]
 
 
