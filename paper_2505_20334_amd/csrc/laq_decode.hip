@@ -31,11 +31,15 @@ namespace {
 
 constexpr float DEC_NEG_BIG = -1.0e30f;
 constexpr int DEC_THREADS = 256, DEC_WAVES = DEC_THREADS / 64;
-// Parts: for about three workgroups per compute unit, which is what it holds of most kernels here (110 to 136 registers: three or four)
-// and fewer than make the folding long (128 caches of 2048 rows, 8 heads, take 41 us in 768 workgroups and 46 in 1408), but no parts
-// shorter than a turn of the workgroup's lane groups; at most DEC_MOST_PARTS of one cache, since one
-// workgroup folds them.  The parts of a call have one length, and what remains of a cache is a part too: 32 caches of 2048 to
-// 128 rows, 8 heads, make 856 workgroups of 5 to 384 rows.
+// Parts: for three workgroups per compute unit, which is what it holds of most kernels here (110 to 136 registers: three or four)
+// and fewer than make the folding long, but no parts shorter than a turn of the workgroup's lane groups; at most DEC_MOST_PARTS of one cache,
+// since one workgroup folds them.  The least length with which the call keeps to that, last parts counted too, and a cache's parts as
+// even as their steps allow: a fourth workgroup on some compute units, or parts of a few rows beside full ones, leave the others idle at
+// the end.  Before (length from the rows of the call alone, the rest of a cache a part of its own) : now, us: 32 caches of 2048 to 128
+// rows, 8 heads 35.8 : 31.7; 90 x 200, 8 heads 27.0 : 15.9; 90 x 2048, 8 heads 166 : 139, fp32, two query heads a KV head 455 : 300; 12 x 2048 to
+// 128 18.2 : 16.5.  The same with 512, 640, 896, 1024 workgroups: 32 caches of 2048 to 128 rows 1024 32.8; grids of 319 calls by rows
+// a part, over 768: 896 and 1024 .88-1.12 (.89-.95 for parts of 128 rows), 640 and 512 .87-1.09.  Shares of one length that end in
+// one cache and go on in the next, 768 of them: 34.3, and shares of up to 512 rows .78-.96 of these (a second sum to merge, a longer kernel).
 constexpr long long DEC_WORKGROUPS = 768;
 constexpr int DEC_PART_STEP = 64;
 constexpr int DEC_MOST_PARTS = 128;
@@ -103,6 +107,11 @@ __device__ __forceinline__ void fetch_row(const float* p, Piece8F32& x) {
   x.b = __builtin_bit_cast(float4, load16<ONCE>(p + 4));
 }
 
+// Rows of each of `parts` parts of a cache (the last one may have less): steps of DEC_PART_STEP, unless it is one part.
+__host__ __device__ inline int even_rows(int bk, int parts) {
+  const int steps = (bk + DEC_PART_STEP - 1) / DEC_PART_STEP;
+  return (steps + parts - 1) / parts * DEC_PART_STEP;
+}
 // Where the parts of a launch lie: part i of the launch belongs to instance inst_of(i) and is number
 // i - part0(inst) of its cache.
 struct DecodeTable {
@@ -119,14 +128,18 @@ struct DecodeTable {
     return lo;
   }
   __device__ int part0(int li) const { return part_before[li]; }
+  __device__ int parts(int li) const { return part_before[li + 1] - part_before[li]; }
+  __device__ int part_rows(int li) const { return even_rows(bk[li], parts(li)); }
   __device__ int rows(int li) const { return bk[li]; }
   __device__ int64_t first(int li) const { return row0[li]; }
 };
 struct DecodeUniform {
   UniformInst u;
-  int32_t parts;           // of every cache
-  __device__ int inst_of(int i) const { return i / parts; }
-  __device__ int part0(int li) const { return li * parts; }
+  int32_t n_parts, rows_per_part;      // of every cache
+  __device__ int inst_of(int i) const { return i / n_parts; }
+  __device__ int part0(int li) const { return li * n_parts; }
+  __device__ int parts(int) const { return n_parts; }
+  __device__ int part_rows(int) const { return rows_per_part; }
   __device__ int rows(int li) const { return u.rows(li); }
   __device__ int64_t first(int li) const { return u.first(li); }
 };
@@ -244,7 +257,7 @@ __device__ void merge_parts(const PartArea& pa, int p0, int S, int d, float* sm,
 // A workgroup works on part blockIdx.y for the query-head batch blockIdx.x: a cache in one part writes `out`;
 // one of several parts leaves its unnormalised sums, maxima and sums of weights to merge_parts.
 template <int GB, bool SHARED, typename T, int PP, typename TAB>
-__global__ __launch_bounds__(DEC_THREADS) void decode_kernel(int Hq, int Hkv, int d, float scale2, int rows_per_part, int inst0,
+__global__ __launch_bounds__(DEC_THREADS) void decode_kernel(int Hq, int Hkv, int d, float scale2, int inst0,
                                                              TAB tab, const T* __restrict__ q,
                                                              const T* __restrict__ kc, const T* __restrict__ vc,
                                                              float* __restrict__ out, PartArea pa) {
@@ -264,7 +277,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(int Hq, int Hkv, in
   const int G = Hq / Hkv, nbatch = (G + GB - 1) / GB;
   const int head = blockIdx.x / nbatch, g0 = (blockIdx.x % nbatch) * GB;
   const int li = tab.inst_of(blockIdx.y), part = blockIdx.y - tab.part0(li), inst = inst0 + li;
-  const int cache_rows = tab.rows(li), start = part * rows_per_part;
+  const int cache_rows = tab.rows(li), rows_per_part = tab.part_rows(li), start = part * rows_per_part;
   const int bk = min(rows_per_part, cache_rows - start);          // rows of this part
   const int tid = threadIdx.x, lane = tid & 63;
   const int dc = tid % PP, ks = tid / PP;
@@ -436,7 +449,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(int Hq, int Hkv, in
     stores_done();
   }
   __syncthreads();
-  merge_parts<GB>(pa, tab.part0(li), (cache_rows + rows_per_part - 1) / rows_per_part, d, sm, out0, G - g0);
+  merge_parts<GB>(pa, tab.part0(li), tab.parts(li), d, sm, out0, G - g0);
 }
 
 // q_cache[inst][h][t][:] = q_step[inst][h][:], 16 bytes per thread
@@ -451,7 +464,7 @@ __global__ __launch_bounds__(256) void qcache_store_kernel(long long rows, int W
 }
 
 struct DecodeCall {
-  int Hq, Hkv, d, rows_per_part, columns, head_batch;
+  int Hq, Hkv, d, columns, head_batch;
   float scale2;
   const void *q, *kc, *vc;
   float* out;
@@ -463,8 +476,7 @@ template <int GB, bool SHARED, typename T, int PP, typename TAB>
 hipError_t launch_pp(const DecodeCall& c, int n_parts, int inst0, const TAB& tab) {
   const int merge = DEC_MOST_PARTS * GB * 2, sums = DEC_WAVES * GB * (c.d + 2);   // floats of the two uses of the LDS
   hipLaunchKernelGGL((decode_kernel<GB, SHARED, T, PP, TAB>), dim3(c.columns, n_parts), dim3(DEC_THREADS),
-                     (c.parts.marks && merge > sums ? merge : sums) * sizeof(float), c.st, c.Hq, c.Hkv, c.d, c.scale2, c.rows_per_part,
-                     inst0, tab, static_cast<const T*>(c.q), static_cast<const T*>(c.kc), static_cast<const T*>(c.vc), c.out, c.parts);
+                     (c.parts.marks && merge > sums ? merge : sums) * sizeof(float), c.st, c.Hq, c.Hkv, c.d, c.scale2, inst0, tab, static_cast<const T*>(c.q), static_cast<const T*>(c.kc), static_cast<const T*>(c.vc), c.out, c.parts);
   return hipGetLastError();
 }
 
@@ -489,7 +501,11 @@ hipError_t launch_for(const DecodeCall& c, int n_parts, int inst0, const TAB& ta
   }
 }
 
-int parts_of(int bk, int rows_per_part) { return (bk + rows_per_part - 1) / rows_per_part; }
+// the parts of a cache where none is to have more than `most` rows, as even as their steps allow
+int parts_of(int bk, int most) {
+  const int steps = (bk + DEC_PART_STEP - 1) / DEC_PART_STEP, each = even_rows(bk, (bk + most - 1) / most) / DEC_PART_STEP;
+  return (steps + each - 1) / each;
+}
 
 }  // namespace
 
@@ -503,7 +519,7 @@ int decode_head_batch(int Hq, int Hkv, int dtype) {
   return gb;
 }
 
-// Rows per part: the caches stay whole where they make enough workgroups, or where they are short.
+// The most rows a part may have: the caches stay whole where they make enough workgroups, or where they are short.
 static int longest(int n, int L, const int32_t* budget) {
   int most = 0;
   for (int i = 0; i < n; ++i) most = most > budget[i] ? most : budget[i];
@@ -522,6 +538,12 @@ int decode_part_rows(int n, int L, int Hq, int Hkv, int dtype, const int32_t* bu
   int part = (int)(rows * columns / DEC_WORKGROUPS / DEC_PART_STEP + 1) * DEC_PART_STEP;
   const int least = (most + DEC_MOST_PARTS - 1) / DEC_MOST_PARTS;
   if (part < least) part = least;
+  // (the caches' last parts count too)
+  for (; part < most; part += DEC_PART_STEP) {
+    long long parts = 0;
+    for (int i = 0; i < n; ++i) parts += parts_of(budget[i] < L ? budget[i] : L, part);
+    if (parts * columns <= DEC_WORKGROUPS) break;
+  }
   return part < most ? part : most;
 }
 
@@ -550,7 +572,7 @@ size_t decode_partial_bytes(int n, int L, int Hq, int Hkv, int d, int dtype, con
 hipError_t launch_decode(int n_inst, int L, int Hq, int Hkv, int d, int dtype, float scale2, int rows_per_part, const int32_t* budget,
                          const void* q, const void* kc, const void* vc, float* out, void* ws, hipStream_t st) {
   static std::atomic<uint32_t> launches{(uint32_t)(std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull >> 32)};
-  DecodeCall c{Hq, Hkv, d, rows_per_part, decode_columns(Hq, Hkv, dtype), decode_head_batch(Hq, Hkv, dtype), scale2, q, kc, vc, out, {}, st};
+  DecodeCall c{Hq, Hkv, d, decode_columns(Hq, Hkv, dtype), decode_head_batch(Hq, Hkv, dtype), scale2, q, kc, vc, out, {}, st};
   const auto launch = [&](int n_parts, int inst0, const auto& tab) {
     if (ws) {
       c.parts.marks = reinterpret_cast<unsigned long long*>((reinterpret_cast<uintptr_t>(ws) + 7) & ~(uintptr_t)7);
@@ -564,9 +586,10 @@ hipError_t launch_decode(int n_inst, int L, int Hq, int Hkv, int d, int dtype, f
     const int n = n_inst - i0 < MAX_INST_PER_LAUNCH ? n_inst - i0 : MAX_INST_PER_LAUNCH;
     hipError_t e;
     if (const int bk = uniform_rows(L, budget, i0, n)) {
-      const DecodeUniform tab{UniformInst{bk, row, (int64_t)Hkv * bk}, parts_of(bk, rows_per_part)};
+      const int parts = parts_of(bk, rows_per_part);
+      const DecodeUniform tab{UniformInst{bk, row, (int64_t)Hkv * bk}, parts, even_rows(bk, parts)};
       row += n * tab.u.per_inst;
-      e = launch(n * tab.parts, i0, tab);
+      e = launch(n * parts, i0, tab);
     } else {
       DecodeTable tab;
       tab.n = n;

@@ -27,6 +27,8 @@ CASES = [
     (BF16, 8, 1, 96, [9000]), (BF16, 9, 1, 128, [700]), (BF16, 40, 2, 256, [513, 70]), (BF16, 6, 2, 200, [128, 128, 128]),
     (F32, 3, 3, 8, [65, 5]), (F32, 4, 2, 64, [320, 1]), (F32, 8, 2, 128, [512]), (F32, 28, 4, 136, [333, 64]), (F32, 5, 1, 256, [1100]),
     (BF16, 1, 1, 128, [20000]),
+    # parts as even as their steps allow, and longer ones where the last parts would make too many workgroups
+    (BF16, 16, 8, 64, [200] * 60), (F32, 8, 8, 72, [1000 - 900 * i // 11 for i in range(12)]), (BF16, 8, 8, 128, [321, 320, 2000] * 5),
 ]
 
 
