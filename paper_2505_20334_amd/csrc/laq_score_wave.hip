@@ -9,7 +9,7 @@
 // of keys, 128 at a time; a wave takes 32 of these in registers, straight from memory in operand layout (lane l: row
 // l % 32, the 16-byte pieces 2t + l / 32), while the next 32 are on their way into others.  Nothing that a wave does
 // per key waits for another wave, so loads and arithmetic of the 8 to 20 waves of a compute unit mix freely.
-//   (1) D = K * Q^T: lane = score row, registers = 16 keys: maximum and sum in registers, the wave's running (m, z) in LDS.
+//   (1) D = K * Q^T: lane = score row, registers = 16 keys: sum (and, where it is needed, maximum) in registers, the wave's running (m, z) in LDS.
 //   (2) D = Q * K^T: lane = key, registers = 16 rows: the sum over the rows in registers.
 // Score rows beyond R repeat the last one and get c = inf, so that they add nothing.
 //
@@ -192,6 +192,22 @@ struct WavePlan {
 // Waves per SIMD the kernels are built for: as many as their registers (and 32 of the score rows per workgroup in LDS) allow.
 template <typename T, int NP> constexpr int waves_per_simd() { return is_f32(T()) ? (NP <= 8 ? 3 : 2) : (NP <= 6 ? 5 : NP <= 8 ? 4 : 2); }
 
+// A wave's sums of exponentials refer to a number near the row's maximum, not to the maximum itself: HEADROOM above that of the first
+// tile, and moved only where a tile's sum reaches OUTGROWN of it (then, and where a row does not see all keys of a tile, or a sum is no number, the
+// maximum of the tile is made).  The terms that count have exponents between -8 and 7, as with a maximum that most keys stay some powers of two below.
+// 63 instead of 87 vector instructions per product of 32 keys and 32 rows; 256 heads x 32768 keys, 128 rows, us: first pass 408 : 404 (cold 386 : 382),
+// bound by the power that memory and matrix cores take; the whole eviction 954 : 946, 112 score rows x 20123 296.0 : 294.7.
+constexpr float HEADROOM = 3.f, OUTGROWN = 128.f;
+// exp2(s * scale - m) of a lane's 16 keys and of the 16 that the other half of the wave has of the same row, summed
+__device__ __forceinline__ float tile_sum(const f32x16& s, float scale, float m) {
+  float z[2] = {0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i & 1] += __builtin_amdgcn_exp2f(fmaf(s[i], scale, -m));
+  z[0] += z[1];
+  const auto zh = __builtin_amdgcn_permlane32_swap(__float_as_uint(z[0]), __float_as_uint(z[0]), false, false);
+  return __uint_as_float(zh[0]) + __uint_as_float(zh[1]);
+}
+
 // Pass 1: part[head][segment][row] = (m, z) of a score row over the segment's visible keys, in log2 units.
 template <typename T, int NP, bool FULL>
 __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, WavePlan pl,
@@ -215,34 +231,34 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
 #pragma unroll 1
     for (int rt = 0; rt < ntile; ++rt) {
       const float2 old = *mine;
-      float m, z;
       f32x16 s = op.template product<true>(rows, w.plane, w.plane / 32);
-      float scale = row_scale.scale2;
+      float z = plain && key0 != w.first ? tile_sum(s, row_scale.scale2, old.x) : INFINITY;
+      if (__builtin_expect(!__any(!(z <= OUTGROWN)), 1)) {
+        mine->y = old.y + z;
+      } else {
+        float m, scale = row_scale.scale2;
 #pragma unroll 1
-      for (bool again = false;; again = true) {
-        if (!plain) {
-          int n = threadIdx.x & 63;
-          asm volatile("" : "+v"(n));                    // (computed here: the common case has no registers for it)
-          const int row = (rt0 + rt) * 32 + (n & 31), last = last_visible_key(g, qp, min(row, g.R - 1) % g.W) - key0;
+        for (bool again = false;; again = true) {
+          if (!plain) {
+            int n = threadIdx.x & 63;
+            asm volatile("" : "+v"(n));                  // (computed here: the common case has no registers for it)
+            const int row = (rt0 + rt) * 32 + (n & 31), last = last_visible_key(g, qp, min(row, g.R - 1) % g.W) - key0;
 #pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (acc_row(i, n >> 5) > last) s[i] = -INFINITY;
+            for (int i = 0; i < 16; ++i)
+              if (acc_row(i, n >> 5) > last) s[i] = -INFINITY;
+          }
+          m = s[0];
+#pragma unroll
+          for (int i = 1; i < 16; ++i) m = fmaxf(m, s[i]);
+          const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+          m = fmaxf(old.x, fmaf(fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1])), scale, HEADROOM));    // (the logit scale is positive)
+          z = tile_sum(s, scale, m);
+          if (!is_f32(T()) || again || __builtin_expect(!__any(z != z), 1)) break;
+          s = product_f32<true>(w.key_row(g, lay, key0), w.score_row(g, rt0 + rt), w.hf, w.row_bytes);
+          scale = g.scale2;
         }
-        m = s[0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) m = fmaxf(m, s[i]);
-        const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-        m = fmaxf(old.x, fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1])) * scale);    // (the logit scale is positive)
-        z = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f(fmaf(s[i], scale, -m));
-        const auto zh = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
-        z = __uint_as_float(zh[0]) + __uint_as_float(zh[1]);
-        if (!is_f32(T()) || again || __builtin_expect(!__any(z != z), 1)) break;
-        s = product_f32<true>(w.key_row(g, lay, key0), w.score_row(g, rt0 + rt), w.hf, w.row_bytes);
-        scale = g.scale2;
+        *mine = make_float2(m, fmaf(old.y, __builtin_amdgcn_exp2f(old.x - m), z));
       }
-      *mine = make_float2(m, fmaf(old.y, __builtin_amdgcn_exp2f(old.x - m), z));
       rows += 32 * w.stride;
       mine += WAVES * 32;
     }

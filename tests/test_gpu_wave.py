@@ -53,6 +53,28 @@ def test_scores_against_the_oracle(dtype, n, Hq, Hkv, d, L, W):
             check_scores(got[i], want, dtype, "instance %d" % i)
 
 
+@pytest.mark.parametrize("shape", ["rising", "falling", "spike", "steps-of-the-headroom"])
+@pytest.mark.parametrize("dtype,d", [(BF16, 64), (BF16, 128), (BF16, 256), (F32, 64), (F32, 128)])
+def test_logits_that_outgrow_the_reference(dtype, d, shape):
+    """The first pass keeps the reference of a wave's exponents until the sum of a tile reaches 128 of it.  Logits that rise over a
+    segment by less than that a tile, by just about that, all at once, and not at all; exponents of 40 at most, rounded by 2^-19."""
+    import paper_2505_20334_amd as laq
+    n, L, W = 9, 4100, 5
+    g = torch.Generator().manual_seed(d)
+    t = torch.arange(L) / L
+    ramp = {"rising": 24 * t, "falling": 24 - 24 * t, "spike": 20.0 * (torch.arange(L) % 1500 == 700),
+            "steps-of-the-headroom": (torch.arange(L) // 128) * 7.0 * 0.6931 % 24}[shape]
+    q = 0.3 * torch.randn(n, 2, W, d, generator=g)
+    q[..., 0] = 8.0
+    k = torch.randn(n, 1, L, d, generator=g)
+    k[..., 0] = ramp * d ** 0.5 / 8.0
+    q, k = q.to(dtype), k.to(dtype)
+    got = laq.laq_score(q.to(DEV), k.to(DEV), 1, q_pos=[L + w for w in range(W)], keep=0, choose="two-pass").cpu()
+    for i in (0, n - 1):
+        want, _, _, _ = oracle.evict(q[i], k[i], k[i], 64, 1, q_pos=[L + w for w in range(W)], keep=0)
+        check_scores(got[i], want, dtype, "instance %d" % i)
+
+
 @pytest.mark.parametrize("d", [64, 104, 128])
 def test_fp32_infinities_and_nans_are_those_of_whole_products(d):
     """A float is taken apart into three for the products; an infinity leaves NaNs, and the tile is scored from whole
