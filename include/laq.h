@@ -154,7 +154,7 @@ size_t laq_workspace_bytes(const laq_shape *shape);
  * Whether the last scoring call that used this workspace completed all its waits.  The single-read
  * scoring kernel lets the workgroups that share a KV head exchange their softmax statistics while
  * it runs; each of those waits is bounded, and a kernel that gives one up (which needs the device
- * to withhold part of a cooperative launch for about a second) finishes with invalid scores and
+ * to withhold part of its launch for about a second) finishes with invalid scores and
  * leaves a mark in the workspace.  Synchronises `stream`, reads the mark: LAQ_OK, LAQ_ERR_TIMEOUT,
  * or an argument / device error.  For callers that want the proof; results of a call that has
  * completed on an otherwise healthy device need no check.
@@ -175,10 +175,14 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *                               faster one; shape.score_choice asks for it or against it.
  *                               Heads of at most 1024 keys that one workgroup holds are read once
  *                               too.  Otherwise K is streamed twice (laq_score_kernel() says which).
- *                               The single-read kernel is started with a cooperative launch,
- *                               which keeps a team of workgroups on the device together; with
- *                               LAQ_COOPERATIVE_LAUNCH=0 in the environment (read at the first
- *                               such call) it is an ordinary launch of the same grid, for
+ *                               The single-read kernel's workgroups wait for the others of their
+ *                               team; it is an ordinary launch where that cannot end in a deadlock
+ *                               with other such launches (at most 64 score rows, a team takes at most
+ *                               an eighth of the workgroups that the device holds, or less where
+ *                               GPU_MAX_HW_QUEUES is more than 4, and the stream may use all
+ *                               compute units and is not being captured), else a cooperative one.
+ *                               With LAQ_COOPERATIVE_LAUNCH=0 in the environment (read at the first
+ *                               such call) it is always an ordinary launch, for
  *                               profilers that cannot follow cooperative launches -- then
  *                               other work on the device can make the call end in LAQ_ERR_TIMEOUT.
  *   scores [n_inst, Hkv, L]     fp32 out.  For each KV head g and key j:

@@ -119,6 +119,7 @@ Workspace carve_workspace(const ScoreGeom& g, void* ws) {
   base += round256(fused_sync_bytes(g));
   w.window = reinterpret_cast<int32_t*>(base - MAX_QPOS * sizeof(int32_t));   // (the end of that area, see make_plan() of the single-read kernel)
   w.status = reinterpret_cast<int*>(base) + 8;
+  w.started = reinterpret_cast<int*>(base) + 32;     // (not in the cache line of the status)
   return w;
 }
 

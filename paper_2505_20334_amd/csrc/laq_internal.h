@@ -68,6 +68,7 @@ struct Workspace {
   void* fused;      // exchange memory of the single-read kernel (fused_sync_bytes)
   int32_t* window;  // position table of a window longer than WINDOW_INLINE (MAX_QPOS entries)
   int* status;      // != 0 after a call whose single-read kernel gave up a wait (results invalid)
+  int* started;     // counters of the single-read kernel's workgroups
 };
 
 size_t workspace_bytes(const ScoreGeom& g);

@@ -41,8 +41,13 @@
 // words, so a word is only overwritten after every member has read it (a member that publishes
 // head n+2 has been through the exchange of head n+1, for which every member had published,
 // which it does after reading head n).  All waits are bounded, and end at once after one of
-// them has timed out (status word of the workspace).  The kernel is started with a cooperative
-// launch, which guarantees that the workgroups of a team are on the device together.
+// them has timed out (status word of the workspace).
+//
+// A workgroup's place in a team is a number that it draws when it starts, so teams are complete one
+// after the other in the order in which workgroups get on the device, and of a launch at most two (there are two
+// counters) are there in part.  An ordinary launch is enough as long as the parts of teams that
+// all launches on the device could leave there do not fill it (ordinary_launch()); else, and
+// for more than 64 score rows, a cooperative one is taken.
 #include <algorithm>
 #include <atomic>
 #include <cstdlib>
@@ -101,6 +106,7 @@ template <int NRT> struct Cfg {
   static constexpr int ROWS = NRT * 32;
   static constexpr int PAIRS = 8;                                   // (key tile, row tile) pairs a wave keeps: 16 registers each
   static constexpr int KT = PAIRS / NRT;                            // key tiles per wave and head
+  static constexpr bool DRAWS = NRT <= 2;                           // places in teams are drawn (NRT 4: the workgroups' numbers, on request only)
   static constexpr bool ROTATE = NRT == 2;                          // see WaveCtx::rot (the other instantiations lose registers to it)
   static constexpr int KEYS_PER_WAVE = KT * 32, KEYS_PER_BLOCK = F_WAVES * KEYS_PER_WAVE;
   static constexpr int Q_BYTES = ROWS * QROWB;
@@ -121,7 +127,7 @@ template <int NRT> struct Cfg {
   static constexpr int OFF_LAST = OFF_FOLD + NSUB * ROWS * 8;       // int[ROWS]: last key every score row sees
   static constexpr int OFF_RAW = OFF_LAST + ROWS * 4;               // float[MAX_HALF + KEYS_PER_BLOCK + MAX_HALF]: the
                                                                     // workgroup's raw scores between zero margins
-  static constexpr int OFF_FLAG = OFF_RAW + (KEYS_PER_BLOCK + 2 * MAX_HALF) * 4;   // int: "a wait has timed out"
+  static constexpr int OFF_FLAG = OFF_RAW + (KEYS_PER_BLOCK + 2 * MAX_HALF) * 4;   // int: "a wait has timed out"; int: the place drawn
   static constexpr int OFF_STAGE = (OFF_FLAG + 16 + 15) & ~15;      // char[F_WAVES][TILE_BYTES]: one key tile per wave, in flight
                                                                     // from memory across the steps that have no registers for it
   static constexpr int BYTES = OFF_STAGE + F_WAVES * TILE_BYTES;
@@ -331,13 +337,25 @@ __device__ __forceinline__ void wave_main(const WaveCtx& w, f32x16 (&E)[Cfg<NRT>
 struct FusedSync {
   float2* stats;           // [n_teams][2][T][rows]
   int* status;             // != 0: a wait has timed out (results are not valid)
+  int* started;            // two counters, SECOND apart: places that have been drawn
 };
 struct FusedPlan {
   int T;                   // workgroups per team = ceil(L / keys per workgroup)
   int n_teams;
+  int early;               // workgroups that draw from the first counter (whole teams of them)
   int n_heads;             // team t takes heads t, t + n_teams, ...
   int half;                // (pool kernel - 1) / 2; 0: raw scores
 };
+
+// The place of a workgroup among those of the launch: member place % T of team place / T.  Drawn from one of two counters, the `early`
+// workgroups with the lowest numbers from the first.  The device takes workgroups in the order of their numbers within an XCD, and two on a compute unit
+// only when each has one; so the teams of either counter have at most one workgroup on a compute unit.  All from one counter, teams had both places
+// of some, whose workgroups do the same at the same time: 256 heads x 16384 keys, 64 rows 294 us, with two counters 279, by number 271.
+constexpr int SECOND = 16;                 // ints between the counters
+__device__ __forceinline__ int drawn_place(int* started, int early) {
+  const int late = (int)blockIdx.x >= early;
+  return late * early + __hip_atomic_fetch_add(started + late * SECOND, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 template <int NRT, bool PAGED>
 __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, WindowPos qp, FusedPlan plan, KvLayout lay,
@@ -360,7 +378,12 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int T = plan.T, half = plan.half;
-  const int team = blockIdx.x / T, member = blockIdx.x - team * T;
+  if constexpr (S::DRAWS) {
+    if (tid == 0) gave_up[1] = drawn_place(sy.started, plan.early);
+    lds_barrier();
+  }
+  const int place = S::DRAWS ? __builtin_amdgcn_readfirstlane(gave_up[1]) : blockIdx.x;
+  const int team = place / T, member = place - team * T;
   if (team >= plan.n_teams || team >= plan.n_heads) return;
   float* zt = reinterpret_cast<float*>(smem + S::OFF_ZT) + wave * 32 * ZT_STRIDE;
 
@@ -717,11 +740,11 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
   stage_wait();                            // (a tile requested before a wait timed out: nothing writes LDS after the end)
 }
 
-// zero in the statistics words (validity bit of "nothing yet") and the status word
-__global__ void fused_reset_kernel(uint4* words, int n_words, int* status) {
+// zero in the statistics words (validity bit of "nothing yet"), the status word and the counters
+__global__ void fused_reset_kernel(uint4* words, int n_words, int* status, int* started) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n_words) words[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (i == 0) *status = 0;
+  if (i == 0) *status = started[0] = started[SECOND] = 0;
 }
 
 // ---- per-device set-up (see score_fused_init) -------------------------------------------------
@@ -730,7 +753,7 @@ std::atomic<int> fused_resident[MAX_DEVICES][3];    // per kernel (32, 64, 128 s
 constexpr int slot_of(int nrt) { return nrt == 4 ? 2 : nrt - 1; }
 // row tiles of the kernel that takes Rpad score rows
 int tiles_for(int Rpad) { return Rpad > 64 ? 4 : Rpad / 32; }
-std::atomic<int> fused_ready[MAX_DEVICES];
+std::atomic<int> fused_cus[MAX_DEVICES], fused_ready[MAX_DEVICES];
 
 template <int NRT>
 hipError_t init_rows(int dev, int cus, int coop) {
@@ -764,11 +787,39 @@ bool make_plan(const ScoreGeom& g, int pool, int resident, FusedPlan* out) {
   plan.n_heads = (int)n_heads;
   plan.n_teams = resident / plan.T;
   if (plan.n_teams > plan.n_heads) plan.n_teams = plan.n_heads;
+  plan.early = std::min(plan.n_teams, resident / 2 / plan.T) * plan.T;
   // the exchange memory is sized for FUSED_MAX_RESIDENT workgroups
   // (less the last 2 KiB of it, which hold the position table of a long window)
   if ((size_t)plan.n_teams * plan.T > (size_t)FUSED_MAX_RESIDENT - 8) return false;
   *out = plan;
   return true;
+}
+
+// Whether an ordinary launch will do.  A workgroup waits only for its own team, and a launch has at most two teams (one per counter) that
+// are on the device in part: their up to T - 1 members wait for workgroups that start as soon as there is a place, and places come free as
+// whole teams end and as other kernels do.  Only if every place were taken by parts of teams, of many launches at a time, would
+// none come free.  Launches at a time: one per hardware queue (a stream's launches follow one another), which HIP makes 4 of, or
+// GPU_MAX_HW_QUEUES.  A stream that is confined to some compute units has fewer places, and what stream a recorded launch will run on is not
+// known: cooperative launches, as for longer teams.
+// us a call (laq_evict), cooperative : ordinary: 256 heads x 16384 keys, 64 rows 290 : 279; x 8001 keys, 32 rows 170 : 151; 32 heads x 32768, 32 rows 100 : 78.
+bool ordinary_launch(const FusedPlan& plan, int resident, int cus, hipStream_t st) {
+  static const long long at_a_time = [] {
+    const char* v = getenv("GPU_MAX_HW_QUEUES");
+    return std::max(4LL, v != nullptr ? atoll(v) : 0LL);
+  }();
+  if (2 * (plan.T - 1) * at_a_time >= resident) return false;
+  constexpr int WORDS = 32;
+  uint32_t mask[WORDS] = {};
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (cus > WORDS * 32) return false;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess ||
+      (capture == hipStreamCaptureStatusNone && hipExtStreamGetCUMask(st, (cus + 31) / 32, mask) != hipSuccess)) {
+    (void)hipGetLastError();                       // (not for the launches that follow to find)
+    return false;
+  }
+  int open = 0;
+  for (const uint32_t m : mask) open += __builtin_popcount(m);
+  return open >= cus;                              // (0 under capture)
 }
 
 template <int NRT>
@@ -783,14 +834,16 @@ hipError_t launch_fused_rows(const ScoreGeom& g, const WindowPos& qp, const KvLa
   constexpr int bytes = Cfg<NRT>::BYTES;
   constexpr int ROWS = NRT * 32;
   FusedPlan plan;
-  if (!make_plan(g, pool, fused_resident[dev][slot_of(NRT)].load(std::memory_order_acquire), &plan)) return hipSuccess;
+  const int resident = fused_resident[dev][slot_of(NRT)].load(std::memory_order_acquire);
+  if (!make_plan(g, pool, resident, &plan)) return hipSuccess;
   const size_t slots = (size_t)plan.n_teams * 2 * plan.T;
   FusedSync sy;
   sy.stats = reinterpret_cast<float2*>(ws.fused);
   sy.status = ws.status;
+  sy.started = ws.started;
   const int n16 = (int)(slots * ROWS / 2);         // 16-byte pieces of the statistics words
   hipLaunchKernelGGL(fused_reset_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st,
-                     reinterpret_cast<uint4*>(sy.stats), n16, sy.status);
+                     reinterpret_cast<uint4*>(sy.stats), n16, sy.status, sy.started);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   ScoreGeom gg = g;
   WindowPos qq = qp;
@@ -799,16 +852,16 @@ hipError_t launch_fused_rows(const ScoreGeom& g, const WindowPos& qp, const KvLa
   const void* fn = lay.table ? reinterpret_cast<const void*>(&fused_kernel<NRT, true>)
                              : reinterpret_cast<const void*>(&fused_kernel<NRT, false>);
   void* args[] = {&gg, &qq, &plan, &ll, &q, &k, &scores, &edge, &sy};
-  // LAQ_COOPERATIVE_LAUNCH=0 in the environment: an ordinary launch of the same grid, for tools that
+  // LAQ_COOPERATIVE_LAUNCH=0 in the environment: always an ordinary launch of the same grid, for tools that
   // cannot follow cooperative launches (a process profiled by rocprofv3 ends in a segmentation fault
-  // after any cooperative launch, also of an empty kernel).  The grid still fits the device, but
-  // nothing then keeps other work from taking its place; the kernel's bounded waits turn a team
-  // that is not on the device together into LAQ_ERR_TIMEOUT.
+  // after any cooperative launch, also of an empty kernel).  Where the rule does not hold, the kernel's
+  // bounded waits turn a team that is not on the device together into LAQ_ERR_TIMEOUT.
   static const bool plain_launch = [] {
     const char* v = getenv("LAQ_COOPERATIVE_LAUNCH");
     return v != nullptr && v[0] == '0';
   }();
-  if (plain_launch) e = hipLaunchKernel(fn, dim3(plan.n_teams * plan.T), dim3(F_THREADS), args, bytes, st);
+  if (plain_launch || (Cfg<NRT>::DRAWS && ordinary_launch(plan, resident, fused_cus[dev].load(std::memory_order_acquire), st)))
+    e = hipLaunchKernel(fn, dim3(plan.n_teams * plan.T), dim3(F_THREADS), args, bytes, st);
   else e = hipLaunchCooperativeKernel(fn, dim3(plan.n_teams * plan.T), dim3(F_THREADS), args, bytes, st);
   if (e != hipSuccess) return e;
   if (plan.half > 0 && plan.T > 1) {
@@ -827,6 +880,7 @@ hipError_t score_fused_init(int dev) {
   hipError_t e;
   if ((e = hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+  fused_cus[dev].store(cus, std::memory_order_release);
   if ((e = init_rows<1>(dev, cus, coop)) != hipSuccess) return e;
   if ((e = init_rows<2>(dev, cus, coop)) != hipSuccess) return e;
   if ((e = init_rows<4>(dev, cus, coop)) != hipSuccess) return e;

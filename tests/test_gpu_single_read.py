@@ -211,6 +211,28 @@ def test_constant_keys_give_uniform_probabilities(laq):
     np.testing.assert_allclose(s[0, 1].numpy(), want.numpy(), rtol=2e-6)
 
 
+@pytest.mark.parametrize("L,W,heads", [(1500, 8, 40), (8200, 8, 24), (16384, 16, 9), (16640, 16, 40), (32768, 16, 10)])
+def test_calls_side_by_side(laq, L, W, heads):
+    # several launches on the device at once, each with teams of which some are there only in part: places are drawn in the order
+    # of start, so every call completes, with the bits of a call that is alone; sizes: few and many workgroups per team, more and fewer
+    # heads than teams, and a team (65 workgroups) whose launch stays cooperative
+    calls = []
+    for i in range(3):
+        q, k = draw(1, heads, 4, L, W, seed=L + i, sinks=False)
+        q, k = q.to(DEV), k.to(DEV)
+        ws = torch.full((laq.laq_workspace_bytes(1, heads * 4, heads, D, L, W, torch.bfloat16),), 0xFF, dtype=torch.uint8, device=DEV)
+        calls.append((q, k, ws, torch.cuda.Stream(), laq.laq_score(q, k, 7, ws=ws, choose="single-read"), torch.empty(1, heads, L, device=DEV)))
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for q, k, ws, stream, alone, out in calls:
+            with torch.cuda.stream(stream):
+                laq.laq_score(q, k, 7, scores=out, ws=ws, choose="single-read")
+    torch.cuda.synchronize()
+    for q, k, ws, stream, alone, out in calls:
+        assert laq.laq_workspace_status(ws, 1, heads * 4, heads, D, L, W, torch.bfloat16) == 0
+        assert torch.equal(out, alone)
+
+
 def test_ordinary_launch_gives_the_same_bits(laq, tmp_path):
     # LAQ_COOPERATIVE_LAUNCH=0 (read once per process, so a child process): the same kernel on the same
     # grid, started without the cooperative guarantee, for profilers that cannot follow cooperative launches
