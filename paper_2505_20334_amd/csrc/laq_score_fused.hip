@@ -7,7 +7,7 @@
 // accumulator registers: eight 32 x 32 tiles (32 keys x 32 rows) -- takes the row maxima m over
 // the workgroup's keys, turns the dot products in place into e = exp2(s - m), and keeps these
 // until the team of workgroups that shares the head has folded the rows' (m, Z = sum_keys e) into
-// c = M + log2 Z.  The key's score is then sum_rows e * exp2(m - c): one multiply-add per stored
+// their M and Z.  The key's score is then sum_rows e * exp2(m - M) / Z: one multiply-add per stored
 // number.  Key rows pass through registers once and are never needed again, so their loads do
 // not depend on the exchange.  For KV heads with at most 128 score rows (32, 64 or 128: one
 // instantiation each).
@@ -23,9 +23,9 @@
 //   C. row maxima over its keys (registers, a transposition through LDS per wave, LDS across
 //      waves), e = exp2(D * scale2 - m) in place, row sums the same way; publishes (m, Z) per row;
 //   D. pools and stores the previous head's scores, stages the next head's Q;
-//   E. reads the statistics of the whole team and folds them, in a fixed order, into c per row
-//      (every member computes the same constants; nobody waits for a combiner), and from them one
-//      weight per row, exp2(m - c);
+//   E. reads the statistics of the whole team and folds them, in a fixed order, into M and Z per row
+//      (every member computes the same numbers; nobody waits for a combiner), and from them one
+//      weight per row, exp2(m - M) / Z;
 //   F. score of a key = sum over rows of e * weight; the workgroup's raw scores meet in LDS,
 //      where the sequence max-pool of every key whose window lies inside the workgroup's keys is
 //      taken; the few keys next to a workgroup boundary are pooled by pool_boundaries_kernel from
@@ -46,7 +46,7 @@
 // A workgroup's place in a team is a number that it draws when it starts, so teams are complete one
 // after the other in the order in which workgroups get on the device, and of a launch at most two (there are two
 // counters) are there in part.  An ordinary launch is enough as long as the parts of teams that
-// all launches on the device could leave there do not fill it (ordinary_launch()); else, and
+// all launches on the device could leave there do not fill it (ordinary_team()); else, and
 // for more than 64 score rows, a cooperative one is taken.
 #include <algorithm>
 #include <atomic>
@@ -66,6 +66,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float NEG_BIG = -1.0e30f;
+// The exponential instruction returns 0 below 2^-126, where fp32 still tells scores apart: a score below this is summed again.
+constexpr float TINY = 0x1p-90f;
 constexpr int D = 128;                       // head size this kernel is written for
 constexpr int KS = D / 16;                   // MFMAs (reduction steps) per 32x32 tile
 constexpr int TILE_BYTES = 32 * D * 2;       // a key tile: 32 rows
@@ -107,6 +109,8 @@ template <int NRT> struct Cfg {
   static constexpr int PAIRS = 8;                                   // (key tile, row tile) pairs a wave keeps: 16 registers each
   static constexpr int KT = PAIRS / NRT;                            // key tiles per wave and head
   static constexpr bool DRAWS = NRT <= 2;                           // places in teams are drawn (NRT 4: the workgroups' numbers, on request only)
+  // scores below TINY are summed again (NRT 4: as they are; it has no registers for it: 21 spills -> 37)
+  static constexpr bool AGAIN = NRT <= 2;
   static constexpr bool ROTATE = NRT == 2;                          // see WaveCtx::rot (the other instantiations lose registers to it)
   static constexpr int KEYS_PER_WAVE = KT * 32, KEYS_PER_BLOCK = F_WAVES * KEYS_PER_WAVE;
   static constexpr int Q_BYTES = ROWS * QROWB;
@@ -121,7 +125,7 @@ template <int NRT> struct Cfg {
   static constexpr int OFF_ZT = ZT_IN_Q ? OFF_Q : OFF_Q + Q_BYTES;
   static constexpr int OFF_STAT = OFF_Q + Q_BYTES + (ZT_IN_Q ? 0 : ZT_BYTES);   // float[F_WAVES][ROWS]: the waves' maxima / sums
   static constexpr int OFF_REF = OFF_STAT + F_WAVES * ROWS * 4;     // float[ROWS]: the rows' maxima over the workgroup (log2 units)
-  static constexpr int OFF_WTS = OFF_REF + ROWS * 4;                // float[ROWS]: the rows' weights exp2(m - c)
+  static constexpr int OFF_WTS = OFF_REF + ROWS * 4;                // float[ROWS]: the rows' weights exp2(m - M) / Z
   static constexpr int RPAIRS = ROWS / 2, NSUB = F_THREADS / RPAIRS;   // the fold: threads per pair of rows
   static constexpr int OFF_FOLD = OFF_WTS + ROWS * 4;               // float2[NSUB][ROWS]: the team's statistics, per member subset
   static constexpr int OFF_LAST = OFF_FOLD + NSUB * ROWS * 8;       // int[ROWS]: last key every score row sees
@@ -538,9 +542,25 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
 #pragma unroll
         for (int b2 = 0; b2 < B; ++b2) {
           const int mb = m0 + b2 * NSUB;
-          v[b2] = u32x4{0u, tag << 31, 0u, tag << 31};
+          v[b2] = u32x4{__float_as_uint(NEG_BIG), tag << 31, __float_as_uint(NEG_BIG), tag << 31};
           if (mb < T) v[b2] = __builtin_amdgcn_raw_buffer_load_b128(words, (mb * ROWS + 2 * rp) * 8, 0, COHERENT);
         }
+        auto fold_batch = [&]() {
+#pragma unroll
+          for (int row = 0; row < 2; ++row) {      // the greatest reference first: one exponential a member
+            float& Mr = row ? M1 : M;
+            float& Zr = row ? Z1 : Z;
+            float Mn = Mr;
+#pragma unroll
+            for (int b2 = 0; b2 < B; ++b2)
+              Mn = fmaxf(Mn, __uint_as_float(v[b2][2 * row]));
+            Zr *= __builtin_amdgcn_exp2f(Mr - Mn);
+#pragma unroll
+            for (int b2 = 0; b2 < B; ++b2)         // (a member that is not there has no sum)
+              Zr = fmaf(__uint_as_float(v[b2][2 * row + 1] & 0x7fffffffu), __builtin_amdgcn_exp2f(__uint_as_float(v[b2][2 * row]) - Mn), Zr);
+            Mr = Mn;
+          }
+        };
         if constexpr (ALL_AT_ONCE) {
           // words that are not there yet are asked for again, all of them at once per round: one
           // round trip per round, however many members are late
@@ -564,14 +584,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
                 v[b2] = __builtin_amdgcn_raw_buffer_load_b128(words, (mb * ROWS + 2 * rp) * 8, 0, COHERENT);
             }
           }
-#pragma unroll
-          for (int b2 = 0; b2 < B; ++b2) {
-            const int mb = m0 + b2 * NSUB;
-            if (mb < T) {
-              merge_stat(M, Z, make_float2(__uint_as_float(v[b2][0]), __uint_as_float(v[b2][1] & 0x7fffffffu)));
-              merge_stat(M1, Z1, make_float2(__uint_as_float(v[b2][2]), __uint_as_float(v[b2][3] & 0x7fffffffu)));
-            }
-          }
+          fold_batch();
         } else {
           // one after the other
 #pragma unroll
@@ -589,6 +602,12 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
                 __builtin_amdgcn_s_sleep(1);
                 v[b2] = __builtin_amdgcn_raw_buffer_load_b128(words, (mb * ROWS + 2 * rp) * 8, 0, COHERENT);
               }
+            }
+          }
+          if constexpr (S::AGAIN) { fold_batch(); } else {
+#pragma unroll
+            for (int b2 = 0; b2 < B; ++b2) {
+              if (m0 + b2 * NSUB >= T) continue;
               merge_stat(M, Z, make_float2(__uint_as_float(v[b2][0]), __uint_as_float(v[b2][1] & 0x7fffffffu)));
               merge_stat(M1, Z1, make_float2(__uint_as_float(v[b2][2]), __uint_as_float(v[b2][3] & 0x7fffffffu)));
             }
@@ -602,11 +621,45 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
     if (tid < ROWS) {
       M = NEG_BIG; Z = 0.f;
 #pragma unroll
-      for (int s2 = 0; s2 < NSUB; ++s2) merge_stat(M, Z, fold_lds[s2 * ROWS + tid]);
+      for (int s2 = 0; s2 < NSUB; ++s2) M = fmaxf(M, fold_lds[s2 * ROWS + tid].x);
+#pragma unroll
+      for (int s2 = 0; s2 < NSUB; ++s2) Z = fmaf(fold_lds[s2 * ROWS + tid].y, __builtin_amdgcn_exp2f(fold_lds[s2 * ROWS + tid].x - M), Z);
       // rows beyond R: weight zero
-      wts_lds[tid] = (tid < g.R) ? __builtin_amdgcn_exp2f(ref_lds[tid] - (M + __builtin_amdgcn_logf(Z))) : 0.f;
+      wts_lds[tid] = tid < g.R ? __builtin_amdgcn_exp2f(ref_lds[tid] - M) / Z : 0.f;
     }
     lds_barrier();
+  };
+
+  // Score of this lane's key of the tile of keys key0 + 32 kp .. + 31 of head hg_, from memory, the exponents of its terms raised: the numbers
+  // kept for a key hold none below 2^-126.  The head's statistics are still in LDS.  (In front of step F's last barrier, or with the row constants
+  // stored for it, this cost registers that step B needs: 262 us became 292 and 267.)
+  auto score_again = [&](const uint16_t* base_, int hg_, int kp) {
+    const KeySource src = key_source(tile_at(base_, S::ROTATE ? (kp - w.rot + KT) % KT : kp), lay.row_bytes);
+    const int lane_ = opaque(threadIdx.x) & 63, hf_ = lane_ >> 5, n32_ = lane_ & 31;
+    const int v = tile_offset(src.row0, lane_, lay.row_bytes);
+    const int key = w.key0 + kp * 32 + n32_;
+    const int mine = lane_ % ROWS;         // (the lanes hold a row's c each)
+    float M = NEG_BIG, Z = 0.f, sum = 0.f;
+#pragma unroll 1
+    for (int s2 = 0; s2 < S::NSUB; ++s2) merge_stat(M, Z, fold_lds[s2 * ROWS + mine]);
+    const float c = mine < g.R ? M + __builtin_amdgcn_logf(Z) : INFINITY;
+#pragma unroll 1
+    for (int rt = 0; rt < NRT; ++rt) {
+      f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      const uint16_t* row = q + ((size_t)hg_ * g.R + min(rt * 32 + n32_, g.R - 1)) * D + hf_ * 8;
+#pragma unroll 1
+      for (int t = 0; t < KS; ++t)
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(row + t * 16), load_operand(src, v, t), s, 0, 0, 0);
+#pragma unroll 1
+      for (int i = 0; i < 16; ++i) {
+        const int r = rt * 32 + acc_row(i, hf_);
+        const float cr = __shfl(c, r);     // (all lanes)
+        const float x = key > last_lds[r] ? -INFINITY : fmaf(s[0], g.scale2, -cr);
+        sum += x < -126.f ? __builtin_amdgcn_exp2f(x + 64.f) * 0x1p-64f : __builtin_amdgcn_exp2f(x);
+        s = __builtin_shufflevector(s, s, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 0);
+      }
+    }
+    return sum + __shfl_xor(sum, 32);
   };
 
   // ---- the team's heads -----------------------------------------------------------------------
@@ -655,7 +708,10 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
 #pragma unroll
       for (int v = 1; v < F_WAVES; ++v) m = fmaxf(m, stat_lds[v * ROWS + tid]);
       // (a row that sees none of the workgroup's keys: a finite "nothing")
-      ref_lds[tid] = (m > NEG_BIG ? m : NEG_BIG) * g.scale2;
+      // A whole number: statistics of different references are then brought together by exact powers of two, and the relative error
+      // that the exponential instruction has on average is in e and Z alike.  Scores, error against 64 bits (2-norm), 8 heads x 30011 keys, 64 rows:
+      // references as they come, merged one by one, weights exp2(m - (M + log2 Z)) 3.8e-7, now 7.8e-8 (two passes: 2.2e-7).
+      ref_lds[tid] = __builtin_ceilf((m > NEG_BIG ? m : NEG_BIG) * g.scale2);
     }
     lds_barrier();
     // ... e = exp2(s - m) in place, and the rows' sums
@@ -703,6 +759,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
     // E
     gather_fold(nth);
     // F: this wave's keys
+    bool tiny = false;
     {
       const int n32f = opaque(w.n32), hff = opaque(w.hf);
       float part[KT];
@@ -718,16 +775,34 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
 #pragma unroll
           for (int i = 0; i < 16; ++i) part[kt] = fmaf(E[kt * NRT + rt][i], wv[i >> 2][i & 3], part[kt]);
       });
+      float least = 1.f;
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) {
         const float tot = part[kt] + __shfl_xor(part[kt], 32);
+        if constexpr (S::AGAIN) least = fminf(least, tot);
         const int kp = S::ROTATE ? (kt + w.rot) % KT : kt;
         const int j = w.key0 + kp * 32 + n32f;
         if (hff == 0) raw_lds[wave * KEYS_PER_WAVE + kp * 32 + n32f] = j < g.L ? tot : 0.f;
       }
+      if constexpr (S::AGAIN) tiny = __any(least < TINY);
     }
     lds_barrier();                         // raw scores complete; weights and maxima free
+    if (S::AGAIN && __builtin_expect(tiny, 0)) {      // this wave's keys (here, where no register holds numbers of a head)
+      const int l = opaque(threadIdx.x) & 63;
+      int furthest = l < g.R ? last_lds[l] : 0;              // the last key any row sees
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) furthest = max(furthest, __shfl_xor(furthest, o));
+      float* mine = raw_lds + wave * KEYS_PER_WAVE;
+#pragma unroll 1
+      for (int kp = 0; kp < KT; ++kp) {
+        const int j = w.key0 + kp * 32 + (l & 31);
+        if (!__any(mine[kp * 32 + (l & 31)] < TINY && j <= furthest)) continue;
+        const float tot = score_again(base, hg, kp);
+        if (l < 32 && j < g.L) mine[kp * 32 + l] = tot;
+      }
+    }
     if (!more || __builtin_amdgcn_readfirstlane(gave_up[0])) {
+      if constexpr (S::AGAIN) lds_barrier();
       pool_head(hg);
       break;
     }
@@ -802,12 +877,14 @@ bool make_plan(const ScoreGeom& g, int pool, int resident, FusedPlan* out) {
 // GPU_MAX_HW_QUEUES.  A stream that is confined to some compute units has fewer places, and what stream a recorded launch will run on is not
 // known: cooperative launches, as for longer teams.
 // us a call (laq_evict), cooperative : ordinary: 256 heads x 16384 keys, 64 rows 290 : 279; x 8001 keys, 32 rows 170 : 151; 32 heads x 32768, 32 rows 100 : 78.
-bool ordinary_launch(const FusedPlan& plan, int resident, int cus, hipStream_t st) {
+bool ordinary_team(const FusedPlan& plan, int resident) {
   static const long long at_a_time = [] {
     const char* v = getenv("GPU_MAX_HW_QUEUES");
     return std::max(4LL, v != nullptr ? atoll(v) : 0LL);
   }();
-  if (2 * (plan.T - 1) * at_a_time >= resident) return false;
+  return 2 * (plan.T - 1) * at_a_time < resident;
+}
+bool ordinary_stream(int cus, hipStream_t st) {
   constexpr int WORDS = 32;
   uint32_t mask[WORDS] = {};
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -860,7 +937,7 @@ hipError_t launch_fused_rows(const ScoreGeom& g, const WindowPos& qp, const KvLa
     const char* v = getenv("LAQ_COOPERATIVE_LAUNCH");
     return v != nullptr && v[0] == '0';
   }();
-  if (plain_launch || (Cfg<NRT>::DRAWS && ordinary_launch(plan, resident, fused_cus[dev].load(std::memory_order_acquire), st)))
+  if (plain_launch || (Cfg<NRT>::DRAWS && ordinary_team(plan, resident) && ordinary_stream(fused_cus[dev].load(std::memory_order_acquire), st)))
     e = hipLaunchKernel(fn, dim3(plan.n_teams * plan.T), dim3(F_THREADS), args, bytes, st);
   else e = hipLaunchCooperativeKernel(fn, dim3(plan.n_teams * plan.T), dim3(F_THREADS), args, bytes, st);
   if (e != hipSuccess) return e;
@@ -910,6 +987,15 @@ hipError_t score_fused_applies(const ScoreGeom& g, const KvLayout& lay, int dtyp
   FusedPlan plan;
   *yes = make_plan(g, 1, fused_resident[dev][slot_of(tiles_for(g.Rpad))].load(std::memory_order_acquire), &plan);
   return hipSuccess;
+}
+
+bool score_fused_light(const ScoreGeom& g, const KvLayout& lay, int dtype, const hipStream_t* st) {
+  int dev = 0;
+  FusedPlan plan;
+  if (!score_fused_supported(g, lay, dtype) || g.Rpad > 64 || hipGetDevice(&dev) != hipSuccess || score_fused_init(dev) != hipSuccess) return false;
+  const int resident = fused_resident[dev][slot_of(tiles_for(g.Rpad))].load(std::memory_order_acquire);
+  return make_plan(g, 1, resident, &plan) && ordinary_team(plan, resident) &&
+         (st == nullptr || ordinary_stream(fused_cus[dev].load(std::memory_order_acquire), *st));
 }
 
 // Scores of every head into `scores`: raw with pool == 1, else max-pooled over the prefix.  *done

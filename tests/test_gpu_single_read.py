@@ -2,7 +2,7 @@
 softmax denominators are known) vs the CPU oracle (needs an MI355X).
 
 laq_score takes that kernel for bf16 caches with d = 128 and at most 64 score rows per KV head
-(R = G * W), by itself from 128 MiB of keys per call on and below that when the shape asks for it, as
+(R = G * W), by itself from some size of the call on and below that when the shape asks for it, as
 the cases here do; a team of workgroups shares a head, 512 keys each with more than 32 score rows,
 1024 otherwise.  The cases walk the team sizes (one workgroup, a ragged last workgroup, a key count
 one past a boundary) for both, the row counts, heads fewer and more than the teams the device
@@ -145,6 +145,32 @@ def test_explicit_query_positions_and_scale(laq):
     score_and_check(laq, q, k, 7, "positions-pooled", [(0, 1)], q_pos=q_pos, keep=0)
     # a sharper softmax (large logits): the probabilities span hundreds of binary orders of magnitude
     score_and_check(laq, q, k, 1, "scale-1.5", [(0, 0), (1, 1)], scale=1.5)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("order", ["spread", "falling"])
+@pytest.mark.parametrize("W", [8, 16])
+def test_denormal_scores(laq, W, order, paged):
+    """Logits 0, -1/4, -1/2, ...: lists that end among scores below 2^-126, in workgroups with large ones and (falling, 64 rows) in one without."""
+    n, Hq, Hkv, L = 2, 8, 2, 1800
+    rank = torch.arange(L) * 11 // 16 if order == "falling" else torch.randperm(L, generator=torch.Generator().manual_seed(W))
+    q, k = torch.zeros(n, Hq, W, D), torch.zeros(n, Hkv, L, D)
+    q[..., :2] = 1.0
+    k[..., 0], k[..., 1] = -8.0 * (rank // 32).clamp(max=64), -0.25 * (rank % 32)
+    pos = [L + w for w in range(W)]
+    kd, kw = k.bfloat16().to(DEV), {}
+    if paged:
+        table = torch.randperm(n * 8, generator=torch.Generator().manual_seed(3)).reshape(n, 8).int().to(DEV)
+        pool = torch.zeros(n * 8, Hkv, 256, D, dtype=torch.bfloat16, device=DEV)
+        pool[table.long()] = torch.nn.functional.pad(kd, (0, 0, 0, 8 * 256 - L)).reshape(n, Hkv, 8, 256, D).transpose(1, 2)
+        kd, kw = pool, dict(block_table=table, L=L)
+    below = int((rank < 400).sum())                  # (2^-126 lies at rank 349, 2^-149 at 413; equal ranks: the lower positions)
+    scores, idx, _, _ = laq.laq_evict(q.bfloat16().to(DEV), kd, None, [below] * n, 1, scale=1.0, q_pos=pos, keep=0, choose="single-read", **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(idx.cpu().reshape(n * Hkv, below), torch.nonzero(rank < 400).flatten().int().expand(n * Hkv, below))
+    want = oracle.raw_scores(q[0].bfloat16(), k[0].bfloat16(), 1.0, q_pos=pos)
+    rows = Hq // Hkv * W                             # (the bound of the other kernels' test of such scores)
+    assert ((scores.cpu().double() - want).abs() <= 1.2e-5 * want + rows * 2.0 ** -149).all()
 
 
 def test_which_kernel(laq):
