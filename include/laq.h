@@ -171,7 +171,8 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *                               head, L up to 1024 / 512 / 256 keys (for at most 32 / 64 / 128
  *                               score rows) x the workgroups the device holds, 512 on an MI355X.
  *                               The library takes that kernel by itself with at most 64 score
- *                               rows and at least 128 MiB of keys in the call, where it is the
+ *                               rows and at least 40 to 48 MiB of keys in the call (128 MiB where its
+ *                               launch is a cooperative one, see below), where it is the
  *                               faster one; shape.score_choice asks for it or against it.
  *                               Heads of at most 1024 keys that one workgroup holds are read once
  *                               too.  Otherwise K is streamed twice (laq_score_kernel() says which).

@@ -208,17 +208,24 @@ static bool usual_shape(const ScoreGeom& g, const KvLayout& lay, int dtype) {
          ((long long)(lay.table ? lay.block_rows : g.L) + CHUNK_ROWS) * lay.row_bytes < 0x7fffffffLL;
 }
 
-// The single-read kernel's cooperative launch and its serial start cost about 15 us more than the
-// launches of the two passes; measured on an MI355X it is the faster one from 128 MiB of
-// keys per call on (21-27 % at 1 GiB and more).
-static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g) {
+// The single-read kernel's serial start, and its cooperative launch where it has one, cost more than the launches of the two
+// passes; from some size of the call on it is the faster one (21-27 % at 1 GiB and more).
+// laq_evict, bf16, the two passes : this one with an ordinary launch, us:
+//   64 rows  36 MiB 1100 to 5000 keys 1.06-1.09, 2 x 8 heads x 8200 35.4 : 36.5;  43 MiB 3100 keys 41.0 : 35.7, 1100 keys 49.8 : 41.5;  49 to 70 MiB
+//            1.08-1.29;  94 to 120 MiB 1.12-1.31
+//   32 rows  36 MiB 1300 to 5000 keys 1.04-1.13, 8200 keys 34.6 : 34.8;  48 to 54 MiB 1300 to 30011 keys 1.02-1.22;  62 to 70 MiB .98 (8200 keys), 1.00-1.24;
+//            94 to 120 MiB 1.06-1.34;  1100 keys (a team's second workgroup nearly empty) 37 MiB .88, 64 MiB .99, 97 MiB 1.05
+// With a cooperative launch (15 to 20 us more) from 128 MiB on.
+static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const hipStream_t* st) {
   if (shape->score_choice == LAQ_CHOOSE_SINGLE_READ) return true;
   if (shape->score_choice == LAQ_CHOOSE_TWO_PASS) return false;
   // by itself: where it is the faster one -- at most 64 score rows per KV head (with more, a
   // workgroup holds 256 keys and reads as many bytes of its team's statistics as of keys) and
-  // enough keys to pay for the cooperative launch
+  // enough keys to pay for its start
   const long long key_bytes = (long long)g.n_inst * g.Hkv * g.L * g.d * (shape->dtype == LAQ_F32 ? 4 : 2);
-  return g.Rpad <= 64 && key_bytes >= (128LL << 20);
+  if (g.Rpad > 64) return false;
+  if (key_bytes >= (128LL << 20)) return true;
+  return key_bytes >= ((g.Rpad > 32 ? 40LL : 48LL) << 20) && (g.Rpad > 32 || g.L > 1280) && score_fused_light(g, lay, shape->dtype, st);
 }
 
 // Heads of a call from which on their gather is spread over enough compute units with a workgroup each.
@@ -286,21 +293,20 @@ static bool head_wanted(const laq_shape* shape, const ScoreGeom& g) {
   return heads >= HEAD_MANY ? heads <= 768 : g.L <= 768 && g.Rpad <= (f32 ? 32 : 64);
 }
 
-static ScorePath score_path(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay) {
+static ScorePath score_path(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, hipStream_t st) {
   if (head_wanted(shape, g)) return ScorePath::head;
-  if (SINGLE_READ_ENABLED && usual_shape(g, lay, shape->dtype) && score_fused_supported(g, lay, shape->dtype) && single_read_wanted(shape, g))
+  if (SINGLE_READ_ENABLED && usual_shape(g, lay, shape->dtype) && score_fused_supported(g, lay, shape->dtype) && single_read_wanted(shape, g, lay, &st))
     return ScorePath::single_read;
   return tile_wanted(shape, g) ? ScorePath::tile : ScorePath::wave;
 }
 
 // Whether scores that are to be pooled come raw from the kernels that make them.
-static bool leaves_raw(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay) {
-  const ScorePath path = score_path(shape, g, lay);
+static bool leaves_raw(const laq_shape* shape, ScorePath path) {
   return path == ScorePath::tile || path == ScorePath::wave || (path == ScorePath::single_read && pool_avg(shape));
 }
 
 // Scores of a validated call into `scores`: pooled, or, with pool == 1, raw.
-static int score_checked(const laq_shape* shape, const ScoreGeom& g, const QueryPos& positions, const KvLayout& lay, const void* q_win,
+static int score_checked(const laq_shape* shape, const ScoreGeom& g, const QueryPos& positions, const KvLayout& lay, ScorePath path, const void* q_win,
                          const void* k, int pool, float* scores, void* ws, hipStream_t st) {
   if (g.Hkv > 65535 || g.n_inst > 65535 || (long long)g.Hkv * g.n_inst > 0x7fffffffLL) return LAQ_ERR_UNSUPPORTED;
   if ((g.L + 255) / 256 > 65535) return LAQ_ERR_UNSUPPORTED;      // grid limit of the pooling kernel
@@ -310,7 +316,6 @@ static int score_checked(const laq_shape* shape, const ScoreGeom& g, const Query
   WindowPos qp;
   hipError_t e = window_positions(g, positions, w, st, &qp);
   if (e != hipSuccess) return LAQ_ERR_DEVICE;
-  const ScorePath path = score_path(shape, g, lay);
   if (path == ScorePath::single_read) {
     const bool apart = pool > 1 && pool_avg(shape);
     bool done = false;
@@ -347,7 +352,7 @@ static int score_impl(const laq_shape* shape, const void* q_win, const void* k, 
   if (make_layout(shape, g, &lay) != LAQ_OK) return LAQ_ERR_INVALID;
   if (!pool_ok(pool) || !q_win || !k || !scores) return LAQ_ERR_INVALID;
   if (!ws || ws_bytes < workspace_bytes(g)) return LAQ_ERR_WORKSPACE;
-  return score_checked(shape, g, qp, lay, q_win, k, pool, scores, ws, st);
+  return score_checked(shape, g, qp, lay, score_path(shape, g, lay, st), q_win, k, pool, scores, ws, st);
 }
 
 // launch(n, i0, table) for runs of at most MAX_INST_PER_LAUNCH instances
@@ -471,14 +476,14 @@ static int decode_impl(const laq_shape* shape, const void* q, const void* kc, co
 // line is one by heads.  32 and 64 rows, 6000 to 16380 keys, several : one:   64 heads 64, 96, 128 KiB 1.03-1.06, 1.01-1.04, .99-1.00
 //   96 heads 96, 128, 192 KiB 1.01-1.04, 1.00-1.02, .95-.98;  128 heads 128, 192 KiB 1.00-1.03, .99-1.00;  160 heads 128, 192 KiB 1.02-1.04, 1.01-1.03
 //   256 heads 128, 192, 256 KiB 1.01-1.04; with rows 2 KiB apart 192 heads x 3867 keys, 217 KiB .97
-static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const int32_t* budget, int pool, const float* raw,
+static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, ScorePath path, const int32_t* budget, int pool, const float* raw,
                           int row_bytes) {
   const long long heads = (long long)g.n_inst * g.Hkv;
   const int keys = g.P + row_shift(raw, g.L);
   if ((pool - 1) / 2 > SELECT_POOL_MAX_HALF || keys > FINISH_MAX_KEYS || heads > 256 || shape->n_inst > MAX_INST_PER_LAUNCH) return false;
   long long gather = 0;
   if (keys <= 2048) gather = 32 << 10;
-  else if (pool > 1 && !leaves_raw(shape, g, lay)) gather = heads < 128 ? heads * 1280 : 160 << 10;
+  else if (pool > 1 && !leaves_raw(shape, path)) gather = heads < 128 ? heads * 1280 : 160 << 10;
   else if (heads >= 160) gather = 128 << 10;
   else if (keys <= 4096 || (keys <= 8192 && heads >= 128)) gather = 96 << 10;
   else if (keys <= 8192) gather = 32 << 10;
@@ -491,10 +496,10 @@ static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, const KvLa
 }
 
 // Whether the selection kernel pools the raw scores of this call on the way: a launch, a read and a write of the scores less.
-static bool select_pools(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, int pool, const float* raw) {
+static bool select_pools(const laq_shape* shape, const ScoreGeom& g, ScorePath path, int pool, const float* raw) {
   const int keys = g.P + row_shift(raw, g.L);
   return pool > 1 && (pool - 1) / 2 <= SELECT_POOL_MAX_HALF && keys <= SELECT_POOL_MAX_KEYS &&
-         (keys <= SELECT_POOL_MANY_KEYS || (long long)g.n_inst * g.Hkv < SELECT_MANY_HEADS) && leaves_raw(shape, g, lay);
+         (keys <= SELECT_POOL_MANY_KEYS || (long long)g.n_inst * g.Hkv < SELECT_MANY_HEADS) && leaves_raw(shape, path);
 }
 
 static FinishArgs finish_args(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const void* k, const void* v, int pool, float* scores,
@@ -656,22 +661,22 @@ static int evict_impl(const laq_shape* shape, const void* q_win, const void* k, 
   if (!scores) scores = w.pooled;        // the hand-over plane between the stages
   const int row_bytes = g.d * (shape->dtype == LAQ_F32 ? 4 : 2);
   float* raw = pool_kernel > 1 ? w.raw : scores;
-  const laq::ScorePath path = laq::score_path(shape, g, lay);
+  const laq::ScorePath path = laq::score_path(shape, g, lay, st);
   if (path == laq::ScorePath::head && laq::head_gathers(shape, g, budget, pool_kernel, row_bytes))
     return laq::head_checked(shape, g, qp, lay, laq::finish_args(shape, g, lay, k, v, pool_kernel, scores, k_out, v_out), q_win, k, budget, idx, ws, st);
-  if (path != laq::ScorePath::head && laq::finish_wanted(shape, g, lay, budget, pool_kernel, raw, row_bytes)) {
-    const int rc = laq::score_checked(shape, g, qp, lay, q_win, k, 1, raw, ws, st);
+  if (path != laq::ScorePath::head && laq::finish_wanted(shape, g, path, budget, pool_kernel, raw, row_bytes)) {
+    const int rc = laq::score_checked(shape, g, qp, lay, path, q_win, k, 1, raw, ws, st);
     if (rc != LAQ_OK) return rc;
     return laq::finish_checked(g, laq::finish_args(shape, g, lay, k, v, pool_kernel, scores, k_out, v_out), budget, raw, idx, st);
   }
   int rc;
-  if (laq::select_pools(shape, g, lay, pool_kernel, raw)) {
-    rc = laq::score_checked(shape, g, qp, lay, q_win, k, 1, raw, ws, st);
+  if (laq::select_pools(shape, g, path, pool_kernel, raw)) {
+    rc = laq::score_checked(shape, g, qp, lay, path, q_win, k, 1, raw, ws, st);
     if (rc != LAQ_OK) return rc;
     const laq::PoolArgs pooling{scores, (pool_kernel - 1) / 2, laq::pool_avg(shape) ? 1 : 0};
     rc = laq::select_impl(shape, raw, budget, 1, idx, st, &pooling);
   } else {
-    rc = laq::score_checked(shape, g, qp, lay, q_win, k, pool_kernel, scores, ws, st);
+    rc = laq::score_checked(shape, g, qp, lay, path, q_win, k, pool_kernel, scores, ws, st);
     if (rc != LAQ_OK) return rc;
     rc = laq::select_impl(shape, scores, budget, 1, idx, st);
   }
@@ -703,7 +708,7 @@ int laq_score_kernel(const laq_shape* shape) {
   if (laq::head_wanted(shape, g)) return LAQ_KERNEL_WHOLE_HEAD;
   if (!laq::usual_shape(g, lay, shape->dtype)) return LAQ_KERNEL_VECTOR;
   bool single = false;
-  if (laq::SINGLE_READ_ENABLED && laq::single_read_wanted(shape, g) &&
+  if (laq::SINGLE_READ_ENABLED && laq::single_read_wanted(shape, g, lay, nullptr) &&
       laq::score_fused_applies(g, lay, shape->dtype, &single) != hipSuccess)
     return LAQ_ERR_DEVICE;
   return single ? LAQ_KERNEL_SINGLE_READ : LAQ_KERNEL_TWO_PASS;
