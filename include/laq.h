@@ -123,7 +123,7 @@ typedef struct laq_shape {
   int64_t kv_stride_block;
   /*
    * Which scoring kernels to take where more than one applies (laq_score_choice; 0 = LAQ_CHOOSE_AUTO:
-   * the single-read kernel for at most 64 score rows per KV head from 128 MiB of keys per call on,
+   * the single-read kernel for at most 64 score rows per KV head from 40 to 48 MiB of keys per call on (see laq_score),
    * otherwise two passes over the keys, which are the faster ones with more rows, in small calls and for unusual
    * head sizes with one chunk of 256 keys per workgroup, or, for heads of at most 512 keys and many of at most
    * 1024, a whole head in one workgroup).  A choice that does not apply to the shape is ignored;

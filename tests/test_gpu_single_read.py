@@ -193,6 +193,35 @@ def test_which_kernel(laq):
         laq.laq_score_kernel(2, 32, 8, 128, 4096, 0, bf)
 
 
+@pytest.mark.parametrize("n,L,W,light", [(3, 6827, 16, True), (3, 6750, 16, False), (5, 4916, 8, True), (5, 4900, 8, False), (24, 1281, 8, True),
+                                          (26, 1280, 8, False)])
+def test_which_kernel_by_the_launch(laq, n, L, W, light):
+    # either side of the lines for an ordinary launch (40 MiB of keys with 64 score rows, 48 with 32, there beyond 1280 keys a head); a captured call
+    # keeps the two passes, on a replay too, and scores and lists agree to within rounding
+    bf = torch.bfloat16
+    kind = laq.laq_score_kernel(n, 32, 8, D, L, W, bf)
+    assert kind == ("single-read" if light else "two-pass")
+    q, k = draw(n, 8, 4, L, W, seed=L, sinks=False)
+    q, k = q.to(DEV), k.to(DEV)
+    ws = torch.full((laq.laq_workspace_bytes(n, 32, 8, D, L, W, bf),), 0xFF, dtype=torch.uint8, device=DEV)
+    out, pooled = torch.empty(n, 8, L, device=DEV), torch.empty(n, 8, L, device=DEV)
+    laq.laq_score(q, k, 7, scores=out, ws=ws)
+    assert torch.equal(out, laq.laq_score(q, k, 7, choose=kind))
+    assert laq.laq_workspace_status(ws, n, 32, 8, D, L, W, bf) == 0
+    got = laq.laq_evict(q, k, k, [200] * n, 7, ws=ws)             # (pooled in another kernel, from the same raw scores)
+    assert torch.equal(got[0], out) and torch.equal(got[1], laq.laq_select(out, [200] * n, 1, W))
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        laq.laq_score(q, k, 7, scores=pooled, ws=ws)
+    two = laq.laq_score(q, k, 7, choose="two-pass")
+    for _ in range(3):
+        pooled.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(pooled, two)
+    np.testing.assert_allclose(out.cpu().numpy(), two.cpu().numpy(), rtol=2e-5, atol=1e-30)
+
+
 def test_status_is_defined_after_every_kind_of_call(laq):
     # a workspace full of ones: whichever kernels score, the call leaves "all waits completed" behind
     for (W, d, dt, kind) in ((8, 128, torch.bfloat16, "single-read"), (32, 128, torch.bfloat16, "two-pass"),
