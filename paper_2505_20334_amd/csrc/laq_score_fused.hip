@@ -889,8 +889,10 @@ bool ordinary_stream(int cus, hipStream_t st) {
   uint32_t mask[WORDS] = {};
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (cus > WORDS * 32) return false;
-  if (hipStreamIsCapturing(st, &capture) != hipSuccess ||
-      (capture == hipStreamCaptureStatusNone && hipExtStreamGetCUMask(st, (cus + 31) / 32, mask) != hipSuccess)) {
+  // (the handles that name a stream without being one: only the per-thread stream can be captured, neither has a mask of its own)
+  const hipStream_t masked = st == hipStreamLegacy || st == hipStreamPerThread ? nullptr : st;
+  if (hipStreamIsCapturing(st == hipStreamLegacy ? nullptr : st, &capture) != hipSuccess ||
+      (capture == hipStreamCaptureStatusNone && hipExtStreamGetCUMask(masked, (cus + 31) / 32, mask) != hipSuccess)) {
     (void)hipGetLastError();                       // (not for the launches that follow to find)
     return false;
   }
