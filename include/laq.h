@@ -123,7 +123,7 @@ typedef struct laq_shape {
   int64_t kv_stride_block;
   /*
    * Which scoring kernels to take where more than one applies (laq_score_choice; 0 = LAQ_CHOOSE_AUTO:
-   * the single-read kernel for at most 64 score rows per KV head from 40 to 48 MiB of keys per call on (see laq_score),
+   * the single-read kernel for at most 64 score rows per KV head where the call has enough keys (see laq_score),
    * otherwise two passes over the keys, which are the faster ones with more rows, in small calls and for unusual
    * head sizes with one chunk of 256 keys per workgroup, or, for heads of at most 512 keys and many of at most
    * 1024, a whole head in one workgroup).  A choice that does not apply to the shape is ignored;
@@ -170,22 +170,34 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *                               are known: bf16, d = 128, at most 128 score rows G * W per KV
  *                               head, L up to 1024 / 512 / 256 keys (for at most 32 / 64 / 128
  *                               score rows) x the workgroups the device holds, 512 on an MI355X.
- *                               The library takes that kernel by itself with at most 64 score
- *                               rows and at least 40 to 48 MiB of keys in the call (128 MiB where its
- *                               launch is a cooperative one, see below), where it is the
- *                               faster one; shape.score_choice asks for it or against it.
+ *                               The library takes that kernel by itself where it is the faster one
+ *                               and its waits are safe (see below): with 33 to 64 score rows from
+ *                               40 MiB of keys in the call on, with at most 32 from 48 MiB on if heads
+ *                               have more than 1280 keys; but captured calls, and heads of more than
+ *                               32768 (with at most 32 rows 65536) keys, from 128 MiB on.
+ *                               shape.score_choice asks for it or against it.
  *                               Heads of at most 1024 keys that one workgroup holds are read once
  *                               too.  Otherwise K is streamed twice (laq_score_kernel() says which).
  *                               The single-read kernel's workgroups wait for the others of their
- *                               team; it is an ordinary launch where that cannot end in a deadlock
- *                               with other such launches (at most 64 score rows, a team takes at most
- *                               an eighth of the workgroups that the device holds, or less where
- *                               GPU_MAX_HW_QUEUES is more than 4, and the stream may use all
- *                               compute units and is not being captured), else a cooperative one.
- *                               With LAQ_COOPERATIVE_LAUNCH=0 in the environment (read at the first
- *                               such call) it is always an ordinary launch, for
- *                               profilers that cannot follow cooperative launches -- then
- *                               other work on the device can make the call end in LAQ_ERR_TIMEOUT.
+ *                               team.  These waits end, whatever other calls of this library the
+ *                               process runs at the same time, as long as a team is at most a quarter
+ *                               of the workgroups that the device holds (L up to 131072 / 65536 /
+ *                               32768 keys on an MI355X) and the launch goes through one of the four
+ *                               hardware queues that a process's streams of normal priority share,
+ *                               with all compute units open to it.  Elsewhere (longer heads, streams
+ *                               confined to some compute units or of another priority) the library
+ *                               takes the two passes, which wait for nobody, unless score_choice asks
+ *                               for this kernel: then a cooperative launch, which may give up
+ *                               (LAQ_ERR_TIMEOUT of laq_workspace_status, invalid scores; the others do
+ *                               not) if other calls on other streams share the device with it.
+ *                               What the library cannot see is the caller's part: a recorded call is
+ *                               replayed on streams of the kind first named, and of P processes that
+ *                               make such calls on one GPU at the same time each keeps to L up to
+ *                               65536/P / 32768/P / 16384/P keys; or choose LAQ_CHOOSE_TWO_PASS.
+ *                               With GPU_MAX_HW_QUEUES above 4 in the environment all launches of the
+ *                               kernel are cooperative.  With LAQ_COOPERATIVE_LAUNCH=0 in the
+ *                               environment (read at the first such call) none is, for profilers that
+ *                               cannot follow cooperative launches.
  *   scores [n_inst, Hkv, L]     fp32 out.  For each KV head g and key j:
  *            raw[g,j] = sum over the G heads of the group and the W queries of
  *                       softmax_j(scale * <q, k_j>) restricted to j <= P + w.

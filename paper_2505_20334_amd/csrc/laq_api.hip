@@ -208,24 +208,25 @@ static bool usual_shape(const ScoreGeom& g, const KvLayout& lay, int dtype) {
          ((long long)(lay.table ? lay.block_rows : g.L) + CHUNK_ROWS) * lay.row_bytes < 0x7fffffffLL;
 }
 
-// The single-read kernel's serial start, and its cooperative launch where it has one, cost more than the launches of the two
-// passes; from some size of the call on it is the faster one (21-27 % at 1 GiB and more).
-// laq_evict, bf16, the two passes : this one with an ordinary launch, us:
+// The single-read kernel's serial start costs more than the launches of the two passes; from some size of the call on it is the faster one (21-27 % at 1 GiB and more).
+// laq_evict, bf16, the two passes : this one, us:
 //   64 rows  36 MiB 1100 to 5000 keys 1.06-1.09, 2 x 8 heads x 8200 35.4 : 36.5;  43 MiB 3100 keys 41.0 : 35.7, 1100 keys 49.8 : 41.5;  49 to 70 MiB
 //            1.08-1.29;  94 to 120 MiB 1.12-1.31
 //   32 rows  36 MiB 1300 to 5000 keys 1.04-1.13, 8200 keys 34.6 : 34.8;  48 to 54 MiB 1300 to 30011 keys 1.02-1.22;  62 to 70 MiB .98 (8200 keys), 1.00-1.24;
 //            94 to 120 MiB 1.06-1.34;  1100 keys (a team's second workgroup nearly empty) 37 MiB .88, 64 MiB .99, 97 MiB 1.05
-// With a cooperative launch (15 to 20 us more) from 128 MiB on.
+// Longer teams (one counter, see laq_team.h) and captured calls from 128 MiB on.
 static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const hipStream_t* st) {
   if (shape->score_choice == LAQ_CHOOSE_SINGLE_READ) return true;
   if (shape->score_choice == LAQ_CHOOSE_TWO_PASS) return false;
   // by itself: where it is the faster one -- at most 64 score rows per KV head (with more, a
   // workgroup holds 256 keys and reads as many bytes of its team's statistics as of keys) and
-  // enough keys to pay for its start
+  // enough keys to pay for its start -- and its waits are safe next to any other calls
   const long long key_bytes = (long long)g.n_inst * g.Hkv * g.L * g.d * (shape->dtype == LAQ_F32 ? 4 : 2);
-  if (g.Rpad > 64) return false;
-  if (key_bytes >= (128LL << 20)) return true;
-  return key_bytes >= ((g.Rpad > 32 ? 40LL : 48LL) << 20) && (g.Rpad > 32 || g.L > 1280) && score_fused_light(g, lay, shape->dtype, st);
+  const bool many = key_bytes >= (128LL << 20);
+  if (g.Rpad > 64 || (!many && (key_bytes < ((g.Rpad > 32 ? 40LL : 48LL) << 20) || (g.Rpad <= 32 && g.L <= 1280)))) return false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (!many && st != nullptr && (hipStreamIsCapturing(*st == hipStreamLegacy ? nullptr : *st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) return false;
+  return score_fused_counters(g, lay, shape->dtype, st) >= (many ? 1 : 2);
 }
 
 // Heads of a call from which on their gather is spread over enough compute units with a workgroup each.

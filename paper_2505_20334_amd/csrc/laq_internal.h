@@ -194,8 +194,9 @@ hipError_t score_fused_init(int dev);
 size_t fused_sync_bytes(const ScoreGeom& g);
 bool score_fused_supported(const ScoreGeom& g, const KvLayout& lay, int dtype);
 hipError_t score_fused_applies(const ScoreGeom& g, const KvLayout& lay, int dtype, bool* yes);
-// whether it would with an ordinary launch (st null: on a stream that is not captured and may use all compute units)
-bool score_fused_light(const ScoreGeom& g, const KvLayout& lay, int dtype, const hipStream_t* st);
+// 0: where the rule for its launches (laq_team.h) does not hold; else the number of counters that its teams draw from (st null: on a
+// stream of normal priority that may use all compute units)
+int score_fused_counters(const ScoreGeom& g, const KvLayout& lay, int dtype, const hipStream_t* st);
 // single-read scoring (K streamed once); *done = false: not launched, take the two-pass kernels
 hipError_t launch_score_fused(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const void* q,
                               const void* k, float* scores, const Workspace& ws, hipStream_t st, bool* done);

@@ -44,16 +44,16 @@
 // them has timed out (status word of the workspace).
 //
 // A workgroup's place in a team is a number that it draws when it starts, so teams are complete one
-// after the other in the order in which workgroups get on the device, and of a launch at most two (there are two
+// after the other in the order in which workgroups get on the device, and of a launch at most two (there are up to two
 // counters) are there in part.  An ordinary launch is enough as long as the parts of teams that
-// all launches on the device could leave there do not fill it (ordinary_team()); else, and
-// for more than 64 score rows, a cooperative one is taken.
+// all launches on the device could leave there do not fill it (laq_team.h).
 #include <algorithm>
 #include <atomic>
 #include <cstdlib>
 #include <type_traits>
 
 #include "laq_internal.h"
+#include "laq_team.h"
 
 namespace laq {
 
@@ -77,6 +77,7 @@ constexpr int F_WAVES = 4, F_THREADS = F_WAVES * 64;   // one wave per SIMD; two
 constexpr int QROWB = D * 2 + 16;
 constexpr int ZT_STRIDE = 36;                // floats per row of a wave's transposition tile (conflict-free 128-bit reads)
 constexpr int SPIN_LIMIT = 1 << 20;          // probes; about a second, far beyond any legitimate wait
+constexpr int SPIN_LIMIT_UNSAFE = 1 << 18;   // of a launch that the rule of laq_team.h does not cover: it gives up before the others do
 constexpr int MAX_HALF = (MAX_POOL - 1) / 2;
 constexpr int COHERENT = 16;                 // cache policy bit "sc1": coherent across the device
 
@@ -108,7 +109,6 @@ template <int NRT> struct Cfg {
   static constexpr int ROWS = NRT * 32;
   static constexpr int PAIRS = 8;                                   // (key tile, row tile) pairs a wave keeps: 16 registers each
   static constexpr int KT = PAIRS / NRT;                            // key tiles per wave and head
-  static constexpr bool DRAWS = NRT <= 2;                           // places in teams are drawn (NRT 4: the workgroups' numbers, on request only)
   // scores below TINY are summed again (NRT 4: as they are; it has no registers for it: 21 spills -> 37)
   static constexpr bool AGAIN = NRT <= 2;
   static constexpr bool ROTATE = NRT == 2;                          // see WaveCtx::rot (the other instantiations lose registers to it)
@@ -343,16 +343,14 @@ struct FusedSync {
   int* status;             // != 0: a wait has timed out (results are not valid)
   int* started;            // two counters, SECOND apart: places that have been drawn
 };
-struct FusedPlan {
-  int T;                   // workgroups per team = ceil(L / keys per workgroup)
-  int n_teams;
-  int early;               // workgroups that draw from the first counter (whole teams of them)
-  int n_heads;             // team t takes heads t, t + n_teams, ...
+struct FusedPlan : TeamPlan {              // (teams of ceil(L / keys per workgroup) workgroups)
+  int n_heads;
   int half;                // (pool kernel - 1) / 2; 0: raw scores
+  int spin_limit;          // probes of a wait
 };
 
-// The place of a workgroup among those of the launch: member place % T of team place / T.  Drawn from one of two counters, the `early`
-// workgroups with the lowest numbers from the first.  The device takes workgroups in the order of their numbers within an XCD, and two on a compute unit
+// The place of a workgroup among those of the launch: member place % T of team place / T.  Drawn from one of two counters (one for the longer
+// teams, see laq_team.h), the `early` workgroups with the lowest numbers from the first.  The device takes workgroups in the order of their numbers within an XCD, and two on a compute unit
 // only when each has one; so the teams of either counter have at most one workgroup on a compute unit.  All from one counter, teams had both places
 // of some, whose workgroups do the same at the same time: 256 heads x 16384 keys, 64 rows 294 us, with two counters 279, by number 271.
 constexpr int SECOND = 16;                 // ints between the counters
@@ -382,11 +380,9 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int T = plan.T, half = plan.half;
-  if constexpr (S::DRAWS) {
-    if (tid == 0) gave_up[1] = drawn_place(sy.started, plan.early);
-    lds_barrier();
-  }
-  const int place = S::DRAWS ? __builtin_amdgcn_readfirstlane(gave_up[1]) : blockIdx.x;
+  if (tid == 0) gave_up[1] = drawn_place(sy.started, plan.early);
+  lds_barrier();
+  const int place = __builtin_amdgcn_readfirstlane(gave_up[1]);
   const int team = place / T, member = place - team * T;
   if (team >= plan.n_teams || team >= plan.n_heads) return;
   float* zt = reinterpret_cast<float*>(smem + S::OFF_ZT) + wave * 32 * ZT_STRIDE;
@@ -570,7 +566,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
             for (int b2 = 0; b2 < B; ++b2) missing |= (v[b2][1] >> 31) != tag || (v[b2][3] >> 31) != tag;
             if (!missing) break;
             if (gave_up[0]) break;
-            if (++probes > SPIN_LIMIT ||
+            if (++probes > plan.spin_limit ||
                 ((probes & 63) == 63 && __hip_atomic_load(sy.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
               __hip_atomic_store(sy.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               gave_up[0] = 1;
@@ -593,7 +589,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
             if (mb < T) {
               while ((v[b2][1] >> 31) != tag || (v[b2][3] >> 31) != tag) {
                 if (gave_up[0]) break;
-                if (++probes > SPIN_LIMIT ||
+                if (++probes > plan.spin_limit ||
                     ((probes & 63) == 63 && __hip_atomic_load(sy.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
                   __hip_atomic_store(sy.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                   gave_up[0] = 1;
@@ -854,15 +850,12 @@ int keys_per_block(int nrt) {
 // has no cooperative launch) and the caller takes the two-pass kernels.
 bool make_plan(const ScoreGeom& g, int pool, int resident, FusedPlan* out) {
   const int nrt = tiles_for(g.Rpad);
-  FusedPlan plan;
-  plan.T = (g.L + keys_per_block(nrt) - 1) / keys_per_block(nrt);
-  plan.half = (pool - 1) / 2;
   const long long n_heads = (long long)g.n_inst * g.Hkv;
-  if (resident <= 0 || plan.T > resident || n_heads > 0x7fffffffLL) return false;
+  FusedPlan plan;
+  if (n_heads > 0x7fffffffLL || !plan_teams((int)n_heads, (g.L + keys_per_block(nrt) - 1) / keys_per_block(nrt), resident, &plan)) return false;
   plan.n_heads = (int)n_heads;
-  plan.n_teams = resident / plan.T;
-  if (plan.n_teams > plan.n_heads) plan.n_teams = plan.n_heads;
-  plan.early = std::min(plan.n_teams, resident / 2 / plan.T) * plan.T;
+  plan.half = (pool - 1) / 2;
+  plan.spin_limit = SPIN_LIMIT;
   // the exchange memory is sized for FUSED_MAX_RESIDENT workgroups
   // (less the last 2 KiB of it, which hold the position table of a long window)
   if ((size_t)plan.n_teams * plan.T > (size_t)FUSED_MAX_RESIDENT - 8) return false;
@@ -870,37 +863,33 @@ bool make_plan(const ScoreGeom& g, int pool, int resident, FusedPlan* out) {
   return true;
 }
 
-// Whether an ordinary launch will do.  A workgroup waits only for its own team, and a launch has at most two teams (one per counter) that
-// are on the device in part: their up to T - 1 members wait for workgroups that start as soon as there is a place, and places come free as
-// whole teams end and as other kernels do.  Only if every place were taken by parts of teams, of many launches at a time, would
-// none come free.  Launches at a time: one per hardware queue (a stream's launches follow one another), which HIP makes 4 of, or
-// GPU_MAX_HW_QUEUES.  A stream that is confined to some compute units has fewer places, and what stream a recorded launch will run on is not
-// known: cooperative launches, as for longer teams.
-// us a call (laq_evict), cooperative : ordinary: 256 heads x 16384 keys, 64 rows 290 : 279; x 8001 keys, 32 rows 170 : 151; 32 heads x 32768, 32 rows 100 : 78.
-bool ordinary_team(const FusedPlan& plan, int resident) {
-  static const long long at_a_time = [] {
+// Whether the process has no more hardware queues than the rule of laq_team.h counts.  With more, every launch is a cooperative one, which
+// follow one another in one queue of the device.
+bool queues_as_counted() {
+  static const bool yes = [] {
     const char* v = getenv("GPU_MAX_HW_QUEUES");
-    return std::max(4LL, v != nullptr ? atoll(v) : 0LL);
+    return v == nullptr || atoll(v) <= HW_QUEUES;
   }();
-  return 2 * (plan.T - 1) * at_a_time < resident;
+  return yes;
 }
-bool ordinary_stream(int cus, hipStream_t st) {
+// Whether the launches of a stream go through the hardware queues that streams of normal priority share, and may use all compute units.  What
+// stream a recorded launch will run on is not known: taken for one of these.
+bool stream_shares_queues(hipStream_t st, int dev) {
   constexpr int WORDS = 32;
   uint32_t mask[WORDS] = {};
+  const int cus = fused_cus[dev].load(std::memory_order_acquire);
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  int priority = 0;
   if (cus > WORDS * 32) return false;
-  // (the handles that name a stream without being one: only the per-thread stream can be captured, neither has a mask of its own)
-  const hipStream_t masked = st == hipStreamLegacy || st == hipStreamPerThread ? nullptr : st;
-  if (hipStreamIsCapturing(st == hipStreamLegacy ? nullptr : st, &capture) != hipSuccess ||
-      (capture == hipStreamCaptureStatusNone && hipExtStreamGetCUMask(masked, (cus + 31) / 32, mask) != hipSuccess)) {
+  if (hipStreamIsCapturing(st == hipStreamLegacy ? nullptr : st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return true;
+  // (the handles that name a stream without being one have neither a mask nor a priority of their own)
+  const hipStream_t named = st == hipStreamLegacy || st == hipStreamPerThread ? nullptr : st;
+  if (hipExtStreamGetCUMask(named, (cus + 31) / 32, mask) != hipSuccess || hipStreamGetPriority(named, &priority) != hipSuccess) {
     (void)hipGetLastError();                       // (not for the launches that follow to find)
     return false;
   }
-  int open = 0;
-  for (const uint32_t m : mask) open += __builtin_popcount(m);
-  return open >= cus;                              // (0 under capture)
+  return stream_counted(mask, cus, priority);
 }
-
 template <int NRT>
 hipError_t launch_fused_rows(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const uint16_t* q,
                              const uint16_t* k,
@@ -928,9 +917,14 @@ hipError_t launch_fused_rows(const ScoreGeom& g, const WindowPos& qp, const KvLa
   WindowPos qq = qp;
   KvLayout ll = lay;
   float* edge = ws.raw;
+  const bool safe = ordinary_team(plan.T, resident) && stream_shares_queues(st, dev);
+  if (!safe && queues_as_counted()) plan.spin_limit = SPIN_LIMIT_UNSAFE;
   const void* fn = lay.table ? reinterpret_cast<const void*>(&fused_kernel<NRT, true>)
                              : reinterpret_cast<const void*>(&fused_kernel<NRT, false>);
   void* args[] = {&gg, &qq, &plan, &ll, &q, &k, &scores, &edge, &sy};
+  // Ordinary launches wherever the rule covers them, else (on request only) cooperative ones, which the runtime does not
+  // let overlap with each other.  laq_evict, us, cooperative : ordinary, in a process whose only stream it is: 256 heads x 16384 keys, 64 rows 290 : 279,
+  // x 8001 keys, 32 rows 170 : 151, 32 heads x 32768, 32 rows 100 : 78; in one that has used other streams and graphs 403 : 265, 283 : 144.
   // LAQ_COOPERATIVE_LAUNCH=0 in the environment: always an ordinary launch of the same grid, for tools that
   // cannot follow cooperative launches (a process profiled by rocprofv3 ends in a segmentation fault
   // after any cooperative launch, also of an empty kernel).  Where the rule does not hold, the kernel's
@@ -939,8 +933,7 @@ hipError_t launch_fused_rows(const ScoreGeom& g, const WindowPos& qp, const KvLa
     const char* v = getenv("LAQ_COOPERATIVE_LAUNCH");
     return v != nullptr && v[0] == '0';
   }();
-  if (plain_launch || (Cfg<NRT>::DRAWS && ordinary_team(plan, resident) && ordinary_stream(fused_cus[dev].load(std::memory_order_acquire), st)))
-    e = hipLaunchKernel(fn, dim3(plan.n_teams * plan.T), dim3(F_THREADS), args, bytes, st);
+  if (plain_launch || (safe && queues_as_counted())) e = hipLaunchKernel(fn, dim3(plan.n_teams * plan.T), dim3(F_THREADS), args, bytes, st);
   else e = hipLaunchCooperativeKernel(fn, dim3(plan.n_teams * plan.T), dim3(F_THREADS), args, bytes, st);
   if (e != hipSuccess) return e;
   if (plan.half > 0 && plan.T > 1) {
@@ -991,13 +984,13 @@ hipError_t score_fused_applies(const ScoreGeom& g, const KvLayout& lay, int dtyp
   return hipSuccess;
 }
 
-bool score_fused_light(const ScoreGeom& g, const KvLayout& lay, int dtype, const hipStream_t* st) {
+int score_fused_counters(const ScoreGeom& g, const KvLayout& lay, int dtype, const hipStream_t* st) {
   int dev = 0;
   FusedPlan plan;
-  if (!score_fused_supported(g, lay, dtype) || g.Rpad > 64 || hipGetDevice(&dev) != hipSuccess || score_fused_init(dev) != hipSuccess) return false;
+  if (!score_fused_supported(g, lay, dtype) || hipGetDevice(&dev) != hipSuccess || score_fused_init(dev) != hipSuccess) return 0;
   const int resident = fused_resident[dev][slot_of(tiles_for(g.Rpad))].load(std::memory_order_acquire);
-  return make_plan(g, 1, resident, &plan) && ordinary_team(plan, resident) &&
-         (st == nullptr || ordinary_stream(fused_cus[dev].load(std::memory_order_acquire), *st));
+  if (!make_plan(g, 1, resident, &plan) || !ordinary_team(plan.T, resident) || (st != nullptr && !stream_shares_queues(*st, dev))) return 0;
+  return counters_of(plan.T, resident);
 }
 
 // Scores of every head into `scores`: raw with pool == 1, else max-pooled over the prefix.  *done

@@ -196,7 +196,7 @@ def test_which_kernel(laq):
 @pytest.mark.parametrize("n,L,W,light", [(3, 6827, 16, True), (3, 6750, 16, False), (5, 4916, 8, True), (5, 4900, 8, False), (24, 1281, 8, True),
                                           (26, 1280, 8, False)])
 def test_which_kernel_by_the_launch(laq, n, L, W, light):
-    # either side of the lines for an ordinary launch (40 MiB of keys with 64 score rows, 48 with 32, there beyond 1280 keys a head); a captured call
+    # either side of the lines (40 MiB of keys with 64 score rows, 48 with 32, there beyond 1280 keys a head); a captured call
     # keeps the two passes, on a replay too, and scores and lists agree to within rounding
     bf = torch.bfloat16
     kind = laq.laq_score_kernel(n, 32, 8, D, L, W, bf)
@@ -266,16 +266,19 @@ def test_constant_keys_give_uniform_probabilities(laq):
     np.testing.assert_allclose(s[0, 1].numpy(), want.numpy(), rtol=2e-6)
 
 
-@pytest.mark.parametrize("L,W,heads", [(1500, 8, 40), (8200, 8, 24), (16384, 16, 9), (16640, 16, 40), (32768, 16, 10)])
+@pytest.mark.parametrize("L,W,heads", [((1500,) * 3, 8, 40), ((8200,) * 3, 8, 24), ((16384,) * 3, 16, 9), ((16640,) * 3, 16, 40), ((32768,) * 3, 16, 10),
+                                       ((33280,) * 3, 16, 10), ((32768, 300, 65000, 9000), 16, 5), ((2100, 32768, 257), 32, 6)])
 def test_calls_side_by_side(laq, L, W, heads):
     # several launches on the device at once, each with teams of which some are there only in part: places are drawn in the order
-    # of start, so every call completes, with the bits of a call that is alone; sizes: few and many workgroups per team, more and fewer
-    # heads than teams, and a team (65 workgroups) whose launch stays cooperative
+    # of start, so every call completes, with the bits of a call that is alone; sizes: few and many workgroups per team (2, 9, 32, 33, and 64, the
+    # longest that draw from two counters, 65 from one), more and fewer heads than teams, unlike launches (64, 1, 127 and 18 workgroups per
+    # team; with 128 score rows 9, 128, the longest that are covered, and 2)
     calls = []
-    for i in range(3):
+    for i, L in enumerate(L):
         q, k = draw(1, heads, 4, L, W, seed=L + i, sinks=False)
         q, k = q.to(DEV), k.to(DEV)
         ws = torch.full((laq.laq_workspace_bytes(1, heads * 4, heads, D, L, W, torch.bfloat16),), 0xFF, dtype=torch.uint8, device=DEV)
+        assert laq.laq_score_kernel(1, heads * 4, heads, D, L, W, torch.bfloat16, choose="single-read") == "single-read"
         calls.append((q, k, ws, torch.cuda.Stream(), laq.laq_score(q, k, 7, ws=ws, choose="single-read"), torch.empty(1, heads, L, device=DEV)))
     torch.cuda.synchronize()
     for _ in range(4):
@@ -284,8 +287,15 @@ def test_calls_side_by_side(laq, L, W, heads):
                 laq.laq_score(q, k, 7, scores=out, ws=ws, choose="single-read")
     torch.cuda.synchronize()
     for q, k, ws, stream, alone, out in calls:
-        assert laq.laq_workspace_status(ws, 1, heads * 4, heads, D, L, W, torch.bfloat16) == 0
+        assert laq.laq_workspace_status(ws, 1, heads * 4, heads, D, k.shape[2], W, torch.bfloat16) == 0
         assert torch.equal(out, alone)
+
+
+@pytest.mark.parametrize("L,W,kind", [(65536, 16, "single-read"), (65537, 16, "two-pass"), (131072, 8, "single-read"), (131073, 8, "two-pass")])
+def test_teams_that_are_not_covered_are_taken_on_request_only(laq, L, W, kind):
+    # 128 workgroups are the longest team whose waits end whatever else the device runs (tests/test_team_places.py)
+    assert laq.laq_score_kernel(1, 32, 8, D, L, W, torch.bfloat16) == kind
+    assert laq.laq_score_kernel(1, 32, 8, D, L, W, torch.bfloat16, choose="single-read") == "single-read"
 
 
 def test_ordinary_launch_gives_the_same_bits(laq, tmp_path):
