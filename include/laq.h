@@ -36,7 +36,11 @@
  *     a call that returns LAQ_ERR_INVALID / _UNSUPPORTED / _WORKSPACE has done nothing.
  *     LAQ_ERR_DEVICE reports a failed launch (hipGetLastError).
  *   - Results are a pure function of the inputs (no floating-point atomics; two runs
- *     give identical bits).
+ *     give identical bits, and so do a call and the replay of the same call recorded in a
+ *     graph).  One thing of the stream counts: on one that is confined to some compute
+ *     units or has another priority the library may choose other scoring kernels (see
+ *     laq_score), whose sums round differently; shape.score_choice LAQ_CHOOSE_TWO_PASS
+ *     takes the same ones on every stream.
  */
 #ifndef LAQ_H
 #define LAQ_H
@@ -173,8 +177,8 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *                               The library takes that kernel by itself where it is the faster one
  *                               and its waits are safe (see below): with 33 to 64 score rows from
  *                               40 MiB of keys in the call on, with at most 32 from 48 MiB on if heads
- *                               have more than 1280 keys; but captured calls, and heads of more than
- *                               32768 (with at most 32 rows 65536) keys, from 128 MiB on.
+ *                               have more than 1280 keys; but heads of more than 32768 (with at most
+ *                               32 rows 65536) keys from 128 MiB on.
  *                               shape.score_choice asks for it or against it.
  *                               Heads of at most 1024 keys that one workgroup holds are read once
  *                               too.  Otherwise K is streamed twice (laq_score_kernel() says which).
@@ -256,7 +260,8 @@ int laq_select_sink_recent(int32_t n_inst, int32_t Hkv, int32_t L, const int32_t
  * LAQ_KERNEL_WHOLE_HEAD (heads of at most 1024 keys, K read once by a workgroup per head; only where the choice is
  * left to the library); a negative error code for an invalid shape.  (The first name is older than its kernels,
  * which work on the matrix cores.)  The strides, the block table and the score_choice of `shape` are taken
- * into account like laq_score does.  Launches nothing.
+ * into account like laq_score does.  The answer is for streams of normal priority that may use all compute units; on
+ * others a call of LAQ_CHOOSE_AUTO takes two passes where this says LAQ_KERNEL_SINGLE_READ.  Launches nothing.
  */
 enum { LAQ_KERNEL_VECTOR = 0, LAQ_KERNEL_TWO_PASS = 1, LAQ_KERNEL_SINGLE_READ = 2, LAQ_KERNEL_WHOLE_HEAD = 3 };
 typedef enum { LAQ_CHOOSE_AUTO = 0, LAQ_CHOOSE_TWO_PASS = 1, LAQ_CHOOSE_SINGLE_READ = 2 } laq_score_choice;

@@ -143,7 +143,9 @@ def laq_score_kernel(n_inst: int, Hq: int, Hkv: int, d: int, L: int, W: int, dty
     """How laq_score reads K for this shape on the current device: "vector" (fp32 and head sizes other than 64
     and 128, K read twice), "two-pass" (bf16, K read twice) or "single-read" (bf16, K read once by teams of
     workgroups); with whole_heads also "whole-head" (heads of at most 1024 keys, K read once by a workgroup per
-    head).  Without, such a call has the name of the kernels that read its K twice, which choose="two-pass" takes."""
+    head).  Without, such a call has the name of the kernels that read its K twice, which choose="two-pass" takes.
+    The answer is for streams of normal priority that may use all compute units; on others a call that leaves the
+    choice to the library takes "two-pass" where this says "single-read"."""
     code = LAQ_F32 if dtype == torch.float32 else LAQ_BF16
     sh = _shape(n_inst, Hq, Hkv, d, L, W, code, 0.0, q_pos, keep, "max", kv_strides, paged, choose)
     rc = int(load_library().laq_score_kernel(ctypes.byref(sh)))

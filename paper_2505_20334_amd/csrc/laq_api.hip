@@ -208,13 +208,15 @@ static bool usual_shape(const ScoreGeom& g, const KvLayout& lay, int dtype) {
          ((long long)(lay.table ? lay.block_rows : g.L) + CHUNK_ROWS) * lay.row_bytes < 0x7fffffffLL;
 }
 
-// The single-read kernel's serial start costs more than the launches of the two passes; from some size of the call on it is the faster one (21-27 % at 1 GiB and more).
+// The single-read kernel's serial start costs more than the launches of the two passes; from some size of the call on it is the
+// faster one (21-27 % at 1 GiB and more).
 // laq_evict, bf16, the two passes : this one, us:
 //   64 rows  36 MiB 1100 to 5000 keys 1.06-1.09, 2 x 8 heads x 8200 35.4 : 36.5;  43 MiB 3100 keys 41.0 : 35.7, 1100 keys 49.8 : 41.5;  49 to 70 MiB
 //            1.08-1.29;  94 to 120 MiB 1.12-1.31
 //   32 rows  36 MiB 1300 to 5000 keys 1.04-1.13, 8200 keys 34.6 : 34.8;  48 to 54 MiB 1300 to 30011 keys 1.02-1.22;  62 to 70 MiB .98 (8200 keys), 1.00-1.24;
 //            94 to 120 MiB 1.06-1.34;  1100 keys (a team's second workgroup nearly empty) 37 MiB .88, 64 MiB .99, 97 MiB 1.05
-// Longer teams (one counter, see laq_team.h) and captured calls from 128 MiB on.
+// Teams of one counter (laq_team.h) from 128 MiB on.  Captured calls take the same kernel, so that a replay gives the eager bits; a graph of one call, the
+// two passes : this one: 8 heads x 24000 46.9 : 47.9, x 30011 53.1 : 51.1, 200 x 1100 59.1 : 55.7, 112 x 2000 55.3 : 47.0, 32 rows, 48 x 5000 53.2 : 44.8.
 static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const hipStream_t* st) {
   if (shape->score_choice == LAQ_CHOOSE_SINGLE_READ) return true;
   if (shape->score_choice == LAQ_CHOOSE_TWO_PASS) return false;
@@ -224,8 +226,6 @@ static bool single_read_wanted(const laq_shape* shape, const ScoreGeom& g, const
   const long long key_bytes = (long long)g.n_inst * g.Hkv * g.L * g.d * (shape->dtype == LAQ_F32 ? 4 : 2);
   const bool many = key_bytes >= (128LL << 20);
   if (g.Rpad > 64 || (!many && (key_bytes < ((g.Rpad > 32 ? 40LL : 48LL) << 20) || (g.Rpad <= 32 && g.L <= 1280)))) return false;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (!many && st != nullptr && (hipStreamIsCapturing(*st == hipStreamLegacy ? nullptr : *st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) return false;
   return score_fused_counters(g, lay, shape->dtype, st) >= (many ? 1 : 2);
 }
 

@@ -725,8 +725,7 @@ def test_qcache_capture_feeds_scoring(laq):
 def test_evict_replays_from_a_captured_graph(laq, choose):
     """laq_evict enqueues kernels only (no allocation, no synchronisation, no memset node), so a
     caller may capture it into a graph; every replay must give the eager bits, also after the
-    inputs changed in place and with eager work in between.  With either scoring kernel (the
-    single-read one is a cooperative launch)."""
+    inputs changed in place and with eager work in between.  With either scoring kernel."""
     cfg = dataclasses.replace(CONFIGS[2], L=3000)
     q, k, v, budgets, _ = make_batch(cfg, device=DEV)
     n = q.shape[0]

@@ -194,10 +194,10 @@ def test_which_kernel(laq):
 
 
 @pytest.mark.parametrize("n,L,W,light", [(3, 6827, 16, True), (3, 6750, 16, False), (5, 4916, 8, True), (5, 4900, 8, False), (24, 1281, 8, True),
-                                          (26, 1280, 8, False)])
-def test_which_kernel_by_the_launch(laq, n, L, W, light):
-    # either side of the lines (40 MiB of keys with 64 score rows, 48 with 32, there beyond 1280 keys a head); a captured call
-    # keeps the two passes, on a replay too, and scores and lists agree to within rounding
+                                          (26, 1280, 8, False), (1, 32768, 16, True), (1, 32769, 16, False)])
+def test_which_kernel_by_the_size_of_the_call(laq, n, L, W, light):
+    # either side of the lines (40 MiB of keys with 64 score rows, 48 with 32, there beyond 1280 keys a head; 64 workgroups per team below
+    # 128 MiB); a captured call takes the same kernels: every replay gives the eager bits
     bf = torch.bfloat16
     kind = laq.laq_score_kernel(n, 32, 8, D, L, W, bf)
     assert kind == ("single-read" if light else "two-pass")
@@ -218,7 +218,8 @@ def test_which_kernel_by_the_launch(laq, n, L, W, light):
         pooled.zero_()
         graph.replay()
         torch.cuda.synchronize()
-        assert torch.equal(pooled, two)
+        assert torch.equal(pooled, out)
+    assert laq.laq_workspace_status(ws, n, 32, 8, D, L, W, bf) == 0
     np.testing.assert_allclose(out.cpu().numpy(), two.cpu().numpy(), rtol=2e-5, atol=1e-30)
 
 
