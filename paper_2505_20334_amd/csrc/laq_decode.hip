@@ -3,8 +3,8 @@
 // continues on.
 //
 // Decode attention reads K' and V' once.  One workgroup serves up to eight query heads that share a KV head
-// (they share every key and value row it reads) over one part of a cache: caches are cut into parts of
-// rows_per_part rows where there would be too few workgroups otherwise (a compute unit alone reads some 25 KB per
+// (they share every key and value row it reads) over one part of a cache: caches are cut into parts (laq_parts.h)
+// where there would be too few workgroups otherwise (a compute unit alone reads some 25 KB per
 // microsecond), and the workgroup that finds all parts of its cache finished folds them (merge_parts).
 // A row is read by a group of PP adjacent lanes, 8 elements each, so a wave's loads cover whole rows contiguously;
 // the lane groups of the workgroup take the rows round-robin, ROWS rows per turn.
@@ -24,6 +24,7 @@
 
 #include "laq_internal.h"
 #include "laq_lanegroup.h"
+#include "laq_parts.h"
 
 namespace laq {
 
@@ -31,19 +32,6 @@ namespace {
 
 constexpr float DEC_NEG_BIG = -1.0e30f;
 constexpr int DEC_THREADS = 256, DEC_WAVES = DEC_THREADS / 64;
-// Parts: for three workgroups per compute unit, which is what it holds of most kernels here (110 to 136 registers: three or four)
-// and fewer than make the folding long, but no parts shorter than a turn of the workgroup's lane groups; at most DEC_MOST_PARTS of one cache,
-// since one workgroup folds them.  The least length with which the call keeps to that, last parts counted too, and a cache's parts as
-// even as their steps allow: a fourth workgroup on some compute units, or parts of a few rows beside full ones, leave the others idle at
-// the end.  Before (length from the rows of the call alone, the rest of a cache a part of its own) : now, us: 32 caches of 2048 to 128
-// rows, 8 heads 35.8 : 31.7; 90 x 200, 8 heads 27.0 : 15.9; 90 x 2048, 8 heads 166 : 139, fp32, two query heads a KV head 455 : 300; 12 x 2048 to
-// 128 18.2 : 16.5.  The same with 512, 640, 896, 1024 workgroups: 32 caches of 2048 to 128 rows 1024 32.8; grids of 319 calls by rows
-// a part, over 768: 896 and 1024 .88-1.12 (.89-.95 for parts of 128 rows), 640 and 512 .87-1.09.  Shares of one length that end in
-// one cache and go on in the next, 768 of them: 34.3, and shares of up to 512 rows .78-.96 of these (a second sum to merge, a longer kernel).
-constexpr long long DEC_WORKGROUPS = 768;
-constexpr int DEC_PART_STEP = 64;
-constexpr int DEC_MOST_PARTS = 128;
-constexpr long long DEC_WHOLE_FROM = 1024;       // with that many workgroups without parts there are no parts
 
 // lane selections within 16 lanes
 template <int CTRL>
@@ -107,11 +95,6 @@ __device__ __forceinline__ void fetch_row(const float* p, Piece8F32& x) {
   x.b = __builtin_bit_cast(float4, load16<ONCE>(p + 4));
 }
 
-// Rows of each of `parts` parts of a cache (the last one may have less): steps of DEC_PART_STEP, unless it is one part.
-__host__ __device__ inline int even_rows(int bk, int parts) {
-  const int steps = (bk + DEC_PART_STEP - 1) / DEC_PART_STEP;
-  return (steps + parts - 1) / parts * DEC_PART_STEP;
-}
 // Where the parts of a launch lie: part i of the launch belongs to instance inst_of(i) and is number
 // i - part0(inst) of its cache.
 struct DecodeTable {
@@ -476,7 +459,8 @@ template <int GB, bool SHARED, typename T, int PP, typename TAB>
 hipError_t launch_pp(const DecodeCall& c, int n_parts, int inst0, const TAB& tab) {
   const int merge = DEC_MOST_PARTS * GB * 2, sums = DEC_WAVES * GB * (c.d + 2);   // floats of the two uses of the LDS
   hipLaunchKernelGGL((decode_kernel<GB, SHARED, T, PP, TAB>), dim3(c.columns, n_parts), dim3(DEC_THREADS),
-                     (c.parts.marks && merge > sums ? merge : sums) * sizeof(float), c.st, c.Hq, c.Hkv, c.d, c.scale2, inst0, tab, static_cast<const T*>(c.q), static_cast<const T*>(c.kc), static_cast<const T*>(c.vc), c.out, c.parts);
+                     (c.parts.marks && merge > sums ? merge : sums) * sizeof(float), c.st, c.Hq, c.Hkv, c.d, c.scale2, inst0,
+                     tab, static_cast<const T*>(c.q), static_cast<const T*>(c.kc), static_cast<const T*>(c.vc), c.out, c.parts);
   return hipGetLastError();
 }
 
@@ -501,12 +485,6 @@ hipError_t launch_for(const DecodeCall& c, int n_parts, int inst0, const TAB& ta
   }
 }
 
-// the parts of a cache where none is to have more than `most` rows, as even as their steps allow
-int parts_of(int bk, int most) {
-  const int steps = (bk + DEC_PART_STEP - 1) / DEC_PART_STEP, each = even_rows(bk, (bk + most - 1) / most) / DEC_PART_STEP;
-  return (steps + each - 1) / each;
-}
-
 }  // namespace
 
 // Query heads of a KV head that one workgroup serves: all of them up to 8 (fp32: 4, for the registers' sake), so that
@@ -519,54 +497,25 @@ int decode_head_batch(int Hq, int Hkv, int dtype) {
   return gb;
 }
 
-// The most rows a part may have: the caches stay whole where they make enough workgroups, or where they are short.
-static int longest(int n, int L, const int32_t* budget) {
-  int most = 0;
-  for (int i = 0; i < n; ++i) most = most > budget[i] ? most : budget[i];
-  return most < L ? most : L;
-}
 static int decode_columns(int Hq, int Hkv, int dtype) {
   const int gb = decode_head_batch(Hq, Hkv, dtype);
   return Hkv * ((Hq / Hkv + gb - 1) / gb);
 }
 int decode_part_rows(int n, int L, int Hq, int Hkv, int dtype, const int32_t* budget) {
-  const long long columns = decode_columns(Hq, Hkv, dtype);
-  const int most = longest(n, L, budget);
-  if (n * columns >= DEC_WHOLE_FROM) return most;
-  long long rows = 0;
-  for (int i = 0; i < n; ++i) rows += budget[i] < L ? budget[i] : L;
-  int part = (int)(rows * columns / DEC_WORKGROUPS / DEC_PART_STEP + 1) * DEC_PART_STEP;
-  const int least = (most + DEC_MOST_PARTS - 1) / DEC_MOST_PARTS;
-  if (part < least) part = least;
-  // The caches' last parts count too.  Longer parts are never more, so the least number of steps is found by halving (one by one 8.6 us of the
-  // host's time for 96 caches of 2048 to 128 rows, so 1.8; a call asks up to three times).
-  if ((long long)n * columns > DEC_WORKGROUPS || part >= most) return most;
-  const auto fits = [&](int rows_of_a_part) {
-    long long parts = 0;
-    for (int i = 0; i < n; ++i) parts += parts_of(budget[i] < L ? budget[i] : L, rows_of_a_part);
-    return parts * columns <= DEC_WORKGROUPS;
-  };
-  int few = 0, many = (most - part + DEC_PART_STEP - 1) / DEC_PART_STEP;      // (whole caches fit)
-  while (few < many) {
-    const int mid = (few + many) / 2;
-    if (fits(part + mid * DEC_PART_STEP)) many = mid;
-    else few = mid + 1;
-  }
-  part += many * DEC_PART_STEP;
-  return part < most ? part : most;
+  return limit_of_parts(n, L, decode_columns(Hq, Hkv, dtype), budget);
 }
 
 // The area of the parts of a launch, in a workspace of any alignment: marks, then sums.
 static size_t part_slots(long long parts, int Hq, int Hkv, int dtype) { return (size_t)parts * decode_columns(Hq, Hkv, dtype) * decode_head_batch(Hq, Hkv, dtype); }
 
 // Bytes that hold the parts of any launch of a call (launches reuse the area; they are ordered on the stream), and of any
-// other call of this shape whose caches are no longer: one workspace serves layers of different budgets.  A part has
-// at least DEC_PART_STEP rows and at least the longest cache's rows / DEC_MOST_PARTS, and more than rows * columns / DEC_WORKGROUPS
-// of the call's rows; each of the three bounds the number of parts and grows with every budget.  (The number itself does not: the
-// length of a part goes in steps, so that 2048 rows can have fewer parts than 1535.)
+// other call of this shape whose caches are no longer: one workspace serves layers of different budgets.  A cache has at most a
+// part for every DEC_PART_STEP rows and at most DEC_MOST_PARTS; and as evening parts out adds none, the caches of a call have no more than
+// parts of the limit would be, one each and DEC_WORKGROUPS / columns in all beside those.  Each of the three bounds grows with every
+// budget.  (The number itself does not: the length of a part goes in steps, so that 2048 rows can have fewer parts than 1535.)
 size_t decode_partial_bytes(int n, int L, int Hq, int Hkv, int d, int dtype, const int32_t* budget) {
   const long long columns = decode_columns(Hq, Hkv, dtype);
-  if (n * columns >= DEC_WHOLE_FROM || longest(n, L, budget) <= DEC_PART_STEP) return 0;
+  if (n * columns >= DEC_WHOLE_FROM || longest_cache(n, L, budget) <= DEC_PART_STEP) return 0;
   long long parts = 0, most = 0;
   for (int i = 0; i < n; ++i) {
     if (i % MAX_INST_PER_LAUNCH == 0) parts = 0;

@@ -230,7 +230,7 @@ hipError_t launch_sink_recent(int n_inst, int Hkv, int L, int n_sink, const Inst
 hipError_t launch_recall(int n_inst, int inst0, int Hkv, const PairTable& tab, const int32_t* idx_pred,
                          const int32_t* idx_gold, int32_t* overlap, float* recall, hipStream_t st);
 int decode_head_batch(int Hq, int Hkv, int dtype);   // query heads of a KV head that one decode workgroup serves
-int decode_part_rows(int n, int L, int Hq, int Hkv, int dtype, const int32_t* budget);   // most rows of a part of the caches of a call
+int decode_part_rows(int n, int L, int Hq, int Hkv, int dtype, const int32_t* budget);   // the limit of the parts' rows, before they are evened out
 size_t decode_partial_bytes(int n, int L, int Hq, int Hkv, int d, int dtype, const int32_t* budget);
 hipError_t launch_decode(int n_inst, int L, int Hq, int Hkv, int d, int dtype, float scale2, int rows_per_part, const int32_t* budget,
                          const void* q, const void* kc, const void* vc, float* out, void* ws, hipStream_t st);

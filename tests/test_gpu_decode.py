@@ -29,6 +29,8 @@ CASES = [
     (BF16, 1, 1, 128, [20000]),
     # parts as even as their steps allow, and longer ones where the last parts would make too many workgroups
     (BF16, 16, 8, 64, [200] * 60), (F32, 8, 8, 72, [1000 - 900 * i // 11 for i in range(12)]), (BF16, 8, 8, 128, [321, 320, 2000] * 5),
+    # one long cache among short ones, that makes more workgroups than the others leave room for; and whole caches that do alone
+    (BF16, 8, 8, 128, [3000] + [64] * 95), (F32, 16, 8, 64, [5000] + [64] * 99), (BF16, 8, 8, 64, [300, 200] * 55),
 ]
 
 
