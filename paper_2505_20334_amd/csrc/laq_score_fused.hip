@@ -349,10 +349,11 @@ struct FusedPlan : TeamPlan {              // (teams of ceil(L / keys per workgr
   int spin_limit;          // probes of a wait
 };
 
-// The place of a workgroup among those of the launch: member place % T of team place / T.  Drawn from one of two counters (one for the longer
-// teams, see laq_team.h), the `early` workgroups with the lowest numbers from the first.  The device takes workgroups in the order of their numbers within an XCD, and two on a compute unit
-// only when each has one; so the teams of either counter have at most one workgroup on a compute unit.  All from one counter, teams had both places
-// of some, whose workgroups do the same at the same time: 256 heads x 16384 keys, 64 rows 294 us, with two counters 279, by number 271.
+// The place of a workgroup among those of the launch: member place % T of team place / T.  Drawn from one of two counters (one for the
+// longer teams, see laq_team.h), the `early` workgroups with the lowest numbers from the first.  The device takes workgroups in the order of
+// their numbers within an XCD, and two on a compute unit only when each has one; so the teams of either counter have at most one workgroup on
+// a compute unit.  All from one counter, teams had both places of some, whose workgroups do the same at the same time: laq_evict, 256 heads x
+// 16384 keys, 64 rows 294 us, with two counters 279, by number 271; 512 x 32768 1108 and 1043, 8 x 30011 45.7 and 43.3.
 constexpr int SECOND = 16;                 // ints between the counters
 __device__ __forceinline__ int drawn_place(int* started, int early) {
   const int late = (int)blockIdx.x >= early;
@@ -872,6 +873,7 @@ bool queues_as_counted() {
   }();
   return yes;
 }
+
 // Whether the launches of a stream go through the hardware queues that streams of normal priority share, and may use all compute units.  What
 // stream a recorded launch will run on is not known: taken for one of these.
 bool stream_shares_queues(hipStream_t st, int dev) {
@@ -881,15 +883,19 @@ bool stream_shares_queues(hipStream_t st, int dev) {
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   int priority = 0;
   if (cus > WORDS * 32) return false;
-  if (hipStreamIsCapturing(st == hipStreamLegacy ? nullptr : st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return true;
-  // (the handles that name a stream without being one have neither a mask nor a priority of their own)
+  // (the handles that name a stream without being one: only the per-thread stream can be captured, neither has a mask or a priority of its own)
   const hipStream_t named = st == hipStreamLegacy || st == hipStreamPerThread ? nullptr : st;
-  if (hipExtStreamGetCUMask(named, (cus + 31) / 32, mask) != hipSuccess || hipStreamGetPriority(named, &priority) != hipSuccess) {
+  hipError_t e = hipStreamIsCapturing(st == hipStreamLegacy ? nullptr : st, &capture);
+  if (e == hipSuccess && capture != hipStreamCaptureStatusNone) return true;
+  if (e == hipSuccess) e = hipExtStreamGetCUMask(named, (cus + 31) / 32, mask);
+  if (e == hipSuccess) e = hipStreamGetPriority(named, &priority);
+  if (e != hipSuccess) {
     (void)hipGetLastError();                       // (not for the launches that follow to find)
     return false;
   }
   return stream_counted(mask, cus, priority);
 }
+
 template <int NRT>
 hipError_t launch_fused_rows(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int pool, const uint16_t* q,
                              const uint16_t* k,
