@@ -198,6 +198,8 @@ int laq_workspace_status(const laq_shape *shape, const void *ws, size_t ws_bytes
  *                               replayed on streams of the kind first named, and of P processes that
  *                               make such calls on one GPU at the same time each keeps to L up to
  *                               65536/P / 32768/P / 16384/P keys; or choose LAQ_CHOOSE_TWO_PASS.
+ *                               With 65 to 128 score rows (on request only) this kernel returns 0 for
+ *                               scores below 2^-126; with fewer it sums those again, as the others do.
  *                               With GPU_MAX_HW_QUEUES above 4 in the environment all launches of the
  *                               kernel are cooperative.  With LAQ_COOPERATIVE_LAUNCH=0 in the
  *                               environment (read at the first such call) none is, for profilers that

@@ -497,13 +497,15 @@ static bool finish_wanted(const laq_shape* shape, const ScoreGeom& g, ScorePath 
 }
 
 // Whether the selection kernel pools the raw scores of this call on the way: a launch, a read and a write of the scores less.  The
-// single-read kernel would pool the maximum itself, all but the keys next to its workgroups' boundaries, which take a launch: laq_evict, pooled there : here,
-// us: 256 heads x 2000 keys 58.4 : 55.4, 48 x 10000 54.4 : 53.4, 512 x 5000 196.9 : 195.4, 96 x 8192 and 128 x 16384 even; 72 x 30011 141.2 : 144.3,
-// 256 x 32768 518 : 524, 720 x 20000 829 : 847.
+// single-read kernel would pool the maximum itself, all but the keys next to its workgroups' boundaries, which take a launch: laq_evict,
+// pooled there : here, us: 256 heads x 2000 keys 58.4 : 55.4, 48 x 10000 54.4 : 53.4, 512 x 5000 196.9 : 195.4, 96 x 8192 and 128 x 16384
+// even; 72 x 30011 141.2 : 144.3, 256 x 32768 518 : 524, 720 x 20000 829 : 847.  (Few long heads, whose selection is on few compute
+// units anyway, are not among these.)
 static bool select_pools(const laq_shape* shape, const ScoreGeom& g, ScorePath path, int pool, const float* raw) {
   const int keys = g.P + row_shift(raw, g.L);
   return pool > 1 && (pool - 1) / 2 <= SELECT_POOL_MAX_HALF && keys <= SELECT_POOL_MAX_KEYS &&
-         (keys <= SELECT_POOL_MANY_KEYS || (long long)g.n_inst * g.Hkv < SELECT_MANY_HEADS) && (leaves_raw(shape, path) || (path == ScorePath::single_read && keys <= FINISH_MAX_KEYS));
+         (keys <= SELECT_POOL_MANY_KEYS || (long long)g.n_inst * g.Hkv < SELECT_MANY_HEADS) &&
+         (leaves_raw(shape, path) || (path == ScorePath::single_read && keys <= FINISH_MAX_KEYS));
 }
 
 static FinishArgs finish_args(const laq_shape* shape, const ScoreGeom& g, const KvLayout& lay, const void* k, const void* v, int pool, float* scores,

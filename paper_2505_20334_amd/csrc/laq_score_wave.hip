@@ -193,10 +193,12 @@ struct WavePlan {
 template <typename T, int NP> constexpr int waves_per_simd() { return is_f32(T()) ? (NP <= 8 ? 3 : 2) : (NP <= 6 ? 5 : NP <= 8 ? 4 : 2); }
 
 // A wave's sums of exponentials refer to a number near the row's maximum, not to the maximum itself: HEADROOM above that of the first
-// tile, and moved only where a tile's sum reaches OUTGROWN of it (then, and where a row does not see all keys of a tile, or a sum is no number, the
-// maximum of the tile is made).  The terms that count have exponents between -8 and 7, as with a maximum that most keys stay some powers of two below.
-// 63 instead of 87 vector instructions per product of 32 keys and 32 rows; 256 heads x 32768 keys, 128 rows, us: first pass 408 : 404 (cold 386 : 382),
-// bound by the power that memory and matrix cores take; the whole eviction 954 : 946, 112 score rows x 20123 296.0 : 294.7.
+// tile, and moved only where a tile's sum reaches OUTGROWN of it (then, and where a row does not see all keys of a tile, or a sum is no
+// number, the maximum of the tile is made).  The terms that count have exponents between -8 and 7, as with a maximum that most keys stay
+// some powers of two below.  A gain in error and in instructions rather than in time: scores against 64 bits (2-norm, logits of deviation 1)
+// bf16 3.0e-7 -> 2.0e-7, fp32 2.2e-7 -> 1.9e-7; 71 instead of 87 vector instructions per product of 32 keys and 32 rows (SQ_INSTS_VALU); the whole
+// eviction of 256 heads x 32768 keys, 128 rows, is not faster beyond noise (934 : 927 us): it is bound by memory and by the power that memory and
+// matrix cores take.
 constexpr float HEADROOM = 3.f, OUTGROWN = 128.f;
 // exp2(s * scale - m) of a lane's 16 keys and of the 16 that the other half of the wave has of the same row, summed
 __device__ __forceinline__ float tile_sum(const f32x16& s, float scale, float m) {
@@ -423,7 +425,8 @@ __global__ __launch_bounds__(256) void row_constants_kernel(ScoreGeom g, const f
 // others take more of them: 1800 heads x 20259 keys, d = 64: 1, 3, 5, 16, 80 segments 2047, 1936, 1862, 1844, 2102 us.
 // More score rows than are staged together are other workgroups' in the first kernel, but in the second the same one takes a group after the other.
 // Its rounds count that often; but where not all workgroups that fit are there, those that are get on faster: a share `enough` of them
-// does what all do (bf16 1.25 waves per SIMD, fp32 2), though never less than the first kernel's.  laq_evict, the second counted as the first : so, us: fp32, 256 rows, d = 128, 64 heads x 3300 285 : 212,
+// does what all do (bf16 1.25 waves per SIMD, fp32 2), though never less than the first kernel's.  laq_evict, the second counted as
+// the first : so, us: fp32, 256 rows, d = 128, 64 heads x 3300 285 : 212,
 // 16 x 4000 114.5 : 87.9, 300 x 3000 866 : 787; 448 rows, d = 96, 16 x 8000 220 : 173.  With all the workgroups that fit counted as needed: bf16, 160 rows,
 // d = 128, 256 x 1500 81 : 91; 224 rows, d = 256, 128 x 1100 80 : 91.
 WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int stride) {
