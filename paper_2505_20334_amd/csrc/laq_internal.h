@@ -187,7 +187,7 @@ bool score_wave_own_size(const ScoreGeom& g, int dtype);      // a head size tha
 hipError_t launch_score_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, const void* q,
                              const void* k, float* raw, const Workspace& ws, hipStream_t st);
 hipError_t score_wave_init();
-hipError_t launch_row_constants(const ScoreGeom& g, const Workspace& ws, hipStream_t st);
+hipError_t launch_row_constants(const ScoreGeom& g, const Workspace& ws, float* rowc, hipStream_t st);
 // kernel attributes and residency of the single-read scoring kernel on device `dev`, which must be
 // the current device; idempotent
 hipError_t score_fused_init(int dev);

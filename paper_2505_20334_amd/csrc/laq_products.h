@@ -142,4 +142,90 @@ __device__ __forceinline__ void stage_rows(char* lds, const char* head_rows, int
   }
 }
 
+// ---- tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16) ----
+// 32 keys by 32 score rows as four of them, t[key half][row half].  Lane l supplies row l % 16 of either operand and the 16-byte pieces
+// 4t + l / 16 of it, and holds, of column l % 16 of a tile, rows 4 (l / 16) .. + 3.
+__device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+template <bool KEYS_AS_ROWS>
+__device__ __forceinline__ f32x4 mm16(u32x4 key, u32x4 q, f32x4 acc) { return KEYS_AS_ROWS ? mfma16(key, q, acc) : mfma16(q, key, acc); }
+struct Tile16 {
+  f32x4 t[2][2];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+};
+// Two values combined over the four lanes of the same number modulo 16: lanes 0 .. 31 end with the first one, the others with the second.
+template <typename OP>
+__device__ __forceinline__ float over_groups(float x, float y, OP op) {
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const float w = op(__uint_as_float(h[0]), __uint_as_float(h[1]));
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w), __float_as_uint(w), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// staged bytes of d bf16 (64 bytes for a product step), and from one staged score row to the next, see plane_bytes(), row_stride()
+__host__ __device__ inline int plane16_bytes(int d) { return (d + 31) / 32 * 64; }
+template <typename T> __host__ __device__ inline int row16_stride(int d) { return (is_f32(T()) ? 3 : 1) * plane16_bytes(d) + 16; }
+
+// product_f32() of the tiles: key[s], q[r] are this lane's rows
+template <bool KEYS_AS_ROWS>
+__device__ __forceinline__ Tile16 product16_f32(const char* const (&key)[2], const char* const (&q)[2], int grp, int row_bytes) {
+  Tile16 a;
+  a.clear();
+#pragma unroll 1
+  for (int o = grp * 16; o < row_bytes + grp * 16; o += 64) {   // (every group of lanes as often: the last pieces of some may be missing)
+    f32x4 x[2], y[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      x[i] = y[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (o < row_bytes) {
+        x[i] = *reinterpret_cast<const f32x4*>(key[i] + o);
+        y[i] = *reinterpret_cast<const f32x4*>(q[i] + o);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          a.t[s][r] = KEYS_AS_ROWS ? __builtin_amdgcn_mfma_f32_16x16x4f32(x[s][j], y[r][j], a.t[s][r], 0, 0, 0)
+                                   : __builtin_amdgcn_mfma_f32_16x16x4f32(y[r][j], x[s][j], a.t[s][r], 0, 0, 0);
+  }
+  return a;
+}
+
+// The same for the products of 16 x 16 tiles.
+template <typename T, bool FULL, int THREADS>
+__device__ __forceinline__ void stage_rows16(char* lds, const char* head_rows, int row_bytes, int plane, int stride, int R, int r0, int n,
+                                           int shift) {
+  const int tid = threadIdx.x, per = plane / 16, total = n * per;
+#pragma unroll(is_f32(T()) ? 2 : 4)
+  for (int p = tid; p < total; p += THREADS) {
+    const int row = p / per, col = p - row * per;
+    const char* src = head_rows + (size_t)min(r0 + row, R - 1) * row_bytes;
+    if constexpr (!is_f32(T())) {
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (FULL || col * 16 < row_bytes) v = *reinterpret_cast<const u32x4*>(src + col * 16);
+      *reinterpret_cast<u32x4*>(lds + row * stride + col * 16) = v;
+    } else {
+      // 8 elements as the key side has them: pieces 8t + grp and 8t + 4 + grp
+      const int a = (col >> 2) * 8 + (col & 3);
+      u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u};
+      if (FULL || a * 16 < row_bytes) x = *reinterpret_cast<const u32x4*>(src + a * 16);
+      if (FULL || (a + 4) * 16 < row_bytes) y = *reinterpret_cast<const u32x4*>(src + (a + 4) * 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[i] = __float_as_uint(__builtin_amdgcn_ldexpf(__uint_as_float(x[i]), shift));
+        y[i] = __float_as_uint(__builtin_amdgcn_ldexpf(__uint_as_float(y[i]), shift));
+      }
+      const Split s = split8(x, y);
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<u32x4*>(lds + row * stride + pl * plane + col * 16) = s.p[pl];
+    }
+  }
+}
+
 }  // namespace laq

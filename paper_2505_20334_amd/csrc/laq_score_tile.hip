@@ -315,7 +315,7 @@ hipError_t launch_tile(const ScoreGeom& g, const WindowPos& qp, const KvLayout& 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const bool fold = g.nchunk <= FOLD_CHUNKS && units <= FOLD_WORKGROUPS;
-  if (!fold && (e = launch_row_constants(g, ws, st)) != hipSuccess) return e;
+  if (!fold && (e = launch_row_constants(g, ws, ws.rowc, st)) != hipSuccess) return e;
   if (split * bytes > MAX_LDS) split = 1;
   const int keys = CHUNK_ROWS / split;
   hipLaunchKernelGGL((tile_score_kernel<T, NP, FULL>), dim3((g.L + keys - 1) / keys, g.Hkv, g.n_inst), dim3(THREADS), split * bytes, st, g, qp, lay,

@@ -1,22 +1,30 @@
 // Scoring in two passes over K without a barrier between keys: every head size up to 256, any number of score
-// rows, fp32 or bf16, on the matrix cores (v_mfma_f32_32x32x16_bf16).
+// rows, fp32 or bf16, on the matrix cores (v_mfma_f32_16x16x32_bf16).
 //
 // Kernel 1 leaves the softmax statistics (m, z) of every score row over a segment of a head's keys, kernel 2 folds
 // the segments' (or finds them folded by row_constants_kernel, where they are many) and sums the probabilities
-// exp2(s - c), c = M + log2 Z, over the rows: raw scores.
+// exp2(s - M) / Z over the rows: raw scores.
 //
 // A workgroup of four waves stages the head's score rows (up to 128 of them) in LDS once and then walks its segment
-// of keys, 128 at a time; a wave takes 32 of these in registers, straight from memory in operand layout (lane l: row
-// l % 32, the 16-byte pieces 2t + l / 32), while the next 32 are on their way into others.  Nothing that a wave does
+// of keys, 128 at a time; a wave takes 32 of these in registers, straight from memory in operand layout (lane l: rows
+// l % 16 and 16 + l % 16, the 16-byte pieces 4t + l / 16), while the next 32 are on their way into others.  Nothing that a wave does
 // per key waits for another wave, so loads and arithmetic of the 8 to 20 waves of a compute unit mix freely.
-//   (1) D = K * Q^T: lane = score row, registers = 16 keys: sum (and, where it is needed, maximum) in registers, the wave's running (m, z) in LDS.
-//   (2) D = Q * K^T: lane = key, registers = 16 rows: the sum over the rows in registers.
-// Score rows beyond R repeat the last one and get c = inf, so that they add nothing.
+//   (1) D = K * Q^T: lane = two score rows, registers = 8 keys: sum (and, where it is needed, maximum) in registers, the wave's running (m, z) in LDS.
+//   (2) D = Q * K^T: lane = two keys, registers = 8 rows: the sum over the rows in registers.
+// Score rows beyond R repeat the last one and get the weight 0, so that they add nothing.
+//
+// 32 keys by 32 rows are four products of 16 x 16 and not one of 32 x 32: as many operations and operand reads, but a fifth less traffic between
+// matrix core and registers, four chains instead of one, 64 bytes of a row per load instruction instead of 32, and half the reads of row constants.
+// laq_evict, us, with 32 x 32 : so: bf16, 128 rows, 256 heads x 32768 keys 937 : 900, 112 rows, 112 x 20123 295 : 288, d = 96, 128 rows, 96 x 16000
+// 152.9 : 147.6; 64 rows and fewer 0.99-1.01; fp32, 64 rows, 64 x 8191 152 : 147, d = 64 and 96 1.04, d = 104 1.06, 128 rows, 64 x 4000 144.5 : 136.
+//
+// References M are whole numbers and the rows' weights 1 / Z are multiplied in, so that everything which brings statistics together is an exact power
+// of two and no logarithm of Z is rounded at the size of M.  Scores, error against 64 bits (2-norm), logits of deviation 1 / 4, with exp2(s - (M + log2 Z)) :
+// so: bf16, d = 128, 128 rows, 32 heads x 5000 keys 2.0e-7 / 6.1e-7 : 6.0e-8 / 4.9e-7; fp32, 64 rows, 24 x 9000 2.0e-7 / 7.1e-7 : 6.2e-8 / 6.1e-7.
 //
 // fp32 takes six bf16 products: a float is the sum of three bf16 (split8), and the three products of parts that together reach
 // 2^-24 of the whole at most are left out.  The sums are fp32, those of the small products apart from those of the large ones: fewer
-// roundings than the fp32 instruction makes.  Error against 64 bits (2-norm of the scores, d = 64, 96, 104, 128, logits of standard
-// deviation 1 / 4): 1.85-1.9e-7 / 4.5-4.9e-7, with the fp32 instruction 1.9e-7 / 7.9-9.7e-7; and 2.7 times its rate.  Rows of a single
+// roundings than the fp32 instruction makes, and 2.7 times its rate.  Rows of a single
 // element (no sum, one rounding) are where it is not the closer one: 2.34e-8 of a logit rms, 9e-8 at most, against 2.31e-8 and 6e-8.
 //
 // What bounds it: for up to 64 score rows the two reads of K (64 heads x 8192 to 16384 keys: 5.6 TB/s of 6.2), with 128 the
@@ -44,7 +52,7 @@ constexpr int FOLD_SEGMENTS = 32;
 // NP: pairs of 16-byte pieces a row may have (32 bytes each); FULL: it has exactly that many.
 template <typename T, int NP, bool FULL> struct Wave {
   static constexpr bool F32 = is_f32(T());
-  int hf, n32, wave;
+  int grp, n16, wave;
   int row_bytes, stride, plane;
   int inst;
   int64_t src_row;         // bytes between key rows
@@ -55,12 +63,12 @@ template <typename T, int NP, bool FULL> struct Wave {
   __device__ __forceinline__ Wave(const ScoreGeom& g, const KvLayout& lay, const T* q, const T* k, int seg, int seg_blocks) {
     const int lane = threadIdx.x & 63, head = blockIdx.y;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    hf = lane >> 5;
-    n32 = lane & 31;
+    grp = lane >> 4;
+    n16 = lane & 15;
     inst = blockIdx.z;
     row_bytes = FULL ? NP * 32 : g.d * (int)sizeof(T);
-    plane = plane_bytes(row_bytes / (int)sizeof(T));
-    stride = row_stride<T>(row_bytes / (int)sizeof(T));
+    plane = plane16_bytes(row_bytes / (int)sizeof(T));
+    stride = row16_stride<T>(row_bytes / (int)sizeof(T));
     src_row = lay.row_bytes;
     head_keys = reinterpret_cast<const char*>(k + (lay.table ? 0 : (int64_t)inst * lay.inst) + (int64_t)head * lay.head);
     head_rows = reinterpret_cast<const char*>(q + ((size_t)inst * g.Hkv + head) * g.R * g.d);
@@ -71,86 +79,112 @@ template <typename T, int NP, bool FULL> struct Wave {
     if (last_tile >= end) last_tile -= BLOCK_KEYS;
     some = first <= last_tile;
   }
-  // this lane's row of the tile of keys key0 .. key0 + 31
-  __device__ __forceinline__ const char* key_row(const ScoreGeom& g, const KvLayout& lay, int key0) const {
+  // this lane's rows of the tile of keys key0 .. key0 + 31: n16 and 16 + n16
+  __device__ __forceinline__ void key_rows(const char* (&rows)[2], const ScoreGeom& g, const KvLayout& lay, int key0) const {
     int r0 = key0;
     const char* p = head_keys;
-    if (lay.table) p += paged_block_offset(lay, inst, key0, &r0) * (int64_t)sizeof(T);      // (a block holds whole tiles)
-    const int row = min(n32, g.L - 1 - key0);            // (keys beyond the last one are masked: any row will do)
-    return p + (int64_t)(r0 + row) * src_row;
+    if (lay.table) p += paged_block_offset(lay, inst, key0, &r0) * (int64_t)sizeof(T);       // (a block holds whole tiles)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)                          // (keys beyond the last one are masked: any row will do)
+      rows[s] = p + (int64_t)(r0 + min(16 * s + n16, g.L - 1 - key0)) * src_row;
   }
   __device__ __forceinline__ void load(u32x4 (&key)[NP], const ScoreGeom& g, const KvLayout& lay, int key0) const {
-    const char* p = key_row(g, lay, key0) + hf * 16;
+    const char* rows[2];
+    key_rows(rows, g, lay, key0);
 #pragma unroll
-    for (int t = 0; t < NP; ++t) {
-      if (FULL) {
-        key[t] = *reinterpret_cast<const u32x4*>(p + t * 32);
-      } else {
-        key[t] = u32x4{0u, 0u, 0u, 0u};
-        if ((2 * t + hf) * 16 < row_bytes) key[t] = *reinterpret_cast<const u32x4*>(p + t * 32);
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int t = 0; t < NP / 2; ++t) {
+        const char* p = rows[s] + grp * 16 + t * 64;
+        u32x4& x = key[s * (NP / 2) + t];
+        if (FULL) {
+          x = *reinterpret_cast<const u32x4*>(p);
+        } else {
+          x = u32x4{0u, 0u, 0u, 0u};
+          if ((4 * t + grp) * 16 < row_bytes) x = *reinterpret_cast<const u32x4*>(p);
+        }
       }
-    }
   }
 
-  // this lane's score row of a tile, in memory
-  __device__ __forceinline__ const char* score_row(const ScoreGeom& g, int rt) const {
-    return head_rows + (size_t)min(rt * 32 + n32, g.R - 1) * row_bytes;
+  // this lane's score rows of a tile, in memory
+  __device__ __forceinline__ void score_rows(const char* (&rows)[2], const ScoreGeom& g, int rt) const {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) rows[r] = head_rows + (size_t)min(rt * 32 + 16 * r + n16, g.R - 1) * row_bytes;
   }
 };
 
 // A key tile as the products take it; fp32: split into its three parts.
 template <typename T, int NP, bool FULL> struct Operand {
   static constexpr bool F32 = is_f32(T());
-  static constexpr int STEPS = F32 ? (NP + 1) / 2 : NP;
-  u32x4 v[F32 ? 3 * STEPS : STEPS];
+  static constexpr int PER_ROW = NP / 2, STEPS = F32 ? PER_ROW / 2 : PER_ROW, PARTS = F32 ? 3 : 1;
+  static_assert(NP % (F32 ? 4 : 2) == 0, "");
+  u32x4 v[2][STEPS * PARTS];
   __device__ __forceinline__ void from(const u32x4 (&key)[NP]) {
 #pragma unroll
-    for (int u = 0; u < STEPS; ++u) {
-      if constexpr (F32) {
-        const u32x4 none = {0u, 0u, 0u, 0u};
-        const Split s = split8(key[2 * u], 2 * u + 1 < NP ? key[2 * u + 1 < NP ? 2 * u + 1 : 0] : none);
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl) v[3 * u + pl] = s.p[pl];
-      } else {
-        v[u] = key[u];
+      for (int u = 0; u < STEPS; ++u) {
+        if constexpr (F32) {
+          const Split x = split8(key[s * PER_ROW + 2 * u], key[s * PER_ROW + 2 * u + 1]);
+#pragma unroll
+          for (int pl = 0; pl < 3; ++pl) v[s][3 * u + pl] = x.p[pl];
+        } else {
+          v[s][u] = key[s * PER_ROW + u];
+        }
       }
-    }
   }
-  // against the score rows at `lds` (this lane's row and half); `steps` of 32 bytes a row has, `plane` bytes between its parts
+  // against the score rows at `lds` (this lane's row and piece); `steps` of 64 bytes a row has, `plane` bytes between its parts
   template <bool KEYS_AS_ROWS>
-  __device__ __forceinline__ f32x16 product(const char* lds, int plane, int steps) const {
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 acc = zero;
+  __device__ __forceinline__ Tile16 product(const char* lds, int stride, int plane, int steps) const {
+    Tile16 acc;
+    acc.clear();
+    const char* lds1 = lds + 16 * stride;
     if constexpr (F32) {
-      f32x16 low = zero;
-      u32x4 q0, q1, q2;
+      Tile16 low;
+      low.clear();
+      u32x4 q[2][3];
       auto fetch = [&](int u) {
-        q0 = *reinterpret_cast<const u32x4*>(lds + u * 32);
-        q1 = *reinterpret_cast<const u32x4*>(lds + plane + u * 32);
-        q2 = *reinterpret_cast<const u32x4*>(lds + 2 * plane + u * 32);
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+          q[0][pl] = *reinterpret_cast<const u32x4*>(lds + pl * plane + u * 64);
+          q[1][pl] = *reinterpret_cast<const u32x4*>(lds1 + pl * plane + u * 64);
+        }
       };
-      fetch(0);
+      auto add = [&](Tile16& to, int u, int key_part, int row_part) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int r = 0; r < 2; ++r) to.t[s][r] = mm16<KEYS_AS_ROWS>(v[s][3 * u + key_part], q[r][row_part], to.t[s][r]);
+      };
 #pragma unroll
       for (int u = 0; u < STEPS; ++u) {
         if (FULL || u < steps) {
-          const u32x4 a0 = q0, a1 = q1, a2 = q2;
-          if (u + 1 < STEPS && (FULL || u + 1 < steps)) fetch(u + 1);      // one step ahead of the products
-          __builtin_amdgcn_sched_barrier(0);
-          low = mm<KEYS_AS_ROWS>(v[3 * u + 2], a0, low);
-          acc = mm<KEYS_AS_ROWS>(v[3 * u], a0, acc);
-          low = mm<KEYS_AS_ROWS>(v[3 * u], a2, low);
-          low = mm<KEYS_AS_ROWS>(v[3 * u + 1], a1, low);
-          low = mm<KEYS_AS_ROWS>(v[3 * u + 1], a0, low);
-          low = mm<KEYS_AS_ROWS>(v[3 * u], a1, low);
+          fetch(u);
+          add(low, u, 2, 0);
+          add(acc, u, 0, 0);
+          add(low, u, 0, 2);
+          add(low, u, 1, 1);
+          add(low, u, 1, 0);
+          add(low, u, 0, 1);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      acc += low;
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) acc.t[s][r] += low.t[s][r];
     } else {
 #pragma unroll
       for (int u = 0; u < STEPS; ++u) {
-        if (FULL || u < steps) acc = mm<KEYS_AS_ROWS>(v[u], *reinterpret_cast<const u32x4*>(lds + u * 32), acc);
-        if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);                 // (at most four operands of Q requested ahead: registers)
+        if (FULL || u < steps) {
+          const u32x4 q0 = *reinterpret_cast<const u32x4*>(lds + u * 64), q1 = *reinterpret_cast<const u32x4*>(lds1 + u * 64);
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            acc.t[s][0] = mm16<KEYS_AS_ROWS>(v[s][u], q0, acc.t[s][0]);
+            acc.t[s][1] = mm16<KEYS_AS_ROWS>(v[s][u], q1, acc.t[s][1]);
+          }
+        }
+        if (u % 2 == 1) __builtin_amdgcn_sched_barrier(0);                 // (at most four operands of Q requested ahead: registers)
       }
     }
     return acc;
@@ -189,25 +223,29 @@ struct WavePlan {
   RowScale row_scale;
 };
 
-// Waves per SIMD the kernels are built for: as many as their registers (and 32 of the score rows per workgroup in LDS) allow.
-template <typename T, int NP> constexpr int waves_per_simd() { return is_f32(T()) ? (NP <= 8 ? 3 : 2) : (NP <= 6 ? 5 : NP <= 8 ? 4 : 2); }
+// Waves per SIMD the kernels are built for: as many as their registers (and 32 of the score rows per workgroup in LDS) allow.  (d = 96, bf16: five waves
+// spill 13 registers in the second kernel; 64 rows, 192 heads x 8001 152 us, with four 134.5.)
+template <typename T, int NP> constexpr int waves_per_simd() { return is_f32(T()) ? (NP <= 8 ? 3 : 2) : (NP <= 4 ? 5 : NP <= 8 ? 4 : 2); }
 
 // A wave's sums of exponentials refer to a number near the row's maximum, not to the maximum itself: HEADROOM above that of the first
 // tile, and moved only where a tile's sum reaches OUTGROWN of it (then, and where a row does not see all keys of a tile, or a sum is no
 // number, the maximum of the tile is made).  The terms that count have exponents between -8 and 7, as with a maximum that most keys stay
-// some powers of two below.  A gain in error and in instructions rather than in time: scores against 64 bits (2-norm, logits of deviation 1)
-// bf16 3.0e-7 -> 2.0e-7, fp32 2.2e-7 -> 1.9e-7; 71 instead of 87 vector instructions per product of 32 keys and 32 rows (SQ_INSTS_VALU); the whole
-// eviction of 256 heads x 32768 keys, 128 rows, is not faster beyond noise (934 : 927 us): it is bound by memory and by the power that memory and
-// matrix cores take.
+// some powers of two below.  A gain in instructions rather than in time: 16 of 87 vector instructions per product of 32 keys and 32 rows less
+// (SQ_INSTS_VALU), and the whole eviction of 256 heads x 32768 keys, 128 rows, was not faster beyond noise (934 : 927 us): it is bound by memory and by
+// the power that memory and matrix cores take.  Whole numbers, see above.
 constexpr float HEADROOM = 3.f, OUTGROWN = 128.f;
-// exp2(s * scale - m) of a lane's 16 keys and of the 16 that the other half of the wave has of the same row, summed
-__device__ __forceinline__ float tile_sum(const f32x16& s, float scale, float m) {
-  float z[2] = {0.f, 0.f};
+// exp2(s * scale - m) of a lane's two rows over the tile's keys: eight of them here, the others in the lanes of the same number modulo 16.
+// Lanes 0 .. 31 end with the sum of row n16, the others with that of row 16 + n16.
+__device__ __forceinline__ float tile_sum(const Tile16& a, float scale, float m0, float m1) {
+  float z0 = 0.f, z1 = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) z[i & 1] += __builtin_amdgcn_exp2f(fmaf(s[i], scale, -m));
-  z[0] += z[1];
-  const auto zh = __builtin_amdgcn_permlane32_swap(__float_as_uint(z[0]), __float_as_uint(z[0]), false, false);
-  return __uint_as_float(zh[0]) + __uint_as_float(zh[1]);
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      z0 += __builtin_amdgcn_exp2f(fmaf(a.t[s][0][i], scale, -m0));
+      z1 += __builtin_amdgcn_exp2f(fmaf(a.t[s][1][i], scale, -m1));
+    }
+  return over_groups(z0, z1, [](float x, float y) { return x + y; });
 }
 
 // Pass 1: part[head][segment][row] = (m, z) of a score row over the segment's visible keys, in log2 units.
@@ -222,44 +260,58 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
   const RowScale row_scale = pl.row_scale;
   u32x4 key[NP];
   if (w.some) w.load(key, g, lay, w.first);
-  stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
+  stage_rows16<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
   float2* stat = reinterpret_cast<float2*>(smem + pl.group_tiles * 32 * w.stride);       // [row tile][wave][row]
   for (int i = threadIdx.x; i < ntile * WAVES * 32; i += THREADS) stat[i] = make_float2(NEG_BIG, 0.f);
   __syncthreads();
   auto work = [&](const Operand<T, NP, FULL>& op, int key0) {
     const bool plain = key0 + 31 <= g.qmin;              // every row sees every key
-    const char* rows = smem + w.n32 * w.stride + w.hf * 16;
-    float2* mine = stat + w.wave * 32 + w.n32;
+    const char* rows = smem + w.n16 * w.stride + w.grp * 16;
+    float2* mine = stat + w.wave * 32 + w.n16;           // this lane's first row; the second: 16 further on
+    const int own = w.grp >> 1 << 4;                     // the one whose sum it ends with
 #pragma unroll 1
     for (int rt = 0; rt < ntile; ++rt) {
-      const float2 old = *mine;
-      f32x16 s = op.template product<true>(rows, w.plane, w.plane / 32);
-      float z = plain && key0 != w.first ? tile_sum(s, row_scale.scale2, old.x) : INFINITY;
+      const float old0 = mine[0].x, old1 = mine[16].x, old_z = mine[own].y;
+      Tile16 a = op.template product<true>(rows, w.stride, w.plane, w.plane / 64);
+      float z = plain && key0 != w.first ? tile_sum(a, row_scale.scale2, old0, old1) : INFINITY;
       if (__builtin_expect(!__any(!(z <= OUTGROWN)), 1)) {
-        mine->y = old.y + z;
+        mine[own].y = old_z + z;
       } else {
-        float m, scale = row_scale.scale2;
+        float m0, m1, scale = row_scale.scale2;
 #pragma unroll 1
         for (bool again = false;; again = true) {
           if (!plain) {
             int n = threadIdx.x & 63;
             asm volatile("" : "+v"(n));                  // (computed here: the common case has no registers for it)
-            const int row = (rt0 + rt) * 32 + (n & 31), last = last_visible_key(g, qp, min(row, g.R - 1) % g.W) - key0;
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-              if (acc_row(i, n >> 5) > last) s[i] = -INFINITY;
+            for (int r = 0; r < 2; ++r) {
+              const int row = (rt0 + rt) * 32 + 16 * r + (n & 15), last = last_visible_key(g, qp, min(row, g.R - 1) % g.W) - key0 - 4 * (n >> 4);
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                if (16 * (e >> 2) + (e & 3) > last) a.t[e >> 2][r][e & 3] = -INFINITY;
+            }
           }
-          m = s[0];
+          m0 = a.t[0][0][0];
+          m1 = a.t[0][1][0];
 #pragma unroll
-          for (int i = 1; i < 16; ++i) m = fmaxf(m, s[i]);
+          for (int e = 1; e < 8; ++e) {
+            m0 = fmaxf(m0, a.t[e >> 2][0][e & 3]);
+            m1 = fmaxf(m1, a.t[e >> 2][1][e & 3]);
+          }
+          const float m = over_groups(m0, m1, [](float x, float y) { return fmaxf(x, y); });
           const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-          m = fmaxf(old.x, fmaf(fmaxf(__uint_as_float(mh[0]), __uint_as_float(mh[1])), scale, HEADROOM));    // (the logit scale is positive)
-          z = tile_sum(s, scale, m);
+          m0 = fmaxf(old0, __builtin_ceilf(fmaf(__uint_as_float(mh[0]), scale, HEADROOM)));      // (the logit scale is positive)
+          m1 = fmaxf(old1, __builtin_ceilf(fmaf(__uint_as_float(mh[1]), scale, HEADROOM)));
+          z = tile_sum(a, scale, m0, m1);
           if (!is_f32(T()) || again || __builtin_expect(!__any(z != z), 1)) break;
-          s = product_f32<true>(w.key_row(g, lay, key0), w.score_row(g, rt0 + rt), w.hf, w.row_bytes);
+          const char *kr[2], *qr[2];
+          w.key_rows(kr, g, lay, key0);
+          w.score_rows(qr, g, rt0 + rt);
+          a = product16_f32<true>(kr, qr, w.grp, w.row_bytes);
           scale = g.scale2;
         }
-        *mine = make_float2(m, fmaf(old.y, __builtin_amdgcn_exp2f(old.x - m), z));
+        const float m = own ? m1 : m0, old = own ? old1 : old0;
+        mine[own] = make_float2(m, fmaf(old_z, __builtin_amdgcn_exp2f(old - m), z));
       }
       rows += 32 * w.stride;
       mine += WAVES * 32;
@@ -280,43 +332,45 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
   }
 }
 
-// c = M + log2 Z of the score rows r0 .. r0 + n - 1 from the statistics of the head's segments: THREADS / n threads share
-// a row, fixed order.  (The caller's next barrier completes it.)
-__device__ __forceinline__ void fold_segments(const float2* __restrict__ part, int segs, int Rpad, int R, int r0, int n, float2* fold, float* rowc) {
-  constexpr int TURN = 8;
-  const int subs = THREADS / n, r = threadIdx.x % n, sub = threadIdx.x / n;
-  if (sub < subs) {
-    const float2* p = part + r0 + r;
-    float M = NEG_BIG, Z = 0.f;
+// The (m, z) of segments i, i + by, .. of a row: the greatest reference first, then the sums, which whole numbers bring together by exact powers of two.
+template <int TURN>
+__device__ __forceinline__ float2 fold_row(const float2* __restrict__ p, int first, int by, int segs, int Rpad) {
+  float M = NEG_BIG, Z = 0.f;
 #pragma unroll 1
-    for (int i = sub; i < segs; i += subs * TURN) {
-      float2 v[TURN];
+  for (int i = first; i < segs; i += by * TURN) {
+    float2 v[TURN];
 #pragma unroll
-      for (int b = 0; b < TURN; ++b) v[b] = p[(size_t)min(i + b * subs, segs - 1) * Rpad];
+    for (int b = 0; b < TURN; ++b) v[b] = p[(size_t)min(i + b * by, segs - 1) * Rpad];
 #pragma unroll
-      for (int b = 0; b < TURN; ++b)
-        if (i + b * subs < segs) merge_stat(M, Z, v[b]);
-    }
-    fold[threadIdx.x] = make_float2(M, Z);
+    for (int b = 0; b < TURN; ++b)
+      if (i + b * by < segs) merge_stat(M, Z, v[b]);
   }
+  return make_float2(M, Z);
+}
+
+// M and the weight 1 / Z of the score rows r0 .. r0 + n - 1 from the statistics of the head's segments: THREADS / n threads share
+// a row, fixed order.  (The caller's next barrier completes it.)
+__device__ __forceinline__ void fold_segments(const float2* __restrict__ part, int segs, int Rpad, int R, int r0, int n, float2* fold, float* rowm, float* roww) {
+  const int subs = THREADS / n, r = threadIdx.x % n, sub = threadIdx.x / n;
+  if (sub < subs) fold[threadIdx.x] = fold_row<8>(part + r0 + r, sub, subs, segs, Rpad);
   __syncthreads();
   if (sub == 0) {
     float M = NEG_BIG, Z = 0.f;
     for (int i = 0; i < subs; ++i) merge_stat(M, Z, fold[i * n + r]);
-    rowc[r] = r0 + r < R ? M + __builtin_amdgcn_logf(Z) : INFINITY;
+    rowm[r] = M;
+    roww[r] = r0 + r < R ? 1.f / Z : 0.f;
   }
 }
 
-// Pass 2: raw[j] = sum over the score rows of exp2(s - c[row]), a group of row tiles after the other.  rowc_all: the heads' row
-// constants, or null: folded here.
+// Pass 2: raw[j] = sum over the score rows of exp2(s - M) / Z, a group of row tiles after the other.  folded: the first segment's place in
+// `part` holds (M, 1 / Z); else they are made here.
 template <typename T, int NP, bool FULL>
 __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, WavePlan pl,
                                                                                const T* __restrict__ q, const T* __restrict__ k,
                                                                                const float2* __restrict__ part,
-                                                                               const float* __restrict__ rowc_all,
-                                                                               float* __restrict__ raw, int* __restrict__ status) {
+                                                                               bool folded, float* __restrict__ raw, int* __restrict__ status) {
   extern __shared__ __align__(16) char smem[];
-  __shared__ __align__(16) float rowc[MAX_TILES * 32];
+  __shared__ __align__(16) float rowm[MAX_TILES * 32], roww[MAX_TILES * 32];
   __shared__ __align__(16) int last[MAX_TILES * 32];     // last key the rows see
   const int tid = threadIdx.x;
   const size_t hg = (size_t)blockIdx.z * g.Hkv + blockIdx.y;
@@ -330,91 +384,104 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
     const int ntile = min(pl.group_tiles, g.Rpad / 32 - rt0);
     if (w.some) w.load(key, g, lay, w.first);
     if (rt0 > 0) __syncthreads();
-    stage_rows<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
+    stage_rows16<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
     if (tid < ntile * 32) {
       const int row = rt0 * 32 + tid;
       last[tid] = last_visible_key(g, qp, min(row, g.R - 1) % g.W);
-      if (rowc_all) rowc[tid] = row < g.R ? rowc_all[hg * g.Rpad + row] : INFINITY;
+      if (folded) {
+        const float2 c = part[hg * pl.segs * g.Rpad + row];
+        rowm[tid] = c.x;
+        roww[tid] = c.y;
+      }
     }
-    if (!rowc_all)
+    if (!folded)
       fold_segments(part + hg * pl.segs * g.Rpad, pl.segs, g.Rpad, g.R, rt0 * 32, ntile * 32,
-                    reinterpret_cast<float2*>(smem + pl.group_tiles * 32 * w.stride), rowc);
+                    reinterpret_cast<float2*>(smem + pl.group_tiles * 32 * w.stride), rowm, roww);
     __syncthreads();
-    const char* rows = smem + w.n32 * w.stride + w.hf * 16;
+    const char* rows = smem + w.n16 * w.stride + w.grp * 16;
     auto work = [&](const Operand<T, NP, FULL>& op, int key0) {
       const bool plain = key0 + 31 <= g.qmin;
-      const int j = key0 + w.n32;
-      auto masked = [&](f32x16 s, int rt) {
+      auto masked = [&](Tile16& a, int rt) {
         if (!plain) {
 #pragma unroll
-          for (int gq = 0; gq < 4; ++gq) {
-            const i32x4 lv = *reinterpret_cast<const i32x4*>(last + rt * 32 + 8 * gq + 4 * w.hf);
+          for (int r = 0; r < 2; ++r) {
+            const i32x4 lv = *reinterpret_cast<const i32x4*>(last + rt * 32 + 16 * r + 4 * w.grp);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (j > lv[i]) s[4 * gq + i] = -INFINITY;
+            for (int e = 0; e < 8; ++e)
+              if (key0 + 16 * (e >> 2) + w.n16 > lv[e & 3]) a.t[e >> 2][r][e & 3] = -INFINITY;
           }
         }
-        return s;
       };
-      float sum = 0.f;
+      float sum0 = 0.f, sum1 = 0.f;                      // of keys n16 and 16 + n16 of the tile
 #pragma unroll 1
       for (int rt = 0; rt < ntile; ++rt) {
-        const f32x16 s = masked(op.template product<false>(rows + rt * 32 * w.stride, w.plane, w.plane / 32), rt);
+        Tile16 a = op.template product<false>(rows + rt * 32 * w.stride, w.stride, w.plane, w.plane / 64);
+        masked(a, rt);
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const f32x4 c = *reinterpret_cast<const f32x4*>(rowc + rt * 32 + 8 * gq + 4 * w.hf);
+        for (int r = 0; r < 2; ++r) {
+          const f32x4 m = *reinterpret_cast<const f32x4*>(rowm + rt * 32 + 16 * r + 4 * w.grp);
+          const f32x4 wt = *reinterpret_cast<const f32x4*>(roww + rt * 32 + 16 * r + 4 * w.grp);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(s[4 * gq + i], row_scale.scale2, -c[i]));
-        }
-      }
-      const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
-      float both = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
-      if (__builtin_expect(__any((both < TINY || (is_f32(T()) && both != both)) && j < g.L), 0)) {
-        sum = 0.f;
-#pragma unroll 1
-        for (int rt = 0; rt < ntile; ++rt) {
-          f32x16 s;
-          if constexpr (is_f32(T())) s = product_f32<false>(w.key_row(g, lay, key0), w.score_row(g, rt0 + rt), w.hf, w.row_bytes);
-          else s = op.template product<false>(rows + rt * 32 * w.stride, w.plane, w.plane / 32);
-          s = masked(s, rt);
-#pragma unroll 1
-          for (int i = 0; i < 16; ++i) {
-            const float x = fmaf(s[0], g.scale2, -rowc[rt * 32 + acc_row(i, w.hf)]);
-            sum += x < -126.f ? __builtin_amdgcn_exp2f(x + 64.f) * 0x1p-64f : __builtin_amdgcn_exp2f(x);
-            s = __builtin_shufflevector(s, s, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 0);
+          for (int i = 0; i < 4; ++i) {
+            sum0 = fmaf(__builtin_amdgcn_exp2f(fmaf(a.t[0][r][i], row_scale.scale2, -m[i])), wt[i], sum0);
+            sum1 = fmaf(__builtin_amdgcn_exp2f(fmaf(a.t[1][r][i], row_scale.scale2, -m[i])), wt[i], sum1);
           }
         }
-        both = sum + __shfl_xor(sum, 32);
       }
-      if (w.hf == 0 && j < w.end) out[j] = rt0 > 0 ? out[j] + both : both;
+      const auto plus = [](float x, float y) { return x + y; };
+      float both = over_groups(sum0, sum1, plus);
+      const int j = key0 + (w.grp >> 1 << 4) + w.n16;    // the key whose sum this lane ends with
+      if (__builtin_expect(__any((both < TINY || (is_f32(T()) && both != both)) && j < g.L), 0)) {
+        sum0 = sum1 = 0.f;
+#pragma unroll 1
+        for (int rt = 0; rt < ntile; ++rt) {
+          Tile16 a;
+          if constexpr (is_f32(T())) {
+            const char *kr[2], *qr[2];
+            w.key_rows(kr, g, lay, key0);
+            w.score_rows(qr, g, rt0 + rt);
+            a = product16_f32<false>(kr, qr, w.grp, w.row_bytes);
+          } else {
+            a = op.template product<false>(rows + rt * 32 * w.stride, w.stride, w.plane, w.plane / 64);
+          }
+          masked(a, rt);
+#pragma unroll 1
+          for (int e = 0; e < 8; ++e) {                  // rows 16 (e / 4) + 4 grp + e % 4
+            const int row = rt * 32 + 16 * (e >> 2) + 4 * w.grp + (e & 3);
+            const float c = rowm[row] - __builtin_amdgcn_logf(roww[row]);                  // (no weight: infinite)
+            const float x0 = fmaf(a.t[0][0][0], g.scale2, -c), x1 = fmaf(a.t[1][0][0], g.scale2, -c);
+            sum0 += x0 < -126.f ? __builtin_amdgcn_exp2f(x0 + 64.f) * 0x1p-64f : __builtin_amdgcn_exp2f(x0);
+            sum1 += x1 < -126.f ? __builtin_amdgcn_exp2f(x1 + 64.f) * 0x1p-64f : __builtin_amdgcn_exp2f(x1);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {                // the next element to the front
+              const float first = a.t[s][1][0];
+              a.t[s][0] = f32x4{a.t[s][0][1], a.t[s][0][2], a.t[s][0][3], first};
+              a.t[s][1] = f32x4{a.t[s][1][1], a.t[s][1][2], a.t[s][1][3], 0.f};
+            }
+          }
+        }
+        both = over_groups(sum0, sum1, plus);
+      }
+      if ((w.grp & 1) == 0 && j < w.end) out[j] = rt0 > 0 ? out[j] + both : both;
     };
     if (w.some) walk_tiles<T, NP, FULL>(key, w.first, w.last_tile, [&](u32x4 (&x)[NP], int key0) { w.load(x, g, lay, key0); }, work);
   }
 }
 
-// Combine the (m, z) of all segments of a head into c = M + log2 Z per score row.  One workgroup per
-// (head, 32-row tile): 8 threads share a row and split the segments; fixed merge order.
-__global__ __launch_bounds__(256) void row_constants_kernel(ScoreGeom g, const float2* __restrict__ part,
-                                                            float* __restrict__ rowc) {
+// Combine the (m, z) of all segments of a head, one workgroup per (head, 32-row tile): 8 threads share a row and split the segments; fixed
+// merge order.  rowc: c = M + log2 Z per score row; null: (M, 1 / Z) take the place of the first segment's.
+__global__ __launch_bounds__(256) void row_constants_kernel(ScoreGeom g, float2* part, float* __restrict__ rowc) {
   __shared__ float2 stat[256];
   const int hg = blockIdx.x, rt = blockIdx.y, tid = threadIdx.x;
   const int r = rt * 32 + (tid & 31), sel = tid >> 5;
-  const float2* p = part + (size_t)hg * g.nchunk * g.Rpad + r;
-  float M = NEG_BIG, Z = 0.f;
-  constexpr int B = 16;
-  for (int c0 = sel; c0 < g.nchunk; c0 += 8 * B) {
-    float2 buf[B];
-#pragma unroll
-    for (int b = 0; b < B; ++b) buf[b] = p[(size_t)min(c0 + 8 * b, g.nchunk - 1) * g.Rpad];
-#pragma unroll
-    for (int b = 0; b < B; ++b)
-      if (c0 + 8 * b < g.nchunk) merge_stat(M, Z, buf[b]);
-  }
-  stat[tid] = make_float2(M, Z);
+  float2* p = part + (size_t)hg * g.nchunk * g.Rpad + r;
+  stat[tid] = fold_row<16>(p, sel, 8, g.nchunk, g.Rpad);
   __syncthreads();
   if (tid < 32) {
+    float M = stat[tid].x, Z = stat[tid].y;
     for (int s2 = 1; s2 < 8; ++s2) merge_stat(M, Z, stat[s2 * 32 + tid]);
-    rowc[(size_t)hg * g.Rpad + r] = (r < g.R) ? M + __builtin_amdgcn_logf(Z) : 1.0e30f;
+    if (rowc) rowc[(size_t)hg * g.Rpad + r] = (r < g.R) ? M + __builtin_amdgcn_logf(Z) : 1.0e30f;
+    else *p = make_float2(M, r < g.R ? 1.f / Z : 0.f);
   }
 }
 
@@ -462,13 +529,13 @@ WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int s
   return pl;
 }
 
-constexpr int MAX_LDS = 160 << 10, STATIC_LDS = 2 * MAX_TILES * 32 * 4;
+constexpr int MAX_LDS = 160 << 10, STATIC_LDS = 3 * MAX_TILES * 32 * 4;
 
 template <typename T, int NP, bool FULL>
 hipError_t launch_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, const T* q, const T* k, float* raw,
                        const Workspace& ws, hipStream_t st) {
   constexpr int per_simd = waves_per_simd<T, NP>();
-  const int stride = row_stride<T>(g.d);
+  const int stride = row16_stride<T>(g.d);
   WavePlan pl = plan_of(g, 256 * per_simd, (is_f32(T()) ? 2.0 : 1.25) / per_simd, (MAX_LDS / per_simd - STATIC_LDS) & ~255, stride);
   pl.row_scale = row_scale_of<T>(g.scale2);
   const int rows = pl.group_tiles * 32;
@@ -480,10 +547,10 @@ hipError_t launch_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& 
   if (!fold) {
     ScoreGeom gs = g;
     gs.nchunk = pl.segs;
-    if ((e = launch_row_constants(gs, ws, st)) != hipSuccess) return e;
+    if ((e = launch_row_constants(gs, ws, nullptr, st)) != hipSuccess) return e;
   }
   hipLaunchKernelGGL((wave_score_kernel<T, NP, FULL>), dim3(pl.segs, g.Hkv, g.n_inst), dim3(THREADS), rows * stride + THREADS * (int)sizeof(float2),
-                     st, g, qp, lay, pl, q, k, ws.part, fold ? (const float*)nullptr : ws.rowc, raw, ws.status);
+                     st, g, qp, lay, pl, q, k, ws.part, !fold, raw, ws.status);
   return hipGetLastError();
 }
 
@@ -497,10 +564,11 @@ template <typename T, int NP, bool FULL> hipError_t init_wave() {
 
 }  // namespace
 
-// c = M + log2 Z of every score row from the statistics of g.nchunk segments of every head
-hipError_t launch_row_constants(const ScoreGeom& g, const Workspace& ws, hipStream_t st) {
+// c = M + log2 Z of every score row from the statistics of g.nchunk segments of every head into rowc; null: (M, 1 / Z) into the statistics'
+// first segment
+hipError_t launch_row_constants(const ScoreGeom& g, const Workspace& ws, float* rowc, hipStream_t st) {
   const long long n_heads = (long long)g.n_inst * g.Hkv;
-  hipLaunchKernelGGL(row_constants_kernel, dim3((unsigned)n_heads, g.Rpad / 32), dim3(256), 0, st, g, ws.part, ws.rowc);
+  hipLaunchKernelGGL(row_constants_kernel, dim3((unsigned)n_heads, g.Rpad / 32), dim3(256), 0, st, g, ws.part, rowc);
   return hipGetLastError();
 }
 
