@@ -83,7 +83,7 @@ template <typename T, int NP, bool FULL> struct Wave {
   __device__ __forceinline__ void key_rows(const char* (&rows)[2], const ScoreGeom& g, const KvLayout& lay, int key0) const {
     int r0 = key0;
     const char* p = head_keys;
-    if (lay.table) p += paged_block_offset(lay, inst, key0, &r0) * (int64_t)sizeof(T);       // (a block holds whole tiles)
+    if (lay.table) p += paged_tile_offset(lay, inst, key0, &r0) * (int64_t)sizeof(T);       // (a block holds whole tiles)
 #pragma unroll
     for (int s = 0; s < 2; ++s)                          // (keys beyond the last one are masked: any row will do)
       rows[s] = p + (int64_t)(r0 + min(16 * s + n16, g.L - 1 - key0)) * src_row;
