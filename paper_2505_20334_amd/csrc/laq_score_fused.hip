@@ -16,7 +16,7 @@
 // them computes while the other waits for its team); a wave holds 8 / (R / 32) key tiles, a
 // workgroup four times that many keys, a team of ceil(L / keys per workgroup) workgroups one head.
 // Per head, every workgroup of the team
-//   B. D = Q * K_tile^T per (key tile, row tile): lane = key, accumulator registers = 16 rows; the
+//   B. D = Q * K_tile^T per (key tile, row tile): lane = two keys, accumulator registers = 8 rows of each; the
 //      next key tiles are loaded while this one is worked on; the first two of the next head are
 //      requested during the pass, one into registers, one into LDS (loads that write LDS directly),
 //      and travel while the other steps run;
@@ -43,6 +43,10 @@
 // which it does after reading head n).  All waits are bounded, and end at once after one of
 // them has timed out (status word of the workspace).
 //
+// A tile is four products of 16 x 16 (v_mfma_f32_16x16x32_bf16) and not one of 32 x 32: a load instruction covers 64 bytes of 16 rows instead of 32
+// of 32, so half as many lines are asked for, and the transpositions are half as large.  laq_evict, us, with 32 x 32 : so: 64 rows, 2048 heads x
+// 32768 keys 3960 : 3800, 256 x 16384 274 : 267; 32 rows, 256 x 8001 150.5 : 148.5; 8 x 30011 even.
+//
 // A workgroup's place in a team is a number that it draws when it starts, so teams are complete one
 // after the other in the order in which workgroups get on the device, and of a launch at most two (there are up to two
 // counters) are there in part.  An ordinary launch is enough as long as the parts of teams that
@@ -53,29 +57,22 @@
 #include <type_traits>
 
 #include "laq_internal.h"
+#include "laq_products.h"
 #include "laq_team.h"
 
 namespace laq {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
-constexpr float NEG_BIG = -1.0e30f;
-// The exponential instruction returns 0 below 2^-126, where fp32 still tells scores apart: a score below this is summed again.
-constexpr float TINY = 0x1p-90f;
 constexpr int D = 128;                       // head size this kernel is written for
-constexpr int KS = D / 16;                   // MFMAs (reduction steps) per 32x32 tile
+constexpr int STEPS = D / 32;                // reduction steps of a product
+constexpr int KS = 2 * STEPS;                // 16-byte pieces of a key tile per lane: of its first row, then of its second
 constexpr int TILE_BYTES = 32 * D * 2;       // a key tile: 32 rows
 constexpr int F_WAVES = 4, F_THREADS = F_WAVES * 64;   // one wave per SIMD; two workgroups share a compute unit
 // LDS row of Q: the d elements and 16 bytes that make 128-bit operand reads of 16 consecutive
 // rows conflict-free
 constexpr int QROWB = D * 2 + 16;
-constexpr int ZT_STRIDE = 36;                // floats per row of a wave's transposition tile (conflict-free 128-bit reads)
+constexpr int ZT_STRIDE = 20;                // floats per row of a wave's transposition tile (writes and 128-bit reads free of conflicts)
 constexpr int SPIN_LIMIT = 1 << 20;          // probes; about a second, far beyond any legitimate wait
 constexpr int SPIN_LIMIT_UNSAFE = 1 << 18;   // of a launch that the rule of laq_team.h does not cover: it gives up before the others do
 constexpr int MAX_HALF = (MAX_POOL - 1) / 2;
@@ -117,7 +114,7 @@ template <int NRT> struct Cfg {
   static constexpr int Q_PIECES = ROWS * (D / 8);                   // 16-byte pieces of one Q_g
   static constexpr int Q_PER_THREAD = (Q_PIECES + F_THREADS - 1) / F_THREADS;
   static constexpr int OFF_Q = 0;                                   // [ROWS][QROWB] bf16 rows of Q_g
-  // float[F_WAVES][32][ZT_STRIDE]: transposition tiles.  They are used between the last read of a
+  // float[F_WAVES][32][ZT_STRIDE]: transposition tiles (16 numbers a row).  They are used between the last read of a
   // head's Q and the arrival of the next head's, so where Q is large enough (128 score rows) they
   // lie inside it; a barrier then separates them from the last matrix product.
   static constexpr int ZT_BYTES = F_WAVES * 32 * ZT_STRIDE * 4;
@@ -143,20 +140,9 @@ __device__ __forceinline__ void coherent_store(float2* p, float2 v) {
   __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void merge_stat(float& M, float& Z, float2 p) {
-  const float Mn = fmaxf(M, p.x);
-  Z = Z * __builtin_amdgcn_exp2f(M - Mn) + p.y * __builtin_amdgcn_exp2f(p.x - Mn);
-  M = Mn;
-}
-
-// Row index (0..31) of accumulator register i for a lane in half hf of the 32x32 output layout.
-__device__ __forceinline__ int acc_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
-
-__device__ __forceinline__ bf16x8 lds_operand(const char* p) { return *reinterpret_cast<const bf16x8*>(p); }
-
 // ---- key rows: global memory -> operand registers -------------------------------------------
-// Lane l of a wave supplies key row l%32 of a tile and the 16-byte slice 2t + l/32 of that row
-// for reduction step t.  Buffer loads against a descriptor that ends with the head's last row (of a
+// Lane l of a wave supplies key rows l%16 and 16 + l%16 of a tile and the 16-byte slice 4u + l/16 of either
+// for reduction step u.  Buffer loads against a descriptor that ends with the head's last row (of a
 // paged cache: the block's last valid row): rows beyond it read as zeros (they are causally
 // masked).  Consecutive rows lie row_bytes apart (256 in a dense cache, more in a token-major or
 // padded one).
@@ -181,21 +167,26 @@ __device__ __forceinline__ KeySource key_source(const TileRef& r, int row_bytes)
   s.row0 = r.row0;
   return s;
 }
-__device__ __forceinline__ bf16x8 load_operand(const KeySource& s, int voff_tile, int t) {
-  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(s.rsrc, voff_tile + t * 32, 0, 0));
+__device__ __forceinline__ u32x4 load_operand(const KeySource& s, int voff, int u) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(s.rsrc, voff + u * 64, 0, 0));
 }
-// Byte offset from the descriptor's first row of (row l%32 of the tile, slice l/32).  Recomputed
+// Byte offset from the descriptor's first row of (row l%16 of the tile, slice l/16).  Recomputed
 // where it is needed (a register held across the whole kernel costs more than three instructions
 // per tile), and opaque to the optimiser so that the step offsets fold into the instructions'
 // immediate fields.
 __device__ __forceinline__ int tile_offset(int row0, int lane, int row_bytes) {
   int l = lane;
   asm volatile("" : "+v"(l));
-  return (row0 + (l & 31)) * row_bytes + (l >> 5) * 16;
+  return (row0 + (l & 15)) * row_bytes + (l >> 4) * 16;
+}
+__device__ __forceinline__ void load_tile(u32x4 (&key)[KS], const KeySource& s, int lane, int row_bytes) {
+  const int v = tile_offset(s.row0, lane, row_bytes), v1 = v + 16 * row_bytes;
+#pragma unroll
+  for (int t = 0; t < KS; ++t) key[t] = load_operand(s, t < STEPS ? v : v1, t % STEPS);
 }
 
 // The same tile, memory -> LDS without passing through registers: eight 16-byte loads per lane
-// whose data the memory pipeline writes to LDS itself, lane l's piece of reduction step t at
+// whose data the memory pipeline writes to LDS itself, piece t of lane l at
 // stage + t * 1024 + l * 16 (rows beyond the descriptor's end arrive as zeros, as in registers).
 // The loads count as vector memory loads of the wave (wait with stage_wait()); the compiler does
 // not see them: its own waits for loads issued earlier can only become longer by that, never
@@ -207,14 +198,14 @@ __device__ __forceinline__ void stage_tile(const TileRef& r, int row_bytes, int 
   words[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32)) & 0xffffu;
   words[2] = __builtin_amdgcn_readfirstlane(r.rows > 0 ? (r.rows - 1) * row_bytes + D * 2 : 0);
   words[3] = 0x00020000u;
-  const int voff = tile_offset(r.row0, lane, row_bytes);
+  const int voff = tile_offset(r.row0, lane, row_bytes), voff1 = voff + 16 * row_bytes;
   const unsigned lds = __builtin_amdgcn_readfirstlane(stage);
 #pragma unroll
   for (int t = 0; t < KS; ++t) {
     unsigned keep;
     asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds\n\ts_mov_b32 m0, %0"
                  : "=&s"(keep)
-                 : "s"(lds + t * 1024), "v"(voff), "s"(words), "s"(t * 32)
+                 : "s"(lds + t * 1024), "v"(t < STEPS ? voff : voff1), "s"(words), "s"(t % STEPS * 64)
                  : "memory");
   }
 }
@@ -224,8 +215,8 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
 }
 
 struct WaveCtx {
-  const char* q_lane;      // LDS: Q row (lane%32), slice (lane/32) of reduction step 0, row tile 0
-  int lane, hf, n32;
+  const char* q_lane;      // LDS: Q row (lane%16), slice (lane/16) of reduction step 0, row tile 0
+  int lane, grp, n16;
   int key0;                // first key of this wave within the head
   int rot;                 // the wave's tile kt holds keys (kt + rot) % KT * 32 .. + 31 of its range
   int L;
@@ -236,8 +227,8 @@ struct WaveCtx {
 };
 
 // ---- step B: the wave's (key tile, row tile) pairs --------------------------------------------
-// E[pair] = Q_rt * K_tile^T over the head size: lane = key, accumulator registers = 16 rows; -inf
-// where a row does not see a key.  Key tile kt is in kring[kt % 4].  Tile 0 is there when the pass
+// E[pair] = Q_rt * K_tile^T over the head size, as four products of 16 x 16 (two halves of the keys by two of the rows): lane = key,
+// accumulator registers = 4 rows; -inf where a row does not see a key.  Key tile kt is in kring[kt % 4].  Tile 0 is there when the pass
 // begins (loaded into registers during the previous head's pass) and tile 1 waits in the wave's LDS
 // stage (requested at the end of the previous head's pass: it travels while the other steps run,
 // which have no registers to receive it); the loads of the next two tiles are issued at once at
@@ -248,69 +239,63 @@ struct WaveCtx {
 constexpr int RING = 4;
 // cur(kt) / next(kt): where key tile kt of this head / of the next head lies.
 template <int NRT, typename CUR, typename NEXT, typename STAGE>
-__device__ __forceinline__ void wave_main(const WaveCtx& w, f32x16 (&E)[Cfg<NRT>::PAIRS], bf16x8 (&kring)[RING][KS],
+__device__ __forceinline__ void wave_main(const WaveCtx& w, Tile16 (&E)[Cfg<NRT>::PAIRS], u32x4 (&kring)[RING][KS],
                                           CUR cur, NEXT next, STAGE stage_next, bool more) {
   constexpr int NP = Cfg<NRT>::PAIRS, KT = Cfg<NRT>::KT;
-  constexpr int AHEAD = 2;                 // Q operands requested from LDS this many MFMAs ahead
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto q_addr = [&](int n) {               // operand of MFMA n = pair * KS + step
-    const int rt = (n / KS) % NRT, t = n % KS;
-    return w.q_lane + rt * 32 * QROWB + t * 32;
+  constexpr int AHEAD = 2;                 // Q operands requested from LDS this many ahead (each is used for two products)
+  constexpr int OPS = 2 * STEPS;           // of a pair: two row halves per step
+  auto q_operand = [&](int n) {            // number n % OPS of pair n / OPS
+    const int rt = (n / OPS) % NRT, u = n % OPS / 2, r = n % 2;
+    return *reinterpret_cast<const u32x4*>(w.q_lane + (rt * 32 + r * 16) * QROWB + u * 64);
   };
-  bf16x8 ring[AHEAD];
+  u32x4 ring[AHEAD];
 #pragma unroll
-  for (int n = 0; n < AHEAD; ++n) ring[n] = lds_operand(q_addr(n));
+  for (int n = 0; n < AHEAD; ++n) ring[n] = q_operand(n);
   {
     static_assert(KT >= 2, "the staged tile is tile 1");
     stage_wait();
     int l = w.lane;
     asm volatile("" : "+v"(l));
 #pragma unroll
-    for (int t = 0; t < KS; ++t) kring[1][t] = lds_operand(w.stage + t * 1024 + l * 16);
+    for (int t = 0; t < KS; ++t) kring[1][t] = *reinterpret_cast<const u32x4*>(w.stage + t * 1024 + l * 16);
   }
 #pragma unroll
-  for (int kt = 2; kt < RING && kt < KT; ++kt) {
-    const KeySource src = cur(kt);
-    const int v = tile_offset(src.row0, w.lane, w.row_bytes);
-#pragma unroll
-    for (int t = 0; t < KS; ++t) kring[kt][t] = load_operand(src, v, t);
-  }
+  for (int kt = 2; kt < RING && kt < KT; ++kt) load_tile(kring[kt], cur(kt), w.lane, w.row_bytes);
 
   static_for<0, NP>([&](auto I) {
     constexpr int i = decltype(I)::value;
     constexpr int kt = i / NRT, rt = i % NRT;
+    // The chains start from zero; in tiles with a key that some row does not see (wave-uniform
+    // test) from -inf where a key is not visible to a row.  The two cases are separate
+    // instructions so that the common one needs no copy of its start value; the bound goes
+    // through an opaque copy so that the start vectors of all pairs are not computed ahead and
+    // kept alive.
+    const int t0 = w.key0 + (Cfg<NRT>::ROTATE ? (kt + w.rot) % KT : kt) * 32;
+    int qmin_here = __builtin_amdgcn_readfirstlane(w.qmin);
+    asm volatile("" : "+s"(qmin_here));
+    const bool masked = t0 + 31 > qmin_here;
 #pragma unroll
-    for (int t = 0; t < KS; ++t) {
-      const int n = i * KS + t;
-      if (t == 0) {
-        // The chain starts from zero; in tiles with a key that some row does not see (wave-uniform
-        // test) from -inf where a key is not visible to a row.  The two cases are separate
-        // instructions so that the common one needs no copy of its start value; the bound goes
-        // through an opaque copy so that the start vectors of all pairs are not computed ahead and
-        // kept alive.
-        const int t0 = w.key0 + (Cfg<NRT>::ROTATE ? (kt + w.rot) % KT : kt) * 32;
-        int qmin_here = __builtin_amdgcn_readfirstlane(w.qmin);
-        asm volatile("" : "+s"(qmin_here));
-        if (t0 + 31 > qmin_here) {
-          int hf_here = w.hf, n32_here = w.n32;
-          asm volatile("" : "+v"(hf_here), "+v"(n32_here));
-          const int key = t0 + n32_here;                               // this lane's key
-          f32x16 start = zero;
+    for (int o = 0; o < OPS; ++o) {
+      const int n = i * OPS + o, u = o / 2, r = o % 2;
+      const u32x4 q = ring[n % AHEAD];
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      if (u == 0 && masked) {
+        int grp_here = w.grp, n16_here = w.n16;
+        asm volatile("" : "+v"(grp_here), "+v"(n16_here));
+        const i32x4 lv = *reinterpret_cast<const i32x4*>(w.last + rt * 32 + 16 * r + 4 * grp_here);
 #pragma unroll
-          for (int gq = 0; gq < 4; ++gq) {                             // rows 8*gq + 4*hf .. +3 of the tile
-            const i32x4 lv = *reinterpret_cast<const i32x4*>(w.last + rt * 32 + 8 * gq + 4 * hf_here);
+        for (int s = 0; s < 2; ++s) {
+          f32x4 start = zero;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (key > lv[j]) start[4 * gq + j] = -INFINITY;
-          }
-          E[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[n % AHEAD], kring[kt % RING][0], start, 0, 0, 0);
-        } else {
-          E[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[n % AHEAD], kring[kt % RING][0], zero, 0, 0, 0);
+          for (int j = 0; j < 4; ++j)
+            if (t0 + 16 * s + n16_here > lv[j]) start[j] = -INFINITY;
+          E[i].t[s][r] = mfma16(q, kring[kt % RING][s * STEPS], start);
         }
       } else {
-        E[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[n % AHEAD], kring[kt % RING][t], E[i], 0, 0, 0);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) E[i].t[s][r] = mfma16(q, kring[kt % RING][s * STEPS + u], u == 0 ? zero : E[i].t[s][r]);
       }
-      if (n + AHEAD < NP * KS) ring[n % AHEAD] = lds_operand(q_addr(n + AHEAD));
+      if (n + AHEAD < NP * OPS) ring[n % AHEAD] = q_operand(n + AHEAD);
       LAQ_SCHED_FENCE();
     }
     if constexpr (rt == NRT - 1) {
@@ -318,17 +303,9 @@ __device__ __forceinline__ void wave_main(const WaveCtx& w, f32x16 (&E)[Cfg<NRT>
       // first tile of the next head (slot 0, once no tile of this head needs it any more)
       constexpr int after = kt + RING;
       if constexpr (after < KT) {
-        const KeySource src = cur(after);
-        const int v = tile_offset(src.row0, w.lane, w.row_bytes);
-#pragma unroll
-        for (int t = 0; t < KS; ++t) kring[kt % RING][t] = load_operand(src, v, t);
+        load_tile(kring[kt % RING], cur(after), w.lane, w.row_bytes);
       } else if constexpr (kt % RING == 0) {
-        if (more) {
-          const KeySource src = next(0);
-          const int v = tile_offset(src.row0, w.lane, w.row_bytes);
-#pragma unroll
-          for (int t = 0; t < KS; ++t) kring[0][t] = load_operand(src, v, t);
-        }
+        if (more) load_tile(kring[0], next(0), w.lane, w.row_bytes);
       }
     }
   });
@@ -389,8 +366,8 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
   float* zt = reinterpret_cast<float*>(smem + S::OFF_ZT) + wave * 32 * ZT_STRIDE;
 
   WaveCtx w;
-  w.lane = lane; w.hf = lane >> 5; w.n32 = lane & 31;
-  w.q_lane = q_lds + w.n32 * QROWB + w.hf * 16;
+  w.lane = lane; w.grp = lane >> 4; w.n16 = lane & 15;
+  w.q_lane = q_lds + w.n16 * QROWB + w.grp * 16;
   w.key0 = member * KEYS_PER_BLOCK + wave * KEYS_PER_WAVE;
   // (the members of a team start at different tiles of their ranges, so that the addresses the
   // device is asked for at the same time do not all lie the same distance into a 32 KiB piece: about
@@ -404,8 +381,8 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
   if (tid < 2 * MAX_HALF) raw_lds[tid < MAX_HALF ? tid - MAX_HALF : KEYS_PER_BLOCK + tid - MAX_HALF] = 0.f;
   if (tid == 0) gave_up[0] = 0;
 
-  f32x16 E[NP];
-  bf16x8 kring[RING][KS];
+  Tile16 E[NP];
+  u32x4 kring[RING][KS];
 
   // (thread and lane numbers go through opaque copies in the steps outside the matrix loop: the
   // addresses derived from them are then computed where they are used, not ahead of the loop over
@@ -504,20 +481,18 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
   auto words_of = [&](int nth) { return sy.stats + ((size_t)(team * 2 + (nth & 1)) * T) * ROWS; };
   auto tag_of = [](int nth) { return (((unsigned)nth >> 1) & 1u) ^ 1u; };
 
-  // A value per (row of tile rt, key of this wave) in v[16] -> per row, combined over the wave's 32
-  // keys with `op`: written [row][key] to the wave's LDS tile, read back by rows (a wave's LDS
-  // operations execute in order), two lanes per row.  Returns the row's value in lanes hf == 0.
-  auto over_keys = [&](const f32x16& v, auto op, int n32, int hf) {
+  // A value per (row of tile rt, key of this wave) in v[2] (16 keys; row halves) -> per row, combined over the 16 lanes with
+  // `op`: written [row][key] to the wave's LDS tile, read back by rows (a wave's LDS
+  // operations execute in order), two lanes per row.  Returns the value of row lane % 32.
+  auto over_keys = [&](const f32x4 (&v)[2], auto op, int lane_) {
+    float* to = zt + (lane_ >> 4) * 4 * ZT_STRIDE + (lane_ & 15);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) zt[acc_row(i, hf) * ZT_STRIDE + n32] = v[i];
-    float r = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const f32x4 x = *reinterpret_cast<const f32x4*>(zt + n32 * ZT_STRIDE + hf * 16 + 4 * j);
-      const float part = op(op(x[0], x[1]), op(x[2], x[3]));
-      r = j == 0 ? part : op(r, part);
-    }
-    return op(r, __shfl_xor(r, 32));
+    for (int e = 0; e < 8; ++e) to[(16 * (e >> 2) + (e & 3)) * ZT_STRIDE] = v[e >> 2][e & 3];
+    const float* from = zt + (lane_ & 31) * ZT_STRIDE + (lane_ >> 5) * 8;
+    const f32x4 x = *reinterpret_cast<const f32x4*>(from), y = *reinterpret_cast<const f32x4*>(from + 4);
+    const float part = op(op(op(x[0], x[1]), op(x[2], x[3])), op(op(y[0], y[1]), op(y[2], y[3])));
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(part), __float_as_uint(part), false, false);
+    return op(__uint_as_float(h[0]), __uint_as_float(h[1]));
   };
 
   // Everybody folds the statistics of the team in the same fixed order; thread (sub, rp) folds the
@@ -632,41 +607,46 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
   // stored for it, this cost registers that step B needs: 262 us became 292 and 267.)
   auto score_again = [&](const uint16_t* base_, int hg_, int kp) {
     const KeySource src = key_source(tile_at(base_, S::ROTATE ? (kp - w.rot + KT) % KT : kp), lay.row_bytes);
-    const int lane_ = opaque(threadIdx.x) & 63, hf_ = lane_ >> 5, n32_ = lane_ & 31;
+    const int lane_ = opaque(threadIdx.x) & 63, grp_ = lane_ >> 4, n16_ = lane_ & 15;
     const int v = tile_offset(src.row0, lane_, lay.row_bytes);
-    const int key = w.key0 + kp * 32 + n32_;
+    const int key = w.key0 + kp * 32 + n16_;
     const int mine = lane_ % ROWS;         // (the lanes hold a row's c each)
-    float M = NEG_BIG, Z = 0.f, sum = 0.f;
+    float M = NEG_BIG, Z = 0.f, sum0 = 0.f, sum1 = 0.f;
 #pragma unroll 1
     for (int s2 = 0; s2 < S::NSUB; ++s2) merge_stat(M, Z, fold_lds[s2 * ROWS + mine]);
     const float c = mine < g.R ? M + __builtin_amdgcn_logf(Z) : INFINITY;
 #pragma unroll 1
-    for (int rt = 0; rt < NRT; ++rt) {
-      f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      const uint16_t* row = q + ((size_t)hg_ * g.R + min(rt * 32 + n32_, g.R - 1)) * D + hf_ * 8;
+    for (int r16 = 0; r16 < 2 * NRT; ++r16) {
+      f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+      const uint16_t* row = q + ((size_t)hg_ * g.R + min(r16 * 16 + n16_, g.R - 1)) * D + grp_ * 8;
 #pragma unroll 1
-      for (int t = 0; t < KS; ++t)
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(row + t * 16), load_operand(src, v, t), s, 0, 0, 0);
+      for (int u = 0; u < STEPS; ++u) {
+        const u32x4 x = *reinterpret_cast<const u32x4*>(row + u * 32);
+        s[0] = mfma16(x, load_operand(src, v, u), s[0]);
+        s[1] = mfma16(x, load_operand(src, v + 16 * lay.row_bytes, u), s[1]);
+      }
 #pragma unroll 1
-      for (int i = 0; i < 16; ++i) {
-        const int r = rt * 32 + acc_row(i, hf_);
+      for (int i = 0; i < 4; ++i) {
+        const int r = r16 * 16 + 4 * grp_ + i;
         const float cr = __shfl(c, r);     // (all lanes)
-        const float x = key > last_lds[r] ? -INFINITY : fmaf(s[0], g.scale2, -cr);
-        sum += x < -126.f ? __builtin_amdgcn_exp2f(x + 64.f) * 0x1p-64f : __builtin_amdgcn_exp2f(x);
-        s = __builtin_shufflevector(s, s, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 0);
+        auto term = [&](float d, int j) {
+          const float x = j > last_lds[r] ? -INFINITY : fmaf(d, g.scale2, -cr);
+          return x < -126.f ? __builtin_amdgcn_exp2f(x + 64.f) * 0x1p-64f : __builtin_amdgcn_exp2f(x);
+        };
+        sum0 += term(s[0][0], key);
+        sum1 += term(s[1][0], key + 16);
+        s[0] = __builtin_shufflevector(s[0], s[0], 1, 2, 3, 0);
+        s[1] = __builtin_shufflevector(s[1], s[1], 1, 2, 3, 0);
       }
     }
-    return sum + __shfl_xor(sum, 32);
+    return over_groups(sum0, sum1, [](float x, float y) { return x + y; });
   };
 
   // ---- the team's heads -----------------------------------------------------------------------
   int hg = team;
   const uint16_t* base = wave_base(hg);
   {
-    const KeySource src = key_source(tile_at(base, 0), lay.row_bytes);
-    const int v = tile_offset(src.row0, lane, lay.row_bytes);
-#pragma unroll
-    for (int t = 0; t < KS; ++t) kring[0][t] = load_operand(src, v, t);
+    load_tile(kring[0], key_source(tile_at(base, 0), lay.row_bytes), lane, lay.row_bytes);
     stage_tile(tile_at(base, 1), lay.row_bytes, lane, lds_address(w.stage));
     u32x4 qv[S::Q_PER_THREAD];
     fetch_q(hg, qv);
@@ -688,15 +668,17 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
     if constexpr (S::ZT_IN_Q) lds_barrier();                  // the transposition tiles lie inside Q: every wave is done with it
     // C: the rows' maxima over this workgroup's keys ...
     __builtin_amdgcn_s_setprio(PRIO_CHAIN);
-    const int n32c = opaque(w.n32), hfc = opaque(w.hf);
+    const int lane_c = opaque(lane), n32c = lane_c & 31, hfc = lane_c >> 5, grp_c = lane_c >> 4;
     static_for<0, NRT>([&](auto RT) {
       constexpr int rt = decltype(RT)::value;
-      f32x16 mx = E[rt];
+      f32x4 mx[2] = {E[rt].t[0][0], E[rt].t[0][1]};
 #pragma unroll
-      for (int kt = 1; kt < KT; ++kt)
+      for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], E[kt * NRT + rt][i]);
-      const float m = over_keys(mx, [](float a, float b) { return fmaxf(a, b); }, n32c, hfc);
+        for (int sr = kt == 0 ? 2 : 0; sr < 4; ++sr)     // (key half, row half)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) mx[sr & 1][i] = fmaxf(mx[sr & 1][i], E[kt * NRT + rt].t[sr >> 1][sr & 1][i]);
+      const float m = over_keys(mx, [](float a, float b) { return fmaxf(a, b); }, lane_c);
       if (hfc == 0) stat_lds[wave * ROWS + rt * 32 + n32c] = m;
     });
     lds_barrier();                         // every wave is done with this head's Q
@@ -715,25 +697,25 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
     __builtin_amdgcn_s_setprio(PRIO_BULK);
     static_for<0, NRT>([&](auto RT) {
       constexpr int rt = decltype(RT)::value;
-      f32x4 mv[4];
+      f32x4 mv[2], zs[2];
 #pragma unroll
-      for (int gq = 0; gq < 4; ++gq) mv[gq] = *reinterpret_cast<const f32x4*>(ref_lds + rt * 32 + 8 * gq + 4 * hfc);
-      f32x16 zs;
+      for (int r = 0; r < 2; ++r) mv[r] = *reinterpret_cast<const f32x4*>(ref_lds + rt * 32 + 16 * r + 4 * grp_c);
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) {
 #pragma unroll
-        for (int h = 0; h < 4; ++h) {      // four rows at a time: few values live next to the stored tiles
+        for (int sr = 0; sr < 4; ++sr) {   // four rows at a time: few values live next to the stored tiles
+          f32x4& e = E[kt * NRT + rt].t[sr >> 1][sr & 1];
           float x[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) x[i] = fmaf(E[kt * NRT + rt][4 * h + i], g.scale2, -mv[h][i]);
+          for (int i = 0; i < 4; ++i) x[i] = fmaf(e[i], g.scale2, -mv[sr & 1][i]);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) E[kt * NRT + rt][4 * h + i] = __builtin_amdgcn_exp2f(x[i]);
+          for (int i = 0; i < 4; ++i) e[i] = __builtin_amdgcn_exp2f(x[i]);
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            zs[4 * h + i] = kt == 0 ? E[kt * NRT + rt][4 * h + i] : zs[4 * h + i] + E[kt * NRT + rt][4 * h + i];
+          for (int i = 0; i < 4; ++i) zs[sr & 1][i] = kt == 0 && sr < 2 ? e[i] : zs[sr & 1][i] + e[i];
+          LAQ_SCHED_FENCE();               // (32 rows: 5 spills without)
         }
       }
-      const float z = over_keys(zs, [](float a, float b) { return a + b; }, n32c, hfc);
+      const float z = over_keys(zs, [](float a, float b) { return a + b; }, lane_c);
       if (hfc == 0) stat_lds[wave * ROWS + rt * 32 + n32c] = z;
     });
     __builtin_amdgcn_s_setprio(PRIO_CHAIN);                  // (until step B of the next head)
@@ -758,28 +740,29 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
     // F: this wave's keys
     bool tiny = false;
     {
-      const int n32f = opaque(w.n32), hff = opaque(w.hf);
-      float part[KT];
+      const int grp_f = opaque(w.grp), n16_f = opaque(w.n16);
+      float part[KT][2];
 #pragma unroll
-      for (int kt = 0; kt < KT; ++kt) part[kt] = 0.f;
+      for (int kt = 0; kt < KT; ++kt) part[kt][0] = part[kt][1] = 0.f;
       static_for<0, NRT>([&](auto RT) {
         constexpr int rt = decltype(RT)::value;
-        f32x4 wv[4];
+        f32x4 wv[2];
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) wv[gq] = *reinterpret_cast<const f32x4*>(wts_lds + rt * 32 + 8 * gq + 4 * hff);
+        for (int r = 0; r < 2; ++r) wv[r] = *reinterpret_cast<const f32x4*>(wts_lds + rt * 32 + 16 * r + 4 * grp_f);
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) part[kt] = fmaf(E[kt * NRT + rt][i], wv[i >> 2][i & 3], part[kt]);
+          for (int sr = 0; sr < 4; ++sr)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[kt][sr >> 1] = fmaf(E[kt * NRT + rt].t[sr >> 1][sr & 1][i], wv[sr & 1][i], part[kt][sr >> 1]);
       });
       float least = 1.f;
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) {
-        const float tot = part[kt] + __shfl_xor(part[kt], 32);
+        const float tot = over_groups(part[kt][0], part[kt][1], [](float x, float y) { return x + y; });
         if constexpr (S::AGAIN) least = fminf(least, tot);
-        const int kp = S::ROTATE ? (kt + w.rot) % KT : kt;
-        const int j = w.key0 + kp * 32 + n32f;
-        if (hff == 0) raw_lds[wave * KEYS_PER_WAVE + kp * 32 + n32f] = j < g.L ? tot : 0.f;
+        const int kp = S::ROTATE ? (kt + w.rot) % KT : kt, at = kp * 32 + (grp_f >> 1 << 4) + n16_f;
+        if ((grp_f & 1) == 0) raw_lds[wave * KEYS_PER_WAVE + at] = w.key0 + at < g.L ? tot : 0.f;
       }
       if constexpr (S::AGAIN) tiny = __any(least < TINY);
     }
@@ -795,7 +778,8 @@ __global__ __launch_bounds__(F_THREADS, 2) void fused_kernel(ScoreGeom g, Window
         const int j = w.key0 + kp * 32 + (l & 31);
         if (!__any(mine[kp * 32 + (l & 31)] < TINY && j <= furthest)) continue;
         const float tot = score_again(base, hg, kp);
-        if (l < 32 && j < g.L) mine[kp * 32 + l] = tot;
+        const int at = kp * 32 + (l >> 5 << 4) + (l & 15);
+        if ((l & 16) == 0 && w.key0 + at < g.L) mine[at] = tot;
       }
     }
     if (!more || __builtin_amdgcn_readfirstlane(gave_up[0])) {
