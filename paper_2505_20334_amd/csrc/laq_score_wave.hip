@@ -35,6 +35,7 @@
 // d = 96, 128 rows, 368 x 1255 264 : 141.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "laq_internal.h"
 #include "laq_products.h"
@@ -134,7 +135,8 @@ template <typename T, int NP, bool FULL> struct Operand {
       }
   }
   // against the score rows at `lds` (this lane's row and piece); `steps` of 64 bytes a row has, `plane` bytes between its parts
-  template <bool KEYS_AS_ROWS>
+  // RH: row halves, 1 where the tile's last 16 rows are beyond R
+  template <bool KEYS_AS_ROWS, int RH>
   __device__ __forceinline__ Tile16 product(const char* lds, int stride, int plane, int steps) const {
     Tile16 acc;
     acc.clear();
@@ -147,14 +149,14 @@ template <typename T, int NP, bool FULL> struct Operand {
 #pragma unroll
         for (int pl = 0; pl < 3; ++pl) {
           q[0][pl] = *reinterpret_cast<const u32x4*>(lds + pl * plane + u * 64);
-          q[1][pl] = *reinterpret_cast<const u32x4*>(lds1 + pl * plane + u * 64);
+          if (RH > 1) q[1][pl] = *reinterpret_cast<const u32x4*>(lds1 + pl * plane + u * 64);
         }
       };
       auto add = [&](Tile16& to, int u, int key_part, int row_part) {
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
-          for (int r = 0; r < 2; ++r) to.t[s][r] = mm16<KEYS_AS_ROWS>(v[s][3 * u + key_part], q[r][row_part], to.t[s][r]);
+          for (int r = 0; r < RH; ++r) to.t[s][r] = mm16<KEYS_AS_ROWS>(v[s][3 * u + key_part], q[r][row_part], to.t[s][r]);
       };
 #pragma unroll
       for (int u = 0; u < STEPS; ++u) {
@@ -172,17 +174,18 @@ template <typename T, int NP, bool FULL> struct Operand {
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int r = 0; r < 2; ++r) acc.t[s][r] += low.t[s][r];
+        for (int r = 0; r < RH; ++r) acc.t[s][r] += low.t[s][r];
     } else {
 #pragma unroll
       for (int u = 0; u < STEPS; ++u) {
         if (FULL || u < steps) {
-          const u32x4 q0 = *reinterpret_cast<const u32x4*>(lds + u * 64), q1 = *reinterpret_cast<const u32x4*>(lds1 + u * 64);
+          u32x4 q[RH];
 #pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            acc.t[s][0] = mm16<KEYS_AS_ROWS>(v[s][u], q0, acc.t[s][0]);
-            acc.t[s][1] = mm16<KEYS_AS_ROWS>(v[s][u], q1, acc.t[s][1]);
-          }
+          for (int r = 0; r < RH; ++r) q[r] = *reinterpret_cast<const u32x4*>((r ? lds1 : lds) + u * 64);
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int r = 0; r < RH; ++r) acc.t[s][r] = mm16<KEYS_AS_ROWS>(v[s][u], q[r], acc.t[s][r]);
         }
         if (u % 2 == 1) __builtin_amdgcn_sched_barrier(0);                 // (at most four operands of Q requested ahead: registers)
       }
@@ -227,6 +230,14 @@ struct WavePlan {
 // spill 13 registers in the second kernel; 64 rows, 192 heads x 8001 152 us, with four 134.5.)
 template <typename T, int NP> constexpr int waves_per_simd() { return is_f32(T()) ? (NP <= 8 ? 3 : 2) : (NP <= 4 ? 5 : NP <= 8 ? 4 : 2); }
 
+// Row tiles, of those staged from rt0 on, that are taken whole.  fp32 leaves the second half of a last one out where it has no rows: laq_evict, us, 112
+// rows, 48 heads x 9000 keys 221 : 209.  bf16 does not: its passes are not bound by products, and the code for it makes others slower (112 rows, 112 x 20123
+// 292 : 290, but 128 rows, 256 x 32768 912 : 930, d = 64, 32 rows, 320 x 9000 181 : 190; fp32 of
+// head sizes without a variant of their own, whose kernels spill: d = 104, 64 rows, 96 x 5000 141.5 : 145).
+template <bool HALVES> __device__ __forceinline__ int whole_tiles(const ScoreGeom& g, int rt0, int ntile) {
+  return HALVES ? min(ntile, (g.R - rt0 * 32 + 15) / 32) : ntile;
+}
+
 // A wave's sums of exponentials refer to a number near the row's maximum, not to the maximum itself: HEADROOM above that of the first
 // tile, and moved only where a tile's sum reaches OUTGROWN of it (then, and where a row does not see all keys of a tile, or a sum is no
 // number, the maximum of the tile is made).  The terms that count have exponents between -8 and 7, as with a maximum that most keys stay
@@ -235,7 +246,8 @@ template <typename T, int NP> constexpr int waves_per_simd() { return is_f32(T()
 // the power that memory and matrix cores take.  Whole numbers, see above.
 constexpr float HEADROOM = 3.f, OUTGROWN = 128.f;
 // exp2(s * scale - m) of a lane's two rows over the tile's keys: eight of them here, the others in the lanes of the same number modulo 16.
-// Lanes 0 .. 31 end with the sum of row n16, the others with that of row 16 + n16.
+// Lanes 0 .. 31 end with the sum of row n16, the others with that of row 16 + n16 (RH 1: of row n16 too).
+template <int RH>
 __device__ __forceinline__ float tile_sum(const Tile16& a, float scale, float m0, float m1) {
   float z0 = 0.f, z1 = 0.f;
 #pragma unroll
@@ -243,9 +255,9 @@ __device__ __forceinline__ float tile_sum(const Tile16& a, float scale, float m0
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       z0 += __builtin_amdgcn_exp2f(fmaf(a.t[s][0][i], scale, -m0));
-      z1 += __builtin_amdgcn_exp2f(fmaf(a.t[s][1][i], scale, -m1));
+      if (RH > 1) z1 += __builtin_amdgcn_exp2f(fmaf(a.t[s][1][i], scale, -m1));
     }
-  return over_groups(z0, z1, [](float x, float y) { return x + y; });
+  return over_groups(z0, RH > 1 ? z1 : z0, [](float x, float y) { return x + y; });
 }
 
 // Pass 1: part[head][segment][row] = (m, z) of a score row over the segment's visible keys, in log2 units.
@@ -256,6 +268,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
   extern __shared__ __align__(16) char smem[];
   const int group = blockIdx.x / pl.segs, seg = blockIdx.x - group * pl.segs;
   const int rt0 = group * pl.group_tiles, ntile = min(pl.group_tiles, g.Rpad / 32 - rt0);
+  const int whole = whole_tiles<is_f32(T()) && FULL>(g, rt0, ntile);
   const Wave<T, NP, FULL> w(g, lay, q, k, seg, pl.seg_blocks);
   const RowScale row_scale = pl.row_scale;
   u32x4 key[NP];
@@ -268,12 +281,12 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
     const bool plain = key0 + 31 <= g.qmin;              // every row sees every key
     const char* rows = smem + w.n16 * w.stride + w.grp * 16;
     float2* mine = stat + w.wave * 32 + w.n16;           // this lane's first row; the second: 16 further on
-    const int own = w.grp >> 1 << 4;                     // the one whose sum it ends with
-#pragma unroll 1
-    for (int rt = 0; rt < ntile; ++rt) {
-      const float old0 = mine[0].x, old1 = mine[16].x, old_z = mine[own].y;
-      Tile16 a = op.template product<true>(rows, w.stride, w.plane, w.plane / 64);
-      float z = plain && key0 != w.first ? tile_sum(a, row_scale.scale2, old0, old1) : INFINITY;
+    auto tile = [&](auto row_halves, int rt) {
+      constexpr int RH = decltype(row_halves)::value;
+      const int own = RH > 1 ? w.grp >> 1 << 4 : 0;      // the one whose sum it ends with
+      const float old0 = mine[0].x, old1 = RH > 1 ? mine[16].x : old0, old_z = mine[own].y;
+      Tile16 a = op.template product<true, RH>(rows, w.stride, w.plane, w.plane / 64);
+      float z = plain && key0 != w.first ? tile_sum<RH>(a, row_scale.scale2, old0, old1) : INFINITY;
       if (__builtin_expect(!__any(!(z <= OUTGROWN)), 1)) {
         mine[own].y = old_z + z;
       } else {
@@ -284,7 +297,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
             int n = threadIdx.x & 63;
             asm volatile("" : "+v"(n));                  // (computed here: the common case has no registers for it)
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
+            for (int r = 0; r < RH; ++r) {
               const int row = (rt0 + rt) * 32 + 16 * r + (n & 15), last = last_visible_key(g, qp, min(row, g.R - 1) % g.W) - key0 - 4 * (n >> 4);
 #pragma unroll
               for (int e = 0; e < 8; ++e)
@@ -292,17 +305,17 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
             }
           }
           m0 = a.t[0][0][0];
-          m1 = a.t[0][1][0];
+          m1 = a.t[0][RH - 1][0];
 #pragma unroll
           for (int e = 1; e < 8; ++e) {
             m0 = fmaxf(m0, a.t[e >> 2][0][e & 3]);
-            m1 = fmaxf(m1, a.t[e >> 2][1][e & 3]);
+            m1 = fmaxf(m1, a.t[e >> 2][RH - 1][e & 3]);
           }
           const float m = over_groups(m0, m1, [](float x, float y) { return fmaxf(x, y); });
           const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
           m0 = fmaxf(old0, __builtin_ceilf(fmaf(__uint_as_float(mh[0]), scale, HEADROOM)));      // (the logit scale is positive)
           m1 = fmaxf(old1, __builtin_ceilf(fmaf(__uint_as_float(mh[1]), scale, HEADROOM)));
-          z = tile_sum(a, scale, m0, m1);
+          z = tile_sum<RH>(a, scale, m0, m1);
           if (!is_f32(T()) || again || __builtin_expect(!__any(z != z), 1)) break;
           const char *kr[2], *qr[2];
           w.key_rows(kr, g, lay, key0);
@@ -313,9 +326,14 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
         const float m = own ? m1 : m0, old = own ? old1 : old0;
         mine[own] = make_float2(m, fmaf(old_z, __builtin_amdgcn_exp2f(old - m), z));
       }
+    };
+#pragma unroll 1
+    for (int rt = 0; rt < whole; ++rt) {
+      tile(std::integral_constant<int, 2>{}, rt);
       rows += 32 * w.stride;
       mine += WAVES * 32;
     }
+    if (is_f32(T()) && FULL && whole < ntile) tile(std::integral_constant<int, 1>{}, whole);
   };
   if (w.some) walk_tiles<T, NP, FULL>(key, w.first, w.last_tile, [&](u32x4 (&x)[NP], int key0) { w.load(x, g, lay, key0); }, work);
   __syncthreads();
@@ -381,7 +399,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
   u32x4 key[NP];
 #pragma unroll 1
   for (int rt0 = 0; rt0 < g.Rpad / 32; rt0 += pl.group_tiles) {
-    const int ntile = min(pl.group_tiles, g.Rpad / 32 - rt0);
+    const int ntile = min(pl.group_tiles, g.Rpad / 32 - rt0), whole = whole_tiles<is_f32(T()) && FULL>(g, rt0, ntile);
     if (w.some) w.load(key, g, lay, w.first);
     if (rt0 > 0) __syncthreads();
     stage_rows16<T, FULL, THREADS>(smem, w.head_rows, w.row_bytes, w.plane, w.stride, g.R, rt0 * 32, ntile * 32, row_scale.shift);
@@ -401,24 +419,26 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
     const char* rows = smem + w.n16 * w.stride + w.grp * 16;
     auto work = [&](const Operand<T, NP, FULL>& op, int key0) {
       const bool plain = key0 + 31 <= g.qmin;
-      auto masked = [&](Tile16& a, int rt) {
+      auto masked = [&](Tile16& a, int rt, int row_halves) {
         if (!plain) {
 #pragma unroll
-          for (int r = 0; r < 2; ++r) {
+          for (int r = 0; r < row_halves; ++r) {
             const i32x4 lv = *reinterpret_cast<const i32x4*>(last + rt * 32 + 16 * r + 4 * w.grp);
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 8; ++e) {
               if (key0 + 16 * (e >> 2) + w.n16 > lv[e & 3]) a.t[e >> 2][r][e & 3] = -INFINITY;
+              if (is_f32(T()) && FULL) __builtin_amdgcn_sched_barrier(0);    // (one comparison at a time: registers)
+            }
           }
         }
       };
       float sum0 = 0.f, sum1 = 0.f;                      // of keys n16 and 16 + n16 of the tile
-#pragma unroll 1
-      for (int rt = 0; rt < ntile; ++rt) {
-        Tile16 a = op.template product<false>(rows + rt * 32 * w.stride, w.stride, w.plane, w.plane / 64);
-        masked(a, rt);
+      auto tile = [&](auto row_halves, int rt) {
+        constexpr int RH = decltype(row_halves)::value;
+        Tile16 a = op.template product<false, RH>(rows + rt * 32 * w.stride, w.stride, w.plane, w.plane / 64);
+        masked(a, rt, RH);
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
+        for (int r = 0; r < RH; ++r) {
           const f32x4 m = *reinterpret_cast<const f32x4*>(rowm + rt * 32 + 16 * r + 4 * w.grp);
           const f32x4 wt = *reinterpret_cast<const f32x4*>(roww + rt * 32 + 16 * r + 4 * w.grp);
 #pragma unroll
@@ -427,7 +447,10 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
             sum1 = fmaf(__builtin_amdgcn_exp2f(fmaf(a.t[1][r][i], row_scale.scale2, -m[i])), wt[i], sum1);
           }
         }
-      }
+      };
+#pragma unroll 1
+      for (int rt = 0; rt < whole; ++rt) tile(std::integral_constant<int, 2>{}, rt);
+      if (is_f32(T()) && FULL && whole < ntile) tile(std::integral_constant<int, 1>{}, whole);
       const auto plus = [](float x, float y) { return x + y; };
       float both = over_groups(sum0, sum1, plus);
       const int j = key0 + (w.grp >> 1 << 4) + w.n16;    // the key whose sum this lane ends with
@@ -442,9 +465,9 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
             w.score_rows(qr, g, rt0 + rt);
             a = product16_f32<false>(kr, qr, w.grp, w.row_bytes);
           } else {
-            a = op.template product<false>(rows + rt * 32 * w.stride, w.stride, w.plane, w.plane / 64);
+            a = op.template product<false, 2>(rows + rt * 32 * w.stride, w.stride, w.plane, w.plane / 64);
           }
-          masked(a, rt);
+          masked(a, rt, 2);
 #pragma unroll 1
           for (int e = 0; e < 8; ++e) {                  // rows 16 (e / 4) + 4 grp + e % 4
             const int row = rt * 32 + 16 * (e >> 2) + 4 * w.grp + (e & 3);
