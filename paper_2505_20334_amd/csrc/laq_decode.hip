@@ -33,46 +33,12 @@ namespace {
 constexpr float DEC_NEG_BIG = -1.0e30f;
 constexpr int DEC_THREADS = 256, DEC_WAVES = DEC_THREADS / 64;
 
-// lane selections within 16 lanes
-template <int CTRL>
-__device__ __forceinline__ float lane_select(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
 template <int FROM, int TO, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
   if constexpr (FROM < TO) {
     f(std::integral_constant<int, FROM>{});
     static_for<FROM + 1, TO>(f);
   }
-}
-
-// One step of group_reduce: lanes whose BIT differs (lane selection CTRL) exchange half of N values, or, with
-// one value left, add them.
-template <int CTRL, int BIT, int N, int NV>
-__device__ __forceinline__ void reduce_step(float (&x)[NV], int lane) {
-  if constexpr (N > 1) {
-    const bool upper = lane & BIT;
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) {
-      const float lo = x[i], hi = x[i + N / 2];
-      const float keep = upper ? hi : lo, give = upper ? lo : hi;
-      x[i] = keep + lane_select<CTRL>(give);
-    }
-  } else {
-    x[0] += lane_select<CTRL>(x[0]);
-  }
-}
-// Sums over the RP (8 or 16) lanes of a group for NV values: lane l of the group ends with value
-// l * NV / RP (NV <= RP).
-template <int RP, int NV>
-__device__ __forceinline__ float group_reduce(float (&x)[NV], int lane) {
-  static_assert(NV <= RP && (NV & (NV - 1)) == 0, "");
-  constexpr int N8 = RP == 16 ? (NV > 1 ? NV / 2 : 1) : NV, N4 = N8 > 1 ? N8 / 2 : 1, N2 = N4 > 1 ? N4 / 2 : 1;
-  if constexpr (RP == 16) reduce_step<0x128, 8, NV>(x, lane);      // rotate by 8: lane ^ 8
-  reduce_step<0x141, 4, N8>(x, lane);                              // mirror of 8 lanes: lane ^ 7
-  reduce_step<0x4E, 2, N4>(x, lane);                               // lane ^ 2
-  reduce_step<0xB1, 1, N2>(x, lane);                               // lane ^ 1
-  return x[0];
 }
 
 // Eight elements of a row that the launch reads once (ONCE: the caches need not keep it, 45 us instead of 50 for 275 MB) or

@@ -58,6 +58,46 @@ def test_short_heads(dtype, n, Hq, Hkv, d, L, W, pool, mode, budgets):
             assert torch.equal(kp[i], oracle.compact(k[i], want)) and torch.equal(vp[i], oracle.compact(v[i], want))
 
 
+# score rows either side of a half tile, a tile and what the registers keep, by variant: (dtype, d, heads, L)
+VARIANTS = [(F32, 64, 3, 500), (F32, 64, 80, 600), (F32, 128, 20, 333), (F32, 72, 20, 129), (BF16, 64, 3, 500), (BF16, 64, 80, 600), (BF16, 128, 3, 500),
+            (BF16, 128, 80, 600), (BF16, 128, 300, 70), (BF16, 96, 3, 97), (BF16, 256, 3, 300), (BF16, 200, 3, 65)]
+
+
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 64, 65, 128, 129])
+@pytest.mark.parametrize("dtype,d,heads,L", VARIANTS)
+def test_rows_kept_and_made_again(dtype, d, heads, L, rows):
+    """One query per window position and head: `rows` score rows.  Ordinary logits, scores below 2^-90 and an infinite key."""
+    import paper_2505_20334_amd as laq
+    print("case:", dtype, d, heads, L, rows, flush=True)
+    if laq.laq_score_kernel(1, heads, heads, d, L, rows, dtype, q_pos=[L] * rows, keep=0, whole_heads=True) != "whole-head":
+        pytest.skip("other kernels")
+    g = torch.Generator().manual_seed(rows + L)
+    q, k = torch.randn(1, heads, rows, d, generator=g), torch.randn(1, heads, L, d, generator=g)
+    pos = [L if w % 2 else (7 * w) % L for w in range(rows)]
+    for kind in ("ordinary", "small"):
+        if kind == "small":
+            q[..., 0] = 8.0 * d ** 0.5
+            k[..., ::5, 0] = -12.0
+        qq, kk = q.to(dtype), k.to(dtype)
+        got = laq.laq_score(qq.to(DEV), kk.to(DEV), 1, q_pos=pos, keep=0).cpu()
+        want, _, _, _ = oracle.evict(qq[0], kk[0], kk[0], 1, 1, q_pos=pos, keep=0)
+        if kind == "ordinary" or dtype == BF16:
+            check_scores(got[0], want, dtype, kind)
+        else:
+            # exponents up to 145 (log2 units), rounded at that size by each of the products that follow the large one (six a step of 32
+            # elements), by the scaling and by the subtraction
+            slack = 145 * (6 * -(-d // 32) + 2) * 2.0 ** -24 * 0.6931
+            err = (got[0].double() - want.double()).abs()
+            assert (err <= (RTOL[dtype] + slack) * want.double().abs() + 1e-30).all(), (err / want.double().abs()).max()
+    q, k = torch.randn(1, heads, rows, d, generator=g), torch.randn(1, heads, L, d, generator=g)
+    k[0, 0, 3] = float("inf")
+    q[0, 0] = -q[0, 0].abs() - 0.5            # the infinite key's logits are -inf: its scores are zero
+    got = laq.laq_score(q.to(dtype).to(DEV), k.to(dtype).to(DEV), 1, q_pos=[L] * rows, keep=0).cpu()
+    assert got[0, 0, 3] == 0.0 and torch.isfinite(got[0]).all()
+    # each row's probabilities: logits below 16, rounded by 2^-24 of that some twenty times
+    assert abs(got[0, 0].double().sum() - rows) <= 16 * 20 * 2.0 ** -24 * rows
+
+
 @pytest.mark.parametrize("L", [300, 512, 700])
 @pytest.mark.parametrize("values", ["equal", "two", "steps", "wide", "crowd"])
 def test_ranking_of_equal_and_crowded_scores(values, L):
