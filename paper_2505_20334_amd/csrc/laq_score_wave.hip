@@ -61,12 +61,12 @@ template <typename T, int NP, bool FULL> struct Wave {
   int first, last_tile, end;
   bool some;
 
-  __device__ __forceinline__ Wave(const ScoreGeom& g, const KvLayout& lay, const T* q, const T* k, int seg, int seg_blocks) {
-    const int lane = threadIdx.x & 63, head = blockIdx.y;
+  __device__ __forceinline__ Wave(const ScoreGeom& g, const KvLayout& lay, const T* q, const T* k, int inst_, int head, int seg, int seg_blocks) {
+    const int lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     grp = lane >> 4;
     n16 = lane & 15;
-    inst = blockIdx.z;
+    inst = inst_;
     row_bytes = FULL ? NP * 32 : g.d * (int)sizeof(T);
     plane = plane16_bytes(row_bytes / (int)sizeof(T));
     stride = row16_stride<T>(row_bytes / (int)sizeof(T));
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
   const int group = blockIdx.x / pl.segs, seg = blockIdx.x - group * pl.segs;
   const int rt0 = group * pl.group_tiles, ntile = min(pl.group_tiles, g.Rpad / 32 - rt0);
   const int whole = whole_tiles<is_f32(T()) && FULL>(g, rt0, ntile);
-  const Wave<T, NP, FULL> w(g, lay, q, k, seg, pl.seg_blocks);
+  const Wave<T, NP, FULL> w(g, lay, q, k, blockIdx.z, blockIdx.y, seg, pl.seg_blocks);
   const RowScale row_scale = pl.row_scale;
   u32x4 key[NP];
   if (w.some) w.load(key, g, lay, w.first);
@@ -391,9 +391,13 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
   __shared__ __align__(16) float rowm[MAX_TILES * 32], roww[MAX_TILES * 32];
   __shared__ __align__(16) int last[MAX_TILES * 32];     // last key the rows see
   const int tid = threadIdx.x;
-  const size_t hg = (size_t)blockIdx.z * g.Hkv + blockIdx.y;
+  // The heads in the other order than in the first kernel: those whose keys it read last may still be in the last-level cache (256 MiB).  laq_evict, us, in the
+  // same order : so: d = 64, 64 rows, 160 heads x 16384 keys 158 : 146, 32 rows, 320 x 9000 181 : 168; d = 96, 160 x 12000 165 : 153; d = 128, 128 rows,
+  // 192 x 8000 190 : 182; 112 rows, 112 x 20123 283 : 277; fp32, 128 x 8191 285 : 279.5.
+  const int inst = gridDim.z - 1 - blockIdx.z, head = gridDim.y - 1 - blockIdx.y;
+  const size_t hg = (size_t)inst * g.Hkv + head;
   if (blockIdx.x == 0 && hg == 0 && tid == 0) *status = 0;    // (these kernels have no wait to give up)
-  const Wave<T, NP, FULL> w(g, lay, q, k, blockIdx.x, pl.seg_blocks);
+  const Wave<T, NP, FULL> w(g, lay, q, k, inst, head, blockIdx.x, pl.seg_blocks);
   const RowScale row_scale = pl.row_scale;
   float* out = raw + hg * g.L;
   u32x4 key[NP];
@@ -513,6 +517,10 @@ __global__ __launch_bounds__(256) void row_constants_kernel(ScoreGeom g, float2*
 // (and a little per segment, which the second kernel folds, or a launch that does): 64 heads x 8191 keys, fp32, 512 resident workgroups: 8, 16,
 // 32 segments (1, 2, 4 rounds) 122, 144, 169 us.  Where a workgroup has many, segments of 10 to 16 blocks, so that workgroups which get ahead of
 // others take more of them: 1800 heads x 20259 keys, d = 64: 1, 3, 5, 16, 80 segments 2047, 1936, 1862, 1844, 2102 us.
+// Where these are few rounds, what the last one leaves idle counts: a round that is not full takes 0.6 of one at least, and a single one, which nothing
+// evens out, 1.08; a segment its blocks and 1.5 (of 8 to 20 blocks).  laq_evict, us, by segments (rounds): 112 rows, 112 heads x 20123 keys 9 (0.98) 277, 16
+// (1.75) 266.5, 18 (1.97) 273; fp32, 128 x 8191 4 (1) 251, 5 (1.25) 279.5, 8 (2) 253, 16 (4) 273; d = 64, 64 rows, 160 x 16384 8 (1) 140.7, 10 (1.25) 146.3,
+// 16 (2) 140.3; 32 rows, 320 x 9000 4 (1) 163, 7 (1.75) 168, 8 (2) 161, 12 (3) 164.
 // More score rows than are staged together are other workgroups' in the first kernel, but in the second the same one takes a group after the other.
 // Its rounds count that often; but where not all workgroups that fit are there, those that are get on faster: a share `enough` of them
 // does what all do (bf16 1.25 waves per SIMD, fp32 2), though never less than the first kernel's.  laq_evict, the second counted as
@@ -532,6 +540,16 @@ WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int s
   int best = 1;
   if (heads * blocks >= 15LL * resident) {
     best = std::max(1, std::min(most, blocks / (8 + 2 * pl.group_tiles)));
+    if (pl.groups == 1 && 2 * heads * best < 9 * resident) {
+      double least = 1e30;
+      for (int sb = 8; sb <= 20; ++sb) {
+        const int used = (blocks + sb - 1) / sb;
+        if (used > most) continue;
+        const double load = (double)(heads * used) / resident, rounds = std::floor(load), rest = load - rounds;
+        const double cost = (load <= 1.0 ? 1.08 : rest > 0.0 ? rounds + std::max(rest, 0.6) : rounds) * (sb + 1.5);
+        if (cost < least) { least = cost; best = used; }
+      }
+    }
   } else {
     double least = 1e30;
     for (const double share : {0.0, 0.25, 0.35, 0.5, 0.7, 1.0, 1.5, 2.0, 3.0}) {
