@@ -285,10 +285,14 @@ static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
 //   81.9 : 63.6; 992 heads 56.9 : 63.9, 1488 heads 111.9 : 121.3, 6912 heads 464 : 568; few heads, one or two row tiles 24 heads x 560 keys 20.1 : 13.3,
 //   16 x 768 22.2 : 19.7, 16 x 1024 24.4 : 27.2, 56 x 1024 23.9 : 25.6; more row tiles 64 x 714 32.7 : 34.5, 8 x 1024 26.0 : 32.1; fp32, 2 to 64 heads, one
 //   row tile 600 keys 1.09-1.16, 768 .98-1.06; two 600 .92-.94, 768 .82-.85
+//   few heads whose products are made once (head_keeps()) always: fp32, d = 64, 32 rows, 8 heads x 768, 1000 keys 22.8 : 18.5, 22.3 : 21.8, 64 x 800, 1000 25.3 : 20.2,
+//   25.6 : 22.8; d = 128, 8 x 330, 500 29.9 : 17.7, 30.1 : 20.9; d = 96, 16 x 500 27.4 : 18.4; bf16, d = 128, 8 x 800, 1000 19.9 : 16.2, 19.6 : 17.5, 56 x 1000 21.9 :
+//   18.6; d = 64, 32 x 1000 17.6 : 13.8, 64 rows 20.6 : 17.1.  (The figures above for such heads are from products made twice.)
 static bool head_wanted(const laq_shape* shape, const ScoreGeom& g) {
   if (shape->score_choice != LAQ_CHOOSE_AUTO || !head_supported(g, shape->dtype)) return false;
   const long long heads = (long long)g.n_inst * g.Hkv;
   const bool f32 = shape->dtype == LAQ_F32;
+  if (heads < HEAD_MANY && head_keeps(g, shape->dtype)) return true;
   if (f32 && ((g.d > 64 && heads <= 16) || (g.Rpad > 128 && heads < HEAD_MANY) || (g.Rpad > 96 && heads < 40 && g.L > 384))) return false;
   if (g.L <= 512) return true;
   return heads >= HEAD_MANY ? heads <= 768 : g.L <= 768 && g.Rpad <= (f32 ? 32 : 64);
@@ -332,7 +336,7 @@ static int score_checked(const laq_shape* shape, const ScoreGeom& g, const Query
     fin.pooled = apart ? w.raw : scores;
     fin.half = apart ? 0 : (pool - 1) / 2;
     fin.avg = pool_avg(shape) ? 1 : 0;
-    e = launch_head(g, qp, lay, shape->dtype, false, q_win, k, g.n_inst, 0, UniformInst{1, 0, 0}, nullptr, fin, w.status, st);
+    e = launch_head(g, qp, lay, shape->dtype, HEAD_SCORES, q_win, k, g.n_inst, 0, UniformInst{1, 0, 0}, nullptr, fin, w.status, st);
     if (e == hipSuccess && apart) e = launch_pool(g, pool, pool_avg(shape), w.raw, scores, st);
     return e == hipSuccess ? LAQ_OK : LAQ_ERR_DEVICE;
   }
@@ -527,18 +531,20 @@ static int finish_checked(const ScoreGeom& g, const FinishArgs& fin, const int32
   return for_instances(g, budget, [&](int n, int i0, const auto& tab) { return launch_finish(n, i0, g.Hkv, g.L, g.keep, raw, tab, idx, fin, st); });
 }
 
-// Whether the kernel that scores short heads selects and gathers too: one workgroup copies a head's rows, which takes longer than a
-// launch that spreads them where heads are few and rows many (8 heads x 1017 keys, 688 rows kept 26.3 us, 20.3 with the old launches).
-static bool head_gathers(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, int row_bytes) {
-  if ((pool - 1) / 2 > SELECT_POOL_MAX_HALF) return false;
-  if (g.L <= 512 || (long long)g.n_inst * g.Hkv >= HEAD_MANY) return true;
+// How far the kernel that scores short heads goes: one workgroup copies a head's rows, which takes longer than a
+// launch that spreads them where heads are few and rows many (8 heads x 1017 keys, 688 rows kept 26.3 us, 20.3 with a launch for it).  The selection it does itself
+// but for the widest pooling (8, 32 heads x 1000 keys, 900 rows kept, bf16, d = 128: in a launch of its own
+// 22.1, 25.5 us, so 18.8, 22.5).
+static HeadSteps head_steps(const laq_shape* shape, const ScoreGeom& g, const int32_t* budget, int pool, int row_bytes) {
+  if ((pool - 1) / 2 > SELECT_POOL_MAX_HALF) return HEAD_SCORES;
+  if (g.L <= 512 || (long long)g.n_inst * g.Hkv >= HEAD_MANY) return HEAD_ROWS;
   int most = 0;
   for (int i = 0; i < shape->n_inst; ++i) most = budget[i] > most ? budget[i] : most;
-  return (long long)(most < g.L ? most : g.L) * row_bytes <= 128 << 10;
+  return (long long)(most < g.L ? most : g.L) * row_bytes <= 128 << 10 ? HEAD_ROWS : HEAD_LIST;
 }
 
-// All of a call of short heads.
-static int head_checked(const laq_shape* shape, const ScoreGeom& g, const QueryPos& positions, const KvLayout& lay, const FinishArgs& fin,
+// A call of short heads up to their lists or their rows.
+static int head_checked(const laq_shape* shape, const ScoreGeom& g, const QueryPos& positions, const KvLayout& lay, const FinishArgs& fin, HeadSteps steps,
                         const void* q_win, const void* k, const int32_t* budget, int32_t* idx, void* ws, hipStream_t st) {
   if (g.Hkv > 65535 || g.n_inst > 65535 || (long long)g.Hkv * g.n_inst > 0x7fffffffLL) return LAQ_ERR_UNSUPPORTED;
   const int rc_init = init_current_device(nullptr);
@@ -547,7 +553,7 @@ static int head_checked(const laq_shape* shape, const ScoreGeom& g, const QueryP
   WindowPos qp;
   if (window_positions(g, positions, w, st, &qp) != hipSuccess) return LAQ_ERR_DEVICE;
   return for_instances(g, budget, [&](int n, int i0, const auto& tab) {
-    return launch_head(g, qp, lay, shape->dtype, true, q_win, k, n, i0, tab, idx, fin, w.status, st);
+    return launch_head(g, qp, lay, shape->dtype, steps, q_win, k, n, i0, tab, idx, fin, w.status, st);
   });
 }
 
@@ -668,8 +674,11 @@ static int evict_impl(const laq_shape* shape, const void* q_win, const void* k, 
   const int row_bytes = g.d * (shape->dtype == LAQ_F32 ? 4 : 2);
   float* raw = pool_kernel > 1 ? w.raw : scores;
   const laq::ScorePath path = laq::score_path(shape, g, lay, st);
-  if (path == laq::ScorePath::head && laq::head_gathers(shape, g, budget, pool_kernel, row_bytes))
-    return laq::head_checked(shape, g, qp, lay, laq::finish_args(shape, g, lay, k, v, pool_kernel, scores, k_out, v_out), q_win, k, budget, idx, ws, st);
+  const laq::HeadSteps steps = path == laq::ScorePath::head ? laq::head_steps(shape, g, budget, pool_kernel, row_bytes) : laq::HEAD_SCORES;
+  if (steps != laq::HEAD_SCORES) {
+    const int rc = laq::head_checked(shape, g, qp, lay, laq::finish_args(shape, g, lay, k, v, pool_kernel, scores, k_out, v_out), steps, q_win, k, budget, idx, ws, st);
+    return rc != LAQ_OK || steps == laq::HEAD_ROWS ? rc : laq::compact_impl(shape, k, v, idx, budget, k_out, v_out, st);
+  }
   if (path != laq::ScorePath::head && laq::finish_wanted(shape, g, path, budget, pool_kernel, raw, row_bytes)) {
     const int rc = laq::score_checked(shape, g, qp, lay, path, q_win, k, 1, raw, ws, st);
     if (rc != LAQ_OK) return rc;

@@ -509,9 +509,9 @@ __device__ __forceinline__ void scores_again(const ScoreGeom& g, const WindowPos
   __syncthreads();
 }
 
-// `gather`: with selection and gather (laq_evict), else scores only.  fin.half: pooling of the scores, 0 for none.
+// `steps`: see HeadSteps.  fin.half: pooling of the scores, 0 for none.
 template <typename T, int NP, bool FULL, int WAVES, int TPW, bool KEEP, typename TAB>
-__global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, HeadPlan pl, bool gather,
+__global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, HeadPlan pl, int steps,
                                                               const T* __restrict__ q, const T* __restrict__ k, TAB tab,
                                                               int inst0, int32_t* __restrict__ idx, FinishArgs fin, int* __restrict__ status) {
   constexpr int THREADS = WAVES * 64;
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
     }
   }
   if (tid < P) scores[tid] = v;
-  if (!gather) return;
+  if (steps == HEAD_SCORES) return;
   // ---- selection ----
   const int bk = tab.rows(li), ksel = bk - g.keep;
   const int64_t row0 = tab.first(li) + (int64_t)head * bk;
@@ -562,17 +562,18 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
       out[at] = tid;
     }
   }
+  if (steps == HEAD_LIST) return;
   __syncthreads();
   gather_rows<THREADS>(fin, inst, head, bk, row0, [&](int r) { return list[r]; });
 }
 
 template <typename T, int NP, bool FULL, int WAVES, int TPW, typename TAB>
-hipError_t launch_one(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, bool gather, const T* q, const T* k, int n, int inst0,
+hipError_t launch_one(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int steps, const T* q, const T* k, int n, int inst0,
                       const TAB& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
   HeadPlan pl;
   pl.row_scale = row_scale_of<T>(g.scale2);
   auto launch = [&](auto kernel, int lds) {
-    hipLaunchKernelGGL(kernel, dim3(g.Hkv, n), dim3(WAVES * 64), lds, st, g, qp, lay, pl, gather, q, k, tab, inst0, idx, fin, status);
+    hipLaunchKernelGGL(kernel, dim3(g.Hkv, n), dim3(WAVES * 64), lds, st, g, qp, lay, pl, steps, q, k, tab, inst0, idx, fin, status);
     return hipGetLastError();
   };
   const int tiles = g.Rpad / 32, tiles16 = (g.R + 15) / 16;
@@ -591,33 +592,33 @@ hipError_t launch_one(const ScoreGeom& g, const WindowPos& qp, const KvLayout& l
 }
 
 template <typename T, int NP, bool FULL, bool SHORT, typename TAB>
-hipError_t launch_for_keys(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, bool gather, const T* q, const T* k, int n, int inst0,
+hipError_t launch_for_keys(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int steps, const T* q, const T* k, int n, int inst0,
                            const TAB& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
   if (g.L <= 512) {
     // one tile of keys per wave: the shortest way through one head; two per wave, half the waves: two heads per compute unit
     if (SHORT || (long long)g.n_inst * g.Hkv <= 256)
-      return launch_one<T, NP, FULL, 16, 1, TAB>(g, qp, lay, gather, q, k, n, inst0, tab, idx, fin, status, st);
-    if constexpr (!SHORT) return launch_one<T, NP, FULL, 8, 2, TAB>(g, qp, lay, gather, q, k, n, inst0, tab, idx, fin, status, st);
+      return launch_one<T, NP, FULL, 16, 1, TAB>(g, qp, lay, steps, q, k, n, inst0, tab, idx, fin, status, st);
+    if constexpr (!SHORT) return launch_one<T, NP, FULL, 8, 2, TAB>(g, qp, lay, steps, q, k, n, inst0, tab, idx, fin, status, st);
   }
-  if constexpr (!SHORT) return launch_one<T, NP, FULL, 16, 2, TAB>(g, qp, lay, gather, q, k, n, inst0, tab, idx, fin, status, st);
+  if constexpr (!SHORT) return launch_one<T, NP, FULL, 16, 2, TAB>(g, qp, lay, steps, q, k, n, inst0, tab, idx, fin, status, st);
   return hipErrorInvalidValue;
 }
 
 template <typename TAB>
-hipError_t launch_for(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, bool gather, const void* q, const void* k, int n, int inst0,
+hipError_t launch_for(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, int steps, const void* q, const void* k, int n, int inst0,
                       const TAB& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
   if (dtype == LAQ_F32) {
     const float *qq = static_cast<const float*>(q), *kk = static_cast<const float*>(k);
-    if (g.d == 64) return launch_for_keys<float, 8, true, false>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
-    if (g.d == 128) return launch_for_keys<float, 16, true, true>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
-    return launch_for_keys<float, 16, false, true>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+    if (g.d == 64) return launch_for_keys<float, 8, true, false>(g, qp, lay, steps, qq, kk, n, inst0, tab, idx, fin, status, st);
+    if (g.d == 128) return launch_for_keys<float, 16, true, true>(g, qp, lay, steps, qq, kk, n, inst0, tab, idx, fin, status, st);
+    return launch_for_keys<float, 16, false, true>(g, qp, lay, steps, qq, kk, n, inst0, tab, idx, fin, status, st);
   }
   const uint16_t *qq = static_cast<const uint16_t*>(q), *kk = static_cast<const uint16_t*>(k);
-  if (g.d == 64) return launch_for_keys<uint16_t, 4, true, false>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
-  if (g.d == 128) return launch_for_keys<uint16_t, 8, true, false>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
-  if (g.d < 128) return launch_for_keys<uint16_t, 8, false, false>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
-  if (g.d == 256) return launch_for_keys<uint16_t, 16, true, true>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
-  return launch_for_keys<uint16_t, 16, false, true>(g, qp, lay, gather, qq, kk, n, inst0, tab, idx, fin, status, st);
+  if (g.d == 64) return launch_for_keys<uint16_t, 4, true, false>(g, qp, lay, steps, qq, kk, n, inst0, tab, idx, fin, status, st);
+  if (g.d == 128) return launch_for_keys<uint16_t, 8, true, false>(g, qp, lay, steps, qq, kk, n, inst0, tab, idx, fin, status, st);
+  if (g.d < 128) return launch_for_keys<uint16_t, 8, false, false>(g, qp, lay, steps, qq, kk, n, inst0, tab, idx, fin, status, st);
+  if (g.d == 256) return launch_for_keys<uint16_t, 16, true, true>(g, qp, lay, steps, qq, kk, n, inst0, tab, idx, fin, status, st);
+  return launch_for_keys<uint16_t, 16, false, true>(g, qp, lay, steps, qq, kk, n, inst0, tab, idx, fin, status, st);
 }
 
 }  // namespace
@@ -627,13 +628,24 @@ bool head_supported(const ScoreGeom& g, int dtype) {
   return g.R <= MAX_ROWS && g.d <= (dtype == LAQ_F32 ? 128 : 256) && g.L <= (two_tiles ? 1024 : 512);
 }
 
-hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, bool gather, const void* q, const void* k, int n, int inst0,
-                       const InstTable& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
-  return launch_for(g, qp, lay, dtype, gather, q, k, n, inst0, tab, idx, fin, status, st);
+// (the variants as launch_for() and launch_for_keys() choose them)
+bool head_keeps(const ScoreGeom& g, int dtype) {
+  const bool two = g.L > 512 || (long long)g.n_inst * g.Hkv > 256;       // tiles per wave, where the variant has registers for them
+  int kept;
+  if (dtype == LAQ_F32) kept = g.d != 64 ? kept_tiles<float, 16, 1>() : two ? kept_tiles<float, 8, 2>() : kept_tiles<float, 8, 1>();
+  else if (g.d == 64) kept = two ? kept_tiles<uint16_t, 4, 2>() : kept_tiles<uint16_t, 4, 1>();
+  else if (g.d <= 128) kept = two ? kept_tiles<uint16_t, 8, 2>() : kept_tiles<uint16_t, 8, 1>();
+  else kept = kept_tiles<uint16_t, 16, 1>();
+  return g.Rpad / 32 <= kept;
 }
-hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, bool gather, const void* q, const void* k, int n, int inst0,
+
+hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, int steps, const void* q, const void* k, int n, int inst0,
+                       const InstTable& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
+  return launch_for(g, qp, lay, dtype, steps, q, k, n, inst0, tab, idx, fin, status, st);
+}
+hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, int steps, const void* q, const void* k, int n, int inst0,
                        const UniformInst& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st) {
-  return launch_for(g, qp, lay, dtype, gather, q, k, n, inst0, tab, idx, fin, status, st);
+  return launch_for(g, qp, lay, dtype, steps, q, k, n, inst0, tab, idx, fin, status, st);
 }
 
 // every variant that launch_for() names

@@ -227,12 +227,15 @@ hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const 
                          const FinishArgs& fin, hipStream_t st);
 hipError_t launch_finish(int n_inst, int inst0, int Hkv, int L, int keep, const float* raw, const UniformInst& tab, int32_t* idx,
                          const FinishArgs& fin, hipStream_t st);
-// all of a short head in one workgroup: scores (pooled by fin.half / fin.avg into fin.pooled) and, with `gather`, selection and gather
+// all of a short head in one workgroup: scores (pooled by fin.half / fin.avg into fin.pooled), with HEAD_LIST the selection too, with HEAD_ROWS that and the
+// gather
+enum HeadSteps { HEAD_SCORES, HEAD_LIST, HEAD_ROWS };
 bool head_supported(const ScoreGeom& g, int dtype);
+bool head_keeps(const ScoreGeom& g, int dtype);   // its products and exponentials are made once: the registers hold those of all score rows
 hipError_t head_init();
-hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, bool gather, const void* q, const void* k, int n_inst,
+hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, int steps, const void* q, const void* k, int n_inst,
                        int inst0, const InstTable& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st);
-hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, bool gather, const void* q, const void* k, int n_inst,
+hipError_t launch_head(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, int dtype, int steps, const void* q, const void* k, int n_inst,
                        int inst0, const UniformInst& tab, int32_t* idx, const FinishArgs& fin, int* status, hipStream_t st);
 hipError_t launch_sink_recent(int n_inst, int Hkv, int L, int n_sink, const InstTable& tab, int32_t* idx,
                               hipStream_t st);

@@ -23,6 +23,8 @@ CASES = [
     (BF16, 1, 2, 1, 8, 1, 1, 1, "max", [1]), (BF16, 300, 2, 1, 64, 70, 4, 7, "max", [8 + i % 40 for i in range(300)]), (BF16, 270, 2, 1, 64, 33, 4, 5, "avg", [9] * 270),
     (BF16, 1, 8, 1, 128, 400, 32, 7, "max", [77]), (BF16, 1, 8, 1, 128, 400, 33, 7, "max", [77]), (BF16, 1, 6, 1, 128, 450, 25, 7, "max", [450]),
     (F32, 1, 4, 2, 64, 512, 8, 7, "max", [64]), (F32, 10, 8, 8, 64, 1000, 6, 7, "avg", [64, 1000] * 5), (F32, 35, 8, 8, 64, 512, 9, 5, "max", [64] * 35),
+    # few heads of many rows: the gather is another launch's
+    (BF16, 1, 8, 2, 128, 900, 8, 7, "max", [700]), (F32, 2, 4, 2, 64, 700, 8, 5, "avg", [690, 20]), (BF16, 2, 4, 4, 128, 1024, 6, 7, "max", [1024, 600]),
     (F32, 3, 14, 7, 128, 512, 20, 7, "max", [200, 21, 512]), (F32, 3, 7, 7, 104, 130, 9, 13, "max", [40] * 3), (F32, 3, 7, 7, 24, 97, 9, 1, "max", [40] * 3),
 ]
 
