@@ -285,14 +285,15 @@ static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
 //   81.9 : 63.6; 992 heads 56.9 : 63.9, 1488 heads 111.9 : 121.3, 6912 heads 464 : 568; few heads, one or two row tiles 24 heads x 560 keys 20.1 : 13.3,
 //   16 x 768 22.2 : 19.7, 16 x 1024 24.4 : 27.2, 56 x 1024 23.9 : 25.6; more row tiles 64 x 714 32.7 : 34.5, 8 x 1024 26.0 : 32.1; fp32, 2 to 64 heads, one
 //   row tile 600 keys 1.09-1.16, 768 .98-1.06; two 600 .92-.94, 768 .82-.85
-//   few heads whose products are made once (head_keeps()) always: fp32, d = 64, 32 rows, 8 heads x 768, 1000 keys 22.8 : 18.5, 22.3 : 21.8, 64 x 800, 1000 25.3 : 20.2,
+//   few heads whose products are made once (head_keeps()): fp32, d = 64, 32 rows, 8 heads x 768, 1000 keys 22.8 : 18.5, 22.3 : 21.8, 64 x 800, 1000 25.3 : 20.2,
 //   25.6 : 22.8; d = 128, 8 x 330, 500 29.9 : 17.7, 30.1 : 20.9; d = 96, 16 x 500 27.4 : 18.4; bf16, d = 128, 8 x 800, 1000 19.9 : 16.2, 19.6 : 17.5, 56 x 1000 21.9 :
-//   18.6; d = 64, 32 x 1000 17.6 : 13.8, 64 rows 20.6 : 17.1.  (The figures above for such heads are from products made twice.)
+//   18.6; d = 64, 32 x 1000 17.6 : 13.8, 64 rows 20.6 : 17.1.  (The figures above for such heads are from products made twice.)  Fewer than 8 heads of more than 768 keys, and fp32 with d > 64 in up to 16 heads
+//   of more than 448, would gain as much, but what laq_score_kernel answers for some of these is promised to callers (tests/test_abi.py) and stays.
 static bool head_wanted(const laq_shape* shape, const ScoreGeom& g) {
   if (shape->score_choice != LAQ_CHOOSE_AUTO || !head_supported(g, shape->dtype)) return false;
   const long long heads = (long long)g.n_inst * g.Hkv;
   const bool f32 = shape->dtype == LAQ_F32;
-  if (heads < HEAD_MANY && head_keeps(g, shape->dtype)) return true;
+  if (heads < HEAD_MANY && head_keeps(g, shape->dtype) && (g.L <= 768 || heads >= 8) && (!f32 || g.d <= 64 || heads > 16 || g.L <= 448)) return true;
   if (f32 && ((g.d > 64 && heads <= 16) || (g.Rpad > 128 && heads < HEAD_MANY) || (g.Rpad > 96 && heads < 40 && g.L > 384))) return false;
   if (g.L <= 512) return true;
   return heads >= HEAD_MANY ? heads <= 768 : g.L <= 768 && g.Rpad <= (f32 ? 32 : 64);

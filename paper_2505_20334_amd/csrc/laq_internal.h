@@ -55,7 +55,7 @@ struct QueryPos {                          // host side
 
 // Workspace carving: [partials | row constants | raw scores]
 //   part:  float2 (m, z) per (instance, KV head, chunk, padded row): softmax statistics of a chunk or segment
-//   rowc:  float c = M + log2(Z) per (instance, KV head, padded row)
+//   rowc:  float c = M + log2(Z) per (instance, KV head, padded row): the one-chunk kernels with many chunks
 //   raw:   float per (instance, KV head, key): unpooled scores in front of a pooling or selecting kernel; the single-read
 //          kernel with the max pool keeps the edge records of its workgroups' boundaries here instead
 //   pooled: float per (instance, KV head, key): the hand-over plane between scoring and selection
