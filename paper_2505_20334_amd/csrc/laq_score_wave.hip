@@ -252,13 +252,28 @@ template <int RH>
 __device__ __forceinline__ float tile_sum(const Tile16& a, float scale, float m0, float m1) {
   float z0 = 0.f, z1 = 0.f;
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      z0 += __builtin_amdgcn_exp2f(fmaf(a.t[s][0][i], scale, -m0));
-      if (RH > 1) z1 += __builtin_amdgcn_exp2f(fmaf(a.t[s][1][i], scale, -m1));
+  for (int e = 0; e < 8; ++e) {
+    const float x0 = __builtin_amdgcn_exp2f(fmaf(a.t[e >> 2][0][e & 3], scale, -m0));
+    z0 = e == 0 ? x0 : z0 + x0;
+    if (RH > 1) {
+      const float x1 = __builtin_amdgcn_exp2f(fmaf(a.t[e >> 2][RH - 1][e & 3], scale, -m1));
+      z1 = e == 0 ? x1 : z1 + x1;
     }
+  }
   return over_groups(z0, RH > 1 ? z1 : z0, [](float x, float y) { return x + y; });
+}
+
+// The greater of two numbers, none where one of them is none.  (fmaxf() takes two instructions more for each that it cannot see the origin of.)
+__device__ __forceinline__ float greater(float x, float y) { return __builtin_elementwise_maximum(x, y); }
+// A lane's own row's number (lanes 0 .. 31: row n16, the others: 16 + n16) -> those of both its rows.  From lane to lane and not by way of LDS, where a lane
+// would read what another one wrote with nothing between; and the reference is made once for the lane's row, not twice.  Kernel 1, us, numbers read from
+// LDS, two references : so: 128 rows, 67 heads x 2042 keys 17.1 : 16.7, d = 64, 67 x 4042 15.2 : 14.5.
+struct RowPair { float m0, m1; };
+template <int RH>
+__device__ __forceinline__ RowPair both_rows(float own) {
+  if constexpr (RH == 1) return {own, own};
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own), false, false);
+  return {__uint_as_float(h[0]), __uint_as_float(h[1])};
 }
 
 // Pass 1: part[head][segment][row] = (m, z) of a score row over the segment's visible keys, in log2 units.
@@ -284,14 +299,18 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
     float2* mine = stat + w.wave * 32 + w.n16;           // this lane's first row; the second: 16 further on
     auto tile = [&](auto row_halves, int rt) {
       constexpr int RH = decltype(row_halves)::value;
-      const int own = RH > 1 ? w.grp >> 1 << 4 : 0;      // the one whose sum it ends with
-      const float old0 = mine[0].x, old1 = RH > 1 ? mine[16].x : old0, old_z = mine[own].y;
+      const int own = RH > 1 ? w.grp >> 1 << 4 : 0;      // the one whose sum it ends with: the only word of `stat` that the lane reads and writes
+      const float2 old = mine[own];
       Tile16 a = op.template product<true, RH>(rows, w.stride, w.plane, w.plane / 64);
-      float z = plain && key0 != w.first ? tile_sum<RH>(a, row_scale.scale2, old0, old1) : INFINITY;
+      float z = INFINITY;
+      if (plain && key0 != w.first) {
+        const RowPair r = both_rows<RH>(old.x);
+        z = tile_sum<RH>(a, row_scale.scale2, r.m0, r.m1);
+      }
       if (__builtin_expect(!__any(!(z <= OUTGROWN)), 1)) {
-        mine[own].y = old_z + z;
+        mine[own].y = old.y + z;
       } else {
-        float m0, m1, scale = row_scale.scale2;
+        float m, scale = row_scale.scale2;
 #pragma unroll 1
         for (bool again = false;; again = true) {
           if (!plain) {
@@ -305,18 +324,16 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
                 if (16 * (e >> 2) + (e & 3) > last) a.t[e >> 2][r][e & 3] = -INFINITY;
             }
           }
-          m0 = a.t[0][0][0];
-          m1 = a.t[0][RH - 1][0];
+          float m0 = greater(a.t[0][0][0], a.t[0][0][1]), m1 = greater(a.t[0][RH - 1][0], a.t[0][RH - 1][1]);
 #pragma unroll
-          for (int e = 1; e < 8; ++e) {
-            m0 = fmaxf(m0, a.t[e >> 2][0][e & 3]);
-            m1 = fmaxf(m1, a.t[e >> 2][RH - 1][e & 3]);
+          for (int e = 2; e < 8; ++e) {
+            m0 = greater(m0, a.t[e >> 2][0][e & 3]);
+            m1 = greater(m1, a.t[e >> 2][RH - 1][e & 3]);
           }
-          const float m = over_groups(m0, m1, [](float x, float y) { return fmaxf(x, y); });
-          const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-          m0 = fmaxf(old0, __builtin_ceilf(fmaf(__uint_as_float(mh[0]), scale, HEADROOM)));      // (the logit scale is positive)
-          m1 = fmaxf(old1, __builtin_ceilf(fmaf(__uint_as_float(mh[1]), scale, HEADROOM)));
-          z = tile_sum<RH>(a, scale, m0, m1);
+          // (the logit scale is positive)
+          m = fmaxf(old.x, __builtin_ceilf(fmaf(over_groups(m0, m1, [](float x, float y) { return greater(x, y); }), scale, HEADROOM)));
+          const RowPair r = both_rows<RH>(m);
+          z = tile_sum<RH>(a, scale, r.m0, r.m1);
           if (!is_f32(T()) || again || __builtin_expect(!__any(z != z), 1)) break;
           const char *kr[2], *qr[2];
           w.key_rows(kr, g, lay, key0);
@@ -324,8 +341,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
           a = product16_f32<true>(kr, qr, w.grp, w.row_bytes);
           scale = g.scale2;
         }
-        const float m = own ? m1 : m0, old = own ? old1 : old0;
-        mine[own] = make_float2(m, fmaf(old_z, __builtin_amdgcn_exp2f(old - m), z));
+        mine[own] = make_float2(m, fmaf(old.y, __builtin_amdgcn_exp2f(old.x - m), z));
       }
     };
 #pragma unroll 1

@@ -75,6 +75,32 @@ def test_logits_that_outgrow_the_reference(dtype, d, shape):
         check_scores(got[i], want, dtype, "instance %d" % i)
 
 
+@pytest.mark.parametrize("rising", ["first half", "second half", "in turn"])
+@pytest.mark.parametrize("dtype,d", [(BF16, 64), (BF16, 96), (BF16, 128), (BF16, 256), (BF16, 200), (F32, 64), (F32, 96), (F32, 128), (F32, 104)])
+def test_each_row_of_a_tile_has_a_reference_of_its_own(dtype, d, rising):
+    """A lane works on rows r and 16 + r of a tile and keeps the reference of one of them.  Rows whose logits outgrow it, several times over a
+    wave's keys, next to rows whose logits never do: 16 score rows of one kind and 16, 32 of the other, or every second one; exponents of 40 at most."""
+    import paper_2505_20334_amd as laq
+    n, L, W = 80, 2100, 16
+    print("case:", dtype, d, rising, flush=True)
+    g = torch.Generator().manual_seed(d)
+    q = 0.3 * torch.randn(n, 3, W, d, generator=g)
+    q[..., 0] = 0.0
+    q[..., 1] = 1.0
+    rows = q.view(n, 3 * W, d)
+    which = {"first half": slice(0, 16), "second half": slice(16, 32), "in turn": slice(1, None, 2)}[rising]
+    rows[:, which, 0] = 8.0
+    k = torch.randn(n, 1, L, d, generator=g)
+    k[..., 0] = 24.0 * torch.arange(L) / L * d ** 0.5 / 8.0
+    k[..., 1] = 0.0
+    q, k = q.to(dtype), k.to(dtype)
+    pos = [L + w for w in range(W)]
+    got = laq.laq_score(q.to(DEV), k.to(DEV), 1, q_pos=pos, keep=0, choose="two-pass").cpu()
+    for i in (0, n - 1):
+        want, _, _, _ = oracle.evict(q[i], k[i], k[i], 64, 1, q_pos=pos, keep=0)
+        check_scores(got[i], want, dtype, "instance %d" % i)
+
+
 @pytest.mark.parametrize("d", [64, 104, 128])
 def test_fp32_infinities_and_nans_are_those_of_whole_products(d):
     """A float is taken apart into three for the products; an infinity leaves NaNs, and the tile is scored from whole
