@@ -8,6 +8,7 @@
 #include <cmath>
 
 #include "laq_internal.h"
+#include "laq_staging.h"
 
 namespace laq {
 
@@ -60,10 +61,9 @@ __device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 acc) {
 constexpr bool is_f32(float) { return true; }
 constexpr bool is_f32(uint16_t) { return false; }
 
-// bytes of d staged bf16 (32 bytes for a product step), and from one staged score row to the next: bf16 as it is, fp32 as three rows
-// of bf16; and 16 more, so that 128-bit reads of 16 consecutive rows fall on distinct banks
-__host__ __device__ inline int plane_bytes(int d) { return (d + 15) / 16 * 32; }
-template <typename T> __host__ __device__ inline int row_stride(int d) { return (is_f32(T()) ? 3 : 1) * plane_bytes(d) + 16; }
+// from one staged score row to the next: bf16 as it is, fp32 as three rows of bf16
+template <typename T> constexpr int row_stride(int d) { return staged_row(d, is_f32(T()) ? 3 : 1); }
+template <typename T> constexpr int row16_stride(int d) { return staged_row16(d, is_f32(T()) ? 3 : 1); }
 
 // The product of fp32 rows by the fp32 instruction, from memory: where the split one holds a NaN (a part of an infinity is one).
 template <bool KEYS_AS_ROWS>
@@ -165,9 +165,6 @@ __device__ __forceinline__ float over_groups(float x, float y, OP op) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(w), __float_as_uint(w), false, false);
   return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-// staged bytes of d bf16 (64 bytes for a product step), and from one staged score row to the next, see plane_bytes(), row_stride()
-__host__ __device__ inline int plane16_bytes(int d) { return (d + 31) / 32 * 64; }
-template <typename T> __host__ __device__ inline int row16_stride(int d) { return (is_f32(T()) ? 3 : 1) * plane16_bytes(d) + 16; }
 
 // product_f32() of the tiles: key[s], q[r] are this lane's rows
 template <bool KEYS_AS_ROWS>

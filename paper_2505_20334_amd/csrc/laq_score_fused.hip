@@ -69,9 +69,7 @@ constexpr int STEPS = D / 32;                // reduction steps of a product
 constexpr int KS = 2 * STEPS;                // 16-byte pieces of a key tile per lane: of its first row, then of its second
 constexpr int TILE_BYTES = 32 * D * 2;       // a key tile: 32 rows
 constexpr int F_WAVES = 4, F_THREADS = F_WAVES * 64;   // one wave per SIMD; two workgroups share a compute unit
-// LDS row of Q: the d elements and 16 bytes that make 128-bit operand reads of 16 consecutive
-// rows conflict-free
-constexpr int QROWB = D * 2 + 16;
+constexpr int QROWB = staged_row16(D, 1);    // LDS row of Q
 constexpr int ZT_STRIDE = 20;                // floats per row of a wave's transposition tile (writes and 128-bit reads free of conflicts)
 constexpr int SPIN_LIMIT = 1 << 20;          // probes; about a second, far beyond any legitimate wait
 constexpr int SPIN_LIMIT_UNSAFE = 1 << 18;   // of a launch that the rule of laq_team.h does not cover: it gives up before the others do

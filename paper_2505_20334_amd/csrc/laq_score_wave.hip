@@ -526,6 +526,8 @@ __global__ __launch_bounds__(256) void row_constants_kernel(ScoreGeom g, float2*
   }
 }
 
+constexpr int MAX_LDS = 160 << 10, STATIC_LDS = 3 * MAX_TILES * 32 * 4;   // (the second kernel's arrays; the first has none)
+
 // How a call's keys are cut into segments.  A segment costs its blocks and about three more (the score rows' way to LDS, the first keys'
 // to the registers).  Where a workgroup has few blocks, the cut with the least of that over the rounds of resident workgroups it takes
 // (and a little per segment, which the second kernel folds, or a launch that does): 64 heads x 8191 keys, fp32, 512 resident workgroups: 8, 16,
@@ -545,7 +547,7 @@ WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int s
   WavePlan pl;
   const int ntile = g.Rpad / 32, blocks = (g.L + BLOCK_KEYS - 1) / BLOCK_KEYS;
   const long long heads = (long long)g.n_inst * g.Hkv;
-  int fit = std::min(lds / (32 * stride + WAVES * 32 * (int)sizeof(float2)), (lds - THREADS * (int)sizeof(float2)) / (32 * stride));
+  int fit = std::min(lds / (32 * stride + WAVES * 32 * (int)sizeof(float2)), (lds - STATIC_LDS - THREADS * (int)sizeof(float2)) / (32 * stride));
   fit = std::max(1, std::min(fit, MAX_TILES));
   pl.groups = (ntile + fit - 1) / fit;
   pl.group_tiles = (ntile + pl.groups - 1) / pl.groups;
@@ -584,14 +586,12 @@ WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int s
   return pl;
 }
 
-constexpr int MAX_LDS = 160 << 10, STATIC_LDS = 3 * MAX_TILES * 32 * 4;
-
 template <typename T, int NP, bool FULL>
 hipError_t launch_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& lay, const T* q, const T* k, float* raw,
                        const Workspace& ws, hipStream_t st) {
   constexpr int per_simd = waves_per_simd<T, NP>();
   const int stride = row16_stride<T>(g.d);
-  WavePlan pl = plan_of(g, 256 * per_simd, (is_f32(T()) ? 2.0 : 1.25) / per_simd, (MAX_LDS / per_simd - STATIC_LDS) & ~255, stride);
+  WavePlan pl = plan_of(g, 256 * per_simd, (is_f32(T()) ? 2.0 : 1.25) / per_simd, MAX_LDS / per_simd, stride);
   pl.row_scale = row_scale_of<T>(g.scale2);
   // Where the keys do not fit the last-level cache (256 MiB), the second kernel begins with the heads that the first one read last.  laq_evict, us, in the
   // same order : so: d = 64, 64 rows, 160 heads x 16384 keys 158 : 146, 32 rows, 320 x 9000 181 : 168; d = 96, 160 x 12000 165 : 153; d = 128, 128 rows,
