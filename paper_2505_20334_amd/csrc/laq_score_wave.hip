@@ -223,7 +223,10 @@ struct WavePlan {
   int seg_blocks;          // blocks of BLOCK_KEYS keys each of them takes
   int group_tiles;         // row tiles staged together
   int groups;
-  int backwards;           // the second kernel takes the heads in the other order
+  // The second kernel's workgroups (., y, z) take head head0 + way * y of instance inst0 + way * z: the heads in the first one's order, or in the other.
+  // (Numbers and no flag: a flag, and the sizes of the grid behind it, are two waits for memory before anything else.  Kernel 2, us, a flag : so: 64 heads x 2042
+  // to 4042 keys 0.2 to 0.25 less of 12 to 16.5.)
+  int head0, inst0, way;
   RowScale row_scale;
 };
 
@@ -408,7 +411,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_score
   __shared__ __align__(16) float rowm[MAX_TILES * 32], roww[MAX_TILES * 32];
   __shared__ __align__(16) int last[MAX_TILES * 32];     // last key the rows see
   const int tid = threadIdx.x;
-  const int inst = pl.backwards ? gridDim.z - 1 - blockIdx.z : blockIdx.z, head = pl.backwards ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+  const int inst = pl.inst0 + pl.way * (int)blockIdx.z, head = pl.head0 + pl.way * (int)blockIdx.y;
   const size_t hg = (size_t)inst * g.Hkv + head;
   if (blockIdx.x == 0 && hg == 0 && tid == 0) *status = 0;    // (these kernels have no wait to give up)
   const Wave<T, NP, FULL> w(g, lay, q, k, inst, head, blockIdx.x, pl.seg_blocks);
@@ -597,7 +600,10 @@ hipError_t launch_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& 
   // same order : so: d = 64, 64 rows, 160 heads x 16384 keys 158 : 146, 32 rows, 320 x 9000 181 : 168; d = 96, 160 x 12000 165 : 153; d = 128, 128 rows,
   // 192 x 8000 190 : 182; 112 rows, 112 x 20123 283 : 277; fp32, 128 x 8191 285 : 279.5.  In small calls the same workgroup numbers find their keys in the L2
   // of their XCD: d = 64, 64 rows, 103 x 1068, 14 MiB, 8.3 : 9.0 the second kernel.
-  pl.backwards = (double)g.n_inst * g.Hkv * g.L * g.d * sizeof(T) > (double)(192 << 20) ? 1 : 0;
+  const bool other = (double)g.n_inst * g.Hkv * g.L * g.d * sizeof(T) > (double)(192 << 20);
+  pl.way = other ? -1 : 1;
+  pl.head0 = other ? g.Hkv - 1 : 0;
+  pl.inst0 = other ? g.n_inst - 1 : 0;
   const int rows = pl.group_tiles * 32;
   hipLaunchKernelGGL((wave_stats_kernel<T, NP, FULL>), dim3(pl.segs * pl.groups, g.Hkv, g.n_inst), dim3(THREADS),
                      rows * (stride + WAVES * (int)sizeof(float2)), st, g, qp, lay, pl, q, k, ws.part);
