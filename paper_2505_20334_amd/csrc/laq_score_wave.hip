@@ -597,10 +597,13 @@ hipError_t launch_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& 
   WavePlan pl = plan_of(g, 256 * per_simd, (is_f32(T()) ? 2.0 : 1.25) / per_simd, MAX_LDS / per_simd, stride);
   pl.row_scale = row_scale_of<T>(g.scale2);
   // Where the keys do not fit the last-level cache (256 MiB), the second kernel begins with the heads that the first one read last.  laq_evict, us, in the
-  // same order : so: d = 64, 64 rows, 160 heads x 16384 keys 158 : 146, 32 rows, 320 x 9000 181 : 168; d = 96, 160 x 12000 165 : 153; d = 128, 128 rows,
-  // 192 x 8000 190 : 182; 112 rows, 112 x 20123 283 : 277; fp32, 128 x 8191 285 : 279.5.  In small calls the same workgroup numbers find their keys in the L2
-  // of their XCD: d = 64, 64 rows, 103 x 1068, 14 MiB, 8.3 : 9.0 the second kernel.
-  const bool other = (double)g.n_inst * g.Hkv * g.L * g.d * sizeof(T) > (double)(192 << 20);
+  // same order : so, on the same cache every time; on one that no earlier call has read:
+  //   bf16, 128 rows, heads x 8192 keys  250 MiB 119 : 118.5, 126.5 : 127;  280 MiB 139.5 : 135, 148 : 144;  500 MiB 243 : 228, 242 : 233
+  //   d = 64, 64 rows, x 8192            230 MiB 98 : 98.5, 111 : 111.5;  280 MiB 140 : 137, 151 : 146;  500 MiB 246 : 224, 243.5 : 230.5
+  //   d = 96, 64 rows, x 4000            230 MiB 107 : 109, 121 : 120.5;  280 MiB 135 : 130, 148 : 140.5;  350 MiB 181 : 165, 185 : 174
+  //   fp32, 64 rows, x 8191              250 MiB 125 : 125, 137 : 138;  280 MiB 153.5 : 152, 161 : 159;  500 MiB 261 : 250, 262 : 257
+  // In small calls the same workgroup numbers find their keys in the L2 of their XCD: d = 64, 64 rows, 24 x 8192, 24 MiB, 28.4 : 30.0, 31.7 : 32.9.
+  const bool other = (double)g.n_inst * g.Hkv * g.L * g.d * sizeof(T) > (double)(256 << 20);
   pl.way = other ? -1 : 1;
   pl.head0 = other ? g.Hkv - 1 : 0;
   pl.inst0 = other ? g.n_inst - 1 : 0;

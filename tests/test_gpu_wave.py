@@ -271,3 +271,33 @@ def test_gather_after_the_single_read_kernel_is_that_of_the_stages(n, L, budgets
     assert torch.equal(idx, laq.laq_select(scores, b, 1, 8))
     for x, y in zip((ko, vo), laq.laq_compact(k, v, idx, b, 8)):
         assert torch.equal(x, y)
+
+
+# (dtype, n, Hq, Hkv, d, L, W, rows of a block): either side of 256 MiB of keys, from which on the second kernel takes the heads in the other order: a last
+# tile of score rows that is half empty, a paged cache, several groups of row tiles, a head size without a variant of its own
+LARGE = [(F32, 137, 6, 2, 128, 1900, 16, 0), (F32, 150, 6, 2, 128, 1900, 16, 0), (F32, 90, 9, 3, 104, 2600, 16, 0), (BF16, 45, 28, 4, 128, 6300, 16, 256),
+         (BF16, 41, 28, 4, 128, 6300, 16, 512), (BF16, 31, 40, 8, 64, 9200, 32, 0)]
+
+
+@pytest.mark.parametrize("dtype,n,Hq,Hkv,d,L,W,block", LARGE)
+def test_heads_in_either_order(dtype, n, Hq, Hkv, d, L, W, block):
+    import paper_2505_20334_amd as laq
+    print("case:", dtype, n, Hq, Hkv, d, L, W, block, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    q = torch.randn(n, Hq, W, d, generator=g, device=DEV).to(dtype)
+    table, kw = None, {}
+    if block:
+        per = -(-L // block)
+        table = torch.randperm(n * per, generator=g, device=DEV).reshape(n, per).int()
+        k = torch.randn(n * per, Hkv, block, d, generator=g, device=DEV).to(dtype)
+        k[table[:, -1].long(), :, L - (per - 1) * block:] = float("nan")
+        kw = dict(block_table=table, L=L)
+    else:
+        k = torch.randn(n, Hkv, L, d, generator=g, device=DEV).to(dtype)
+    pos = [L + w for w in range(W)]
+    assert laq.laq_score_kernel(n, Hq, Hkv, d, L, W, dtype, q_pos=pos, keep=0, whole_heads=True) != "single-read"
+    got = laq.laq_score(q, k, 1, q_pos=pos, keep=0, **kw).cpu()
+    for i in (0, 1, n // 2, n - 1):
+        ki = k[i].cpu() if table is None else oracle.gather_paged(k[table[i].long()].cpu(), torch.arange(per)[None].int(), L)[0]
+        want, _, _, _ = oracle.evict(q[i].cpu(), ki, ki, 64, 1, q_pos=pos, keep=0)
+        check_scores(got[i], want, dtype, "instance %d" % i)
