@@ -233,6 +233,9 @@ struct WavePlan {
 // Waves per SIMD the kernels are built for: as many as their registers (and 32 of the score rows per workgroup in LDS) allow.  (d = 96, bf16: five waves
 // spill 13 registers in the second kernel; 64 rows, 192 heads x 8001 152 us, with four 134.5.)
 template <typename T, int NP> constexpr int waves_per_simd() { return is_f32(T()) ? (NP <= 8 ? 3 : 2) : (NP <= 4 ? 5 : NP <= 8 ? 4 : 2); }
+// (The first kernel of bf16 with d > 128 or a head size without a variant of its own: 168 registers.  With 176, two waves, 448 rows, 3000 heads x 120 keys,
+// d = 16 342 us : 298, d = 104 616 : 546.)
+template <typename T, int NP> constexpr int stats_waves_per_simd() { return !is_f32(T()) && NP > 8 ? 3 : waves_per_simd<T, NP>(); }
 
 // Row tiles, of those staged from rt0 on, that are taken whole.  fp32 leaves the second half of a last one out where it has no rows: laq_evict, us, 112
 // rows, 48 heads x 9000 keys 221 : 209.  bf16 does not: its passes are not bound by products, and the code for it makes others slower (112 rows, 112 x 20123
@@ -281,7 +284,7 @@ __device__ __forceinline__ RowPair both_rows(float own) {
 
 // Pass 1: part[head][segment][row] = (m, z) of a score row over the segment's visible keys, in log2 units.
 template <typename T, int NP, bool FULL>
-__global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, WavePlan pl,
+__global__ __launch_bounds__(THREADS, (stats_waves_per_simd<T, NP>())) void wave_stats_kernel(ScoreGeom g, WindowPos qp, KvLayout lay, WavePlan pl,
                                                                                const T* __restrict__ q, const T* __restrict__ k,
                                                                                float2* __restrict__ part) {
   extern __shared__ __align__(16) char smem[];
@@ -317,11 +320,12 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<T, NP>())) void wave_stats
 #pragma unroll 1
         for (bool again = false;; again = true) {
           if (!plain) {
-            int n = threadIdx.x & 63;
+            int n = threadIdx.x & 63, W = g.W;
             asm volatile("" : "+v"(n));                  // (computed here: the common case has no registers for it)
+            if constexpr (!is_f32(T())) asm volatile("" : "+s"(W));   // (nor for what a division by W has ready: bf16, d = 256; fp32, d = 64: 2 spills with this)
 #pragma unroll
             for (int r = 0; r < RH; ++r) {
-              const int row = (rt0 + rt) * 32 + 16 * r + (n & 15), last = last_visible_key(g, qp, min(row, g.R - 1) % g.W) - key0 - 4 * (n >> 4);
+              const int row = (rt0 + rt) * 32 + 16 * r + (n & 15), last = last_visible_key(g, qp, min(row, g.R - 1) % W) - key0 - 4 * (n >> 4);
 #pragma unroll
               for (int e = 0; e < 8; ++e)
                 if (16 * (e >> 2) + (e & 3) > last) a.t[e >> 2][r][e & 3] = -INFINITY;
