@@ -249,6 +249,12 @@ __device__ __forceinline__ void scores_kept(const ScoreGeom& g, const WindowPos&
     for (int w = 0; w < WAVES / 4; ++w) Z = fmaf(v[w].y, __builtin_amdgcn_exp2f(v[w].x - M), Z);
     return make_float2(M, over_groups(Z, Z, plus));
   };
+  // Of more than 32 rows each wave folds 16 for all, into the first wave's place.  (Every wave all of them: laq_evict, us, that : this, bf16, 128 rows, 64 heads
+  // x 400 keys, d = 64 15.9 : 13.9, 128 18.8 : 16.9, with products made twice 15.2, 18.7; 64 rows, 8 x 512, d = 128 14.9 : 14.0, 100 x 512, fp32, d = 64
+  // 18.6 : 18.0.)
+  constexpr int KT = kept_tiles<T, NP, TPW>();
+  const bool once = KT > 1 && tiles16 > 2;
+  auto folded = [&](int t16) { return once ? stat[t16 * WAVES * 16 + n16] : fold(t16); };
   using One = std::integral_constant<int, 1>;
   using Two = std::integral_constant<int, 2>;
   float sum[TPW][8];                       // of keys 16 (c / 4) + 4 grp + c % 4 of the tiles, over this lane's rows
@@ -256,7 +262,6 @@ __device__ __forceinline__ void scores_kept(const ScoreGeom& g, const WindowPos&
   for (int i = 0; i < TPW; ++i)
 #pragma unroll
     for (int c = 0; c < 8; ++c) sum[i][c] = 0.f;
-  constexpr int KT = kept_tiles<T, NP, TPW>();
   Tile16 kept[KT][TPW];
   float m[KT][TPW][2];
 #pragma unroll
@@ -265,10 +270,18 @@ __device__ __forceinline__ void scores_kept(const ScoreGeom& g, const WindowPos&
     else if (2 * rt < tiles16) statistics(One{}, rt * 32, rows + rt * 32 * stride, kept[rt], m[rt]);
   }
   __syncthreads();
+  if (once) {
+    static_assert(2 * KT <= WAVES, "");
+    if (wave < tiles16) {
+      const float2 f = fold(wave);
+      if (grp == 0) stat[wave * WAVES * 16 + n16] = f;
+    }
+    __syncthreads();
+  }
 #pragma unroll
   for (int t16 = 0; t16 < 2 * KT; ++t16) {
     if (t16 >= tiles16) continue;
-    const float2 f = fold(t16);
+    const float2 f = folded(t16);
     const float per = t16 * 16 + n16 < g.R ? 1.f / f.y : 0.f;
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
@@ -310,7 +323,7 @@ __device__ __forceinline__ void scores_kept(const ScoreGeom& g, const WindowPos&
           }
         }
         mask(a, t16 * 16, 1, key0);
-        const float2 f = fold(t16);
+        const float2 f = folded(t16);
         const float cr = row < g.R ? f.x + __builtin_amdgcn_logf(f.y) : INFINITY;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
@@ -523,10 +536,15 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int head = blockIdx.x, li = blockIdx.y, inst = inst0 + li;
   const size_t hg = (size_t)inst * g.Hkv + head;
-  if (head == 0 && inst == 0 && tid == 0) *status = 0;   // (no wait to give up here)
+  // (No wait to give up here.  In front of the keys' loads its address is a trip to memory that these are behind: bf16, and fp32 with d = 64, 2 to 80 heads x
+  // 300 to 800 keys, 16 and 32 rows, with the store behind the scores .97-1.00 of the time.  What the compiler makes of fp32 with d > 64 is 1.00-1.03 then.)
+  constexpr bool STATUS_FIRST = is_f32(T()) && NP > 8;
+  const bool clears = head == 0 && inst == 0 && tid == 0;
+  if (STATUS_FIRST && clears) *status = 0;
   float* scores = fin.pooled + hg * g.L;
   if constexpr (KEEP) scores_kept<T, NP, FULL, WAVES, TPW>(g, qp, lay, pl, q, k, inst, head, smem, last, rank.bins, raw, scores);
   else scores_again<T, NP, FULL, WAVES, TPW>(g, qp, lay, pl, q, k, inst, head, smem, last, rank.bins, raw, scores);
+  if (!STATUS_FIRST && clears) *status = 0;
   // ---- pooling: position tid ----
   const int P = g.P, half = fin.half;
   float v = raw[MARGIN + tid];
