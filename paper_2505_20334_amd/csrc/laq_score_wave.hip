@@ -555,6 +555,9 @@ constexpr int MAX_LDS = 160 << 10, STATIC_LDS = 3 * MAX_TILES * 32 * 4;   // (th
 // evens out, 1.08; a segment its blocks and 1.5 (of 8 to 20 blocks).  laq_evict, us, by segments (rounds): 112 rows, 112 heads x 20123 keys 9 (0.98) 277, 16
 // (1.75) 266.5, 18 (1.97) 273; fp32, 128 x 8191 4 (1) 251, 5 (1.25) 279.5, 8 (2) 253, 16 (4) 273; d = 64, 64 rows, 160 x 16384 8 (1) 140.7, 10 (1.25) 146.3,
 // 16 (2) 140.3; 32 rows, 320 x 9000 4 (1) 163, 7 (1.75) 168, 8 (2) 161, 12 (3) 164.
+// Fewer segments than these 10 to 16 blocks make are not taken for it: token-major caches, d = 64, 32 rows, 280 heads x 19097 keys 15 (3.28) 292, 8 (1.75) 342; 1008 x 3759 3 (2.36)
+// 234, 2 (1.57) 265; fp32, d = 96, 64 rows, 144 x 15336 10 (2.81) 396, 6 (1.69) 420; d = 64, 32 rows, 112 x 26356 19 (2.77) 306.5, 11 (1.60) 321.5.  (66 such calls
+// .85-1.05 of the time with the more of them, two 1.05-1.11.)
 // More score rows than are staged together are other workgroups' in the first kernel, but in the second the same one takes a group after the other.
 // Its rounds count that often; but where not all workgroups that fit are there, those that are get on faster: a share `enough` of them
 // does what all do (bf16 1.25 waves per SIMD, fp32 2), though never less than the first kernel's.  laq_evict, the second counted as
@@ -575,10 +578,11 @@ WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int s
   if (heads * blocks >= 15LL * resident) {
     best = std::max(1, std::min(most, blocks / (8 + 2 * pl.group_tiles)));
     if (pl.groups == 1 && 2 * heads * best < 9 * resident) {
+      const int before = best;
       double least = 1e30;
       for (int sb = 8; sb <= 20; ++sb) {
         const int used = (blocks + sb - 1) / sb;
-        if (used > most) continue;
+        if (used > most || used < before) continue;
         const double load = (double)(heads * used) / resident, rounds = std::floor(load), rest = load - rounds;
         const double cost = (load <= 1.0 ? 1.08 : rest > 0.0 ? rounds + std::max(rest, 0.6) : rounds) * (sb + 1.5);
         if (cost < least) { least = cost; best = used; }
