@@ -536,9 +536,10 @@ __global__ __launch_bounds__(WAVES * 64, 4) void head_kernel(ScoreGeom g, Window
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int head = blockIdx.x, li = blockIdx.y, inst = inst0 + li;
   const size_t hg = (size_t)inst * g.Hkv + head;
-  // (No wait to give up here.  In front of the keys' loads its address is a trip to memory that these are behind: bf16, and fp32 with d = 64, 2 to 80 heads x
-  // 300 to 800 keys, 16 and 32 rows, with the store behind the scores .97-1.00 of the time.  What the compiler makes of fp32 with d > 64 is 1.00-1.03 then.)
-  constexpr bool STATUS_FIRST = is_f32(T()) && NP > 8;
+  // (No wait to give up here.  In front of the keys' loads its address is a trip to memory that these are behind: bf16, and fp32 with d = 64 and a tile per wave, 2 to 80
+  // heads x 300 to 800 keys, 16 and 32 rows, with the store behind the scores .97-1.00 of the time.  What the compiler makes of the other fp32 variants is 1.00-1.04
+  // then.)
+  constexpr bool STATUS_FIRST = is_f32(T()) && (NP > 8 || TPW > 1);
   const bool clears = head == 0 && inst == 0 && tid == 0;
   if (STATUS_FIRST && clears) *status = 0;
   float* scores = fin.pooled + hg * g.L;
