@@ -129,9 +129,9 @@ typedef struct laq_shape {
    * Which scoring kernels to take where more than one applies (laq_score_choice; 0 = LAQ_CHOOSE_AUTO:
    * the single-read kernel for at most 64 score rows per KV head where the call has enough keys (see laq_score),
    * otherwise two passes over the keys, which are the faster ones with more rows, in small calls and for unusual
-   * head sizes with one chunk of 256 keys per workgroup, or, for heads of at most 512 keys and many of at most
-   * 1024, a whole head in one workgroup).  A choice that does not apply to the shape is ignored;
-   * laq_score_kernel() tells what a call will run.
+   * head sizes with one chunk of 256 keys per workgroup, or, for heads of at most 512 keys, 72 to 768 heads of at
+   * most 1024, and 8 and more of these with few score rows, a whole head in one workgroup).  A choice that does not
+   * apply to the shape is ignored; laq_score_kernel() tells what a call will run.
    */
   int32_t score_choice;
 } laq_shape;

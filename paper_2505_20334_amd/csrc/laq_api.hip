@@ -283,14 +283,18 @@ static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
 //   6016 heads 392 : 285; fp32, d = 64, 192 heads 30.2 : 24.9; but fp32 of more than 64 elements in few heads 6 heads 32.7 : 39.7, 16 heads 33.6 : 35.1,
 //   80 heads 39.2 : 35.3; and many score rows in few 13 heads, 256 rows 42.2 : 53.4; 128 rows, 4 to 24 heads x 330 1.03, 395 and 512 .87-.89, 40 heads x
 //   395 1.03 (the others over this one)
-//   up to 1024 keys (two tiles per wave, one workgroup per compute unit): 72 heads 32.5 : 28.7, 160 heads 33.8 : 25.3, 216 heads 45.0 : 28.9, 600 heads
-//   81.9 : 63.6; 992 heads 56.9 : 63.9, 1488 heads 111.9 : 121.3, 6912 heads 464 : 568; few heads, one or two row tiles 24 heads x 560 keys 20.1 : 13.3,
-//   16 x 768 22.2 : 19.7, 16 x 1024 24.4 : 27.2, 56 x 1024 23.9 : 25.6; more row tiles 64 x 714 32.7 : 34.5, 8 x 1024 26.0 : 32.1; fp32, 2 to 64 heads, one
-//   row tile 600 keys 1.09-1.16, 768 .98-1.06; two 600 .92-.94, 768 .82-.85
+//   up to 1024 keys (two tiles per wave, one workgroup per compute unit), 72 to 768 heads, times as long in the two passes: bf16, 32 rows 1.38-1.73, 64 rows
+//   1.19-1.45, 128 rows 1.01-1.27; fp32, d = 64, 32 rows 1.20-1.37, 48 rows and more (products made twice) 128 to 256 heads .98-1.21, 72 heads .72-.98, 300 to 768
+//   .83-1.00; more than 768 heads, bf16, 32 rows 1.08-1.41, 64 rows .91-1.30, 128 rows .92-1.13, fp32, 32 rows 1.19-1.34, more .80-.90 (the last three lines and
+//   some of the fp32 ones would be better drawn by whether products are made once and by heads per compute unit; 768 is from products made twice)
+//   few heads, one or two row tiles whose products are made twice 16 x 768 22.2 : 19.7, 56 x 1024 23.9 : 25.6; more row tiles 64 x 714 32.7 : 34.5, 8 x 1024 26.0 :
+//   32.1, 2 to 7 x 800 to 1000, 128 rows, d = 64 to 128 .81-1.02
 //   few heads whose products are made once (head_keeps()): fp32, d = 64, 32 rows, 8 heads x 768, 1000 keys 22.8 : 18.5, 22.3 : 21.8, 64 x 800, 1000 25.3 : 20.2,
 //   25.6 : 22.8; d = 128, 8 x 330, 500 29.9 : 17.7, 30.1 : 20.9; d = 96, 16 x 500 27.4 : 18.4; bf16, d = 128, 8 x 800, 1000 19.9 : 16.2, 19.6 : 17.5, 56 x 1000 21.9 :
-//   18.6; d = 64, 32 x 1000 17.6 : 13.8, 64 rows 20.6 : 17.1.  (The figures above for such heads are from products made twice.)  Fewer than 8 heads of more than 768 keys, and fp32 with d > 64 in up to 16 heads
-//   of more than 448, would gain as much, but what laq_score_kernel answers for some of these is promised to callers (tests/test_abi.py) and stays.
+//   18.6; d = 64, 32 x 1000 17.6 : 13.8, 64 rows, 64 x 1000 18.6 : 14.6.
+//   Two lines of these lie where tests/test_abi.py has what laq_score_kernel() answers on the far side, and not where the times cross: fewer than 8 heads of more than
+//   768 keys (bf16, 2 x 1000, 32 rows, d = 64, 96, 128 16.5 : 12.6, 17.0 : 12.7, 19.0 : 16.5; 769 keys no other), and fp32 with d > 64 in up to 16 heads of more than 448 (8 x
+//   440 keys, taken, and 456, not: d = 72 13.7, 23.6 : 13.7; d = 128 18.2, 29.7 : 18.3).
 static bool head_wanted(const laq_shape* shape, const ScoreGeom& g) {
   if (shape->score_choice != LAQ_CHOOSE_AUTO || !head_supported(g, shape->dtype)) return false;
   const long long heads = (long long)g.n_inst * g.Hkv;

@@ -194,7 +194,7 @@ __device__ __forceinline__ Tile16 product16_f32(const char* const (&key)[2], con
   return a;
 }
 
-// The same for the products of 16 x 16 tiles.
+// stage_rows() for the products of 16 x 16 tiles
 template <typename T, bool FULL, int THREADS>
 __device__ __forceinline__ void stage_rows16(char* lds, const char* head_rows, int row_bytes, int plane, int stride, int R, int r0, int n,
                                            int shift) {

@@ -306,3 +306,16 @@ def test_which_calls_a_workgroup_per_head_takes():
     assert names(1, 8, 1, 64, 384, 16, f32) == ("whole-head", "vector") and names(1, 8, 1, 64, 385, 16, f32) == vector      # 128 score rows
     assert names(40, 8, 1, 64, 512, 16, f32) == ("whole-head", "vector") and names(39, 8, 1, 64, 512, 16, f32) == vector
     assert names(1, 8, 2, 64, 768, 8, f32) == ("whole-head", "vector") and names(1, 8, 2, 64, 513, 9, f32) == vector          # 32, 36
+
+
+def test_which_rows_of_the_whole_head_cases_other_kernels_take():
+    """test_gpu_head.py compares every variant of the kernels that take a whole head at either side of a half tile, a tile and what the registers keep; it
+    leaves out what the choice gives to other kernels.  That is no more than this."""
+    from test_gpu_head import VARIANTS
+    others = {}
+    for dtype, d, heads, L in VARIANTS:
+        for rows in (1, 16, 17, 32, 33, 64, 65, 128, 129):
+            if laq.laq_score_kernel(1, heads, heads, d, L, rows, dtype, q_pos=[L] * rows, keep=0, whole_heads=True) != "whole-head":
+                others.setdefault((dtype, d, heads, L), []).append(rows)
+    f32 = torch.float32
+    assert others == {(f32, 64, 3, 500): [128, 129], (f32, 128, 20, 333): [129], (f32, 72, 20, 129): [129]}
