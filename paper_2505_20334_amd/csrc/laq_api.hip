@@ -254,12 +254,12 @@ enum class ScorePath { single_read, head, tile, wave };
 //   bf16, d = 8 to 112   1, 2 tiles .74-1.06, 4 .67-1.07, 8 .70-1.13, 14 .76-1.08; but heads of half a chunk, 4 and 14 tiles, 100 heads and more 1.0-1.28
 //   bf16, d = 136 to 232   1 tile, up to 1500 chunks .77-1.07; 2, 4 tiles, up to 320 chunks .66-1.05, 512 .83-.94, 640 to 1500 .97-1.20 (900 heads of one chunk .83-.95), 8000 1.1-1.28;
 //                   7, 8 tiles, up to 1024 chunks .66-1.08, 8000 1.02-1.17; 14 tiles .73-1.07; half a chunk, 4 and 14 tiles, d = 136 .89-1.25, 232 .82-1.04
-//                   half a chunk, 14 tiles, 60 and 120 keys, d = 168, 176 300 heads 1.06-1.15, 450 .93-1.02, 600 .88-.95, 1000 .83-.91; d = 192 300 1.0-1.12, 450 .87-.99,
-//                   1000 .78-.88
 //   fp32, d = 8, 16   .71-1.10, half a chunk and 4, 14 tiles .93-1.62;  d = 40   1 tile .69-1.04, 2 tiles 8 heads x 288 .97, 640 on 1.03-1.14, 4 tiles 4 heads
 //                   x 256 .72, 8 heads x 192, 288 1.05, 1.06, 640 on 1.16-1.34;  d = 88, 112   1 tile, up to 512 chunks .74-1.06, 640 on 1.02-1.15; 2 tiles and
 //                   more, 8 heads and more x 192 on 1.02-1.5;  1 to 6 heads, all types, up to 500 chunks .66-.98, 512 to 564 .75-.96, 780 to 940 .80-1.16,
 //                   1096 on .92-1.14
+//   Heads of half a chunk with d below 200 stay with the others however many they are: these kernels' scores are further from 64 bits (2-norm error, 512 heads x
+//                   120 keys, 448 rows, d = 176: 1.28e-7 against 4.8e-8)
 static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
   if (!score_wave_supported(g, shape->dtype)) return true;
   const bool f32 = shape->dtype == LAQ_F32;
@@ -267,7 +267,7 @@ static bool tile_wanted(const laq_shape* shape, const ScoreGeom& g) {
   const long long heads = (long long)g.n_inst * g.Hkv, chunks = heads * g.nchunk;
   const int tiles = g.Rpad / 32;
   const bool half = 2 * g.L <= CHUNK_ROWS;               // (half of a workgroup's waves have no keys)
-  if (!score_wave_own_size(g, shape->dtype) && !(half && tiles > 2 && (f32 || g.d < 168 || (g.d < 200 && chunks < 450)))) {
+  if (!score_wave_own_size(g, shape->dtype) && !(half && tiles > 2 && (f32 || g.d < 200))) {
     if (heads < 8 && chunks <= 1024) return true;
     if (f32 && (g.d <= 32 || (tiles == 1 && (g.d < 64 || chunks <= 512)))) return true;
     if (!f32 && (g.d < 128 || tiles > 8 || g.nchunk == 1 || chunks <= (tiles > 4 ? 4096 : 512))) return true;

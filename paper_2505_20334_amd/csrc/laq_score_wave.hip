@@ -564,12 +564,16 @@ constexpr int MAX_LDS = 160 << 10, STATIC_LDS = 3 * MAX_TILES * 32 * 4;   // (th
 // the first : so, us: fp32, 256 rows, d = 128, 64 heads x 3300 285 : 212,
 // 16 x 4000 114.5 : 87.9, 300 x 3000 866 : 787; 448 rows, d = 96, 16 x 8000 220 : 173.  With all the workgroups that fit counted as needed: bf16, 160 rows,
 // d = 128, 256 x 1500 81 : 91; 224 rows, d = 256, 128 x 1100 80 : 91.
-WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int stride) {
+WavePlan plan_of(const ScoreGeom& g, int resident, double enough, int lds, int first_per_simd, int stride) {
   WavePlan pl;
   const int ntile = g.Rpad / 32, blocks = (g.L + BLOCK_KEYS - 1) / BLOCK_KEYS;
   const long long heads = (long long)g.n_inst * g.Hkv;
   int fit = std::min(lds / (32 * stride + WAVES * 32 * (int)sizeof(float2)), (lds - STATIC_LDS - THREADS * (int)sizeof(float2)) / (32 * stride));
   fit = std::max(1, std::min(fit, MAX_TILES));
+  // Heads of one block: row tiles so few that as many of the first kernel's workgroups fit as its registers allow.  laq_evict, us, four tiles : three, 448 rows, d = 168,
+  // 1000 heads x 60 keys 202 : 183.5, x 120 245 : 232, 300 x 60 88 : 79; d = 192, 1000 x 60 215.5 : 202.5.  (Longer heads are read once more by the second kernel.)
+  const int first_fit = MAX_LDS / first_per_simd / (32 * stride + WAVES * 32 * (int)sizeof(float2));
+  if (blocks == 1 && first_fit >= 3) fit = std::min(fit, first_fit);
   pl.groups = (ntile + fit - 1) / fit;
   pl.group_tiles = (ntile + pl.groups - 1) / pl.groups;
   pl.groups = (ntile + pl.group_tiles - 1) / pl.group_tiles;
@@ -613,7 +617,7 @@ hipError_t launch_wave(const ScoreGeom& g, const WindowPos& qp, const KvLayout& 
                        const Workspace& ws, hipStream_t st) {
   constexpr int per_simd = waves_per_simd<T, NP>();
   const int stride = row16_stride<T>(g.d);
-  WavePlan pl = plan_of(g, 256 * per_simd, (is_f32(T()) ? 2.0 : 1.25) / per_simd, MAX_LDS / per_simd, stride);
+  WavePlan pl = plan_of(g, 256 * per_simd, (is_f32(T()) ? 2.0 : 1.25) / per_simd, MAX_LDS / per_simd, stats_waves_per_simd<T, NP>(), stride);
   pl.row_scale = row_scale_of<T>(g.scale2);
   // Where the keys do not fit the last-level cache (256 MiB), the second kernel begins with the heads that the first one read last.  laq_evict, us, in the
   // same order : so, on the same cache every time; on one that no earlier call has read:

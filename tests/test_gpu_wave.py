@@ -305,6 +305,5 @@ def test_heads_in_either_order(dtype, n, Hq, Hkv, d, L, W, block):
 
 @pytest.mark.parametrize("n,d,L,W", [(449, 168, 128, 32), (450, 168, 128, 32), (449, 176, 100, 21), (450, 176, 100, 21), (450, 200, 60, 32), (450, 160, 97, 32)])
 def test_short_heads_of_more_than_256_rows(n, d, L, W):
-    """Either side of the number of heads from which on a workgroup takes one, 14 query heads each, where the other kernels' rows leave room for two
-    workgroups on a compute unit; head sizes next to these."""
+    """14 query heads each: groups of three row tiles where four leave room for two workgroups on a compute unit, and of four; head sizes next to these."""
     test_scores_against_the_oracle(BF16, n, 14, 1, d, L, W)
